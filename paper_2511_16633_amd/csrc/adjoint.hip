@@ -11,9 +11,21 @@
 // cores.  The complex product is expanded into real MFMAs and the reduction
 // over e against G_e(x) is fused into the epilogue, so Y and Z never leave
 // registers.  A k-permutation (lane group kk supplies k = 4 kk + s at MFMA
-// step s) lets each lane fetch its A fragment with one vector load.  Blocks
-// of A whose weights are all zero (the receiver selection removes a band
-// around the diagonal) are skipped per 16x16 block.
+// step s) lets each lane fetch its A fragment with one vector load.
+//
+// Both sums are symmetric in (e, r) apart from A and W, so each unordered
+// pair is contracted once, with (A_er + A_re) / 2 and (W_er + W_re) / 2 and
+// the factor 2 in the constants (k_adj_prep).  Of the two 32 x 32 blocks (I,
+// J) and (J, I) the one whose J follows I by less than half the ring, in
+// circular block order, is kept: every emitter block then has about half the
+// ring's receiver blocks, whatever its place in the ring, and passes of
+// consecutive emitter blocks share most of theirs.  Blocks that are not kept,
+// and blocks whose weights are all zero (the receiver selection removes a
+// band around the diagonal), are skipped: neither staged nor multiplied.
+// Against contracting both orders (1024 elements / 1100^2, four frequencies;
+// bound by the matrix cores): FP32 209.9 -> 107.9 ms, BF16 32.8 -> 20.0 ms;
+// 256 / 480^2, three frequencies, FP32: 2.31 -> 1.59 ms (three or four
+// chunks per pass are left, so a pass's fixed cost weighs more).
 #include <algorithm>
 #include <cmath>
 #include <mutex>
@@ -63,8 +75,8 @@ __global__ void __launch_bounds__(256) k_adjoint(AdjParams P, const T *__restric
                 bool any = false;
 #pragma unroll
                 for (int b = 0; b < RB; ++b) {
-                    const int eb = ec / 16 + b;
-                    on[b] = (eb < P.nb) && fl[eb * P.nb + rc / 16];
+                    const int eb = (ec + 16 * b) / 32;
+                    on[b] = (eb < P.nb) && fl[eb * P.nb + rc / 32];
                     any |= on[b];
                 }
                 if (!any) continue;
@@ -145,10 +157,6 @@ __global__ void __launch_bounds__(256) k_adjoint(AdjParams P, const T *__restric
     }
 }
 
-// Operands of the adjoint: A = W . D (re, im) and W in the storage type,
-// padded to mp x mp with zeros.  For 16-bit types A is divided by ascale[k]
-// = max |W D| (1 if that is 0; W is 0/1-valued in the inversion, stored
-// unscaled).
 template <typename T>
 __device__ __forceinline__ T cvt(double v);
 template <>
@@ -160,66 +168,31 @@ __device__ __forceinline__ __hip_bfloat16 cvt<__hip_bfloat16>(double v) { return
 template <>
 __device__ __forceinline__ __half cvt<__half>(double v) { return __float2half((float)v); }
 
-// PERMUTE: within every 32-column chunk, receiver 4 s + kk is stored at
-// column 8 kk + s (the operand order of k_adjoint_f32).
-template <typename T, bool SCALED, bool PERMUTE = false>
-__global__ void k_adj_prep(int m, int mp, int nf, const double *__restrict__ d, const double *__restrict__ w,
-                           const float *__restrict__ ascale, T *__restrict__ Ar, T *__restrict__ Ai,
-                           T *__restrict__ Wt) {
-    const int64_t per = (int64_t)mp * mp;
-    const int64_t tot = per * nf;
-    for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < tot;
-         idx += (int64_t)gridDim.x * blockDim.x) {
-        const int k = (int)(idx / per);
-        const int64_t rem = idx - (int64_t)k * per;
-        const int e = (int)(rem / mp), r = (int)(rem - (int64_t)e * mp);
-        double re = 0.0, im = 0.0, wv = 0.0;
-        if (e < m && r < m) {
-            const int64_t q = ((int64_t)k * m + e) * m + r;
-            wv = w[q];
-            re = wv * d[2 * q];
-            im = wv * d[2 * q + 1];
-            if (SCALED) {
-                const float a = ascale[k];   // 0 when every weight is zero
-                const double inv = a > 0.0f ? 1.0 / (double)a : 1.0;
-                re *= inv;
-                im *= inv;
-            }
-        }
-        int64_t o = idx;
-        if (PERMUTE) {
-            const int kr = r & 31;
-            o = idx - kr + 8 * (kr & 3) + (kr >> 2);
-        }
-        Ar[o] = cvt<T>(re);
-        Ai[o] = cvt<T>(im);
-        Wt[o] = cvt<T>(wv);
-    }
+// Which of the blocks (I, J) and (J, I), I != J, of nb blocks around the ring
+// is kept: the one whose J lies less than nb / 2 after I; at exactly nb / 2,
+// the one with I < J.  Diagonal blocks are kept as they are.
+__device__ __forceinline__ bool adj_kept(int I, int J, int nb) {
+    const int d = J >= I ? J - I : J - I + nb;
+    return 2 * d < nb || (2 * d == nb && I < J);
 }
 
-// One workgroup per 16x16 block (eb, rb) and frequency, one thread per
-// entry: flags[k][eb][rb] = 1 if any weight of the block is nonzero, and
-// for 16-bit operands (amax != null) the block's max |W D| (as float bits;
-// max is order-independent) folded into amax[k], which starts at zero.
-__global__ void __launch_bounds__(256) k_adj_blocks(int m, int nb, const double *__restrict__ d,
-                                                    const double *__restrict__ w, uint8_t *__restrict__ flags,
-                                                    unsigned *__restrict__ amax) {
+// max |W D| of every kept pair of blocks (as float bits; max is
+// order-independent) folded into amax[k], which starts at zero.  One
+// workgroup per 32 x 32 block and frequency.
+__global__ void __launch_bounds__(256) k_adj_amax(int m, int nb, const double *__restrict__ d,
+                                                  const double *__restrict__ w, unsigned *__restrict__ amax) {
     __shared__ float sm[4];
-    const int k = blockIdx.y, eb = blockIdx.x / nb, rb = blockIdx.x - (blockIdx.x / nb) * nb;
-    const int e = eb * 16 + (threadIdx.x >> 4), r = rb * 16 + (threadIdx.x & 15);
-    double wv = 0.0, re = 0.0, im = 0.0;
-    if (e < m && r < m) {
-        const int64_t q = ((int64_t)k * m + e) * m + r;
-        wv = w[q];
-        if (amax) {
-            re = wv * d[2 * q];
-            im = wv * d[2 * q + 1];
+    const int k = blockIdx.y, I = blockIdx.x / nb, J = blockIdx.x - (blockIdx.x / nb) * nb;
+    float v = 0.0f;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int e = I * 32 + (threadIdx.x >> 5) + 8 * q, r = J * 32 + (threadIdx.x & 31);
+        if (e < m && r < m) {
+            const int64_t o = ((int64_t)k * m + e) * m + r;
+            const double wv = w[o];
+            v = fmaxf(v, (float)fmax(fabs(wv * d[2 * o]), fabs(wv * d[2 * o + 1])));
         }
     }
-    const int any = __syncthreads_or(wv != 0.0);
-    if (threadIdx.x == 0) flags[((int64_t)k * nb + eb) * nb + rb] = any ? 1 : 0;
-    if (!amax) return;
-    float v = (float)fmax(fabs(re), fabs(im));
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
     if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = v;
@@ -229,6 +202,95 @@ __global__ void __launch_bounds__(256) k_adj_blocks(int m, int nb, const double 
         if (b > 0.0f) atomicMax(amax + k, __float_as_uint(b));
     }
 }
+
+// Operands of the adjoint in the storage type, [nf][mp][mp], one workgroup
+// per 32 x 32 block (I, J) and frequency: half of A = W . D plus its
+// transpose (re, im), and of W, in the kept blocks; half of A and W in the
+// diagonal blocks; entries beyond m are zero.  The other blocks are left
+// unwritten: flags[k][I][J], 1 for a kept block with a nonzero weight, keeps
+// the contraction from reading them.  The transposed block passes through
+// LDS so that both blocks are read along rows.  For 16-bit types A is
+// divided by ascale[k] = max |W D| (1 if that is 0); W is 0/1-valued in the
+// inversion and stored unscaled (the mean of two weights stays in range).
+// PERMUTE: within every 32-column chunk, receiver 4 s + kk is stored at
+// column 8 kk + s (the operand order of k_adjoint_f32).
+template <typename T, bool SCALED, bool PERMUTE = false>
+__global__ void __launch_bounds__(256) k_adj_prep(int m, int mp, const double *__restrict__ d,
+                                                  const double *__restrict__ w, const float *__restrict__ ascale,
+                                                  T *__restrict__ Ar, T *__restrict__ Ai, T *__restrict__ Wt,
+                                                  uint8_t *__restrict__ flags) {
+    __shared__ double tr[32][33], ti[32][33], tw[32][33];
+    const int nb = mp / 32;
+    const int k = blockIdx.y, I = blockIdx.x / nb, J = blockIdx.x - (blockIdx.x / nb) * nb;
+    uint8_t *fl = flags + ((int64_t)k * nb + I) * nb + J;
+    if (!adj_kept(I, J, nb)) {   // workgroup-uniform
+        if (threadIdx.x == 0) *fl = 0;
+        return;
+    }
+    const int col = threadIdx.x & 31, row0 = threadIdx.x >> 5;
+    auto load = [&](int e, int r, double &re, double &im, double &wv) {
+        re = im = wv = 0.0;
+        if (e < m && r < m) {
+            const int64_t q = ((int64_t)k * m + e) * m + r;
+            wv = w[q];
+            re = wv * d[2 * q];
+            im = wv * d[2 * q + 1];
+        }
+    };
+    if (I != J) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int i = row0 + 8 * q;
+            load(J * 32 + i, I * 32 + col, tr[i][col], ti[i][col], tw[i][col]);
+        }
+    }
+    __syncthreads();
+    double half = 0.5;
+    if (SCALED) {
+        const float a = ascale[k];   // 0 when every weight is zero
+        half = a > 0.0f ? 0.5 / (double)a : 0.5;
+    }
+    bool any = false;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int i = row0 + 8 * q;
+        double re, im, wv;
+        load(I * 32 + i, J * 32 + col, re, im, wv);
+        any |= wv != 0.0;
+        if (I != J) {
+            any |= tw[col][i] != 0.0;
+            re += tr[col][i];
+            im += ti[col][i];
+            wv += tw[col][i];
+        }
+        const int c = PERMUTE ? 8 * (col & 3) + (col >> 2) : col;
+        const int64_t o = ((int64_t)k * mp + I * 32 + i) * mp + J * 32 + c;
+        Ar[o] = cvt<T>(re * half);
+        Ai[o] = cvt<T>(im * half);
+        Wt[o] = cvt<T>(wv * 0.5);
+    }
+    const int on = __syncthreads_or(any);
+    if (threadIdx.x == 0) *fl = on ? 1 : 0;
+}
+
+// The receiver chunks (32 receivers each, at most 128) an emitter pass works
+// on, as wave-uniform bit masks, taken in increasing order.
+struct AdjChunks {
+    uint64_t m0, m1;
+    __device__ __forceinline__ int count() const { return __popcll(m0) + __popcll(m1); }
+    __device__ __forceinline__ bool has(int c) const { return (((c < 64 ? m0 : m1) >> (c & 63)) & 1) != 0; }
+    // the next chunk (0 once there is none left; see count())
+    __device__ __forceinline__ int pop() {
+        if (m0) {
+            const int c = __ffsll((unsigned long long)m0) - 1;
+            m0 &= m0 - 1;
+            return c;
+        }
+        const int c = m1 ? 63 + __ffsll((unsigned long long)m1) : 0;
+        m1 &= m1 - 1;
+        return c;
+    }
+};
 
 // ------------------------------------------------------------------ FP32, LDS-staged
 // Backprojection.  The workgroup owns 64 pixels; its four waves are 2
@@ -454,26 +516,26 @@ __global__ void __launch_bounds__(256, HESS ? 2 : 3) k_adjoint_f32(const A args)
             for (int b = 0; b < 2; ++b)
 #pragma unroll
                 for (int c = 0; c < 2; ++c) p1[b][c] = p2[b][c] = p3[b][c] = z[b][c] = f4{0, 0, 0, 0};
-            // Chunks of 32 receivers in which one of this wave's two 16-row
-            // blocks has a nonzero weight, as wave-uniform bit masks
-            // (nch <= 128): a flag load inside the loop would make the MFMAs
-            // of a chunk wait for the next chunk's tile, which is issued first.
-            uint64_t cm[2] = {0, 0};
+            // Chunks of 32 receivers to work on, as wave-uniform bit masks
+            // taken before the chunk loop: a flag load inside it would make
+            // the MFMAs of a chunk wait for the next chunk's tile, which is
+            // issued first.  `all`: of either emitter half (staged), `mine`:
+            // of this wave's half.
+            AdjChunks all{0, 0}, mine{0, 0};
 #pragma unroll
-            for (int b = 0; b < 2; ++b)
+            for (int h = 0; h < 2; ++h) {
+                const int c = 64 * h + lane;
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const int eb = (ec >> 4) + 2 * we + b, c = 64 * h + lane;
-                    const bool on =
-                        eb < P.nb && c < nch && (fl[eb * P.nb + 2 * c] | fl[eb * P.nb + 2 * c + 1]) != 0;
-                    cm[h] |= __ballot(on);
+                for (int q = 0; q < 2; ++q) {
+                    const int eb = (ec >> 5) + q;
+                    const uint64_t b = __ballot(eb < P.nb && c < nch && fl[eb * P.nb + c] != 0);
+                    (h ? all.m1 : all.m0) |= b;
+                    if (q == we) (h ? mine.m1 : mine.m0) = b;
                 }
-            // The A fragments of chunk c + 1 are loaded during chunk c, along
-            // with its G tile, so the MFMAs of a chunk wait only for LDS.
-            auto chunk_on = [&](int rc) {
-                const int c = rc / kAdjKC;
-                return ((((c < 64) ? cm[0] : cm[1]) >> (c & 63)) & 1) != 0;
-            };
+            }
+            const int nstep = all.count();
+            // The A fragments of the next chunk are loaded during a chunk,
+            // along with its G tile, so the MFMAs of a chunk wait only for LDS.
             auto load_a = [&](int rc, f4 (&va)[2][2], f4 (&vi)[2][2], f4 (&vw)[2][2]) {
 #pragma unroll
                 for (int b = 0; b < 2; ++b) {
@@ -497,26 +559,27 @@ __global__ void __launch_bounds__(256, HESS ? 2 : 3) k_adjoint_f32(const A args)
                     adj_stage_regs(gr, gi, P.m, N, rc, x0, dst);
             };
             f4 va[2][2], vi[2][2], vw[2][2];
-            stage(0, sB[0]);
-            bool on = chunk_on(0);
-            if (on) load_a(0, va, vi, vw);
+            bool on = false;
+            if (nstep > 0) {   // workgroup-uniform
+                const int c = all.pop();
+                stage(c * kAdjKC, sB[0]);
+                on = mine.has(c);
+                if (on) load_a(c * kAdjKC, va, vi, vw);
+            }
             __builtin_amdgcn_s_waitcnt(0);   // this wave's direct-to-LDS loads have landed
             __syncthreads();
-            for (int c = 0; c < nch; ++c) {
-                const int rc = c * kAdjKC, buf = c & 1;
+            for (int s = 0; s < nstep; ++s) {
+                const int buf = s & 1;
                 bool on_n = false;
                 f4 na[2][2], ni[2][2], nw[2][2];
-                if (c + 1 < nch) {
-                    stage(rc + kAdjKC, sB[buf ^ 1]);
-                    on_n = chunk_on(rc + kAdjKC);
-                    if (on_n) load_a(rc + kAdjKC, na, ni, nw);
+                if (s + 1 < nstep) {
+                    const int c = all.pop();
+                    stage(c * kAdjKC, sB[buf ^ 1]);
+                    on_n = mine.has(c);
+                    if (on_n) load_a(c * kAdjKC, na, ni, nw);
                 }
-                if (on) {
-                    // a block that is off holds exact zeros in A and W, so it
-                    // may be computed along with the other one
-                    adj_mma_steps<2, HESS>(va, vi, vw, sB[buf], sB[buf] + kAdjTile, kk, coff, p1, p2, p3, z, 0);
-                }
-                __builtin_amdgcn_s_waitcnt(0);   // chunk c + 1 has landed in LDS
+                if (on) adj_mma_steps<2, HESS>(va, vi, vw, sB[buf], sB[buf] + kAdjTile, kk, coff, p1, p2, p3, z, 0);
+                __builtin_amdgcn_s_waitcnt(0);   // the next chunk has landed in LDS
                 __syncthreads();
                 on = on_n;
                 if (on) {
@@ -614,9 +677,8 @@ using Idx = std::integral_constant<int, I>;
 // A fragments (eight receivers of one emitter) come from L2 as 16-byte
 // loads, one step ahead.
 //
-// Every pass takes the k-steps in the same order, so the passes of a tile
-// (adjacent workgroups on one XCD) read each G chunk at about the same time
-// and share it in L2.  The epilogue then loads the pass's own emitter rows
+// The passes of a tile are adjacent workgroups on one XCD, so that they share
+// the tile's chunks in L2.  The epilogue loads the pass's own emitter rows
 // into the freed tile buffers once more and takes G_e from them with the
 // same transposing read (four emitters of one pixel per lane).
 constexpr int kT16NT = 128;                   // pixels per tile
@@ -771,15 +833,6 @@ __global__ void __launch_bounds__(256, HESS ? 1 : 2) k_adjoint16_tr(const A args
     const int pass0 = qg * npass / npg, pass1 = (qg + 1) * npass / npg;
     for (int ec = pass0 * kT16NE; ec < pass1 * kT16NE; ec += kT16NE) {
         const int e0 = ec + 32 * wave;
-        // every pass takes the receiver chunks in the same order, so that the
-        // passes of a tile (adjacent workgroups on one XCD) read each G chunk
-        // at about the same time and share it in L2
-        // (opaque to the compiler, which would otherwise keep a strength-
-        // reduced address per unrolled step live in registers)
-        auto chunk = [&](int s) {
-            asm volatile("" : "+s"(s));
-            return s;
-        };
         f4 yr[EB][8], yn[EB][8], z[EB][8];
 #pragma unroll
         for (int b = 0; b < EB; ++b)
@@ -797,26 +850,39 @@ __global__ void __launch_bounds__(256, HESS ? 1 : 2) k_adjoint16_tr(const A args
                 if (HESS) vw[b] = *reinterpret_cast<const V *>(wt + co + aoff[b]);
             }
         };
-        // chunks in which a 16-row block of this wave has a nonzero weight
-        uint64_t cm[2] = {0, 0};
+        // the pass's receiver chunks: `all` of its four waves (staged), `mine`
+        // of this wave's 32 emitters
+        AdjChunks all{0, 0}, mine{0, 0};
 #pragma unroll
-        for (int b = 0; b < EB; ++b)
+        for (int h = 0; h < 2; ++h) {
+            const int c = 64 * h + lane;
 #pragma unroll
-            for (int hh = 0; hh < 2; ++hh) {
-                const int eb = (e0 >> 4) + b, c = 64 * hh + lane;
-                const bool on =
-                    eb < P.nb && c < nch && (fl[eb * P.nb + 2 * c] | fl[eb * P.nb + 2 * c + 1]) != 0;
-                cm[hh] |= __ballot(on);
+            for (int q = 0; q < 4; ++q) {
+                const int eb = (ec >> 5) + q;
+                const uint64_t b = __ballot(eb < P.nb && c < nch && fl[eb * P.nb + c] != 0);
+                (h ? all.m1 : all.m0) |= b;
+                if (q == wave) (h ? mine.m1 : mine.m0) = b;
             }
+        }
+        const int nstep = all.count();
+        // the chunks of the current step and the next two (opaque to the
+        // compiler, which would otherwise keep a strength-reduced address per
+        // unrolled step live in registers)
+        auto next_chunk = [&]() {
+            int c = all.pop();
+            asm volatile("" : "+s"(c));
+            return c;
+        };
+        int c0 = next_chunk(), c1 = next_chunk(), c2 = next_chunk();
         auto stage = [&](int c, unsigned char *dst, auto vtag) {
             if (decltype(vtag)::value)
                 t16_stage_async(gr + ((int64_t)c * kT16KC * N + x0), gi + ((int64_t)c * kT16KC * N + x0), goff, dst);
             else
                 t16_stage_regs(gr, gi, P.m, N, c * kT16KC, x0, dst);
         };
-        // One k-step s (chunk c = chunk(s)) on the tile in buffer s mod 4:
-        // wait for its tile and A(c), issue A(next) and the tile of step
-        // s + 2, then the MFMAs.  Per step a wave issues A(s + 1) (2 EB or
+        // One k-step s (chunk c0) on the tile in buffer s mod 4: wait for its
+        // tile and A(c0), issue A(c1) and the tile of step s + 2 (chunk c2),
+        // then the MFMAs.  Per step a wave issues A(s + 1) (2 EB or
         // 3 EB loads) and then the tile of s + 2 (4 direct loads), so at the
         // wait only the tile of s + 1 may still be in flight.  `mode` says
         // what the step issues when that is known at compile time (3: A and
@@ -826,19 +892,22 @@ __global__ void __launch_bounds__(256, HESS ? 1 : 2) k_adjoint16_tr(const A args
                          V (&nw)[EB], auto vtag, auto mode) {
             constexpr int I = decltype(itag)::value;
             constexpr int M = decltype(mode)::value;
-            const bool has_a = M == 3 || M == 2 || (M == 0 && s + 1 < nch);
-            const bool has_t = M == 3 || (M == 0 && s + 2 < nch);
+            const bool has_a = M == 3 || M == 2 || (M == 0 && s + 1 < nstep);
+            const bool has_t = M == 3 || (M == 0 && s + 2 < nstep);
             if (has_a)
                 __builtin_amdgcn_s_waitcnt(vmcnt_imm(4));   // tile s + 1
             else
                 __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
             lds_barrier();
-            const int c = chunk(s);
-            if (has_a) load_a(chunk(s + 1), na, ni, nw);
+            const bool on = mine.has(c0);
+            if (has_a) load_a(c1, na, ni, nw);
             __builtin_amdgcn_sched_barrier(0);
-            if (has_t) stage(chunk(s + 2), buf(Idx<I + 2>()), vtag);
+            if (has_t) stage(c2, buf(Idx<I + 2>()), vtag);
             __builtin_amdgcn_sched_barrier(0);
-            if (!(((c < 64 ? cm[0] : cm[1]) >> (c & 63)) & 1)) return;
+            c0 = c1;
+            c1 = c2;
+            c2 = next_chunk();
+            if (!on) return;
             const unsigned char *sb = buf(Idx<I>());
             V nva[EB];
 #pragma unroll
@@ -873,31 +942,33 @@ __global__ void __launch_bounds__(256, HESS ? 1 : 2) k_adjoint16_tr(const A args
             using M0 = std::integral_constant<int, 0>;
             V va[EB], vi[EB], vw[EB], na[EB], ni[EB], nw[EB];
             lds_barrier();   // the previous pass is done with the tile buffers
-            stage(chunk(0), sG0, vtag);
-            load_a(chunk(0), va, vi, vw);
-            // unconditional (a one-chunk pass stages its chunk twice), so that
+            stage(c0, sG0, vtag);
+            load_a(c0, va, vi, vw);
+            // unconditional (a one-chunk pass stages chunk 0, unused), so that
             // the loop is always entered with the same loads in flight and
             // the compiler's load-counter waits at its head stay exact
-            stage(chunk(min(1, nch - 1)), sG1, vtag);
+            stage(c1, sG1, vtag);
             int s = 0;
-            for (; s + 6 <= nch; s += 4) {
+            for (; s + 6 <= nstep; s += 4) {
                 kstep(s, Idx<0>(), va, vi, vw, na, ni, nw, vtag, M3());
                 kstep(s + 1, Idx<1>(), na, ni, nw, va, vi, vw, vtag, M3());
                 kstep(s + 2, Idx<2>(), va, vi, vw, na, ni, nw, vtag, M3());
                 kstep(s + 3, Idx<3>(), na, ni, nw, va, vi, vw, vtag, M3());
             }
-            if (s < nch) kstep(s, Idx<0>(), va, vi, vw, na, ni, nw, vtag, M0());
-            if (s + 1 < nch) kstep(s + 1, Idx<1>(), na, ni, nw, va, vi, vw, vtag, M0());
-            if (s + 2 < nch) kstep(s + 2, Idx<2>(), va, vi, vw, na, ni, nw, vtag, M0());
-            if (s + 3 < nch) kstep(s + 3, Idx<3>(), na, ni, nw, va, vi, vw, vtag, M0());
-            if (s + 4 < nch) kstep(s + 4, Idx<0>(), va, vi, vw, na, ni, nw, vtag, M0());
+            if (s < nstep) kstep(s, Idx<0>(), va, vi, vw, na, ni, nw, vtag, M0());
+            if (s + 1 < nstep) kstep(s + 1, Idx<1>(), na, ni, nw, va, vi, vw, vtag, M0());
+            if (s + 2 < nstep) kstep(s + 2, Idx<2>(), va, vi, vw, na, ni, nw, vtag, M0());
+            if (s + 3 < nstep) kstep(s + 3, Idx<3>(), na, ni, nw, va, vi, vw, vtag, M0());
+            if (s + 4 < nstep) kstep(s + 4, Idx<0>(), va, vi, vw, na, ni, nw, vtag, M0());
             // keep the epilogue's work out of the last k-steps' schedule
             __builtin_amdgcn_sched_barrier(0);
         };
-        if (vec)
-            kloop(std::true_type());
-        else
-            kloop(std::false_type());
+        if (nstep > 0) {   // workgroup-uniform
+            if (vec)
+                kloop(std::true_type());
+            else
+                kloop(std::false_type());
+        }
         // fused epilogue: Re sum_e conj(G_e) Y_e and sum_e |G_e|^2 Z_e.  The
         // tile buffers are free once every wave is done with the k-loop:
         // wave w copies the chunk of its 32 emitter rows (both arrays) into
@@ -1004,15 +1075,15 @@ static AdjParams adj_params(const rb_geometry *g, const double *freqs, int nf) {
     AdjParams P;
     P.m = g->m;
     P.mp = pad_m(g->m);
-    P.nb = P.mp / 16;
+    P.nb = P.mp / 32;
     P.N = (int64_t)g->nx * g->ny;
     P.nf = nf;
     const double dA = g->h * g->h;
     for (int k = 0; k < nf; ++k) {
         const double om = 2.0 * M_PI * freqs[k];
         const double c = om * om * dA;
-        P.cg[k] = c;
-        P.ch[k] = c * c;
+        P.cg[k] = 2.0 * c;       // 2: the operands hold half of A + A^T and W + W^T
+        P.ch[k] = 2.0 * c * c;
     }
     return P;
 }
@@ -1056,7 +1127,7 @@ static AdjWs carve_adj(Carver &c, const rb_geometry *g, int nf, rb_dtype dt) {
     w.Ar = c.take<char>(per * es);
     w.Ai = c.take<char>(per * es);
     w.Wt = c.take<char>(per * es);
-    w.flags = c.take<uint8_t>((size_t)nf * (mp / 16) * (mp / 16));
+    w.flags = c.take<uint8_t>((size_t)nf * (mp / 32) * (mp / 32));
     w.ascale = c.take<float>(RB_MAX_NF);
     w.pg = c.take<double>((size_t)nf * npg * g->nx * g->ny);
     w.ph = c.take<double>((size_t)nf * npg * g->nx * g->ny);
@@ -1079,30 +1150,29 @@ rb_status adjoint_prepare(const rb_geometry *g, const void *G_re, const void *G_
     Carver c(ws, ws_bytes);
     AdjWs w = carve_adj(c, g, nf, dt);
     AdjParams P = adj_params(g, freqs, nf);
-    const int64_t tot = (int64_t)nf * P.mp * P.mp;
-    const unsigned bp = (unsigned)std::min<int64_t>(blocks_for(tot, 256), 8192);
-    const bool scaled = (dt == RB_BF16 || dt == RB_F16);
-    if (scaled) RB_TRY(fill_f32(w.ascale, 0.0f, nf, st));
-    k_adj_blocks<<<dim3(P.nb * P.nb, nf), 256, 0, st>>>(g->m, P.nb, d_res, w_data, w.flags,
-                                                        scaled ? reinterpret_cast<unsigned *>(w.ascale) : nullptr);
-    RB_LAUNCHED();
+    const dim3 gp(P.nb * P.nb, nf);
+    if (dt == RB_BF16 || dt == RB_F16) {
+        RB_TRY(fill_f32(w.ascale, 0.0f, nf, st));
+        k_adj_amax<<<gp, 256, 0, st>>>(g->m, P.nb, d_res, w_data, reinterpret_cast<unsigned *>(w.ascale));
+        RB_LAUNCHED();
+    }
     switch (dt) {
         case RB_F64:
-            k_adj_prep<double, false><<<bp, 256, 0, st>>>(g->m, P.mp, nf, d_res, w_data, nullptr, (double *)w.Ar,
-                                                          (double *)w.Ai, (double *)w.Wt);
+            k_adj_prep<double, false><<<gp, 256, 0, st>>>(g->m, P.mp, d_res, w_data, nullptr, (double *)w.Ar,
+                                                          (double *)w.Ai, (double *)w.Wt, w.flags);
             break;
         case RB_F32:
-            k_adj_prep<float, false, true><<<bp, 256, 0, st>>>(g->m, P.mp, nf, d_res, w_data, nullptr,
-                                                               (float *)w.Ar, (float *)w.Ai, (float *)w.Wt);
+            k_adj_prep<float, false, true><<<gp, 256, 0, st>>>(g->m, P.mp, d_res, w_data, nullptr, (float *)w.Ar,
+                                                               (float *)w.Ai, (float *)w.Wt, w.flags);
             break;
         case RB_BF16:
-            k_adj_prep<__hip_bfloat16, true><<<bp, 256, 0, st>>>(g->m, P.mp, nf, d_res, w_data, w.ascale,
+            k_adj_prep<__hip_bfloat16, true><<<gp, 256, 0, st>>>(g->m, P.mp, d_res, w_data, w.ascale,
                                                                  (__hip_bfloat16 *)w.Ar, (__hip_bfloat16 *)w.Ai,
-                                                                 (__hip_bfloat16 *)w.Wt);
+                                                                 (__hip_bfloat16 *)w.Wt, w.flags);
             break;
         case RB_F16:
-            k_adj_prep<__half, true><<<bp, 256, 0, st>>>(g->m, P.mp, nf, d_res, w_data, w.ascale, (__half *)w.Ar,
-                                                         (__half *)w.Ai, (__half *)w.Wt);
+            k_adj_prep<__half, true><<<gp, 256, 0, st>>>(g->m, P.mp, d_res, w_data, w.ascale, (__half *)w.Ar,
+                                                         (__half *)w.Ai, (__half *)w.Wt, w.flags);
             break;
     }
     RB_LAUNCHED();

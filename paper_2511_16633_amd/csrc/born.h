@@ -6,10 +6,10 @@
 namespace rb {
 
 struct AdjParams {
-    int m, mp, nb, nf;
+    int m, mp, nb, nf;     // nb = mp / 32 blocks of elements
     int64_t N;
-    double cg[RB_MAX_NF];  // omega^2 h^2
-    double ch[RB_MAX_NF];  // omega^4 h^4
+    double cg[RB_MAX_NF];  // 2 omega^2 h^2
+    double ch[RB_MAX_NF];  // 2 omega^4 h^4
 };
 
 // One problem's backprojection as the contraction kernel sees it, for
