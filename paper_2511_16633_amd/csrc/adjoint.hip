@@ -168,6 +168,16 @@ __device__ __forceinline__ __hip_bfloat16 cvt<__hip_bfloat16>(double v) { return
 template <>
 __device__ __forceinline__ __half cvt<__half>(double v) { return __float2half((float)v); }
 
+// The power of two that brings a value of magnitude `top` into [2^(e-1),
+// 2^e) (1 for 0): exact to apply and to take back.
+constexpr int kSplitTopA = 14, kSplitTopG = 9;
+__device__ __forceinline__ float split_scale(float top, int e) {
+    if (!(top > 0.0f)) return 1.0f;
+    int x;
+    (void)frexpf(fminf(top, 3.0e38f), &x);
+    return ldexpf(1.0f, min(max(e - x, -100), 100));
+}
+
 // Which of the blocks (I, J) and (J, I), I != J, of nb blocks around the ring
 // is kept: the one whose J lies less than nb / 2 after I; at exactly nb / 2,
 // the one with I < J.  Diagonal blocks are kept as they are.
@@ -212,13 +222,19 @@ __global__ void __launch_bounds__(256) k_adj_amax(int m, int nb, const double *_
 // LDS so that both blocks are read along rows.  For 16-bit types A is
 // divided by ascale[k] = max |W D| (1 if that is 0); W is 0/1-valued in the
 // inversion and stored unscaled (the mean of two weights stays in range).
-// PERMUTE: within every 32-column chunk, receiver 4 s + kk is stored at
-// column 8 kk + s (the operand order of k_adjoint_f32).
-template <typename T, bool SCALED, bool PERMUTE = false>
+// Orders: LAYOUT 0: rows of mp; 1: the same with receiver 4 s + kk of every
+// 32-column chunk at column 8 kk + s (the operand order of k_adjoint_f32); 2:
+// the blocks one after the other, [I][J], each as the A fragments of its two
+// 16-row halves (lane 16 kk + row holds columns 8 kk .. 8 kk + 7 of the row),
+// so that a fragment is one contiguous 1 KB load.  With `shi` (FP32 only) A is
+// also stored as two FP16 pieces of A split_scale(amax[k]), each [I][J][re,
+// im] in fragments, and W, which only the Hessian diagonal needs, is not.
+template <typename T, bool SCALED, int LAYOUT = 0>
 __global__ void __launch_bounds__(256) k_adj_prep(int m, int mp, const double *__restrict__ d,
                                                   const double *__restrict__ w, const float *__restrict__ ascale,
                                                   T *__restrict__ Ar, T *__restrict__ Ai, T *__restrict__ Wt,
-                                                  uint8_t *__restrict__ flags) {
+                                                  uint8_t *__restrict__ flags, _Float16 *__restrict__ shi = nullptr,
+                                                  _Float16 *__restrict__ slo = nullptr) {
     __shared__ double tr[32][33], ti[32][33], tw[32][33];
     const int nb = mp / 32;
     const int k = blockIdx.y, I = blockIdx.x / nb, J = blockIdx.x - (blockIdx.x / nb) * nb;
@@ -263,23 +279,42 @@ __global__ void __launch_bounds__(256) k_adj_prep(int m, int mp, const double *_
             im += ti[col][i];
             wv += tw[col][i];
         }
-        const int c = PERMUTE ? 8 * (col & 3) + (col >> 2) : col;
-        const int64_t o = ((int64_t)k * mp + I * 32 + i) * mp + J * 32 + c;
+        const int c = LAYOUT == 1 ? 8 * (col & 3) + (col >> 2) : col;
+        const int64_t blk = ((int64_t)k * nb + I) * nb + J;
+        const int fr = 512 * (i >> 4) + 8 * (16 * (col >> 3) + (i & 15)) + (col & 7);
+        const int64_t o = LAYOUT == 2 ? 1024 * blk + fr : ((int64_t)k * mp + I * 32 + i) * mp + J * 32 + c;
         Ar[o] = cvt<T>(re * half);
         Ai[o] = cvt<T>(im * half);
-        Wt[o] = cvt<T>(wv * 0.5);
+        if (SCALED || !shi) {
+            Wt[o] = cvt<T>(wv * 0.5);
+        } else {
+            const float sa = split_scale(ascale[k], kSplitTopA);
+            const float vr = (float)(re * half) * sa, vi = (float)(im * half) * sa;
+            const _Float16 hr = (_Float16)vr, hi = (_Float16)vi;
+            const int64_t q = 2048 * blk + fr;
+            shi[q] = hr;
+            shi[q + 1024] = hi;
+            slo[q] = (_Float16)(vr - (float)hr);
+            slo[q + 1024] = (_Float16)(vi - (float)hi);
+        }
     }
     const int on = __syncthreads_or(any);
     if (threadIdx.x == 0) *fl = on ? 1 : 0;
 }
 
 // The receiver chunks (32 receivers each, at most 128) an emitter pass works
-// on, as wave-uniform bit masks, taken in increasing order.
+// on, as wave-uniform bit masks.  Bit 2 t stands for chunk t and bit 2 t + 1
+// for chunk t + half, half a ring further on, and the chunks are taken in bit
+// order: of each such pair a pass keeps about one, so that at any time the
+// passes of a tile, which start together, are on the same two chunks of G
+// and find them in L2 (taken in the order of the ring, the passes were four
+// chunks apart and L2 served a third of the requests).
 struct AdjChunks {
     uint64_t m0, m1;
+    __device__ __forceinline__ static int chunk(int bit, int half) { return (bit >> 1) + (bit & 1) * half; }
     __device__ __forceinline__ int count() const { return __popcll(m0) + __popcll(m1); }
-    __device__ __forceinline__ bool has(int c) const { return (((c < 64 ? m0 : m1) >> (c & 63)) & 1) != 0; }
-    // the next chunk (0 once there is none left; see count())
+    __device__ __forceinline__ bool has(int bit) const { return (((bit < 64 ? m0 : m1) >> (bit & 63)) & 1) != 0; }
+    // the next bit (0 once there is none left; see count())
     __device__ __forceinline__ int pop() {
         if (m0) {
             const int c = __ffsll((unsigned long long)m0) - 1;
@@ -291,6 +326,24 @@ struct AdjChunks {
         return c;
     }
 };
+
+// The chunks of `nq` emitter blocks from eb0 on: `all` of any of them, `mine`
+// of block eb0 + q.
+__device__ __forceinline__ void adj_chunks(const uint8_t *__restrict__ fl, int nb, int eb0, int nq, int q,
+                                           AdjChunks &all, AdjChunks &mine) {
+    const int lane = threadIdx.x & 63, half = (nb + 1) / 2;
+    all = mine = AdjChunks{0, 0};
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int bit = 64 * h + lane, c = AdjChunks::chunk(bit, half);
+        const bool ok = (bit >> 1) < half && c < nb;
+        for (int i = 0; i < nq; ++i) {
+            const uint64_t b = __ballot(ok && eb0 + i < nb && fl[(eb0 + i) * nb + c] != 0);
+            (h ? all.m1 : all.m0) |= b;
+            if (i == q) (h ? mine.m1 : mine.m0) = b;
+        }
+    }
+}
 
 // ------------------------------------------------------------------ FP32, LDS-staged
 // Backprojection.  The workgroup owns 64 pixels; its four waves are 2
@@ -305,6 +358,7 @@ struct AdjChunks {
 // two float4 loads (served from L2: A is shared by every workgroup),
 // prefetched one chunk ahead.
 constexpr int kAdjNT = 64, kAdjKC = 32, kAdjTile = kAdjKC * 64;
+constexpr int kT16NE = 128;   // emitters per pass of the kernels on the 16-bit cores (4 waves x 32)
 
 typedef __attribute__((address_space(3))) void lds_void_t;
 
@@ -468,10 +522,11 @@ struct AdjGroupArg {
 // its registers allow three workgroups per CU (34 KB of LDS each).  The
 // argument is one problem (AdjOne: grid = pixel tiles x frequencies) or a
 // group of problems (AdjGroup: flat grid over every problem's work items).
-template <bool HESS, typename A>
-__global__ void __launch_bounds__(256, HESS ? 2 : 3) k_adjoint_f32(const A args) {
-    typename A::Loc loc;
-    const AdjItem &it = args.locate(loc);
+// Pixel tile `tile` of frequency k: the partial of emitter-pass group qg of
+// npg, its passes [pass0, pass1) of 64 emitters.
+template <bool HESS>
+__device__ __forceinline__ void adj_f32_tile(const AdjItem &it, int64_t tile, int k, int npg, int qg, int pass0,
+                                             int pass1) {
     const AdjParams &P = it.P;
     const float *__restrict__ Gr = (const float *)it.Gr;
     const float *__restrict__ Gi = (const float *)it.Gi;
@@ -488,21 +543,16 @@ __global__ void __launch_bounds__(256, HESS ? 2 : 3) k_adjoint_f32(const A args)
     const int row = lane & 15, kk = lane >> 4;
     const int we = wave >> 1, wp = wave & 1;
     const int64_t N = P.N;
-    const int64_t x0 = (int64_t)loc.tile() * kAdjNT;
+    const int64_t x0 = tile * kAdjNT;
     const bool vec = ((N & 3) == 0) && (x0 + kAdjNT <= N);   // workgroup-uniform
     // this lane's column offsets in the swizzled tile (rows 4 s + kk)
     int coff[2];
 #pragma unroll
     for (int cb = 0; cb < 2; ++cb) coff[cb] = adj_off(kk, 32 * wp + 16 * cb + row) - kk * 64;
-    const int nch = P.mp / kAdjKC;
+    const int half = (P.nb + 1) / 2;   // see AdjChunks
     double gacc[2] = {0.0, 0.0}, hacc[2] = {0.0, 0.0};
-    // this workgroup's emitter passes (64 emitters each): group qg of npg
-    const int npg = A::kSplit ? it.npg : 1, qg = A::kSplit ? loc.group() : 0;
-    const int npass = P.mp / 64 + ((P.mp & 63) ? 1 : 0);
-    const int pass0 = A::kSplit ? qg * npass / npg : 0, pass1 = A::kSplit ? (qg + 1) * npass / npg : npass;
 
     {
-        const int k = loc.k();   // one frequency per workgroup (finer work units)
         const float *gr = Gr + (int64_t)k * P.m * N;
         const float *gi = Gi + (int64_t)k * P.m * N;
         const float *ar = Ar + (int64_t)k * P.mp * P.mp;
@@ -521,18 +571,8 @@ __global__ void __launch_bounds__(256, HESS ? 2 : 3) k_adjoint_f32(const A args)
             // the MFMAs of a chunk wait for the next chunk's tile, which is
             // issued first.  `all`: of either emitter half (staged), `mine`:
             // of this wave's half.
-            AdjChunks all{0, 0}, mine{0, 0};
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int c = 64 * h + lane;
-#pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    const int eb = (ec >> 5) + q;
-                    const uint64_t b = __ballot(eb < P.nb && c < nch && fl[eb * P.nb + c] != 0);
-                    (h ? all.m1 : all.m0) |= b;
-                    if (q == we) (h ? mine.m1 : mine.m0) = b;
-                }
-            }
+            AdjChunks all, mine;
+            adj_chunks(fl, P.nb, ec >> 5, 2, we, all, mine);
             const int nstep = all.count();
             // The A fragments of the next chunk are loaded during a chunk,
             // along with its G tile, so the MFMAs of a chunk wait only for LDS.
@@ -561,9 +601,9 @@ __global__ void __launch_bounds__(256, HESS ? 2 : 3) k_adjoint_f32(const A args)
             f4 va[2][2], vi[2][2], vw[2][2];
             bool on = false;
             if (nstep > 0) {   // workgroup-uniform
-                const int c = all.pop();
+                const int bit = all.pop(), c = AdjChunks::chunk(bit, half);
                 stage(c * kAdjKC, sB[0]);
-                on = mine.has(c);
+                on = mine.has(bit);
                 if (on) load_a(c * kAdjKC, va, vi, vw);
             }
             __builtin_amdgcn_s_waitcnt(0);   // this wave's direct-to-LDS loads have landed
@@ -573,9 +613,9 @@ __global__ void __launch_bounds__(256, HESS ? 2 : 3) k_adjoint_f32(const A args)
                 bool on_n = false;
                 f4 na[2][2], ni[2][2], nw[2][2];
                 if (s + 1 < nstep) {
-                    const int c = all.pop();
+                    const int bit = all.pop(), c = AdjChunks::chunk(bit, half);
                     stage(c * kAdjKC, sB[buf ^ 1]);
-                    on_n = mine.has(c);
+                    on_n = mine.has(bit);
                     if (on_n) load_a(c * kAdjKC, na, ni, nw);
                 }
                 if (on) adj_mma_steps<2, HESS>(va, vi, vw, sB[buf], sB[buf] + kAdjTile, kk, coff, p1, p2, p3, z, 0);
@@ -636,9 +676,36 @@ __global__ void __launch_bounds__(256, HESS ? 2 : 3) k_adjoint_f32(const A args)
     if (tid < kAdjNT) {
         const int64_t x = x0 + tid;
         if (x < N) {
-            pg[((int64_t)loc.k() * npg + qg) * N + x] = sred[0][0][tid] + sred[1][0][tid];
-            if (HESS) ph[((int64_t)loc.k() * npg + qg) * N + x] = sred[0][1][tid] + sred[1][1][tid];
+            pg[((int64_t)k * npg + qg) * N + x] = sred[0][0][tid] + sred[1][0][tid];
+            if (HESS) ph[((int64_t)k * npg + qg) * N + x] = sred[0][1][tid] + sred[1][1][tid];
         }
+    }
+}
+
+template <bool HESS, typename A>
+__global__ void __launch_bounds__(256, HESS ? 2 : 3) k_adjoint_f32(const A args) {
+    typename A::Loc loc;
+    const AdjItem &it = args.locate(loc);
+    // one frequency per workgroup (finer work units), and this workgroup's
+    // emitter passes (64 emitters each): group qg of npg
+    const int npg = A::kSplit ? it.npg : 1, qg = A::kSplit ? loc.group() : 0;
+    const int npass = (it.P.mp + 63) / 64;
+    adj_f32_tile<HESS>(it, loc.tile(), loc.k(), npg, qg, qg * npass / npg, (qg + 1) * npass / npg);
+}
+
+// The work items that k_adjoint_split listed, again from the FP32 tables and
+// operands: one of its items is two of this kernel's tiles, and each of its
+// passes two of this kernel's.
+__global__ void __launch_bounds__(256, 3) k_adjoint_f32_list(const AdjItem it) {
+    const int n = 2 * it.redo[0];
+    const int np16 = (it.P.mp + kT16NE - 1) / kT16NE, np = (it.P.mp + 63) / 64;
+    for (int i = blockIdx.x; i < n; i += gridDim.x) {
+        const int id = it.redo[1 + (i >> 1)], per = it.ntiles * it.npg;
+        const int k = id / per, rem = id - k * per, q = rem % it.npg;
+        const int64_t tile = 2 * (int64_t)(rem / it.npg) + (i & 1);
+        if (tile * kAdjNT < it.P.N)
+            adj_f32_tile<false>(it, tile, k, it.npg, q, 2 * (q * np16 / it.npg), min(2 * ((q + 1) * np16 / it.npg), np));
+        __syncthreads();   // the next item reuses the LDS
     }
 }
 
@@ -685,7 +752,6 @@ constexpr int kT16NT = 128;                   // pixels per tile
 constexpr int kT16KC = 32;                    // receivers per k-step
 constexpr int kT16Row = 2 * kT16NT;           // bytes per tile row
 constexpr int kT16Arr = kT16KC * kT16Row;     // bytes of one array of a tile
-constexpr int kT16NE = 128;                   // emitters per pass (4 waves x 32)
 
 typedef short t16v4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) t16v4 t16lds_v4;
@@ -719,6 +785,22 @@ __device__ __forceinline__ void t16_tr4(unsigned addr, t16v4 &a, t16v4 &b, t16v4
         "ds_read_b64_tr_b16 %3, %4 offset:9216\n\t"
         "s_waitcnt lgkmcnt(0)"
         : "=&v"(a), "=&v"(b), "=&v"(c), "=&v"(d)
+        : "v"(addr));
+}
+
+// The same for four arrays (k_adjoint_split): eight reads, one wait.
+__device__ __forceinline__ void t16_tr8(unsigned addr, t16v4 (&r)[8]) {
+    asm volatile(
+        "ds_read_b64_tr_b16 %0, %8\n\t"
+        "ds_read_b64_tr_b16 %1, %8 offset:1024\n\t"
+        "ds_read_b64_tr_b16 %2, %8 offset:8192\n\t"
+        "ds_read_b64_tr_b16 %3, %8 offset:9216\n\t"
+        "ds_read_b64_tr_b16 %4, %8 offset:16384\n\t"
+        "ds_read_b64_tr_b16 %5, %8 offset:17408\n\t"
+        "ds_read_b64_tr_b16 %6, %8 offset:24576\n\t"
+        "ds_read_b64_tr_b16 %7, %8 offset:25600\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(r[0]), "=&v"(r[1]), "=&v"(r[2]), "=&v"(r[3]), "=&v"(r[4]), "=&v"(r[5]), "=&v"(r[6]), "=&v"(r[7])
         : "v"(addr));
 }
 
@@ -806,7 +888,7 @@ __global__ void __launch_bounds__(256, HESS ? 1 : 2) k_adjoint16_tr(const A args
     const S *ai = Ai + (int64_t)k * P.mp * P.mp;
     const S *wt = Wt + (int64_t)k * P.mp * P.mp;
     const uint8_t *fl = flags + (int64_t)k * P.nb * P.nb;
-    const int nch = P.mp / kT16KC;
+    const int half = (P.nb + 1) / 2;   // see AdjChunks
     // lane's element offsets of its four direct-load chunks within a step
     unsigned goff[4];
 #pragma unroll
@@ -838,50 +920,40 @@ __global__ void __launch_bounds__(256, HESS ? 1 : 2) k_adjoint16_tr(const A args
         for (int b = 0; b < EB; ++b)
 #pragma unroll
             for (int cb = 0; cb < 8; ++cb) yr[b][cb] = yn[b][cb] = z[b][cb] = f4{0, 0, 0, 0};
-        unsigned aoff[EB];
-#pragma unroll
-        for (int b = 0; b < EB; ++b) aoff[b] = (unsigned)(min(e0 + 16 * b + row, P.mp - 1) * P.mp + 8 * kk);
+        // fragments of block (e0 / 32, c); emitter blocks beyond mp read the
+        // last one (their Y is dropped)
+        const int eblk = min(e0 >> 5, P.nb - 1) * P.nb;
         auto load_a = [&](int c, V (&va)[EB], V (&vi)[EB], V (&vw)[EB]) {
-            const int co = c * kT16KC;   // uniform
+            const int64_t co = (int64_t)(eblk + c) * 1024;   // uniform
 #pragma unroll
             for (int b = 0; b < EB; ++b) {
-                va[b] = *reinterpret_cast<const V *>(ar + co + aoff[b]);
-                vi[b] = *reinterpret_cast<const V *>(ai + co + aoff[b]);
-                if (HESS) vw[b] = *reinterpret_cast<const V *>(wt + co + aoff[b]);
+                va[b] = *reinterpret_cast<const V *>(ar + co + 512 * b + 8 * lane);
+                vi[b] = *reinterpret_cast<const V *>(ai + co + 512 * b + 8 * lane);
+                if (HESS) vw[b] = *reinterpret_cast<const V *>(wt + co + 512 * b + 8 * lane);
             }
         };
         // the pass's receiver chunks: `all` of its four waves (staged), `mine`
         // of this wave's 32 emitters
-        AdjChunks all{0, 0}, mine{0, 0};
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int c = 64 * h + lane;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int eb = (ec >> 5) + q;
-                const uint64_t b = __ballot(eb < P.nb && c < nch && fl[eb * P.nb + c] != 0);
-                (h ? all.m1 : all.m0) |= b;
-                if (q == wave) (h ? mine.m1 : mine.m0) = b;
-            }
-        }
+        AdjChunks all, mine;
+        adj_chunks(fl, P.nb, ec >> 5, 4, wave, all, mine);
         const int nstep = all.count();
         // the chunks of the current step and the next two (opaque to the
         // compiler, which would otherwise keep a strength-reduced address per
         // unrolled step live in registers)
-        auto next_chunk = [&]() {
+        auto next_bit = [&]() {
             int c = all.pop();
             asm volatile("" : "+s"(c));
             return c;
         };
-        int c0 = next_chunk(), c1 = next_chunk(), c2 = next_chunk();
+        int b0 = next_bit(), b1 = next_bit(), b2 = next_bit();
         auto stage = [&](int c, unsigned char *dst, auto vtag) {
             if (decltype(vtag)::value)
                 t16_stage_async(gr + ((int64_t)c * kT16KC * N + x0), gi + ((int64_t)c * kT16KC * N + x0), goff, dst);
             else
                 t16_stage_regs(gr, gi, P.m, N, c * kT16KC, x0, dst);
         };
-        // One k-step s (chunk c0) on the tile in buffer s mod 4: wait for its
-        // tile and A(c0), issue A(c1) and the tile of step s + 2 (chunk c2),
+        // One k-step s (chunk bit b0) on the tile in buffer s mod 4: wait for
+        // its tile and its A, issue A of b1 and the tile of step s + 2 (b2),
         // then the MFMAs.  Per step a wave issues A(s + 1) (2 EB or
         // 3 EB loads) and then the tile of s + 2 (4 direct loads), so at the
         // wait only the tile of s + 1 may still be in flight.  `mode` says
@@ -899,14 +971,14 @@ __global__ void __launch_bounds__(256, HESS ? 1 : 2) k_adjoint16_tr(const A args
             else
                 __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
             lds_barrier();
-            const bool on = mine.has(c0);
-            if (has_a) load_a(c1, na, ni, nw);
+            const bool on = mine.has(b0);
+            if (has_a) load_a(AdjChunks::chunk(b1, half), na, ni, nw);
             __builtin_amdgcn_sched_barrier(0);
-            if (has_t) stage(c2, buf(Idx<I + 2>()), vtag);
+            if (has_t) stage(AdjChunks::chunk(b2, half), buf(Idx<I + 2>()), vtag);
             __builtin_amdgcn_sched_barrier(0);
-            c0 = c1;
-            c1 = c2;
-            c2 = next_chunk();
+            b0 = b1;
+            b1 = b2;
+            b2 = next_bit();
             if (!on) return;
             const unsigned char *sb = buf(Idx<I>());
             V nva[EB];
@@ -942,12 +1014,12 @@ __global__ void __launch_bounds__(256, HESS ? 1 : 2) k_adjoint16_tr(const A args
             using M0 = std::integral_constant<int, 0>;
             V va[EB], vi[EB], vw[EB], na[EB], ni[EB], nw[EB];
             lds_barrier();   // the previous pass is done with the tile buffers
-            stage(c0, sG0, vtag);
-            load_a(c0, va, vi, vw);
+            stage(AdjChunks::chunk(b0, half), sG0, vtag);
+            load_a(AdjChunks::chunk(b0, half), va, vi, vw);
             // unconditional (a one-chunk pass stages chunk 0, unused), so that
             // the loop is always entered with the same loads in flight and
             // the compiler's load-counter waits at its head stay exact
-            stage(c1, sG1, vtag);
+            stage(AdjChunks::chunk(b1, half), sG1, vtag);
             int s = 0;
             for (; s + 6 <= nstep; s += 4) {
                 kstep(s, Idx<0>(), va, vi, vw, na, ni, nw, vtag, M3());
@@ -1050,6 +1122,293 @@ __global__ void __launch_bounds__(256, HESS ? 1 : 2) k_adjoint16_tr(const A args
 }
 
 
+// ------------------------------------------------------------------ FP32 tables on the FP16 matrix cores
+// Gradient-only backprojection of FP32 tables with every operand split into
+// two FP16 pieces, x s = hi + lo: hi = x s rounded to FP16, lo = the exact
+// remainder rounded to FP16, s a power of two.  hi hi + hi lo + lo hi on the
+// 16x16x32 FP16 cores (products exact, FP32 accumulation) keeps about 22 bits
+// of every product, and an MFMA sums 32 products at a time instead of 4, so
+// that the result is nearer to FP64 than the FP32 cores' (relative L2 error of
+// the gradient, rounded to FP32: 1024 elements / 1100^2 8.1e-8 -> 6.3e-8, 256 /
+// 480^2 1.4e-7 -> 1.2e-7).
+//
+// 1024 elements / 1100^2, four frequencies: 107.9 ms on the FP32 cores, 43.0
+// ms here (12 MFMAs per complex product of blocks: 1.1 PFLOP/s).  The matrix
+// cores are busy 0.55 of the time at 1.9 GHz, the clock that the card's power
+// leaves (2.3 GHz at 0.36 busy), so what is left is mostly power.  256 / 480^2,
+// three frequencies: 1.59 -> 0.77 ms.  On the way there: rows of G loaded half
+// a chunk ahead 55.1 ms, passes four chunks apart (AdjChunks) 64.8 ms.
+//
+// Scales: A by its largest magnitude per frequency; G per (frequency, pixel)
+// by its largest magnitude over kSplitRows sampled elements, brought to 2^9
+// (k_adj_colscale).  FP16 then has 2^7 of headroom over the sampled maximum
+// and resolves 2^-32 of it.  A workgroup that meets a |G s| beyond the range
+// (nonzero G at a pixel that no sampled element reaches; infinities) puts its
+// work item on a list, and k_adjoint_f32_list computes it from FP32, so that
+// any table an FP32 call accepts gives an FP32 result.
+//
+// Workgroup tile, receiver chunks, transposing reads and LDS swizzle are
+// those of k_adjoint16_tr; here a chunk's 32 x 128 FP32 tile passes through
+// registers (four float4 per array and thread, loaded during the MFMAs of the
+// previous chunk), is split there once for all four waves and stored as four
+// FP16 arrays of 8 KB, double buffered.
+constexpr int kSplitRows = 16, kSplitRowsMore = 128;
+constexpr float kSplitMax = 65504.0f;   // largest FP16 value
+typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+
+// scale[k][x] = split_scale(max over the sampled rows of |re|, |im|).  Pixels
+// that none of the kSplitRows rows covers (outside the ring, or at its edge,
+// where rays end) take kSplitRowsMore rows; 2^100 where those are zero too,
+// so that any normal value of the other rows overflows.  Also clears what
+// the following launches accumulate into: amax [nf] and the list's length.
+__global__ void __launch_bounds__(256) k_adj_colscale(int m, int nf, int64_t N, const float *__restrict__ Gr,
+                                                      const float *__restrict__ Gi, float *__restrict__ scale,
+                                                      float *__restrict__ amax, int *__restrict__ redo) {
+    const int k = blockIdx.y;
+    const int64_t x = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (blockIdx.x == 0 && k == 0) {
+        if (threadIdx.x < nf) amax[threadIdx.x] = 0.0f;
+        if (threadIdx.x == 0) redo[0] = 0;
+    }
+    if (x >= N) return;
+    const float *gr = Gr + (int64_t)k * m * N + x, *gi = Gi + (int64_t)k * m * N + x;
+    float top = 0.0f;
+#pragma unroll
+    for (int q = 0; q < kSplitRows; ++q) {
+        const int64_t r = (int64_t)q * m / kSplitRows;
+        top = fmaxf(top, fmaxf(fabsf(gr[r * N]), fabsf(gi[r * N])));
+    }
+    if (!(top > 0.0f)) {
+        const int nr = min(m, kSplitRowsMore);
+#pragma unroll 8
+        for (int q = 0; q < nr; ++q) {
+            const int64_t r = (int64_t)q * m / nr;
+            top = fmaxf(top, fmaxf(fabsf(gr[r * N]), fabsf(gi[r * N])));
+        }
+    }
+    scale[(int64_t)k * N + x] = top > 0.0f ? split_scale(top, kSplitTopG) : 0x1p100f;
+}
+
+template <typename A>
+__global__ void __launch_bounds__(256, 2) k_adjoint_split(const A args) {
+    typename A::Loc loc;
+    const AdjItem &it = args.locate(loc);
+    const AdjParams &P = it.P;
+    const uint8_t *__restrict__ flags = it.flags;
+    double *__restrict__ pg = it.pg;
+    constexpr int EB = 2;   // 16-row emitter blocks per wave
+    __shared__ __align__(16) unsigned char sT[2][4 * kT16Arr];   // re hi, im hi, re lo, im lo
+    __shared__ float sred[4][kT16NT];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int row = lane & 15, kk = lane >> 4;
+    const int64_t N = P.N;
+    const int k = loc.k();
+    const int64_t x0 = (int64_t)loc.tile() * kT16NT;
+    const float *__restrict__ gr = (const float *)it.Gr + (int64_t)k * P.m * N;
+    const float *__restrict__ gi = (const float *)it.Gi + (int64_t)k * P.m * N;
+    const bool vec = ((N & 3) == 0) && (x0 + kT16NT <= N);   // workgroup-uniform
+    const int64_t per = (int64_t)P.mp * P.mp;
+    const _Float16 *__restrict__ ahi = (const _Float16 *)it.split_hi + 2 * k * per;
+    const _Float16 *__restrict__ alo = (const _Float16 *)it.split_lo + 2 * k * per;
+    const uint8_t *fl = flags + (int64_t)k * P.nb * P.nb;
+    const float *__restrict__ sc = it.pscale + (int64_t)k * N;
+    const int half = (P.nb + 1) / 2;   // see AdjChunks
+
+    // staging: this thread's four pixels (p4 ..) of tile rows r8 + 8 j
+    const int p4 = (tid & 31) * 4, r8 = tid >> 5;
+    f4 ps;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) ps[q] = sc[min(x0 + p4 + q, N - 1)];
+    float top = 0.0f;   // largest |G s| this thread has staged
+    // byte offsets are taken from the chunk's first row and pixel, uniform
+    // bases, and fit 32 bits (32 N < 2^30 elements)
+    auto at = [](const float *base, unsigned off) {
+        return reinterpret_cast<const float *>(reinterpret_cast<const char *>(base) + off);
+    };
+    const unsigned nb4 = 4u * (unsigned)N;
+    const int xl = (int)min(N - 1 - x0, (int64_t)kT16NT);   // last pixel of the tile's range
+    auto load = [&](const float *__restrict__ g, int c, f4 (&v)[4], auto vtag) {
+        const float *base = g + (int64_t)c * kT16KC * N + x0;
+        const int rl = P.m - 1 - c * kT16KC;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            // rows at or beyond m read row m - 1: their A entries are zero;
+            // pixels at or beyond N read the last one: theirs are dropped
+            const unsigned ro = (unsigned)min(r8 + 8 * j, rl) * nb4;
+            if (decltype(vtag)::value) {
+                v[j] = *reinterpret_cast<const f4 *>(at(base, ro + 4u * p4));
+            } else {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) v[j][q] = *at(base, ro + 4u * (unsigned)min(p4 + q, xl));
+            }
+        }
+    };
+    auto store = [&](const f4 (&v)[4], unsigned char *hi, unsigned char *lo) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const f4 w = v[j] * ps;
+            const h4 h = __builtin_convertvector(w, h4);
+            f4 rem;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) rem[q] = __builtin_fmaf(v[j][q], ps[q], -(float)h[q]);
+            const h4 l = __builtin_convertvector(rem, h4);
+            top = fmaxf(top, fmaxf(fmaxf(fabsf(w[0]), fabsf(w[1])), fmaxf(fabsf(w[2]), fabsf(w[3]))));
+            const int o = t16_off(r8 + 8 * j, p4);
+            *reinterpret_cast<h4 *>(hi + o) = h;
+            *reinterpret_cast<h4 *>(lo + o) = l;
+        }
+    };
+    // transposing-read offset of column block 0, rows 8 kk + (row >> 2);
+    // block cb is at t0 ^ 32 cb (the swizzle is an XOR of the chunk number), the
+    // rows 4 further on at + 4 kT16Row
+    const int t0 = t16_off(8 * kk + (row >> 2), 4 * (row & 3));
+    float gp[8];
+#pragma unroll
+    for (int cb = 0; cb < 8; ++cb) gp[cb] = 0.0f;
+
+    const int npass = (P.mp + kT16NE - 1) / kT16NE, npg = it.npg, qg = loc.group();
+    const int pass0 = qg * npass / npg, pass1 = (qg + 1) * npass / npg;
+    for (int ec = pass0 * kT16NE; ec < pass1 * kT16NE; ec += kT16NE) {
+        const int e0 = ec + 32 * wave;
+        f4 yr[EB][8], yn[EB][8];
+#pragma unroll
+        for (int b = 0; b < EB; ++b)
+#pragma unroll
+            for (int cb = 0; cb < 8; ++cb) yr[b][cb] = yn[b][cb] = f4{0, 0, 0, 0};
+        AdjChunks all, mine;
+        adj_chunks(fl, P.nb, ec >> 5, 4, wave, all, mine);
+        const int nstep = all.count();
+        // fragments [re hi, im hi, re lo, im lo][b] of block (e0 / 32, c)
+        const int eblk = min(e0 >> 5, P.nb - 1) * P.nb;
+        auto load_a = [&](int c, h8 (&a)[4][EB]) {
+            const int64_t o = (int64_t)(eblk + c) * 2048 + 8 * lane;
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int b = 0; b < EB; ++b)
+                    a[t][b] = *reinterpret_cast<const h8 *>((t < 2 ? ahi : alo) + o + 1024 * (t & 1) + 512 * b);
+        };
+        auto mma_cb = [&](unsigned sba, const h8 (&a)[4][EB], const h8 (&n)[2][EB], int cb) {
+            using M = MM16<__half>;
+            t16v4 r[8];
+            t16_tr8(sba + (unsigned)(t0 ^ (32 * cb)), r);
+            const h8 b0 = t16_join<h8>(r[0], r[1]), b1 = t16_join<h8>(r[2], r[3]);
+            const h8 b2 = t16_join<h8>(r[4], r[5]), b3 = t16_join<h8>(r[6], r[7]);
+            auto term = [&](const h8 (&x)[EB], const h8 &u, const h8 (&y)[EB], const h8 &v) {
+#pragma unroll
+                for (int b = 0; b < EB; ++b) {
+                    yr[b][cb] = M::mma(x[b], u, yr[b][cb]);
+                    yn[b][cb] = M::mma(y[b], v, yn[b][cb]);
+                }
+            };
+            term(a[0], b0, a[0], b1);
+            term(a[1], b1, n[0], b0);
+            term(a[0], b2, a[0], b3);
+            term(a[1], b3, n[0], b2);
+            term(a[2], b0, a[2], b1);
+            term(a[3], b1, n[1], b0);
+        };
+        // the MFMAs of the chunk in buffer s mod 2
+        auto mma = [&](int s, const h8 (&a)[4][EB]) {
+            const unsigned sba =
+                (unsigned)(uintptr_t)(const __attribute__((address_space(3))) unsigned char *)sT[s & 1];
+            h8 n[2][EB];
+#pragma unroll
+            for (int b = 0; b < EB; ++b) {
+                n[0][b] = neg(a[1][b]);
+                n[1][b] = neg(a[3][b]);
+            }
+#pragma unroll
+            for (int cb = 0; cb < 8; ++cb) mma_cb(sba, a, n, cb);
+        };
+        // The steps but the last issue the next chunk's loads without a
+        // condition, so that the compiler's load-counter waits stay exact: the
+        // rows of G at the start, used at the end, and A, whose registers are
+        // in use until then, before the conversions.
+        auto kloop = [&](auto vtag) {
+            f4 vr[4], vi[4];
+            h8 a[4][EB];
+            int bit = all.pop(), c = AdjChunks::chunk(bit, half);
+            load(gr, c, vr, vtag);
+            load(gi, c, vi, vtag);
+            load_a(c, a);
+            lds_barrier();   // the previous pass is done with the tile buffers
+            store(vr, sT[0], sT[0] + 2 * kT16Arr);
+            store(vi, sT[0] + kT16Arr, sT[0] + 3 * kT16Arr);
+            int s = 0;
+            for (; s + 1 < nstep; ++s) {
+                lds_barrier();   // chunk s is in LDS, and no wave still reads the other buffer
+                const bool on = mine.has(bit);
+                bit = all.pop();
+                c = AdjChunks::chunk(bit, half);
+                load(gr, c, vr, vtag);
+                load(gi, c, vi, vtag);
+                __builtin_amdgcn_sched_barrier(0);
+                if (on) mma(s, a);
+                load_a(c, a);
+                __builtin_amdgcn_sched_barrier(0);
+                unsigned char *sn = sT[(s & 1) ^ 1];
+                store(vr, sn, sn + 2 * kT16Arr);
+                store(vi, sn + kT16Arr, sn + 3 * kT16Arr);
+            }
+            lds_barrier();
+            if (mine.has(bit)) mma(s, a);
+        };
+        if (nstep > 0) {   // workgroup-uniform
+            if (vec)
+                kloop(std::true_type());
+            else
+                kloop(std::false_type());
+        }
+        // fused epilogue: Re sum_e conj(G_e) Y_e, with G_e in FP32.  Rows at or
+        // beyond m read row m - 1 (their Y is zero), pixels at or beyond N the
+        // last one (dropped below).
+        if (e0 < P.mp) {   // wave-uniform
+            const float *br = gr + (int64_t)e0 * N + x0, *bi = gi + (int64_t)e0 * N + x0;
+            const int rl = P.m - 1 - e0;
+#pragma unroll
+            for (int b = 0; b < EB; ++b) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const unsigned ro = (unsigned)min(16 * b + 4 * kk + i, rl) * nb4;
+                    float ger[8], gei[8];
+#pragma unroll
+                    for (int cb = 0; cb < 8; ++cb) {
+                        const unsigned o = ro + 4u * (unsigned)min(16 * cb + row, xl);
+                        ger[cb] = *at(br, o);
+                        gei[cb] = *at(bi, o);
+                    }
+#pragma unroll
+                    for (int cb = 0; cb < 8; ++cb) gp[cb] += ger[cb] * yr[b][cb][i] - gei[cb] * yn[b][cb][i];
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        }
+    }
+    const int beyond = __syncthreads_or(!(top < kSplitMax));
+    if (beyond && tid == 0)
+        it.redo[1 + atomicAdd(it.redo, 1)] = (int)(((int64_t)k * it.ntiles + loc.tile()) * npg + qg);
+    // the four lane groups of a column, then the waves, in a fixed order
+#pragma unroll
+    for (int cb = 0; cb < 8; ++cb) {
+        float g = gp[cb];
+        g += __shfl_xor(g, 16);
+        g += __shfl_xor(g, 32);
+        if (kk == 0) sred[wave][16 * cb + row] = g;
+    }
+    __syncthreads();
+    if (tid < kT16NT) {
+        const int64_t x = x0 + tid;
+        if (x < N) {
+            const double g = ((double)sred[0][tid] + (double)sred[1][tid]) +
+                             ((double)sred[2][tid] + (double)sred[3][tid]);
+            const double s = (double)split_scale(it.ascale[k], kSplitTopA) * (double)sc[x];
+            pg[((int64_t)k * npg + qg) * N + x] = g * P.cg[k] / s;
+        }
+    }
+}
+
 // grad += sum_k sum_q pg[k][q], hd += sum_k sum_q ph[k][q] in frequency
 // order, then emitter-pass group order.
 __global__ void k_adj_sum(int64_t N, int nf, int npg, const double *__restrict__ pg, const double *__restrict__ ph,
@@ -1069,6 +1428,8 @@ __global__ void k_adj_sum(int64_t N, int nf, int npg, const double *__restrict__
 
 // ---------------------------------------------------------------- host side
 // rows/columns of the adjoint operands are padded to a multiple of 32
+constexpr int kRedoBlocks = 768;   // of k_adjoint_f32_list: three per compute unit
+
 static int pad_m(int m) { return (m + 31) / 32 * 32; }
 
 static AdjParams adj_params(const rb_geometry *g, const double *freqs, int nf) {
@@ -1118,6 +1479,29 @@ static int adj_groups(const rb_geometry *g, rb_dtype dt) {
     return npass >= 4 ? npass : 1;
 }
 
+// Whether a gradient-only FP32 problem takes k_adjoint_split: from 65
+// elements (a pass has 128, and at 64 half of its waves are idle) and with
+// more workgroups than compute units.  us per call, k_adjoint_f32 against
+// k_adjoint_split, two frequencies: 64 elements / 480^2 156 / 163, 80 / 480^2
+// 291 / 200, 96 / 128^2 (256 workgroups) 39 / 43, 96 / 256^2 103 / 75, 128 /
+// 256^2 130 / 86, 256 / 181^2 209 / 122, 512 / 480^2 2947 / 1314; one
+// frequency, 256 / 128x150 (300 workgroups) 70 / 61.
+static bool adj_split(const rb_geometry *g, int nf, rb_dtype dt, bool hess) {
+    if (dt != RB_F32 || hess || g->m <= 64) return false;
+    const int npass = (pad_m(g->m) + kT16NE - 1) / kT16NE;
+    const int64_t tiles = blocks_for((int64_t)g->nx * g->ny, kT16NT);
+    if (nf * tiles * (adj_groups(g, dt) > 1 ? npass : 1) <= 256) return false;
+    if ((int64_t)g->nx * g->ny >= (int64_t)1 << 25) return false;   // 32-bit offsets within 32 rows
+    // its high operands live in place of W, the low ones and the scales in
+    // the Hessian partials, neither of which a gradient needs
+    const int64_t mp = pad_m(g->m), N = (int64_t)g->nx * g->ny;
+    Carver c(nullptr, 0);
+    c.take<_Float16>((size_t)nf * 2 * mp * mp);
+    c.take<float>((size_t)nf * N);
+    c.take<int>(1 + (size_t)nf * blocks_for(N, kT16NT) * adj_groups(g, dt));
+    return c.used <= (size_t)nf * adj_groups(g, dt) * N * sizeof(double);
+}
+
 static AdjWs carve_adj(Carver &c, const rb_geometry *g, int nf, rb_dtype dt) {
     const int mp = pad_m(g->m);
     const size_t npg = (size_t)adj_groups(g, dt);
@@ -1151,6 +1535,24 @@ rb_status adjoint_prepare(const rb_geometry *g, const void *G_re, const void *G_
     AdjWs w = carve_adj(c, g, nf, dt);
     AdjParams P = adj_params(g, freqs, nf);
     const dim3 gp(P.nb * P.nb, nf);
+    AdjItem &it = task->item;
+    it.split_hi = it.split_lo = nullptr;
+    it.pscale = nullptr;
+    it.redo = nullptr;
+    task->split = adj_split(g, nf, dt, hdiag != nullptr);
+    if (task->split) {
+        Carver h(w.ph, (size_t)-1);
+        it.split_hi = w.Wt;
+        it.split_lo = h.take<_Float16>((size_t)nf * 2 * P.mp * P.mp);
+        float *ps = h.take<float>((size_t)nf * P.N);
+        it.pscale = ps;
+        it.redo = h.take<int>(1 + (size_t)nf * blocks_for(P.N, kT16NT) * adj_groups(g, dt));
+        k_adj_colscale<<<dim3(blocks_for(P.N, 256), nf), 256, 0, st>>>(
+            g->m, nf, P.N, (const float *)G_re, (const float *)G_im, ps, w.ascale, it.redo);
+        RB_LAUNCHED();
+        k_adj_amax<<<gp, 256, 0, st>>>(g->m, P.nb, d_res, w_data, reinterpret_cast<unsigned *>(w.ascale));
+        RB_LAUNCHED();
+    }
     if (dt == RB_BF16 || dt == RB_F16) {
         RB_TRY(fill_f32(w.ascale, 0.0f, nf, st));
         k_adj_amax<<<gp, 256, 0, st>>>(g->m, P.nb, d_res, w_data, reinterpret_cast<unsigned *>(w.ascale));
@@ -1162,21 +1564,21 @@ rb_status adjoint_prepare(const rb_geometry *g, const void *G_re, const void *G_
                                                           (double *)w.Ai, (double *)w.Wt, w.flags);
             break;
         case RB_F32:
-            k_adj_prep<float, false, true><<<gp, 256, 0, st>>>(g->m, P.mp, d_res, w_data, nullptr, (float *)w.Ar,
-                                                               (float *)w.Ai, (float *)w.Wt, w.flags);
+            k_adj_prep<float, false, 1><<<gp, 256, 0, st>>>(g->m, P.mp, d_res, w_data, w.ascale, (float *)w.Ar,
+                                                               (float *)w.Ai, (float *)w.Wt, w.flags,
+                                                               (_Float16 *)it.split_hi, (_Float16 *)it.split_lo);
             break;
         case RB_BF16:
-            k_adj_prep<__hip_bfloat16, true><<<gp, 256, 0, st>>>(g->m, P.mp, d_res, w_data, w.ascale,
+            k_adj_prep<__hip_bfloat16, true, 2><<<gp, 256, 0, st>>>(g->m, P.mp, d_res, w_data, w.ascale,
                                                                  (__hip_bfloat16 *)w.Ar, (__hip_bfloat16 *)w.Ai,
                                                                  (__hip_bfloat16 *)w.Wt, w.flags);
             break;
         case RB_F16:
-            k_adj_prep<__half, true><<<gp, 256, 0, st>>>(g->m, P.mp, d_res, w_data, w.ascale, (__half *)w.Ar,
+            k_adj_prep<__half, true, 2><<<gp, 256, 0, st>>>(g->m, P.mp, d_res, w_data, w.ascale, (__half *)w.Ar,
                                                          (__half *)w.Ai, (__half *)w.Wt, w.flags);
             break;
     }
     RB_LAUNCHED();
-    AdjItem &it = task->item;
     it.P = P;
     it.Gr = G_re;
     it.Gi = G_im;
@@ -1188,9 +1590,10 @@ rb_status adjoint_prepare(const rb_geometry *g, const void *G_re, const void *G_
     it.ascale = w.ascale;
     it.pg = w.pg;
     it.ph = w.ph;
-    it.ntiles = (int)blocks_for(P.N, dt == RB_F32 ? kAdjNT : kT16NT);
+    it.ntiles = (int)blocks_for(P.N, dt == RB_F32 && !task->split ? kAdjNT : kT16NT);
     it.begin = 0;
-    it.npg = adj_groups(g, dt);
+    // (fewer than four passes of k_adjoint_f32: one group, as carved)
+    it.npg = task->split && adj_groups(g, dt) > 1 ? (P.mp + kT16NE - 1) / kT16NE : adj_groups(g, dt);
     task->dt = dt;
     task->grad = grad;
     task->hdiag = hdiag;
@@ -1211,7 +1614,11 @@ rb_status adjoint_run(const AdjTask &task, hipStream_t st) {
             break;
         }
         case RB_F32: {
-            if (it.npg == 1) {
+            if (task.split) {
+                k_adjoint_split<<<dim3((unsigned)it.ntiles * it.npg, nf), 256, 0, st>>>(AdjOneSplit{it});
+                RB_LAUNCHED();
+                k_adjoint_f32_list<<<kRedoBlocks, 256, 0, st>>>(it);
+            } else if (it.npg == 1) {
                 dim3 ga(blocks_for(P.N, kAdjNT), nf);
                 const AdjOne one{it};
                 if (hdiag)
@@ -1255,9 +1662,9 @@ rb_status adjoint_run(const AdjTask &task, hipStream_t st) {
 }
 
 rb_status adjoint_run_grouped(AdjTask *const *tasks, int n, hipStream_t st) {
-    // contraction type and variant of a task: f32 / bf16 / f16, with or
-    // without the Hessian diagonal; f64 runs alone
-    auto kind = [](const AdjTask &t) { return 2 * (int)t.dt + (t.hdiag ? 1 : 0); };
+    // contraction type and variant of a task: f32 / bf16 / f16, FP32 on the
+    // FP16 cores, with or without the Hessian diagonal; f64 runs alone
+    auto kind = [](const AdjTask &t) { return 4 * (int)t.dt + (t.split ? 2 : 0) + (t.hdiag ? 1 : 0); };
     bool done[256] = {};
     RB_CHECK_ARG(n >= 0 && n <= 256, "grouped backprojection: %d problems (at most 256)", n);
     for (int i = 0; i < n; ++i) {
@@ -1286,7 +1693,14 @@ rb_status adjoint_run_grouped(AdjTask *const *tasks, int n, hipStream_t st) {
         const bool hess = tasks[i]->hdiag != nullptr;
         switch (tasks[i]->dt) {
             case RB_F32:
-                if (hess)
+                if (tasks[i]->split) {
+                    k_adjoint_split<<<(unsigned)blocks, 256, 0, st>>>(arg);
+                    RB_LAUNCHED();
+                    for (int q = 0; q < G.n; ++q) {
+                        k_adjoint_f32_list<<<kRedoBlocks, 256, 0, st>>>(tasks[idx[q]]->item);
+                        RB_LAUNCHED();
+                    }
+                } else if (hess)
                     k_adjoint_f32<true><<<(unsigned)blocks, 256, 0, st>>>(arg);
                 else
                     k_adjoint_f32<false><<<(unsigned)blocks, 256, 0, st>>>(arg);

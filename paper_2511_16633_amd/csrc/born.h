@@ -25,6 +25,11 @@ struct AdjItem {
     double *pg, *ph;
     int ntiles, begin;
     int npg;   // emitter-pass groups per pixel tile, each a workgroup of its own (partials [nf][npg][N])
+    // FP32 tables on the FP16 cores: split operands, G scales [nf][N], and
+    // the list of work items to compute in FP32 (its length, then the items)
+    void *split_hi, *split_lo;
+    const float *pscale;
+    int *redo;
 };
 constexpr int kAdjGroupMax = 8;   // problems per grouped launch (kernel-argument size)
 struct AdjGroup {
@@ -37,6 +42,7 @@ struct AdjGroup {
 struct AdjTask {
     AdjItem item;
     rb_dtype dt;
+    bool split;   // FP32 tables, gradient by k_adjoint_split
     double *grad, *hdiag;
 };
 

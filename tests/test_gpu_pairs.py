@@ -76,3 +76,74 @@ def test_adjoint_of_unsymmetric_data_and_weights(rb, dtype, shape):
         close(grad.cpu().numpy(), g_o, TOL[dtype], f"grad {dtype} {shape} hess={hess}")
         if hess:
             close(hd.cpu().numpy(), h_o, TOL[dtype], f"hdiag {dtype} {shape}")
+
+
+def _random_g(nf, m, N, seed):
+    rng = np.random.default_rng(seed)
+    mag = np.exp(rng.uniform(np.log(1e-2), 0.0, (nf, m, N)))      # two decades
+    ph = rng.uniform(0.0, 2 * np.pi, (nf, m, N))
+    return (mag * np.cos(ph)).astype(np.float32), (mag * np.sin(ph)).astype(np.float32)
+
+
+def _gradient(rb, geom, gr, gi, freqs, D, w):
+    grad = torch.zeros(geom.n_pixels, dtype=torch.float64, device=DEV)
+    rb.born_adjoint_weighted(geom, torch.as_tensor(gr, device=DEV), torch.as_tensor(gi, device=DEV), None, "f32", freqs,
+                             torch.as_tensor(np.stack([D.real, D.imag], -1), device=DEV),
+                             torch.as_tensor(w, device=DEV), grad, None)
+    return grad.cpu().numpy()
+
+
+# FP32 gradients large enough for the FP16 matrix cores (k_adjoint_split): odd
+# pixel counts and rows that are not 16-byte aligned, the last tile holding 1
+# to 127 pixels, rings of whole and partial 32- and 128-element blocks, one and
+# several emitter passes per workgroup.  2e-6 is 40 times 2^-24 sqrt(2 rounding
+# steps per MFMA of a 1024-receiver row): the FP32 kernel's own bound is 1e-5.
+@pytest.mark.parametrize("shape", [(137, 143, 256), (160, 128, 300), (200, 181, 130), (190, 190, 515), (129, 257, 192),
+                                   (183, 180, 65), (257, 256, 96)])
+def test_fp32_gradient_in_two_fp16_pieces(rb, shape):
+    nx, ny, m = shape
+    geom, freqs = _geom(nx, ny, m), [3e5, 7e5]
+    print(f"[gpu-test] split gradient {shape}", flush=True)
+    gr, gi = _random_g(2, m, geom.n_pixels, 7)
+    D = W.random_residual(2, m, 8)
+    w = np.random.default_rng(9).uniform(0.0, 2.0, (2, m, m))
+    w[:, :32, 32:64] = w[:, 32:64, :32] = 0.0
+    ref = sum(born.born_adjoint(gr[k] + 1j * gi[k].astype(np.float64), w[k] * D[k], f, geom.h ** 2)
+              for k, f in enumerate(freqs))
+    close(_gradient(rb, geom, gr, gi, freqs, D, w), ref, 2e-6, f"split gradient {shape}")
+
+
+def test_fp32_gradient_outside_the_fp16_range(rb):
+    """Pixels whose tables a 16-element sample misjudges or that FP16 cannot
+    hold: each pixel must be as exact as an FP32 contraction makes it, whatever
+    its neighbours hold (errors relative to the pixel's own value)."""
+    nx, ny, m = 140, 144, 256
+    geom, freqs = _geom(nx, ny, m), [4e5]
+    N = geom.n_pixels
+    print("[gpu-test] split gradient, wide-ranging tables", flush=True)
+    gr, gi = _random_g(1, m, N, 10)
+    s = np.ones((m, N), np.float32)
+    s[:, :4096] = np.float32(2.0) ** np.random.default_rng(11).integers(-60, 40, 4096)   # any scale per pixel
+    s[::16, 5000:5100] = 0.0           # sampled elements see nothing
+    s[::16, 6000:6050] = 1e-6          # ... or a millionth
+    s[7, 7000:7003] = 3e5              # one element far above the sample
+    s[:, 8000:8200] = 0.0              # uncovered by every element
+    gr, gi = gr * s, gi * s
+    D = W.random_residual(1, m, 12)
+    w = np.ones((1, m, m))
+    g = gr[0] + 1j * gi[0].astype(np.float64)
+    ref = born.born_adjoint(g, D[0], freqs[0], geom.h ** 2)
+    size = (2 * np.pi * freqs[0]) ** 2 * geom.h ** 2 * (np.abs(g) * (np.abs(D[0]) @ np.abs(g))).sum(0)
+    got = _gradient(rb, geom, gr, gi, freqs, D, w)
+    assert np.all(got[8000:8200] == 0.0)
+    ok = size > 0
+    # |error| <= 2^-24 (sqrt(256) additions + 2 roundings) of the sum of magnitudes
+    assert np.max(np.abs(got - ref)[ok] / size[ok]) <= 18 * 2.0 ** -24
+    bad = gr.copy()
+    bad[0, 9, 33] = np.nan
+    bad[0, 9, 9033] = np.inf
+    nan = _gradient(rb, geom, bad, gi, freqs, D, w)
+    assert not np.isfinite(nan[33]) and not np.isfinite(nan[9033])
+    keep = np.ones(N, bool)
+    keep[[33, 9033]] = False
+    assert np.max(np.abs(nan - ref)[keep & ok] / size[keep & ok]) <= 18 * 2.0 ** -24
