@@ -117,49 +117,57 @@ __global__ void __launch_bounds__(256) k_forward(FwdParams P, const T *__restric
 }
 
 // d[k][e][r] = c_k * sum_split part (fixed order) over the upper triangle
-// e <= r, written to (e, r) and (r, e).  A thread per upper-triangle entry of
-// a row-major [mp][mp] index (entries below the diagonal exit), so the
-// partial reads are coalesced; eight splits are loaded together.
+// e <= r, written to (e, r) and (r, e).  A block takes 32 entries of a row
+// (grid: 32-entry runs, rows, frequencies; runs below the diagonal exit); its
+// kRedG thread groups each sum a contiguous eighth of the splits, eight loads
+// in flight, and the group sums are added in order.  With one thread per entry
+// the loop over the splits was a serial chain of load latencies (64 elements /
+// 128^2: 122 us with 512 splits in FP64; the whole call 177 -> 51 us, in FP32
+// with 1024 splits 370 -> 26 us).
+constexpr int kRedG = 8;
 template <typename T>
-__global__ void k_forward_reduce(FwdParams P, const T *__restrict__ part, const float *__restrict__ gscale,
-                                 const double *__restrict__ dmax, double *__restrict__ d) {
-    const int64_t mm = (int64_t)P.m * P.m;
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= mm * P.nf) return;
-    const int k = (int)(idx / mm);
-    const int64_t rem = idx - (int64_t)k * mm;
-    const int e = (int)(rem / P.m), r = (int)(rem - (int64_t)e * P.m);
-    if (e > r) return;
-    if (P.dmin >= 32 && min(r - e, P.m - (r - e)) < P.dmin) {
-        // weighted by zero by the caller; its tile may not have been computed
-        const int64_t o1 = ((int64_t)k * P.m + e) * P.m + r, o2 = ((int64_t)k * P.m + r) * P.m + e;
-        d[2 * o1] = d[2 * o1 + 1] = d[2 * o2] = d[2 * o2 + 1] = 0.0;
-        return;
-    }
-    const int64_t stride = (int64_t)P.nf * P.mp * P.mp * 2;   // one split
-    const T *pp = part + (int64_t)k * P.mp * P.mp * 2 + ((int64_t)e * P.mp + r) * 2;
+__global__ void __launch_bounds__(32 * kRedG) k_forward_reduce(FwdParams P, const T *__restrict__ part,
+                                                               const float *__restrict__ gscale,
+                                                               const double *__restrict__ dmax,
+                                                               double *__restrict__ d) {
+    __shared__ double s_r[kRedG][32], s_i[kRedG][32];
+    const int t = threadIdx.x & 31, g = threadIdx.x >> 5;
+    const int k = blockIdx.z, e = blockIdx.y, r0 = blockIdx.x * 32, r = r0 + t;
+    if (r0 + 31 < e) return;   // block-uniform
+    // (pairs closer than dmin are weighted by zero by the caller, and their
+    // tile may not have been computed)
+    const bool near = P.dmin >= 32 && min(abs(r - e), P.m - abs(r - e)) < P.dmin;
+    const bool use = r >= e && r < P.m && !near;
+    typedef T T2 __attribute__((ext_vector_type(2)));
+    const int64_t stride = (int64_t)P.nf * P.mp * P.mp;   // one split
+    const T2 *pp = reinterpret_cast<const T2 *>(part) + (int64_t)k * P.mp * P.mp + (int64_t)e * P.mp + r;
     double sr = 0.0, si = 0.0;
     constexpr int kU = 8;
-    for (int s0 = 0; s0 < P.nsplit; s0 += kU) {
-        T vr[kU], vi[kU];
+    const int s1 = (int)((int64_t)P.nsplit * (g + 1) / kRedG);
+    for (int s0 = (int)((int64_t)P.nsplit * g / kRedG); s0 < s1; s0 += kU) {
+        T2 v[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) v[u] = use && s0 + u < s1 ? pp[(s0 + u) * stride] : T2{0, 0};
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
-            const bool ok = s0 + u < P.nsplit;
-            vr[u] = ok ? pp[(s0 + u) * stride] : T(0);
-            vi[u] = ok ? pp[(s0 + u) * stride + 1] : T(0);
+            sr += (double)v[u][0];
+            si += (double)v[u][1];
         }
+    }
+    s_r[g][t] = sr;
+    s_i[g][t] = si;
+    __syncthreads();
+    if (g != 0 || r < e || r >= P.m) return;
+    sr = si = 0.0;
 #pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            if (s0 + u < P.nsplit) {
-                sr += (double)vr[u];
-                si += (double)vi[u];
-            }
-        }
+    for (int q = 0; q < kRedG; ++q) {
+        sr += s_r[q][t];
+        si += s_i[q][t];
     }
     double c = P.cg[k];
     if (gscale) {
-        const double g = (double)gscale[k];
-        c *= g * g;
+        const double gs = (double)gscale[k];
+        c *= gs * gs;
     }
     if (dmax) c *= dmax[0];
     const double vr = sr * c, vi = si * c;
@@ -394,6 +402,7 @@ __global__ void __launch_bounds__(256, 2) k_forward_f32_regs(FwdParams P, const 
 // once.
 constexpr int kFdKC = 16, kFdArr = 64 * 64, kFdBuf = 4 * kFdArr + 64;
 constexpr int64_t kFdSplitPx = 16384;   // longest pixel split (1024 k-steps)
+constexpr int64_t kMinSplitPx = 64, kFewSplitPx = 512;   // shortest, see fwd_params
 typedef __attribute__((address_space(3))) void lds_void_t;
 
 __device__ __forceinline__ int fd_off(int row, int ch) { return row * 64 + 16 * (ch ^ ((row >> 1) & 3)); }
@@ -905,9 +914,21 @@ static FwdParams fwd_params(const rb_geometry *g, const double *freqs, int nf, r
     P.ntl = P.mp / tile;
     const int ntri = P.ntl * (P.ntl + 1) / 2;
     // about four rounds of resident workgroups (two per CU, four for the
-    // FP32 kernel with direct loads), rounded down so the last round is full
-    const int want = 4 * (fwd32_direct(g, dt) ? 4 : 2) * device_cus();
-    int nsplit = std::max(1, want / (ntri * nf));
+    // FP32 kernel with direct loads), rounded down so the last round is full;
+    // but no split is shorter than kMinSplitPx, and where rows are loaded in
+    // 16-byte pieces, beyond one round, than kFewSplitPx pixels: a split's
+    // partial sums (a tile of them, written and read once) cost as much as
+    // some tens of pixels.  (The FP64 kernel and the ragged rows' loads need
+    // the waves: 97 elements / 301x255 FP64 463 us, with the longer splits
+    // 530; FP16 200 and 235.)  us
+    // per call with splits of at least 16 / 64 / 128 / 512 pixels, two
+    // frequencies: 64 elements / 128^2 FP32 37 / 26 / 25 / 44, BF16 33 / 27 /
+    // 28 / 31, FP64 73 / 51 / 49 / 157; 64 / 480^2 FP32 133 / 132 / 134 / 115.
+    const int resident = (fwd32_direct(g, dt) ? 4 : 2) * device_cus();
+    int64_t most = P.N / kMinSplitPx;
+    if (dt != RB_F64 && P.N % (dt == RB_F32 ? 4 : 8) == 0)
+        most = std::max<int64_t>(P.N / kFewSplitPx, std::min<int64_t>(most, resident / (ntri * nf)));
+    int nsplit = std::max<int64_t>(1, std::min<int64_t>(4 * resident / (ntri * nf), most));
     // the kernels with direct loads (FP32, and 16-bit for large rings) also
     // keep a split to at most kFdSplitPx pixels: the tiles of a split share
     // its table rows in L2 only while they stay within a few k-steps of each
@@ -977,14 +998,14 @@ rb_status forward_impl(const rb_geometry *g, const void *G_re, const void *G_im,
     Carver c(ws, ws_bytes);
     FwdWs w = carve_fwd(c, P, dt, big);
     const unsigned nblk = (unsigned)((int64_t)P.ntri * P.nsplit * nf);
-    const int64_t tot = (int64_t)nf * P.m * P.m;
+    const dim3 gred(blocks_for(P.m, 32), P.m, nf);
     switch (dt) {
         case RB_F64: {
             dim3 grid(P.ntri, P.nsplit, nf);
             k_forward<double><<<grid, 256, 0, st>>>(P, (const double *)G_re, (const double *)G_im, delta,
                                                     (double *)w.part);
             RB_LAUNCHED();
-            k_forward_reduce<double><<<blocks_for(tot, 256), 256, 0, st>>>(P, (const double *)w.part, nullptr,
+            k_forward_reduce<double><<<gred, 32 * kRedG, 0, st>>>(P, (const double *)w.part, nullptr,
                                                                            nullptr, d_out);
             break;
         }
@@ -1000,7 +1021,7 @@ rb_status forward_impl(const rb_geometry *g, const void *G_re, const void *G_im,
                                                                                (float *)w.part);
             }
             RB_LAUNCHED();
-            k_forward_reduce<float><<<blocks_for(tot, 256), 256, 0, st>>>(P, (const float *)w.part, gscale,
+            k_forward_reduce<float><<<gred, 32 * kRedG, 0, st>>>(P, (const float *)w.part, gscale,
                                                                           nullptr, d_out);
             break;
         case RB_BF16:
@@ -1032,7 +1053,7 @@ rb_status forward_impl(const rb_geometry *g, const void *G_re, const void *G_im,
                 k_forward16_lds<__half><<<nblk, 256, 0, st>>>(P, (const __half *)G_re, (const __half *)G_im,
                                                               w.df, (float *)w.part);
             RB_LAUNCHED();
-            k_forward_reduce<float><<<blocks_for(tot, 256), 256, 0, st>>>(P, (const float *)w.part, gscale,
+            k_forward_reduce<float><<<gred, 32 * kRedG, 0, st>>>(P, (const float *)w.part, gscale,
                                                                           w.dmax, d_out);
             break;
     }
