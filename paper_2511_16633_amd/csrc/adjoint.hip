@@ -633,22 +633,34 @@ __device__ __forceinline__ void adj_f32_tile(const AdjItem &it, int64_t tile, in
                         }
                 }
             }
-            // fused epilogue: Re sum_e conj(G_e) Y_e and sum_e |G_e|^2 Z_e
+            // fused epilogue: Re sum_e conj(G_e) Y_e and sum_e |G_e|^2 Z_e.
+            // Emitters at or beyond m read row m - 1 (their Y and Z are zero),
+            // pixels at or beyond N the last one (dropped below), so that no
+            // load waits on a test; a half beyond mp holds rows of another.
+            if (ec + 32 * we < P.mp) {   // wave-uniform
 #pragma unroll
-            for (int b = 0; b < 2; ++b) {
+                for (int b = 0; b < 2; ++b) {
+                    float ger[4][2], gei[4][2];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int e = ec + 32 * we + 16 * b + MM<float>::out_row(kk, i);
+                    for (int i = 0; i < 4; ++i) {
+                        const int e = min(ec + 32 * we + 16 * b + MM<float>::out_row(kk, i), P.m - 1);
 #pragma unroll
-                    for (int cb = 0; cb < 2; ++cb) {
-                        const int64_t x = x0 + 32 * wp + 16 * cb + row;
-                        const bool ok = (e < P.m) && (x < N);
-                        const float ge_r = ok ? gr[(int64_t)e * N + x] : 0.0f;
-                        const float ge_i = ok ? gi[(int64_t)e * N + x] : 0.0f;
-                        const float yr = p1[b][cb][i] + p2[b][cb][i];
-                        const float yi = (p3[b][cb][i] - p1[b][cb][i]) + p2[b][cb][i];
-                        gp[cb] += ge_r * yr + ge_i * yi;
-                        if (HESS) hp[cb] += (ge_r * ge_r + ge_i * ge_i) * z[b][cb][i];
+                        for (int cb = 0; cb < 2; ++cb) {
+                            const int64_t x = min(x0 + 32 * wp + 16 * cb + row, N - 1);
+                            ger[i][cb] = gr[(int64_t)e * N + x];
+                            gei[i][cb] = gi[(int64_t)e * N + x];
+                        }
+                    }
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+#pragma unroll
+                        for (int cb = 0; cb < 2; ++cb) {
+                            const float ge_r = ger[i][cb], ge_i = gei[i][cb];
+                            const float yr = p1[b][cb][i] + p2[b][cb][i];
+                            const float yi = (p3[b][cb][i] - p1[b][cb][i]) + p2[b][cb][i];
+                            gp[cb] += ge_r * yr + ge_i * yi;
+                            if (HESS) hp[cb] += (ge_r * ge_r + ge_i * ge_i) * z[b][cb][i];
+                        }
                     }
                 }
             }
