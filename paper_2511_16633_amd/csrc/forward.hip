@@ -125,11 +125,16 @@ __global__ void __launch_bounds__(256) k_forward(FwdParams P, const T *__restric
 // 128^2: 122 us with 512 splits in FP64; the whole call 177 -> 51 us, in FP32
 // with 1024 splits 370 -> 26 us).
 constexpr int kRedG = 8;
+struct FwdSplitOut {   // of k_forward_split, or null
+    const uint8_t *flags;
+    const float *scale, *dscale;
+    int tile;
+};
 template <typename T>
 __global__ void __launch_bounds__(32 * kRedG) k_forward_reduce(FwdParams P, const T *__restrict__ part,
                                                                const float *__restrict__ gscale,
                                                                const double *__restrict__ dmax,
-                                                               double *__restrict__ d) {
+                                                               double *__restrict__ d, FwdSplitOut so) {
     __shared__ double s_r[kRedG][32], s_i[kRedG][32];
     const int t = threadIdx.x & 31, g = threadIdx.x >> 5;
     const int k = blockIdx.z, e = blockIdx.y, r0 = blockIdx.x * 32, r = r0 + t;
@@ -142,6 +147,16 @@ __global__ void __launch_bounds__(32 * kRedG) k_forward_reduce(FwdParams P, cons
     const int64_t stride = (int64_t)P.nf * P.mp * P.mp;   // one split
     const T2 *pp = reinterpret_cast<const T2 *>(part) + (int64_t)k * P.mp * P.mp + (int64_t)e * P.mp + r;
     double sr = 0.0, si = 0.0;
+    // k_forward_split's partials carry the scales of their two rows, unless
+    // the split's tile is flagged
+    double inv = 1.0, dsc = 1.0;
+    const uint8_t *fl = nullptr;
+    if (so.flags && use) {
+        inv = 1.0 / ((double)so.scale[k * P.m + e] * (double)so.scale[k * P.m + r]);
+        dsc = 1.0 / (double)so.dscale[0];
+        const int te = e / so.tile, tr = r / so.tile;
+        fl = so.flags + (int64_t)k * P.nsplit * P.ntri + te * P.ntl - te * (te - 1) / 2 + (tr - te);
+    }
     constexpr int kU = 8;
     const int s1 = (int)((int64_t)P.nsplit * (g + 1) / kRedG);
     for (int s0 = (int)((int64_t)P.nsplit * g / kRedG); s0 < s1; s0 += kU) {
@@ -150,12 +165,13 @@ __global__ void __launch_bounds__(32 * kRedG) k_forward_reduce(FwdParams P, cons
         for (int u = 0; u < kU; ++u) v[u] = use && s0 + u < s1 ? pp[(s0 + u) * stride] : T2{0, 0};
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
-            sr += (double)v[u][0];
-            si += (double)v[u][1];
+            const double f = fl && s0 + u < s1 && fl[(int64_t)(s0 + u) * P.ntri] ? 1.0 : inv;
+            sr += (double)v[u][0] * f;
+            si += (double)v[u][1] * f;
         }
     }
-    s_r[g][t] = sr;
-    s_i[g][t] = si;
+    s_r[g][t] = sr * dsc;
+    s_i[g][t] = si * dsc;
     __syncthreads();
     if (g != 0 || r < e || r >= P.m) return;
     sr = si = 0.0;
@@ -208,8 +224,9 @@ struct FwdStage {
     double dl[8];
 };
 
+template <typename D>
 __device__ __forceinline__ void fwd_stage_load(const float *__restrict__ gr, const float *__restrict__ gi,
-                                               const double *__restrict__ delta, int m, int64_t N, int e_row,
+                                               const D *__restrict__ delta, int m, int64_t N, int e_row,
                                                int r_row, int64_t xc, int64_t ke, bool vec, FwdStage &v) {
     const int c8 = (threadIdx.x & 3) * 8;
     const int64_t xs = xc + c8;
@@ -241,7 +258,7 @@ __device__ __forceinline__ void fwd_stage_load(const float *__restrict__ gr, con
         for (int q = 0; q < 8; ++q) {
             const int64_t x = xs + q;
             const bool okx = x < ke;
-            v.dl[q] = okx ? delta[x] : 0.0;
+            v.dl[q] = okx ? (double)delta[x] : 0.0;
             const bool oka = okx && e_row < m, okb = okx && r_row < m;
             v.ar[q >> 2][q & 3] = oka ? gr[(int64_t)e_row * N + x] : 0.0f;
             v.ai[q >> 2][q & 3] = oka ? gi[(int64_t)e_row * N + x] : 0.0f;
@@ -251,19 +268,16 @@ __device__ __forceinline__ void fwd_stage_load(const float *__restrict__ gr, con
     }
 }
 
-__global__ void __launch_bounds__(256, 2) k_forward_f32_regs(FwdParams P, const float *__restrict__ Gr,
-                                                             const float *__restrict__ Gi,
-                                                             const double *__restrict__ delta,
-                                                             float *__restrict__ part) {
+template <typename D>
+__device__ __forceinline__ void fwd_f32_regs_tile(const FwdParams &P, const float *__restrict__ Gr,
+                                                  const float *__restrict__ Gi, const D *__restrict__ delta,
+                                                  float *__restrict__ part, int te, int tr, int split, int k) {
     __shared__ float sA[2][2][64][kFwdLD];
     __shared__ float sBm[2][2][64][kFwdLD];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int row = lane & 15, kk = lane >> 4;
     const int we = wave >> 1, wr = wave & 1;
-    int te, tr;
-    tri_tile(blockIdx.x, P.ntl, te, tr);
-    const int split = blockIdx.y, k = blockIdx.z;
     const int64_t N = P.N;
     const float *gr = Gr + (int64_t)k * P.m * N;
     const float *gi = Gi + (int64_t)k * P.m * N;
@@ -385,6 +399,15 @@ __global__ void __launch_bounds__(256, 2) k_forward_f32_regs(FwdParams P, const 
     }
 }
 
+__global__ void __launch_bounds__(256, 2) k_forward_f32_regs(FwdParams P, const float *__restrict__ Gr,
+                                                             const float *__restrict__ Gi,
+                                                             const double *__restrict__ delta,
+                                                             float *__restrict__ part) {
+    int te, tr;
+    tri_tile(blockIdx.x, P.ntl, te, tr);
+    fwd_f32_regs_tile(P, Gr, Gi, delta, part, te, tr, blockIdx.y, blockIdx.z);
+}
+
 // Forward, FP32 tables with 16-byte aligned rows (N a multiple of 4).  The
 // same tiles and waves as above, pixels consumed 16 at a time, and no
 // staging registers: the tile rows of G_e and G_r (re, im) go from global
@@ -413,16 +436,14 @@ __global__ void k_delta_cast(int64_t N, int64_t n, const double *__restrict__ de
     if (x < n) out[x] = x < N ? (float)delta[x] : 0.0f;
 }
 
-__global__ void __launch_bounds__(256, 4) k_forward_f32(FwdParams P, const float *__restrict__ Gr,
-                                                        const float *__restrict__ Gi, const float *__restrict__ df,
-                                                        float *__restrict__ part) {
+__device__ __forceinline__ void fwd_f32_tile(const FwdParams &P, const float *__restrict__ Gr,
+                                             const float *__restrict__ Gi, const float *__restrict__ df,
+                                             float *__restrict__ part, int te, int tr, int split, int k) {
     __shared__ __align__(16) unsigned char sm[2][kFdBuf];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int row = lane & 15, kk = lane >> 4;
     const int we = wave >> 1, wr = wave & 1;
-    int te, tr, split, k;
-    fwd_block(P, te, tr, split, k);
     if (P.dmin >= 32 && max_circ_dist(P.m, te * 64, 64, tr * 64, 64) < P.dmin) return;
     const bool idle = fwd_block_idle(P, te, tr, we, wr);
     const int64_t N = P.N;
@@ -518,6 +539,320 @@ __global__ void __launch_bounds__(256, 4) k_forward_f32(FwdParams P, const float
     }
 }
 
+__global__ void __launch_bounds__(256, 4) k_forward_f32(FwdParams P, const float *__restrict__ Gr,
+                                                        const float *__restrict__ Gi, const float *__restrict__ df,
+                                                        float *__restrict__ part) {
+    int te, tr, split, k;
+    fwd_block(P, te, tr, split, k);
+    fwd_f32_tile(P, Gr, Gi, df, part, te, tr, split, k);
+}
+
+// byte offset of 16-byte chunk ch of row `row` in a tile of 64-byte rows
+__device__ __forceinline__ int f16_off(int row, int ch) { return row * 64 + 16 * (ch ^ ((row >> 1) & 3)); }
+
+// ------------------------------------------------------------------ FP32 tables on the FP16 matrix cores
+// Forward with FP32 tables, both operands split into two FP16 pieces (x s =
+// hi + lo, s a power of two) and hi hi + hi lo + lo hi accumulated in FP32 on
+// the 16x16x32 FP16 cores, as the backprojection's k_adjoint_split.  Scales:
+// row r of G at frequency k by its largest magnitude over kFsSamples sampled
+// pixels (2^8 there, 2^8 of headroom), delta by its largest magnitude.
+//
+// A 128 x 128 (e, r) tile per workgroup of eight waves, 4 x 2 of 32 x 64, 32
+// pixels per k-step.  A step's 256 rows of G (128 bytes each and array) pass
+// through registers, are scaled (those of the r side times delta) and split
+// there, and stored as eight FP16 arrays of 8 KB, double buffered (128 KB: one
+// workgroup per compute unit, two waves per SIMD).  During a step a wave
+// multiplies, and converts its part of the next step's rows, which it loaded a
+// step earlier, and loads that of the one after: waves 0 to 3 convert first
+// and waves 4 to 7, which share their SIMDs, multiply first, so that the matrix
+// cores work while vector instructions convert.
+//
+// 1024 elements / 1100^2, four frequencies: 130.8 ms on the FP32 cores, 68.7
+// here (62.4 with the hi lo products in the main sums; 12 MFMAs per complex
+// product of blocks: 1.0 PFLOP/s, as the backprojection, whose clock power
+// holds at 1.9 GHz); 256 / 480^2, three frequencies: 1.36 -> 0.76 ms; 1024 /
+// 255x301 (rows not 16-byte aligned): 11.8 -> 2.5 ms.  Relative L2 error
+// against FP64, rounded to FP32: 256 / 480^2 5.7e-7 -> 2.6e-7 (5.8e-7 with the
+// hi lo products in the main sums), 97 / 301x255 1.6e-7 -> 6e-8.  Four waves of
+// 64 x 64 with 512 registers each spilled: the compiler moved accumulators
+// between register files at every step.
+//
+// A workgroup that meets a value beyond FP16's range puts its (tile, split,
+// frequency) on a list and flags it; k_forward_f32_list computes those from
+// FP32 (unscaled partials, which the reduction tells by the flag).
+constexpr int kFsT = 128, kFsKC = 32, kFsArr = kFsT * kFsKC * 2, kFsSamples = 256;
+constexpr int kFsTop = 8;
+constexpr float kFsMax = 65504.0f;   // largest FP16 value
+typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+typedef float f2 __attribute__((ext_vector_type(2)));
+
+// The power of two that brings `top` > 0 into [2^(e-1), 2^e) (1 otherwise).
+__device__ __forceinline__ float fs_scale(float top, int e) {
+    if (!(top > 0.0f)) return 1.0f;
+    int x;
+    (void)frexpf(fminf(top, 3.0e38f), &x);
+    return ldexpf(1.0f, min(max(e - x, -100), 100));
+}
+
+// Blocks 0 .. rows - 1: scale[row] of the rows (k m + r); 2^100 for a row that
+// is zero at every sampled pixel, so that any normal value overflows.  The
+// other blocks: partial maxima of |delta| (kReduceBlocks of them).
+__global__ void __launch_bounds__(256) k_fs_scales(int64_t N, int rows, const float *__restrict__ Gr,
+                                                   const float *__restrict__ Gi, const double *__restrict__ delta,
+                                                   float *__restrict__ scale, float *__restrict__ dpart) {
+    __shared__ float sm[4];
+    float v = 0.0f;
+    if ((int)blockIdx.x < rows) {
+        const int64_t o = (int64_t)blockIdx.x * N + (int64_t)threadIdx.x * N / kFsSamples;
+        v = fmaxf(fabsf(Gr[o]), fabsf(Gi[o]));
+    } else {
+        for (int64_t i = (int64_t)(blockIdx.x - rows) * 256 + threadIdx.x; i < N; i += kReduceBlocks * 256)
+            v = fmaxf(v, fabsf((float)delta[i]));
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
+    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        v = fmaxf(fmaxf(sm[0], sm[1]), fmaxf(sm[2], sm[3]));
+        if ((int)blockIdx.x < rows)
+            scale[blockIdx.x] = v > 0.0f ? fs_scale(v, kFsTop) : 0x1p100f;
+        else
+            dpart[blockIdx.x - rows] = v;
+    }
+}
+
+// df[x] = (float)delta[x] sd (zero from N to n), sd = fs_scale(max |delta|, 0)
+// to dscale[0]; clears the list and the flags.
+__global__ void __launch_bounds__(256) k_fs_delta(int64_t N, int64_t n, const double *__restrict__ delta,
+                                                  const float *__restrict__ dpart, float *__restrict__ df,
+                                                  float *__restrict__ dscale, int *__restrict__ redo,
+                                                  uint8_t *__restrict__ flags, int64_t nflags) {
+    __shared__ float sm[4];
+    float v = 0.0f;
+#pragma unroll
+    for (int q = 0; q < kReduceBlocks / 256; ++q) v = fmaxf(v, dpart[q * 256 + threadIdx.x]);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
+    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = v;
+    __syncthreads();
+    const float sd = fs_scale(fmaxf(fmaxf(sm[0], sm[1]), fmaxf(sm[2], sm[3])), 0);
+    const int64_t x = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (x == 0) {
+        dscale[0] = sd;
+        redo[0] = 0;
+    }
+    if (x < n) df[x] = x < N ? (float)delta[x] * sd : 0.0f;
+    for (int64_t q = x; q < nflags; q += (int64_t)gridDim.x * 256) flags[q] = 0;
+}
+
+// VEC: rows of whole 16-byte pieces (N a multiple of 4).
+template <bool VEC>
+__global__ void __launch_bounds__(512, 2) k_forward_split(FwdParams P, const float *__restrict__ Gr,
+                                                          const float *__restrict__ Gi,
+                                                          const float *__restrict__ df,
+                                                          const float *__restrict__ scale, float *__restrict__ part,
+                                                          int *__restrict__ redo, uint8_t *__restrict__ flags) {
+    using M = MM16<__half>;
+    // [buffer][e re hi, e im hi, e re lo, e im lo, then the r side]
+    __shared__ __align__(16) unsigned char sT[2][8 * kFsArr];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int row = lane & 15, kk = lane >> 4;
+    const int we = wave & 3, wr = wave >> 2;
+    int te, tr, split, k;
+    fwd_block(P, te, tr, split, k);
+    if (P.dmin >= 32 && max_circ_dist(P.m, te * kFsT, kFsT, tr * kFsT, kFsT) < P.dmin) return;
+    const bool idle = (te == tr && 32 * we >= 64 * (wr + 1)) ||
+                      (P.dmin >= 32 && max_circ_dist(P.m, te * kFsT + 32 * we, 32, tr * kFsT + 64 * wr, 64) < P.dmin);
+    const int64_t N = P.N;
+    const int64_t ks = (int64_t)split * P.kchunk;
+    const int64_t ke = std::min<int64_t>(N, ks + P.kchunk);
+    const int last = (int)((ke - ks + kFsKC - 1) / kFsKC) - 1;   // last chunk
+    // staging: pixels p4 .. p4 + 3 of rows r8, r8 + 64 of either side.  Rows
+    // at or beyond m read row m - 1 (their outputs are never read), pixels at
+    // or beyond N the last ones of the row (delta is zero there; the other
+    // splits end with a whole chunk).
+    const int p4 = (tid & 7) * 4, r8 = tid >> 3;
+    const float *rowp[4];     // e rows, then r rows
+    float sc[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int r = std::min((j < 2 ? te : tr) * kFsT + r8 + 64 * (j & 1), P.m - 1);
+        rowp[j] = Gr + ((int64_t)k * P.m + r) * N;
+        sc[j] = scale[k * P.m + r];
+    }
+    const int64_t im = Gi - Gr;
+    f4 v[4][2], dl;
+    float top = 0.0f;
+    auto load = [&](int c) {
+        const int64_t xc = ks + (int64_t)c * kFsKC + p4;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (VEC) {
+                const int64_t x = std::min<int64_t>(xc, N - 4);
+                v[j][0] = *reinterpret_cast<const f4 *>(rowp[j] + x);
+                v[j][1] = *reinterpret_cast<const f4 *>(rowp[j] + im + x);
+            } else {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int64_t x = std::min<int64_t>(xc + q, N - 1);
+                    v[j][0][q] = rowp[j][x];
+                    v[j][1][q] = rowp[j][im + x];
+                }
+            }
+        }
+        dl = *reinterpret_cast<const f4 *>(df + xc);
+    };
+    auto store = [&](unsigned char *buf) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const f4 s = j < 2 ? f4{sc[j], sc[j], sc[j], sc[j]} : dl * sc[j];
+#pragma unroll
+            for (int a = 0; a < 2; ++a) {
+                const f4 w = v[j][a] * s;
+                const h4 h = __builtin_convertvector(w, h4);
+                f4 rem;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) rem[q] = w[q] - (float)h[q];
+                const h4 l = __builtin_convertvector(rem, h4);
+                top = fmaxf(top, fmaxf(fmaxf(fabsf(w[0]), fabsf(w[1])), fmaxf(fabsf(w[2]), fabsf(w[3]))));
+                unsigned char *d =
+                    buf + ((j < 2 ? 0 : 4) + a) * kFsArr + f16_off(r8 + 64 * (j & 1), p4 >> 3) + 2 * (p4 & 4);
+                *reinterpret_cast<h4 *>(d) = h;
+                *reinterpret_cast<h4 *>(d + 2 * kFsArr) = l;
+            }
+        }
+    };
+    f4 re[2][4], imv[2][4];
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) re[b][c] = imv[b][c] = f4{0, 0, 0, 0};
+    auto frag = [&](const unsigned char *q, int r) { return *reinterpret_cast<const h8 *>(q + f16_off(r, kk)); };
+    auto mma = [&](const unsigned char *sa, const unsigned char *sb) {
+        h8 a[4][2], n[2][2];
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) a[t][b] = frag(sa + t * kFsArr, 32 * we + 16 * b + row);
+            n[0][b] = neg(a[1][b]);
+            n[1][b] = neg(a[3][b]);
+        }
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) {
+            h8 u[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) u[t] = frag(sb + t * kFsArr, 64 * wr + 16 * cb + row);
+            // (ar + i ai)(br + i bi) = ar br - ai bi + i (ar bi + ai br)
+            // The hi lo products are summed apart and added once per step: in
+            // the long sums over pixels it is the number of roundings at the
+            // sum's own size that sets the error (three a step, not six).
+            f4 tr_[2], ti_[2];
+#pragma unroll
+            for (int b = 0; b < 2; ++b) tr_[b] = ti_[b] = f4{0, 0, 0, 0};
+            auto term = [&](const h8 (&x)[2], const h8 &p, const h8 (&y)[2], const h8 &q) {
+#pragma unroll
+                for (int b = 0; b < 2; ++b) {
+                    tr_[b] = M::mma(x[b], p, tr_[b]);
+                    ti_[b] = M::mma(y[b], q, ti_[b]);
+                }
+            };
+            term(a[0], u[2], a[0], u[3]);
+            term(n[0], u[3], a[1], u[2]);
+            term(a[2], u[0], a[2], u[1]);
+            term(n[1], u[1], a[3], u[0]);
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                re[b][cb] = M::mma(a[0][b], u[0], re[b][cb]);
+                imv[b][cb] = M::mma(a[0][b], u[1], imv[b][cb]);
+            }
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                re[b][cb] = M::mma(n[0][b], u[1], re[b][cb]);
+                imv[b][cb] = M::mma(a[1][b], u[0], imv[b][cb]);
+            }
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                re[b][cb] += tr_[b];
+                imv[b][cb] += ti_[b];
+            }
+        }
+    };
+    load(0);
+    store(sT[0]);
+    load(std::min(1, last));
+    auto kloop = [&](auto first) {   // first: convert before multiplying
+        for (int c = 0; c <= last; ++c) {
+            lds_barrier();   // chunk c is in LDS, and no wave still reads the other buffer
+            const unsigned char *sa = sT[c & 1];
+            unsigned char *sn = sT[(c & 1) ^ 1];
+            // (the last two steps convert and load the last chunk again, unused)
+            if (decltype(first)::value) {
+                store(sn);
+                load(std::min(c + 2, last));
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (!idle) mma(sa, sa + 4 * kFsArr);
+            if (!decltype(first)::value) {
+                __builtin_amdgcn_sched_barrier(0);
+                store(sn);
+                load(std::min(c + 2, last));
+            }
+        }
+    };
+    if (wr == 0)
+        kloop(std::true_type());
+    else
+        kloop(std::false_type());
+    const int beyond = __syncthreads_or(!(top < kFsMax));
+    if (beyond && tid == 0) {
+        const int64_t id = ((int64_t)k * P.nsplit + split) * P.ntri + te * P.ntl - te * (te - 1) / 2 + (tr - te);
+        flags[id] = 1;
+        redo[1 + atomicAdd(redo, 1)] = (int)id;
+    }
+    if (idle) return;
+    float *pp = part + ((int64_t)split * P.nf + k) * P.mp * P.mp * 2;
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) {
+            const int r = tr * kFsT + 64 * wr + 16 * cb + row;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int ee = te * kFsT + 32 * we + 16 * b + 4 * kk + i;
+                *reinterpret_cast<f2 *>(pp + ((int64_t)ee * P.mp + r) * 2) = f2{re[b][cb][i], imv[b][cb][i]};
+            }
+        }
+    }
+}
+
+// The listed (tile, split, frequency)s of k_forward_split from FP32: each is
+// three or four 64 x 64 tiles.  Partials in units of (float)delta sd, G
+// unscaled.
+template <bool VEC>
+__global__ void __launch_bounds__(256, 2) k_forward_f32_list(FwdParams P, const float *__restrict__ Gr,
+                                                             const float *__restrict__ Gi,
+                                                             const float *__restrict__ df,
+                                                             float *__restrict__ part, const int *__restrict__ redo) {
+    const int n = 4 * redo[0];
+    for (int i = blockIdx.x; i < n; i += gridDim.x) {
+        const int id = redo[1 + (i >> 2)];
+        const int rest = id / P.ntri;
+        int te, tr;
+        tri_tile(id - rest * P.ntri, P.ntl, te, tr);
+        const int split = rest % P.nsplit, k = rest / P.nsplit;
+        const int e64 = 2 * te + ((i >> 1) & 1), r64 = 2 * tr + (i & 1);
+        if (e64 <= r64) {   // workgroup-uniform
+            if (VEC)
+                fwd_f32_tile(P, Gr, Gi, df, part, e64, r64, split, k);
+            else
+                fwd_f32_regs_tile(P, Gr, Gi, df, part, e64, r64, split, k);
+        }
+        __syncthreads();   // the next item reuses the LDS
+    }
+}
+
 // ------------------------------------------------------------------ 16-bit, LDS-staged
 // Forward with 16-bit tables on the 16x16x32 matrix cores (FP32
 // accumulation), tiled as the FP32 kernel: a 64 x 64 (e, r) tile per
@@ -531,8 +866,6 @@ __global__ void __launch_bounds__(256, 4) k_forward_f32(FwdParams P, const float
 constexpr int kF16KC = 32, kF16Arr = 64 * kF16KC * 2;   // one array of a tile (bytes)
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ int f16_off(int row, int ch) { return row * 64 + 16 * (ch ^ ((row >> 1) & 3)); }
 
 // out[x] = delta[x] / max |delta| as float (0 if delta is zero)
 __global__ void k_delta_f32(int64_t N, const double *__restrict__ delta, const double *__restrict__ dmax,
@@ -899,6 +1232,16 @@ static bool fwd16_big(const rb_geometry *g, rb_dtype dt) {
     return (dt == RB_BF16 || dt == RB_F16) && g->m >= kF16BigM && N % 8 == 0;
 }
 
+// FP32 tables on the FP16 cores: rings that fill more than half of a 128-element
+// tile, and problems large enough to pay for its two more launches.  us per
+// call on the FP32 cores / split, two frequencies: 64 elements / 480^2 108 /
+// 191; 96 / 64x66 24 / 32, 96 / 128^2 42 / 39, 96 / 480^2 300 / 203; 256 /
+// 64x66 43 / 44, 256 / 128^2 89 / 68, 256 / 255x301 909 / 305; 512 / 64x66 98 /
+// 86; 1024 / 480^2 12272 / 6769.
+static bool fwd32_split(const rb_geometry *g, rb_dtype dt) {
+    return dt == RB_F32 && g->m > 64 && ((int64_t)g->nx * g->ny >= 8192 || g->m > 256);
+}
+
 // The FP32 kernel with direct loads: rows of whole 16-byte chunks.
 static bool fwd32_direct(const rb_geometry *g, rb_dtype dt) {
     return dt == RB_F32 && ((int64_t)g->nx * g->ny) % 4 == 0;
@@ -906,7 +1249,8 @@ static bool fwd32_direct(const rb_geometry *g, rb_dtype dt) {
 
 static FwdParams fwd_params(const rb_geometry *g, const double *freqs, int nf, rb_dtype dt) {
     FwdParams P;
-    const int tile = fwd16_big(g, dt) ? kFBT : 64;
+    const bool fs = fwd32_split(g, dt);
+    const int tile = fs ? kFsT : (fwd16_big(g, dt) ? kFBT : 64);
     P.m = g->m;
     P.mp = (g->m + tile - 1) / tile * tile;
     P.N = (int64_t)g->nx * g->ny;
@@ -924,7 +1268,7 @@ static FwdParams fwd_params(const rb_geometry *g, const double *freqs, int nf, r
     // per call with splits of at least 16 / 64 / 128 / 512 pixels, two
     // frequencies: 64 elements / 128^2 FP32 37 / 26 / 25 / 44, BF16 33 / 27 /
     // 28 / 31, FP64 73 / 51 / 49 / 157; 64 / 480^2 FP32 133 / 132 / 134 / 115.
-    const int resident = (fwd32_direct(g, dt) ? 4 : 2) * device_cus();
+    const int resident = (fs ? 1 : (fwd32_direct(g, dt) ? 4 : 2)) * device_cus();
     int64_t most = P.N / kMinSplitPx;
     if (dt != RB_F64 && P.N % (dt == RB_F32 ? 4 : 8) == 0)
         most = std::max<int64_t>(P.N / kFewSplitPx, std::min<int64_t>(most, resident / (ntri * nf)));
@@ -935,9 +1279,9 @@ static FwdParams fwd_params(const rb_geometry *g, const double *freqs, int nf, r
     // other, and long workgroups drift apart (FP32, 1024 elements / 1100^2:
     // 7 splits 144.4 ms, 30 splits 138.1 ms, 60 splits 135.0 ms for the
     // public call)
-    if (fwd32_direct(g, dt) || fwd16_big(g, dt))
+    if (fs || fwd32_direct(g, dt) || fwd16_big(g, dt))
         nsplit = std::max<int64_t>(nsplit, (P.N + kFdSplitPx - 1) / kFdSplitPx);
-    const int kq = (dt == RB_BF16 || dt == RB_F16) ? 32 : 16;
+    const int kq = (fs || dt == RB_BF16 || dt == RB_F16) ? 32 : 16;
     int64_t kchunk = (P.N + nsplit - 1) / nsplit;
     kchunk = (kchunk + kq - 1) / kq * kq;
     if (kchunk < kq) kchunk = kq;
@@ -962,26 +1306,39 @@ struct FwdWs {
     float *df;
     void *dr, *di;
     int64_t np;
+    // k_forward_split: row scales, |delta| maxima, delta's scale, list, flags
+    float *fscale, *fpart, *fdscale;
+    int *redo;
+    uint8_t *flags;
+    int64_t nflags;
 };
 
-static FwdWs carve_fwd(Carver &c, const FwdParams &P, rb_dtype dt, bool big) {
+static FwdWs carve_fwd(Carver &c, const FwdParams &P, rb_dtype dt, bool big, bool fs) {
     const size_t es = dt == RB_F64 ? 8 : 4;
     FwdWs w;
     w.dmax = c.take<double>(1);
     w.dparts = (dt == RB_BF16 || dt == RB_F16) ? c.take<double>(kReduceBlocks) : nullptr;
     w.part = c.take<char>((size_t)P.nsplit * P.nf * P.mp * P.mp * 2 * es);
-    w.df = (dt == RB_BF16 || dt == RB_F16 || (dt == RB_F32 && P.N % 4 == 0)) ? c.take<float>((size_t)P.N + 16)
-                                                                               : nullptr;
+    w.df = (fs || dt == RB_BF16 || dt == RB_F16 || (dt == RB_F32 && P.N % 4 == 0)) ? c.take<float>((size_t)P.N + 32)
+                                                                                     : nullptr;
     w.np = (P.N + kF16KC - 1) / kF16KC * kF16KC;
     w.dr = big ? (void *)c.take<uint16_t>((size_t)P.nf * P.m * w.np) : nullptr;
     w.di = big ? (void *)c.take<uint16_t>((size_t)P.nf * P.m * w.np) : nullptr;
+    w.nflags = fs ? (int64_t)P.nf * P.nsplit * P.ntri : 0;
+    if (fs) {
+        w.fscale = c.take<float>((size_t)P.nf * P.m);
+        w.fpart = c.take<float>(kReduceBlocks);
+        w.fdscale = c.take<float>(1);
+        w.redo = c.take<int>((size_t)w.nflags + 1);
+        w.flags = c.take<uint8_t>((size_t)w.nflags);
+    }
     return w;
 }
 
 size_t forward_workspace_bytes(const rb_geometry *g, int nf, rb_dtype dt) {
     FwdParams P = fwd_params(g, nullptr, nf, dt);
     Carver c(nullptr, 0);
-    carve_fwd(c, P, dt, fwd16_big(g, dt));
+    carve_fwd(c, P, dt, fwd16_big(g, dt), fwd32_split(g, dt));
     return c.used + 256;
 }
 
@@ -996,7 +1353,9 @@ rb_status forward_impl(const rb_geometry *g, const void *G_re, const void *G_im,
     P.dmin = dmin;
     const bool big = fwd16_big(g, dt);
     Carver c(ws, ws_bytes);
-    FwdWs w = carve_fwd(c, P, dt, big);
+    const bool fs = fwd32_split(g, dt);
+    FwdWs w = carve_fwd(c, P, dt, big, fs);
+    FwdSplitOut so{nullptr, nullptr, nullptr, kFsT};
     const unsigned nblk = (unsigned)((int64_t)P.ntri * P.nsplit * nf);
     const dim3 gred(blocks_for(P.m, 32), P.m, nf);
     switch (dt) {
@@ -1006,11 +1365,31 @@ rb_status forward_impl(const rb_geometry *g, const void *G_re, const void *G_im,
                                                     (double *)w.part);
             RB_LAUNCHED();
             k_forward_reduce<double><<<gred, 32 * kRedG, 0, st>>>(P, (const double *)w.part, nullptr,
-                                                                           nullptr, d_out);
+                                                                           nullptr, d_out, so);
             break;
         }
         case RB_F32:
-            if (fwd32_direct(g, dt)) {
+            if (fs) {
+                const float *gr = (const float *)G_re, *gi = (const float *)G_im;
+                float *pt = (float *)w.part;
+                k_fs_scales<<<nf * P.m + kReduceBlocks, 256, 0, st>>>(P.N, nf * P.m, gr, gi, delta, w.fscale,
+                                                                      w.fpart);
+                RB_LAUNCHED();
+                k_fs_delta<<<blocks_for(P.N + 32, 256), 256, 0, st>>>(P.N, P.N + 32, delta, w.fpart, w.df, w.fdscale,
+                                                                      w.redo, w.flags, w.nflags);
+                RB_LAUNCHED();
+                const unsigned nl = (unsigned)std::min<int64_t>(4 * w.nflags, 2 * device_cus());
+                if (P.N % 4 == 0) {
+                    k_forward_split<true><<<nblk, 512, 0, st>>>(P, gr, gi, w.df, w.fscale, pt, w.redo, w.flags);
+                    RB_LAUNCHED();
+                    k_forward_f32_list<true><<<nl, 256, 0, st>>>(P, gr, gi, w.df, pt, w.redo);
+                } else {
+                    k_forward_split<false><<<nblk, 512, 0, st>>>(P, gr, gi, w.df, w.fscale, pt, w.redo, w.flags);
+                    RB_LAUNCHED();
+                    k_forward_f32_list<false><<<nl, 256, 0, st>>>(P, gr, gi, w.df, pt, w.redo);
+                }
+                so = FwdSplitOut{w.flags, w.fscale, w.fdscale, kFsT};
+            } else if (fwd32_direct(g, dt)) {
                 k_delta_cast<<<blocks_for(P.N + 16, 256), 256, 0, st>>>(P.N, P.N + 16, delta, w.df);
                 RB_LAUNCHED();
                 k_forward_f32<<<nblk, 256, 0, st>>>(P, (const float *)G_re, (const float *)G_im, w.df,
@@ -1022,7 +1401,7 @@ rb_status forward_impl(const rb_geometry *g, const void *G_re, const void *G_im,
             }
             RB_LAUNCHED();
             k_forward_reduce<float><<<gred, 32 * kRedG, 0, st>>>(P, (const float *)w.part, gscale,
-                                                                          nullptr, d_out);
+                                                                          nullptr, d_out, so);
             break;
         case RB_BF16:
         case RB_F16:
@@ -1054,7 +1433,7 @@ rb_status forward_impl(const rb_geometry *g, const void *G_re, const void *G_im,
                                                               w.df, (float *)w.part);
             RB_LAUNCHED();
             k_forward_reduce<float><<<gred, 32 * kRedG, 0, st>>>(P, (const float *)w.part, gscale,
-                                                                          w.dmax, d_out);
+                                                                          w.dmax, d_out, so);
             break;
     }
     RB_LAUNCHED();

@@ -2,7 +2,11 @@
 of the pair's two weighted residuals.  These cases give the two orders of a
 pair different data and weights, down to whole 32 x 32 blocks that are zero in
 one order only, on rings whose block count is even (two blocks half a ring
-apart), odd, and one."""
+apart), odd, and one.
+
+The FP32 contractions that run on the FP16 matrix cores in two pieces are
+checked here too, at the edges of their tiles and of FP16's range.
+"""
 import dataclasses
 
 import numpy as np
@@ -147,3 +151,71 @@ def test_fp32_gradient_outside_the_fp16_range(rb):
     keep = np.ones(N, bool)
     keep[[33, 9033]] = False
     assert np.max(np.abs(nan - ref)[keep & ok] / size[keep & ok]) <= 18 * 2.0 ** -24
+
+
+def _forward(rb, geom, gr, gi, freqs, delta):
+    d = torch.zeros((len(freqs), geom.m, geom.m, 2), dtype=torch.float64, device=DEV)
+    rb.born_forward(geom, torch.as_tensor(gr, device=DEV), torch.as_tensor(gi, device=DEV), None, "f32", freqs,
+                    torch.as_tensor(delta, device=DEV), d)
+    return torch.view_as_complex(d).cpu().numpy()
+
+
+# Pixel counts with rows of whole 16-byte pieces and without, a last chunk of 1
+# to 32 pixels, one and several pixel splits; rings of one 128-element tile, a
+# tile and two elements, and three tiles.
+@pytest.mark.parametrize("shape", [(64, 80, 128), (67, 71, 130), (97, 103, 128), (75, 59, 300), (160, 129, 256)])
+@pytest.mark.parametrize("kind", ["dense", "point", "zero"])
+def test_fp32_forward_in_two_fp16_pieces(rb, shape, kind):
+    nx, ny, m = shape
+    geom, freqs = _geom(nx, ny, m), [3e5, 7e5]
+    print(f"[gpu-test] split forward {shape} {kind}", flush=True)
+    gr, gi = _random_g(2, m, geom.n_pixels, 13)
+    delta = W.random_delta(geom.n_pixels, 14)
+    if kind == "point":
+        delta[:-1] = 0.0             # the last pixel alone
+    if kind == "zero":
+        delta[:] = 0.0
+    got = _forward(rb, geom, gr, gi, freqs, delta)
+    for k, f in enumerate(freqs):
+        ref = born.born_forward(gr[k] + 1j * gi[k].astype(np.float64), delta, f, geom.h ** 2)
+        assert np.array_equal(got[k], got[k].T)
+        if kind == "zero":
+            assert np.all(got[k] == 0.0)
+        else:
+            close(got[k].view(np.float64), ref.view(np.float64), 2e-6, f"split forward {shape} {kind} k={k}")
+
+
+def test_fp32_forward_outside_the_fp16_range(rb):
+    """Rows that a sample of their pixels misjudges, or of any scale: every pair
+    as exact as an FP32 contraction makes it, relative to its sum of magnitudes."""
+    nx, ny, m = 70, 74, 160
+    geom, freqs = _geom(nx, ny, m), [4e5]
+    N = geom.n_pixels
+    print("[gpu-test] split forward, wide-ranging tables", flush=True)
+    gr, gi = _random_g(1, m, N, 15)
+    s = np.ones((m, N), np.float32)
+    s[:32] = (np.float32(2.0) ** np.random.default_rng(16).integers(-30, 20, 32))[:, None]
+    sampled = np.arange(256) * N // 256
+    s[40, sampled] = 0.0               # the sample sees nothing
+    s[41, sampled] = 1e-5              # ... or a hundred-thousandth
+    s[42, 777] = 4e4                   # one pixel far above the rest
+    s[150] = 0.0                       # an element that covers nothing
+    gr, gi = gr * s, gi * s
+    delta = W.random_delta(N, 17)
+    g = gr[0] + 1j * gi[0].astype(np.float64)
+    c = (2 * np.pi * freqs[0]) ** 2 * geom.h ** 2
+    ref = c * (g * delta) @ g.T
+    size = c * (np.abs(g) * np.abs(delta)) @ np.abs(g).T
+    got = _forward(rb, geom, gr, gi, freqs, delta)[0]
+    assert np.all(got[150] == 0.0) and np.all(got[:, 150] == 0.0)
+    ok = size > 0
+    # |error| <= 2^-24 (sqrt(5180) additions + 2 roundings) of the sum of magnitudes
+    assert np.max(np.abs(got - ref)[ok] / size[ok]) <= 74 * 2.0 ** -24
+    bad = gr.copy()
+    bad[0, 50, 3] = np.inf
+    nan = _forward(rb, geom, bad, gi, freqs, delta)[0]
+    assert not np.any(np.isfinite(nan[50])) and not np.any(np.isfinite(nan[:, 50]))
+    keep = np.ones(m, bool)
+    keep[50] = False
+    keep = np.outer(keep, keep) & ok
+    assert np.max(np.abs(nan - ref)[keep] / size[keep]) <= 74 * 2.0 ** -24
