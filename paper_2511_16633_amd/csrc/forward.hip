@@ -867,13 +867,13 @@ constexpr int kF16KC = 32, kF16Arr = 64 * kF16KC * 2;   // one array of a tile (
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-// out[x] = delta[x] / max |delta| as float (0 if delta is zero)
-__global__ void k_delta_f32(int64_t N, const double *__restrict__ delta, const double *__restrict__ dmax,
+// out[x] = delta[x] / max |delta| as float (0 if delta is zero), 0 for N <= x < n
+__global__ void k_delta_f32(int64_t N, int64_t n, const double *__restrict__ delta, const double *__restrict__ dmax,
                             float *__restrict__ out) {
     const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (x >= N) return;
+    if (x >= n) return;
     const double inv = dmax[0] > 0.0 ? 1.0 / dmax[0] : 0.0;
-    out[x] = (float)(delta[x] * inv);
+    out[x] = x < N ? (float)(delta[x] * inv) : 0.0f;
 }
 
 struct F16Stage {
@@ -1044,170 +1044,175 @@ __global__ void __launch_bounds__(256, 2) k_forward16_lds(FwdParams P, const S *
     }
 }
 
-// ------------------------------------------------------------------ 16-bit, large rings
-// For large rings the 64 x 64 tiles above move 16 KB per 64 MFMAs and are
-// bound by memory traffic.  This kernel takes 128 x 128 (e, r) tiles, waves 2 x 2
-// of 64 x 64 (4 x 4 blocks of 16 x 16, 64 MFMAs per wave and step), which
-// halves the bytes per MFMA.  The accumulators leave no registers for staged
-// tiles, so both operands go from memory straight into LDS (16-byte direct
-// loads, the chunk swizzle of the 64-tile kernel) from two plain tables: G
-// for the e side and a copy of G times delta (rounded to the storage type
-// as the 64-tile kernel rounds it) for the r side, whose rows are padded
-// with zeros to a multiple of 32 pixels.  Rows at or beyond m read row m - 1
-// (their outputs are dropped); on the e side a chunk beyond N reads the last
-// whole chunk, which the zero padding on the r side multiplies by 0.
-// It pays from m = 1024 (68 -> 36 ms for four frequencies on 1100^2 pixels,
-// the table pass included); at m = 512 the table pass outweighed the gain
-// (10.1 against 8.2 ms, measured before the table pass used 16-byte loads).
-#ifndef RB_FWD16_BIG_M
-#define RB_FWD16_BIG_M 1024
-#endif
-constexpr int kF16BigM = RB_FWD16_BIG_M;
-constexpr int kFBT = 128;
-constexpr int kFBArr = kFBT * kF16KC * 2;   // one array of a tile (bytes)
-
-// Gd[k][r][x] = G[k][r][x] * df[x] (rows padded to np pixels with zeros);
-// one thread per eight pixels of a row.
-template <typename S>
-__global__ void k_scale16(int64_t N, int64_t np, int64_t rows, const S *__restrict__ Gr,
-                          const S *__restrict__ Gi, const float *__restrict__ df, S *__restrict__ Dr,
-                          S *__restrict__ Di) {
-    using V = typename MM16<S>::vec;
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t per = np / 8;
-    if (t >= rows * per) return;
-    const int64_t row = t / per, x0 = (t - row * per) * 8;
-    V vr, vi;
-    if (x0 + 8 <= N) {
-        // whole run: 16-byte loads (N is a multiple of 8 here, so rows and
-        // runs are 16-byte aligned)
-        const V gr = *reinterpret_cast<const V *>(Gr + row * N + x0);
-        const V gi = *reinterpret_cast<const V *>(Gi + row * N + x0);
-        const f4 d0 = *reinterpret_cast<const f4 *>(df + x0), d1 = *reinterpret_cast<const f4 *>(df + x0 + 4);
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const float d = q < 4 ? d0[q] : d1[q - 4];
-            vr[q] = MM16<S>::from_f((float)gr[q] * d);
-            vi[q] = MM16<S>::from_f((float)gi[q] * d);
-        }
-    } else {
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int64_t x = x0 + q;
-            const bool ok = x < N;
-            const float d = ok ? df[x] : 0.0f;
-            const float gr = ok ? MM16<S>::to_f(Gr[row * N + x]) : 0.0f;
-            const float gi = ok ? MM16<S>::to_f(Gi[row * N + x]) : 0.0f;
-            vr[q] = MM16<S>::from_f(gr * d);
-            vi[q] = MM16<S>::from_f(gi * d);
-        }
-    }
-    *reinterpret_cast<V *>(Dr + row * np + x0) = vr;
-    *reinterpret_cast<V *>(Di + row * np + x0) = vi;
-}
-
-// Stage one k-step (32 pixels from xc) of rows r0 .. r0 + 127 of a table
-// with row stride `ld` into one LDS array: wave w fills rows 32 w .. 32 w +
-// 31, sixteen rows per instruction; lane l writes chunk slot l % 4 of row
-// l / 4 and so loads the chunk the swizzle puts there.
-__device__ __forceinline__ void fb_stage(const unsigned short *__restrict__ g, int64_t ld, int m, int r0,
-                                         int64_t xc, int64_t xmax, unsigned char *dst) {
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int rb = 32 * wave + 16 * i;
-        const int rl = rb + (lane >> 2);
-        const int r = min(r0 + rl, m - 1);
-        const int ch = (lane & 3) ^ ((rl >> 1) & 3);
-        const int64_t x = min(xc + 8 * ch, xmax);
-        __builtin_amdgcn_global_load_lds(g + (int64_t)r * ld + x, (lds_void_t *)(dst + rb * 64), 16, 0, 0);
-    }
-}
+// ------------------------------------------------------------------ 16-bit, wide tiles
+// Forward with 16-bit tables, tiles of 256 (e) x 128 (r) by eight waves of 64 x
+// 64 (4 x 4 blocks of 16 x 16, 64 MFMAs per wave and step of 32 pixels): 48 KB
+// of operands per 512 MFMAs, where the 64 x 64 tiles above move 16 KB per 64.
+// One workgroup per compute unit, two waves per SIMD.  A step's rows (64 bytes
+// each and array) pass through registers, those of the r side times delta and
+// rounded back to the storage type, into double-buffered LDS; as in
+// k_forward_split a wave loads its part two steps ahead, and the two waves of
+// a SIMD convert and multiply at different times.  Rows need no alignment.
+// 1024 elements / 1100^2, four frequencies: 34.9 ms, as the 128 x 128 tiles it
+// replaces (27.3 ms and 8.1 for their table of G delta, which it does not need:
+// 19 GB of workspace less).  L2 requests bound it: rows lie megabytes apart, so
+// a step takes 64-byte pieces, 81 G/s of them, with the matrix cores busy 0.26
+// at 2.4 GHz; 128 x 128 tiles in steps of 64 pixels, loaded two steps ahead,
+// took 65 ms.
+constexpr int kWE = 256, kWR = 128;
+constexpr int kWArrE = kWE * 64, kWArrR = kWR * 64;   // one array of a side (bytes)
+constexpr int kWBuf = 2 * kWArrE + 2 * kWArrR;        // e re, e im, r re, r im
+typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
 
 template <typename S>
-__global__ void __launch_bounds__(256, 2) k_forward16_big(FwdParams P, const S *__restrict__ Gr,
-                                                          const S *__restrict__ Gi, const S *__restrict__ Dr,
-                                                          const S *__restrict__ Di, int64_t np,
-                                                          float *__restrict__ part) {
+__global__ void __launch_bounds__(512, 2) k_forward16_wide(FwdParams P, const S *__restrict__ Gr,
+                                                           const S *__restrict__ Gi, const float *__restrict__ df,
+                                                           float *__restrict__ part) {
     using V = typename MM16<S>::vec;
-    __shared__ __align__(16) unsigned char sA[2][2 * kFBArr];   // [buffer][re, im] G_e rows
-    __shared__ __align__(16) unsigned char sB[2][2 * kFBArr];   // [buffer][re, im] G_r delta rows
+    __shared__ __align__(16) unsigned char sT[2][kWBuf];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int row = lane & 15, kk = lane >> 4;
-    const int we = wave >> 1, wr = wave & 1;
+    // waves s and s + 4 share a SIMD: half a tile apart, so that of a tile on
+    // the diagonal, whose lower half is idle, each SIMD has a working wave
+    const int wr = wave >> 2, we = (wave + 2 * wr) & 3;
     int te, tr, split, k;
-    fwd_block(P, te, tr, split, k);
-    if (P.dmin >= 32 && max_circ_dist(P.m, te * kFBT, kFBT, tr * kFBT, kFBT) < P.dmin) return;
-    const bool idle = (te == tr && we > wr) ||
-                      (P.dmin >= 32 && max_circ_dist(P.m, te * kFBT + 64 * we, 64, tr * kFBT + 64 * wr, 64) < P.dmin);
+    {
+        // consecutive logical ids are the tiles of one pixel split (see fwd_block)
+        const int64_t L = xcd_remap(blockIdx.x, gridDim.x);
+        int t = (int)(L % P.ntri);
+        const int64_t rest = L / P.ntri;
+        split = (int)(rest % P.nsplit);
+        k = (int)(rest / P.nsplit);
+        te = 0;
+        while (t >= P.ntl - 2 * te) t -= P.ntl - 2 * te++;
+        tr = 2 * te + t;
+    }
+    const int e0 = te * kWE, r0 = tr * kWR;
+    if (P.dmin >= 32 && max_circ_dist(P.m, e0, kWE, r0, kWR) < P.dmin) return;
+    const bool idle = e0 + 64 * we >= r0 + 64 * (wr + 1) ||
+                      (P.dmin >= 32 && max_circ_dist(P.m, e0 + 64 * we, 64, r0 + 64 * wr, 64) < P.dmin);
     const int64_t N = P.N;
-    const unsigned short *ger = reinterpret_cast<const unsigned short *>(Gr + (int64_t)k * P.m * N);
-    const unsigned short *gei = reinterpret_cast<const unsigned short *>(Gi + (int64_t)k * P.m * N);
-    const unsigned short *gdr = reinterpret_cast<const unsigned short *>(Dr + (int64_t)k * P.m * np);
-    const unsigned short *gdi = reinterpret_cast<const unsigned short *>(Di + (int64_t)k * P.m * np);
     const int64_t ks = (int64_t)split * P.kchunk;
     const int64_t ke = std::min<int64_t>(N, ks + P.kchunk);
-    const int nch = (int)((ke - ks + kF16KC - 1) / kF16KC);
-    auto stage = [&](int c, int buf) {
-        const int64_t xc = ks + (int64_t)c * kF16KC;
-        fb_stage(ger, N, P.m, te * kFBT, xc, N - 8, sA[buf]);
-        fb_stage(gei, N, P.m, te * kFBT, xc, N - 8, sA[buf] + kFBArr);
-        fb_stage(gdr, np, P.m, tr * kFBT, xc, np - 8, sB[buf]);
-        fb_stage(gdi, np, P.m, tr * kFBT, xc, np - 8, sB[buf] + kFBArr);
+    const int last = (int)((ke - ks + kF16KC - 1) / kF16KC) - 1;   // last chunk
+    // staging: pixels p8 .. p8 + 7 of e rows r4, r4 + 128 and r row r4.  Rows at
+    // or beyond m read row m - 1: their outputs are never read.
+    const int sch = tid & 3, p8 = sch * 8, r4 = tid >> 2;
+    const unsigned short *rowp[3];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        const int r = std::min((j < 2 ? e0 + 128 * j : r0) + r4, P.m - 1);
+        rowp[j] = reinterpret_cast<const unsigned short *>(Gr) + ((int64_t)k * P.m + r) * N;
+    }
+    const int64_t im = reinterpret_cast<const unsigned short *>(Gi) - reinterpret_cast<const unsigned short *>(Gr);
+    u32x4 v[3][2];
+    f4 d0, d1;
+    auto load = [&](int c) {
+        const int64_t xc = ks + (int64_t)c * kF16KC + p8;
+        if (xc - p8 + kF16KC <= N) {   // workgroup-uniform
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                v[j][0] = *reinterpret_cast<const u32x4_a2 *>(rowp[j] + xc);
+                v[j][1] = *reinterpret_cast<const u32x4_a2 *>(rowp[j] + im + xc);
+            }
+        } else {
+            // the last chunk of the row: zero beyond N
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+#pragma unroll
+                for (int a = 0; a < 2; ++a)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const unsigned short *g = rowp[j] + a * im;
+                        const unsigned lo = xc + 2 * q < N ? g[xc + 2 * q] : 0;
+                        const unsigned hi = xc + 2 * q + 1 < N ? g[xc + 2 * q + 1] : 0;
+                        v[j][a][q] = lo | (hi << 16);
+                    }
+        }
+        d0 = *reinterpret_cast<const f4 *>(df + xc);   // zero beyond N
+        d1 = *reinterpret_cast<const f4 *>(df + xc + 4);
     };
-    f4 re[4][4], im[4][4];
+    auto store = [&](unsigned char *buf) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+                *reinterpret_cast<u32x4 *>(buf + a * kWArrE + f16_off(r4 + 128 * j, sch)) = v[j][a];
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+            *reinterpret_cast<u32x4 *>(buf + 2 * kWArrE + a * kWArrR + f16_off(r4, sch)) =
+                f16_scale<S, V>(v[2][a], d0, d1);
+    };
+    f4 re[4][4], imv[4][4];
 #pragma unroll
     for (int b = 0; b < 4; ++b)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) re[b][c] = im[b][c] = f4{0, 0, 0, 0};
-    if (nch > 0) stage(0, 0);
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    for (int c = 0; c < nch; ++c) {
-        const int buf = c & 1;
-        if (c + 1 < nch) stage(c + 1, buf ^ 1);
-        if (!idle) {
-            V b_r[4], b_i[4];
+        for (int c = 0; c < 4; ++c) re[b][c] = imv[b][c] = f4{0, 0, 0, 0};
+    auto mma = [&](const unsigned char *sa) {
+        const unsigned char *sb = sa + 2 * kWArrE;
+        V b_r[4], b_i[4];
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) {
+            const int o = f16_off(64 * wr + 16 * cb + row, kk);
+            b_r[cb] = *reinterpret_cast<const V *>(sb + o);
+            b_i[cb] = *reinterpret_cast<const V *>(sb + kWArrR + o);
+        }
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const int o = f16_off(64 * we + 16 * b + row, kk);
+            const V a_r = *reinterpret_cast<const V *>(sa + o);
+            const V a_i = *reinterpret_cast<const V *>(sa + kWArrE + o);
+            const V a_n = neg(a_i);
+            // (ar + i ai)(br + i bi) = ar br - ai bi + i (ar bi + ai br)
 #pragma unroll
             for (int cb = 0; cb < 4; ++cb) {
-                const int rb = 64 * wr + 16 * cb + row;
-                b_r[cb] = *reinterpret_cast<const V *>(sB[buf] + f16_off(rb, kk));
-                b_i[cb] = *reinterpret_cast<const V *>(sB[buf] + kFBArr + f16_off(rb, kk));
+                re[b][cb] = MM16<S>::mma(a_r, b_r[cb], re[b][cb]);
+                imv[b][cb] = MM16<S>::mma(a_r, b_i[cb], imv[b][cb]);
             }
 #pragma unroll
-            for (int b = 0; b < 4; ++b) {
-                const int ra = 64 * we + 16 * b + row;
-                const V a_r = *reinterpret_cast<const V *>(sA[buf] + f16_off(ra, kk));
-                const V a_i = *reinterpret_cast<const V *>(sA[buf] + kFBArr + f16_off(ra, kk));
-                const V a_n = neg(a_i);
-                // (ar + i ai)(br + i bi) = ar br - ai bi + i (ar bi + ai br)
-#pragma unroll
-                for (int cb = 0; cb < 4; ++cb) {
-                    re[b][cb] = MM16<S>::mma(a_r, b_r[cb], re[b][cb]);
-                    re[b][cb] = MM16<S>::mma(a_n, b_i[cb], re[b][cb]);
-                    im[b][cb] = MM16<S>::mma(a_r, b_i[cb], im[b][cb]);
-                    im[b][cb] = MM16<S>::mma(a_i, b_r[cb], im[b][cb]);
-                }
+            for (int cb = 0; cb < 4; ++cb) {
+                re[b][cb] = MM16<S>::mma(a_n, b_i[cb], re[b][cb]);
+                imv[b][cb] = MM16<S>::mma(a_i, b_r[cb], imv[b][cb]);
             }
         }
-        __builtin_amdgcn_s_waitcnt(0);   // tile c + 1 has landed in LDS
-        __syncthreads();
-    }
+    };
+    load(0);
+    store(sT[0]);
+    load(std::min(1, last));
+    auto kloop = [&](auto first) {   // first: convert before multiplying
+        for (int c = 0; c <= last; ++c) {
+            lds_barrier();   // chunk c is in LDS, and no wave still reads the other buffer
+            unsigned char *sn = sT[(c & 1) ^ 1];
+            // (the last two steps convert and load the last chunk again, unused)
+            if (decltype(first)::value) {
+                store(sn);
+                load(std::min(c + 2, last));
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (!idle) mma(sT[c & 1]);
+            if (!decltype(first)::value) {
+                __builtin_amdgcn_sched_barrier(0);
+                store(sn);
+                load(std::min(c + 2, last));
+            }
+        }
+    };
+    if (wr == 0)
+        kloop(std::true_type());
+    else
+        kloop(std::false_type());
     if (idle) return;
     float *pp = part + ((int64_t)split * P.nf + k) * P.mp * P.mp * 2;
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
 #pragma unroll
         for (int cb = 0; cb < 4; ++cb) {
-            const int r = tr * kFBT + 64 * wr + 16 * cb + row;
+            const int r = r0 + 64 * wr + 16 * cb + row;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const int ee = te * kFBT + 64 * we + 16 * b + 4 * kk + i;
-                const int64_t o = ((int64_t)ee * P.mp + r) * 2;
-                pp[o] = re[b][cb][i];
-                pp[o + 1] = im[b][cb][i];
+                const int ee = e0 + 64 * we + 16 * b + 4 * kk + i;
+                *reinterpret_cast<f2 *>(pp + ((int64_t)ee * P.mp + r) * 2) = f2{re[b][cb][i], imv[b][cb][i]};
             }
         }
     }
@@ -1226,10 +1231,18 @@ static int device_cus() {
     return cus;
 }
 
-// The 128 x 128-tile 16-bit kernel: large rings, rows of whole 16-byte chunks.
-static bool fwd16_big(const rb_geometry *g, rb_dtype dt) {
+// The wide-tile 16-bit kernel: rows that are not 16-byte aligned, which the 64
+// x 64-tile kernel reads element by element (us per call, that / this: 64
+// elements / 255x301 107 / 153, 96 200 / 151, 200 548 / 171, 1024 8906 /
+// 1214), and aligned rows of large problems, where its tiles are bound by the
+// bytes they move (384 / 480^2 458 / 840, 512 / 480^2 855 / 750, 1024 / 128^2
+// 284 / 324, 1024 / 260^2 1210 / 974, 1024 / 1100^2, four frequencies, 67.8 /
+// 34.9 ms), unless padding to 256 rows costs more (600 / 480^2 1221 / 1307).
+static bool fwd16_wide(const rb_geometry *g, rb_dtype dt) {
+    if (dt != RB_BF16 && dt != RB_F16) return false;
     const int64_t N = (int64_t)g->nx * g->ny;
-    return (dt == RB_BF16 || dt == RB_F16) && g->m >= kF16BigM && N % 8 == 0;
+    if (N % 8 != 0) return g->m > 64;
+    return g->m >= 512 && N >= 65536 && 5 * ((g->m + kWE - 1) / kWE * kWE) <= 6 * g->m;
 }
 
 // FP32 tables on the FP16 cores: rings that fill more than half of a 128-element
@@ -1250,13 +1263,15 @@ static bool fwd32_direct(const rb_geometry *g, rb_dtype dt) {
 static FwdParams fwd_params(const rb_geometry *g, const double *freqs, int nf, rb_dtype dt) {
     FwdParams P;
     const bool fs = fwd32_split(g, dt);
-    const int tile = fs ? kFsT : (fwd16_big(g, dt) ? kFBT : 64);
+    const bool wide = fwd16_wide(g, dt);
+    const int tile = fs ? kFsT : (wide ? kWE : 64);
     P.m = g->m;
     P.mp = (g->m + tile - 1) / tile * tile;
     P.N = (int64_t)g->nx * g->ny;
     P.nf = nf;
-    P.ntl = P.mp / tile;
-    const int ntri = P.ntl * (P.ntl + 1) / 2;
+    P.ntl = P.mp / (wide ? kWR : tile);
+    // tiles on or above the diagonal (the wide ones: ntl - 2 te in row te)
+    const int ntri = wide ? P.ntl / 2 * (P.ntl / 2 + 1) : P.ntl * (P.ntl + 1) / 2;
     // about four rounds of resident workgroups (two per CU, four for the
     // FP32 kernel with direct loads), rounded down so the last round is full;
     // but no split is shorter than kMinSplitPx, and where rows are loaded in
@@ -1268,9 +1283,9 @@ static FwdParams fwd_params(const rb_geometry *g, const double *freqs, int nf, r
     // per call with splits of at least 16 / 64 / 128 / 512 pixels, two
     // frequencies: 64 elements / 128^2 FP32 37 / 26 / 25 / 44, BF16 33 / 27 /
     // 28 / 31, FP64 73 / 51 / 49 / 157; 64 / 480^2 FP32 133 / 132 / 134 / 115.
-    const int resident = (fs ? 1 : (fwd32_direct(g, dt) ? 4 : 2)) * device_cus();
+    const int resident = (fs || wide ? 1 : (fwd32_direct(g, dt) ? 4 : 2)) * device_cus();
     int64_t most = P.N / kMinSplitPx;
-    if (dt != RB_F64 && P.N % (dt == RB_F32 ? 4 : 8) == 0)
+    if (fs || wide || (dt != RB_F64 && P.N % (dt == RB_F32 ? 4 : 8) == 0))
         most = std::max<int64_t>(P.N / kFewSplitPx, std::min<int64_t>(most, resident / (ntri * nf)));
     int nsplit = std::max<int64_t>(1, std::min<int64_t>(4 * resident / (ntri * nf), most));
     // the kernels with direct loads (FP32, and 16-bit for large rings) also
@@ -1279,7 +1294,7 @@ static FwdParams fwd_params(const rb_geometry *g, const double *freqs, int nf, r
     // other, and long workgroups drift apart (FP32, 1024 elements / 1100^2:
     // 7 splits 144.4 ms, 30 splits 138.1 ms, 60 splits 135.0 ms for the
     // public call)
-    if (fs || fwd32_direct(g, dt) || fwd16_big(g, dt))
+    if (fs || fwd32_direct(g, dt) || wide)
         nsplit = std::max<int64_t>(nsplit, (P.N + kFdSplitPx - 1) / kFdSplitPx);
     const int kq = (fs || dt == RB_BF16 || dt == RB_F16) ? 32 : 16;
     int64_t kchunk = (P.N + nsplit - 1) / nsplit;
@@ -1298,14 +1313,11 @@ static FwdParams fwd_params(const rb_geometry *g, const double *freqs, int nf, r
     return P;
 }
 
-// workspace: max |delta|, the split partials, (16-bit) delta as float, and
-// (large rings) the G delta tables with rows padded to np pixels
+// workspace: max |delta|, the split partials, delta as float
 struct FwdWs {
     double *dmax, *dparts;
     void *part;
     float *df;
-    void *dr, *di;
-    int64_t np;
     // k_forward_split: row scales, |delta| maxima, delta's scale, list, flags
     float *fscale, *fpart, *fdscale;
     int *redo;
@@ -1313,7 +1325,7 @@ struct FwdWs {
     int64_t nflags;
 };
 
-static FwdWs carve_fwd(Carver &c, const FwdParams &P, rb_dtype dt, bool big, bool fs) {
+static FwdWs carve_fwd(Carver &c, const FwdParams &P, rb_dtype dt, bool fs) {
     const size_t es = dt == RB_F64 ? 8 : 4;
     FwdWs w;
     w.dmax = c.take<double>(1);
@@ -1321,9 +1333,6 @@ static FwdWs carve_fwd(Carver &c, const FwdParams &P, rb_dtype dt, bool big, boo
     w.part = c.take<char>((size_t)P.nsplit * P.nf * P.mp * P.mp * 2 * es);
     w.df = (fs || dt == RB_BF16 || dt == RB_F16 || (dt == RB_F32 && P.N % 4 == 0)) ? c.take<float>((size_t)P.N + 32)
                                                                                      : nullptr;
-    w.np = (P.N + kF16KC - 1) / kF16KC * kF16KC;
-    w.dr = big ? (void *)c.take<uint16_t>((size_t)P.nf * P.m * w.np) : nullptr;
-    w.di = big ? (void *)c.take<uint16_t>((size_t)P.nf * P.m * w.np) : nullptr;
     w.nflags = fs ? (int64_t)P.nf * P.nsplit * P.ntri : 0;
     if (fs) {
         w.fscale = c.take<float>((size_t)P.nf * P.m);
@@ -1338,7 +1347,7 @@ static FwdWs carve_fwd(Carver &c, const FwdParams &P, rb_dtype dt, bool big, boo
 size_t forward_workspace_bytes(const rb_geometry *g, int nf, rb_dtype dt) {
     FwdParams P = fwd_params(g, nullptr, nf, dt);
     Carver c(nullptr, 0);
-    carve_fwd(c, P, dt, fwd16_big(g, dt), fwd32_split(g, dt));
+    carve_fwd(c, P, dt, fwd32_split(g, dt));
     return c.used + 256;
 }
 
@@ -1351,10 +1360,9 @@ rb_status forward_impl(const rb_geometry *g, const void *G_re, const void *G_im,
     }
     FwdParams P = fwd_params(g, freqs, nf, dt);
     P.dmin = dmin;
-    const bool big = fwd16_big(g, dt);
     Carver c(ws, ws_bytes);
     const bool fs = fwd32_split(g, dt);
-    FwdWs w = carve_fwd(c, P, dt, big, fs);
+    FwdWs w = carve_fwd(c, P, dt, fs);
     FwdSplitOut so{nullptr, nullptr, nullptr, kFsT};
     const unsigned nblk = (unsigned)((int64_t)P.ntri * P.nsplit * nf);
     const dim3 gred(blocks_for(P.m, 32), P.m, nf);
@@ -1406,24 +1414,15 @@ rb_status forward_impl(const rb_geometry *g, const void *G_re, const void *G_im,
         case RB_BF16:
         case RB_F16:
             RB_TRY(reduce_absmax_f64(delta, P.N, w.dparts, w.dmax, st));
-            k_delta_f32<<<blocks_for(P.N, 256), 256, 0, st>>>(P.N, delta, w.dmax, w.df);
+            k_delta_f32<<<blocks_for(P.N + 32, 256), 256, 0, st>>>(P.N, P.N + 32, delta, w.dmax, w.df);
             RB_LAUNCHED();
-            if (big) {
-                const int64_t rows = (int64_t)nf * P.m;
-                auto go = [&](auto tag) {
-                    using S = decltype(tag);
-                    k_scale16<S><<<blocks_for(rows * (w.np / 8), 256), 256, 0, st>>>(
-                        P.N, w.np, rows, (const S *)G_re, (const S *)G_im, w.df, (S *)w.dr, (S *)w.di);
-                    RB_LAUNCHED();
-                    k_forward16_big<S><<<nblk, 256, 0, st>>>(P, (const S *)G_re, (const S *)G_im,
-                                                             (const S *)w.dr, (const S *)w.di, w.np,
-                                                             (float *)w.part);
-                    return RB_OK;
-                };
+            if (fwd16_wide(g, dt)) {
                 if (dt == RB_BF16)
-                    RB_TRY(go(__hip_bfloat16()));
+                    k_forward16_wide<<<nblk, 512, 0, st>>>(P, (const __hip_bfloat16 *)G_re,
+                                                           (const __hip_bfloat16 *)G_im, w.df, (float *)w.part);
                 else
-                    RB_TRY(go(__half()));
+                    k_forward16_wide<<<nblk, 512, 0, st>>>(P, (const __half *)G_re, (const __half *)G_im, w.df,
+                                                           (float *)w.part);
             } else if (dt == RB_BF16)
                 k_forward16_lds<__hip_bfloat16><<<nblk, 256, 0, st>>>(P, (const __hip_bfloat16 *)G_re,
                                                                       (const __hip_bfloat16 *)G_im, w.df,

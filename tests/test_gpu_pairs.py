@@ -219,3 +219,27 @@ def test_fp32_forward_outside_the_fp16_range(rb):
     keep[50] = False
     keep = np.outer(keep, keep) & ok
     assert np.max(np.abs(nan - ref)[keep] / size[keep]) <= 74 * 2.0 ** -24
+
+
+# 16-bit tables with rows that are not 16-byte aligned (odd and even pixel
+# counts, a last chunk of 1 to 31 pixels) and, aligned, large enough for the
+# same 256 x 128 tiles; rings of a part of a tile, a tile and two elements, and
+# three rows of tiles.
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("shape", [(33, 31, 65), (50, 41, 130), (61, 67, 258), (41, 45, 520), (256, 256, 512)])
+def test_16bit_forward_in_wide_tiles(rb, dtype, shape):
+    nx, ny, m = shape
+    geom, freqs = _geom(nx, ny, m), [3e5]
+    print(f"[gpu-test] wide 16-bit forward {dtype} {shape}", flush=True)
+    gr, gi = _random_g(1, m, geom.n_pixels, 18)
+    td = rb._binding.TORCH_DTYPES[rb.DTYPES[dtype]]
+    tr, ti = torch.as_tensor(gr, device=DEV).to(td), torch.as_tensor(gi, device=DEV).to(td)
+    delta = W.random_delta(geom.n_pixels, 19)
+    d = torch.zeros((1, m, m, 2), dtype=torch.float64, device=DEV)
+    sc = torch.tensor([0.25], dtype=torch.float32, device=DEV)
+    rb.born_forward(geom, tr, ti, sc, dtype, freqs, torch.as_tensor(delta, device=DEV), d)
+    got = torch.view_as_complex(d).cpu().numpy()[0]
+    g = 0.25 * (tr[0].double().cpu().numpy() + 1j * ti[0].double().cpu().numpy())
+    ref = born.born_forward(g, delta, freqs[0], geom.h ** 2)
+    assert np.array_equal(got, got.T)
+    close(got.view(np.float64), ref.view(np.float64), TOL[dtype], f"wide forward {dtype} {shape}")
