@@ -1219,7 +1219,8 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_split(const A args) {
     const int64_t x0 = (int64_t)loc.tile() * kT16NT;
     const float *__restrict__ gr = (const float *)it.Gr + (int64_t)k * P.m * N;
     const float *__restrict__ gi = (const float *)it.Gi + (int64_t)k * P.m * N;
-    const bool vec = ((N & 3) == 0) && (x0 + kT16NT <= N);   // workgroup-uniform
+    const bool vec = x0 + kT16NT <= N;   // workgroup-uniform; rows need no alignment
+    typedef f4 f4_a4 __attribute__((aligned(4)));
     const int64_t per = (int64_t)P.mp * P.mp;
     const _Float16 *__restrict__ ahi = (const _Float16 *)it.split_hi + 2 * k * per;
     const _Float16 *__restrict__ alo = (const _Float16 *)it.split_lo + 2 * k * per;
@@ -1249,7 +1250,7 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_split(const A args) {
             // pixels at or beyond N read the last one: theirs are dropped
             const unsigned ro = (unsigned)min(r8 + 8 * j, rl) * nb4;
             if (decltype(vtag)::value) {
-                v[j] = *reinterpret_cast<const f4 *>(at(base, ro + 4u * p4));
+                v[j] = *reinterpret_cast<const f4_a4 *>(at(base, ro + 4u * p4));
             } else {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) v[j][q] = *at(base, ro + 4u * (unsigned)min(p4 + q, xl));

@@ -646,8 +646,6 @@ __global__ void __launch_bounds__(256) k_fs_delta(int64_t N, int64_t n, const do
     for (int64_t q = x; q < nflags; q += (int64_t)gridDim.x * 256) flags[q] = 0;
 }
 
-// VEC: rows of whole 16-byte pieces (N a multiple of 4).
-template <bool VEC>
 __global__ void __launch_bounds__(512, 2) k_forward_split(FwdParams P, const float *__restrict__ Gr,
                                                           const float *__restrict__ Gi,
                                                           const float *__restrict__ df,
@@ -685,22 +683,24 @@ __global__ void __launch_bounds__(512, 2) k_forward_split(FwdParams P, const flo
     const int64_t im = Gi - Gr;
     f4 v[4][2], dl;
     float top = 0.0f;
+    typedef f4 f4_a4 __attribute__((aligned(4)));   // rows need no alignment
     auto load = [&](int c) {
         const int64_t xc = ks + (int64_t)c * kFsKC + p4;
+        if (xc - p4 + kFsKC <= N) {   // workgroup-uniform
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if (VEC) {
-                const int64_t x = std::min<int64_t>(xc, N - 4);
-                v[j][0] = *reinterpret_cast<const f4 *>(rowp[j] + x);
-                v[j][1] = *reinterpret_cast<const f4 *>(rowp[j] + im + x);
-            } else {
+            for (int j = 0; j < 4; ++j) {
+                v[j][0] = *reinterpret_cast<const f4_a4 *>(rowp[j] + xc);
+                v[j][1] = *reinterpret_cast<const f4_a4 *>(rowp[j] + im + xc);
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const int64_t x = std::min<int64_t>(xc + q, N - 1);
                     v[j][0][q] = rowp[j][x];
                     v[j][1][q] = rowp[j][im + x];
                 }
-            }
         }
         dl = *reinterpret_cast<const f4 *>(df + xc);
     };
@@ -829,7 +829,7 @@ __global__ void __launch_bounds__(512, 2) k_forward_split(FwdParams P, const flo
 
 // The listed (tile, split, frequency)s of k_forward_split from FP32: each is
 // three or four 64 x 64 tiles.  Partials in units of (float)delta sd, G
-// unscaled.
+// unscaled.  VEC: rows of whole 16-byte pieces (N a multiple of 4).
 template <bool VEC>
 __global__ void __launch_bounds__(256, 2) k_forward_f32_list(FwdParams P, const float *__restrict__ Gr,
                                                              const float *__restrict__ Gi,
@@ -1387,15 +1387,12 @@ rb_status forward_impl(const rb_geometry *g, const void *G_re, const void *G_im,
                                                                       w.redo, w.flags, w.nflags);
                 RB_LAUNCHED();
                 const unsigned nl = (unsigned)std::min<int64_t>(4 * w.nflags, 2 * device_cus());
-                if (P.N % 4 == 0) {
-                    k_forward_split<true><<<nblk, 512, 0, st>>>(P, gr, gi, w.df, w.fscale, pt, w.redo, w.flags);
-                    RB_LAUNCHED();
+                k_forward_split<<<nblk, 512, 0, st>>>(P, gr, gi, w.df, w.fscale, pt, w.redo, w.flags);
+                RB_LAUNCHED();
+                if (P.N % 4 == 0)
                     k_forward_f32_list<true><<<nl, 256, 0, st>>>(P, gr, gi, w.df, pt, w.redo);
-                } else {
-                    k_forward_split<false><<<nblk, 512, 0, st>>>(P, gr, gi, w.df, w.fscale, pt, w.redo, w.flags);
-                    RB_LAUNCHED();
+                else
                     k_forward_f32_list<false><<<nl, 256, 0, st>>>(P, gr, gi, w.df, pt, w.redo);
-                }
                 so = FwdSplitOut{w.flags, w.fscale, w.fdscale, kFsT};
             } else if (fwd32_direct(g, dt)) {
                 k_delta_cast<<<blocks_for(P.N + 16, 256), 256, 0, st>>>(P.N, P.N + 16, delta, w.df);
