@@ -243,3 +243,34 @@ def test_16bit_forward_in_wide_tiles(rb, dtype, shape):
     ref = born.born_forward(g, delta, freqs[0], geom.h ** 2)
     assert np.array_equal(got, got.T)
     close(got.view(np.float64), ref.view(np.float64), TOL[dtype], f"wide forward {dtype} {shape}")
+
+
+# The outlier selection of small rings runs in one block per frequency: rings
+# of 1024 pairs (one stripe of its threads), of 10000 (a part of the last) and
+# of 16384 (all it holds), and one beyond, with ties across the threshold that
+# spread over all stripes, so that the flat index decides which are zeroed.
+@pytest.mark.parametrize("m", [32, 100, 128, 130])
+def test_outlier_selection_with_ties(rb, m):
+    from oracle import invert
+    p = W.custom(33, 0.5e-3, m, 8e-3, 90, [[2.4e5, 3.1e5]], seed=23)
+    topts = W.resolve_trace_opts(p.geom, p.c_start, 90)
+    f = p.freq_sets[0]
+    print(f"[gpu-test] outlier ties m={m}", flush=True)
+    pm = p.p_meas[0].copy()
+    sel = np.flatnonzero(invert.receiver_mask(m, p.inv.recv_fraction).reshape(-1))
+    kz = int(np.floor(p.inv.outlier_fraction * sel.size))
+    rng = np.random.default_rng(m)
+    for k in range(2):
+        big = np.abs(pm[k]).max()
+        tied = rng.choice(sel, size=2 * kz, replace=False)
+        pm[k].reshape(-1)[tied] = 2.0 * big * np.exp(0.3j)
+        pm[k].reshape(-1)[tied[:kz // 2]] *= 1.5          # half above the ties
+    ref, _ = invert.invert_frequency_set(p.geom, topts, p.inv, p.c_start, p.alpha0, f, pm)
+    c_in = torch.as_tensor(p.c_start.reshape(-1), device=DEV)
+    c_out = torch.empty_like(c_in)
+    rb.invert_frequency_set(p.geom, topts, p.inv, "f64", c_in, torch.as_tensor(p.alpha0.reshape(-1), device=DEV), f,
+                            torch.as_tensor(np.stack([pm.real, pm.imag], -1), device=DEV), c_out)
+    dc = c_out.cpu().numpy() - p.c_start.reshape(-1)
+    dc_o = ref.reshape(-1) - p.c_start.reshape(-1)
+    # the bound of the tied-outlier test at 64 elements; one pair more or less moves the update by 1e-3
+    assert np.linalg.norm(dc - dc_o) <= 1e-6 * np.linalg.norm(dc_o)
