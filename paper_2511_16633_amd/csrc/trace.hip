@@ -81,29 +81,31 @@ __device__ __forceinline__ void field(const double2 *__restrict__ sa, const TP &
     a = a0 + fv * (a1 - a0);
 }
 
-// The same evaluation with the four corner records of the last cell kept in
+// The same evaluation with the four corner records of a cell kept in
 // registers: a lane reloads them only when its point has left that cell.
 // The four RK4 stages of a step lie within one step length (less than a
 // cell), so most stages of most lanes reuse the corners, and the gathers -
 // the tracer's bottleneck in the vector-memory path - shrink to the lanes
 // that crossed a cell edge.  The values are those of field().
 struct FieldCache {
-    int i = -1, j = -1;   // padded cell whose corners are held (none yet)
+    int i = INT_MIN, j = INT_MIN;   // cell whose corners are held (none yet)
     double2 c00, c10, c01, c11;
 };
 
-__device__ __forceinline__ void field_cached(const double2 *__restrict__ sa, const TP &P, double x, double y,
-                                             FieldCache &fc, double &s, double &gx, double &gy, double &a) {
-#pragma clang fp contract(fast)
-    double u = (x - P.x0) * P.inv_h;
-    double v = (y - P.y0) * P.inv_h;
-    double fi = floor(u), fj = floor(v);
-    const int i = (int)fmin(fmax(fi, -2.0), (double)P.nx) + 2;
-    const int j = (int)fmin(fmax(fj, -2.0), (double)P.ny) + 2;
-    double fu = u - fi, fv = v - fj;
+// Clamped cell index of an integer-valued coordinate (saturating conversion:
+// any point far outside ends in an outer ring of water).
+__device__ __forceinline__ int field_cell(double f, int n) {
+    int i;
+    asm("v_cvt_i32_f64 %0, %1" : "=v"(i) : "v"(f));
+    return min(max(i, -2), n);
+}
+
+// Loads the corners of cell (i, j) unless held.
+__device__ __forceinline__ void field_fetch(const double2 *__restrict__ sa, const TP &P, int i, int j,
+                                            FieldCache &fc) {
     if (i != fc.i || j != fc.j) {
         const int ld = P.nx + 4;
-        const double2 *q = sa + (j * ld + i);
+        const double2 *q = sa + ((j + 2) * ld + i + 2);
         fc.c00 = q[0];
         fc.c10 = q[1];
         fc.c01 = q[ld];
@@ -111,6 +113,23 @@ __device__ __forceinline__ void field_cached(const double2 *__restrict__ sa, con
         fc.i = i;
         fc.j = j;
     }
+}
+
+// Starts the loads of the cell that holds (x, y).
+__device__ __forceinline__ void field_prefetch(const double2 *__restrict__ sa, const TP &P, double x, double y,
+                                               FieldCache &fc) {
+    const double u = (x - P.x0) * P.inv_h, v = (y - P.y0) * P.inv_h;
+    field_fetch(sa, P, field_cell(floor(u), P.nx), field_cell(floor(v), P.ny), fc);
+}
+
+__device__ __forceinline__ void field_cached(const double2 *__restrict__ sa, const TP &P, double x, double y,
+                                             FieldCache &fc, double &s, double &gx, double &gy, double &a) {
+#pragma clang fp contract(fast)
+    double u = (x - P.x0) * P.inv_h;
+    double v = (y - P.y0) * P.inv_h;
+    double fi = floor(u), fj = floor(v);
+    double fu = u - fi, fv = v - fj;
+    field_fetch(sa, P, field_cell(fi, P.nx), field_cell(fj, P.ny), fc);
     double dx0 = fc.c10.x - fc.c00.x, dx1 = fc.c11.x - fc.c01.x;
     double s0 = fc.c00.x + fu * dx0;
     double s1 = fc.c01.x + fu * dx1;
@@ -120,6 +139,17 @@ __device__ __forceinline__ void field_cached(const double2 *__restrict__ sa, con
     double a0 = fc.c00.y + fu * (fc.c10.y - fc.c00.y);
     double a1 = fc.c01.y + fu * (fc.c11.y - fc.c01.y);
     a = a0 + fv * (a1 - a0);
+}
+
+// The value of the next lower / next higher lane (the lane's own at the end
+// of the wave): one vector move, without LDS.
+__device__ __forceinline__ int lane_below(int v) { return __builtin_amdgcn_update_dpp(v, v, 0x138, 0xf, 0xf, false); }
+__device__ __forceinline__ int lane_above(int v) { return __builtin_amdgcn_update_dpp(v, v, 0x130, 0xf, 0xf, false); }
+__device__ __forceinline__ double lane_below(double v) {
+    return __hiloint2double(lane_below(__double2hiint(v)), lane_below(__double2loint(v)));
+}
+__device__ __forceinline__ double lane_above(double v) {
+    return __hiloint2double(lane_above(__double2hiint(v)), lane_above(__double2loint(v)));
 }
 
 // 1/s from the hardware reciprocal refined by two Newton steps (to within
@@ -220,12 +250,13 @@ __global__ void __launch_bounds__(256) k_trace(TP P, const double2 *__restrict__
     const int64_t seg = (int64_t)eb * nw + wv;
     uint64_t *lp = list_px + seg * cap;
     uint64_t *lr = list_rx + seg * cap;
-    const uint64_t below = (1ull << lane) - 1ull;
+    // set bits of a ballot below this lane
+    auto below = [](uint64_t b) { return __builtin_amdgcn_mbcnt_hi((unsigned)(b >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)b, 0u)); };
     const bool has_right = own && j + 1 < P.nr;   // cells (., j) exist
     int cp = 0, cr = 0;                          // wave-uniform list counts
-    double xp = 0.0, yp = 0.0;                   // node n - 1 of this ray
+    double xp = 0.0, yp = 0.0, xrp = 0.0, yrp = 0.0;   // node n - 1 of this ray and of the next
     bool alive = valid;   // alive at the current node n
-    FieldCache fc;
+    FieldCache fc, fm;    // cells of the step's ends, of its middle
     bool last = false;    // the current node is the ray's last
     for (int n = 0; n <= P.nmax; ++n) {
         if (!__any(alive)) break;
@@ -233,11 +264,10 @@ __global__ void __launch_bounds__(256) k_trace(TP P, const double2 *__restrict__
         double s0 = 1.0, g0x = 0.0, g0y = 0.0, a0 = 0.0;
         if (alive) field_cached(sa, P, st[0], st[1], fc, s0, g0x, g0y, a0);
         // neighbours at equal travel time
-        const double xl = __shfl_up(st[0], 1), yl = __shfl_up(st[1], 1);
-        const double xr = __shfl_down(st[0], 1), yr = __shfl_down(st[1], 1);
-        const int al = __shfl_up((int)alive, 1), ar = __shfl_down((int)alive, 1);
+        const double xl = lane_below(st[0]), yl = lane_below(st[1]);
+        const double xr = lane_above(st[0]), yr = lane_above(st[1]);
+        const int al = lane_below((int)alive), ar = lane_above((int)alive);
         // cell (n - 1, j): nodes n - 1 and n of rays j and j + 1
-        const double xrp = __shfl_down(xp, 1), yrp = __shfl_down(yp, 1);
         bool pix = false, ring = false;
         if (n >= 1 && has_right && alive && ar) {
             const double cxmin = fmin(fmin(xp, xrp), fmin(st[0], xr));
@@ -256,8 +286,8 @@ __global__ void __launch_bounds__(256) k_trace(TP P, const double2 *__restrict__
         {
             const uint64_t mp = __ballot(pix), mr = __ballot(ring);
             const uint64_t id = cell_id(eb, n - 1, j);
-            if (pix) lp[cp + __popcll(mp & below)] = id;
-            if (ring) lr[cr + __popcll(mr & below)] = id;
+            if (pix) lp[cp + below(mp)] = id;
+            if (ring) lr[cr + below(mr)] = id;
             cp += __popcll(mp);
             cr += __popcll(mr);
         }
@@ -293,6 +323,8 @@ __global__ void __launch_bounds__(256) k_trace(TP P, const double2 *__restrict__
         }
         xp = st[0];
         yp = st[1];
+        xrp = xr;
+        yrp = yr;
         if (alive && (last || n == P.nmax)) {
             if (own) L[(size_t)eb * P.nr + j] = n;
             alive = false;
@@ -309,10 +341,17 @@ __global__ void __launch_bounds__(256) k_trace(TP P, const double2 *__restrict__
             }
 #pragma unroll
             for (int q = 0; q < 5; ++q) t[q] = st[q] + hdt * k1[q];
-            rhs(sa, P, t, fc, k2);
+            // Both cells that the step will need, those of its middle and
+            // (by a first-order step) of its end, are loaded at once: loaded
+            // as the stages reach them they were two gather latencies
+            // per step, one after the other.
+            fm = fc;
+            field_prefetch(sa, P, t[0], t[1], fm);
+            field_prefetch(sa, P, st[0] + dt * k1[0], st[1] + dt * k1[1], fc);
+            rhs(sa, P, t, fm, k2);
 #pragma unroll
             for (int q = 0; q < 5; ++q) t[q] = st[q] + hdt * k2[q];
-            rhs(sa, P, t, fc, k3);
+            rhs(sa, P, t, fm, k3);
 #pragma unroll
             for (int q = 0; q < 5; ++q) t[q] = st[q] + dt * k3[q];
             rhs(sa, P, t, fc, k4);
