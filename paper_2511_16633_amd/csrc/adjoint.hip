@@ -38,121 +38,122 @@
 namespace rb {
 namespace {
 
-// ------------------------------------------------------------------ adjoint
-// WG = 4 waves; wave w owns 16*CB pixels; rows are processed 16*RB at a time.
-template <typename T, int RB, int CB>
+// ------------------------------------------------------------------ FP64
+// WG = 4 waves; wave w owns 16 CB pixels of one frequency and takes the
+// emitters of its pass group, 16 RB at a time, against all their receivers.
+// An FP64 MFMA runs 64 cycles, so the operands come straight from memory; what
+// bounds the kernel is that every SIMD has a wave: a workgroup per (pixel
+// tile, frequency), 64 pixels where 128 would leave compute units idle.  With
+// a workgroup per 128 pixels over all frequencies and the Hessian product
+// always formed, and now, two frequencies: 64 elements / 128^2 64 -> 37 us,
+// 256 / 480^2 4.18 -> 2.65 ms (1.5 ms of MFMA time at 78.6 TFLOP/s).
+template <typename T, int RB, int CB, bool HESS>
 __global__ void __launch_bounds__(256) k_adjoint(AdjParams P, const T *__restrict__ Gr, const T *__restrict__ Gi,
                                                  const T *__restrict__ Ar, const T *__restrict__ Ai,
                                                  const T *__restrict__ Wt, const uint8_t *__restrict__ flags,
-                                                 double *__restrict__ grad, double *__restrict__ hd) {
+                                                 double *__restrict__ pg, double *__restrict__ ph) {
     using acc_t = typename MM<T>::acc;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int row = lane & 15, kk = lane >> 4;
     const int64_t N = P.N;
     const int64_t xw = (int64_t)blockIdx.x * (64 * CB) + (int64_t)wave * 16 * CB;
-    double gacc[CB], hacc[CB];
+    const int k = blockIdx.y;
+    const T *gr = Gr + (int64_t)k * P.m * N;
+    const T *gi = Gi + (int64_t)k * P.m * N;
+    const T *ar = Ar + (int64_t)k * P.mp * P.mp;
+    const T *ai = Ai + (int64_t)k * P.mp * P.mp;
+    const T *wt = Wt + (int64_t)k * P.mp * P.mp;
+    const uint8_t *fl = flags + (int64_t)k * P.nb * P.nb;
+    T gp[CB], hp[CB];
+    int64_t xs[CB];
 #pragma unroll
-    for (int c = 0; c < CB; ++c) gacc[c] = hacc[c] = 0.0;
-
-    for (int k = 0; k < P.nf; ++k) {
-        const T *gr = Gr + (int64_t)k * P.m * N;
-        const T *gi = Gi + (int64_t)k * P.m * N;
-        const T *ar = Ar + (int64_t)k * P.mp * P.mp;
-        const T *ai = Ai + (int64_t)k * P.mp * P.mp;
-        const T *wt = Wt + (int64_t)k * P.mp * P.mp;
-        const uint8_t *fl = flags + (int64_t)k * P.nb * P.nb;
-        T gp[CB], hp[CB];
+    for (int c = 0; c < CB; ++c) {
+        gp[c] = hp[c] = T(0);
+        xs[c] = min(xw + 16 * c + row, N - 1);   // pixels beyond N: the last one, dropped below
+    }
+    for (int ec = 0; ec < P.mp; ec += 16 * RB) {
+        acc_t yr[RB][CB], yn[RB][CB], z[RB][CB];
 #pragma unroll
-        for (int c = 0; c < CB; ++c) gp[c] = hp[c] = T(0);
-        for (int ec = 0; ec < P.mp; ec += 16 * RB) {
-            acc_t yr[RB][CB], yn[RB][CB], z[RB][CB];
+        for (int b = 0; b < RB; ++b)
 #pragma unroll
-            for (int b = 0; b < RB; ++b)
-#pragma unroll
-                for (int c = 0; c < CB; ++c) yr[b][c] = yn[b][c] = z[b][c] = acc_t{0, 0, 0, 0};
-            for (int rc = 0; rc < P.mp; rc += 16) {
-                bool on[RB];
-                bool any = false;
-#pragma unroll
-                for (int b = 0; b < RB; ++b) {
-                    const int eb = (ec + 16 * b) / 32;
-                    on[b] = (eb < P.nb) && fl[eb * P.nb + rc / 32];
-                    any |= on[b];
-                }
-                if (!any) continue;
-                T br[4][CB], bi[4][CB], b2[4][CB];
-#pragma unroll
-                for (int s = 0; s < 4; ++s) {
-                    const int r = rc + 4 * kk + s;
-#pragma unroll
-                    for (int c = 0; c < CB; ++c) {
-                        const int64_t x = xw + 16 * c + row;
-                        const bool ok = (r < P.m) && (x < N);
-                        br[s][c] = ld(gr + (int64_t)r * N + x, ok);
-                        bi[s][c] = ld(gi + (int64_t)r * N + x, ok);
-                        b2[s][c] = br[s][c] * br[s][c] + bi[s][c] * bi[s][c];
-                    }
-                }
-#pragma unroll
-                for (int b = 0; b < RB; ++b) {
-                    if (!on[b]) continue;
-                    const int64_t off = (int64_t)(ec + 16 * b + row) * P.mp + rc + 4 * kk;
-                    T va[4], vi[4], vw[4];
-#pragma unroll
-                    for (int s = 0; s < 4; ++s) {
-                        va[s] = ar[off + s];
-                        vi[s] = ai[off + s];
-                        vw[s] = wt[off + s];
-                    }
-#pragma unroll
-                    for (int s = 0; s < 4; ++s) {
-#pragma unroll
-                        for (int c = 0; c < CB; ++c) {
-                            yr[b][c] = MM<T>::mma(va[s], br[s][c], yr[b][c]);
-                            yr[b][c] = MM<T>::mma(vi[s], bi[s][c], yr[b][c]);
-                            yn[b][c] = MM<T>::mma(va[s], bi[s][c], yn[b][c]);
-                            yn[b][c] = MM<T>::mma(-vi[s], br[s][c], yn[b][c]);
-                            z[b][c] = MM<T>::mma(vw[s], b2[s][c], z[b][c]);
-                        }
-                    }
-                }
-            }
-            // fused epilogue: reduce over the e rows of this chunk against G_e
+            for (int c = 0; c < CB; ++c) yr[b][c] = yn[b][c] = z[b][c] = acc_t{0, 0, 0, 0};
+        for (int rc = 0; rc < P.mp; rc += 16) {
+            bool on[RB];
+            bool any = false;
 #pragma unroll
             for (int b = 0; b < RB; ++b) {
+                const int eb = (ec + 16 * b) / 32;
+                on[b] = (eb < P.nb) && fl[eb * P.nb + rc / 32];
+                any |= on[b];
+            }
+            if (!any) continue;
+            T br[4][CB], bi[4][CB], b2[4][CB];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int e = ec + 16 * b + MM<T>::out_row(kk, i);
+            for (int s = 0; s < 4; ++s) {
+                // rows at or beyond m: the last one (their A and W are zero)
+                const int64_t ro = (int64_t)min(rc + 4 * kk + s, P.m - 1) * N;
+#pragma unroll
+                for (int c = 0; c < CB; ++c) {
+                    br[s][c] = gr[ro + xs[c]];
+                    bi[s][c] = gi[ro + xs[c]];
+                    if (HESS) b2[s][c] = br[s][c] * br[s][c] + bi[s][c] * bi[s][c];
+                }
+            }
+#pragma unroll
+            for (int b = 0; b < RB; ++b) {
+                if (!on[b]) continue;
+                const int64_t off = (int64_t)(ec + 16 * b + row) * P.mp + rc + 4 * kk;
+                T va[4], vi[4], vw[4];
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    va[s] = ar[off + s];
+                    vi[s] = ai[off + s];
+                    if (HESS) vw[s] = wt[off + s];
+                }
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
 #pragma unroll
                     for (int c = 0; c < CB; ++c) {
-                        const int64_t x = xw + 16 * c + row;
-                        const bool ok = (e < P.m) && (x < N);
-                        const T ge_r = ld(gr + (int64_t)e * N + x, ok);
-                        const T ge_i = ld(gi + (int64_t)e * N + x, ok);
-                        gp[c] += ge_r * yr[b][c][i] - ge_i * yn[b][c][i];
-                        hp[c] += (ge_r * ge_r + ge_i * ge_i) * z[b][c][i];
+                        yr[b][c] = MM<T>::mma(va[s], br[s][c], yr[b][c]);
+                        yn[b][c] = MM<T>::mma(va[s], bi[s][c], yn[b][c]);
+                    }
+#pragma unroll
+                    for (int c = 0; c < CB; ++c) {
+                        yr[b][c] = MM<T>::mma(vi[s], bi[s][c], yr[b][c]);
+                        yn[b][c] = MM<T>::mma(-vi[s], br[s][c], yn[b][c]);
+                        if (HESS) z[b][c] = MM<T>::mma(vw[s], b2[s][c], z[b][c]);
                     }
                 }
             }
         }
+        // fused epilogue: reduce over the e rows of this chunk against G_e
+        // (rows at or beyond m: the last one, whose Y and Z are zero)
 #pragma unroll
-        for (int c = 0; c < CB; ++c) {
-            gacc[c] += (double)gp[c] * P.cg[k];
-            hacc[c] += (double)hp[c] * P.ch[k];
+        for (int b = 0; b < RB; ++b) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int64_t eo = (int64_t)min(ec + 16 * b + MM<T>::out_row(kk, i), P.m - 1) * N;
+#pragma unroll
+                for (int c = 0; c < CB; ++c) {
+                    const T ge_r = gr[eo + xs[c]], ge_i = gi[eo + xs[c]];
+                    gp[c] += ge_r * yr[b][c][i] - ge_i * yn[b][c][i];
+                    if (HESS) hp[c] += (ge_r * ge_r + ge_i * ge_i) * z[b][c][i];
+                }
+            }
         }
     }
     // sum the four lane groups that hold the same pixel (fixed order)
 #pragma unroll
     for (int c = 0; c < CB; ++c) {
-        double g = gacc[c], h = hacc[c];
+        double g = (double)gp[c] * P.cg[k], h = (double)hp[c] * P.ch[k];
         g += __shfl_xor(g, 16);
         h += __shfl_xor(h, 16);
         g += __shfl_xor(g, 32);
         h += __shfl_xor(h, 32);
         const int64_t x = xw + 16 * c + row;
         if (kk == 0 && x < N) {
-            grad[x] += g;
-            if (hd) hd[x] += h;
+            pg[(int64_t)k * N + x] = g;
+            if (HESS) ph[(int64_t)k * N + x] = h;
         }
     }
 }
@@ -1620,10 +1621,20 @@ rb_status adjoint_run(const AdjTask &task, hipStream_t st) {
     double *grad = task.grad, *hdiag = task.hdiag;
     switch (task.dt) {
         case RB_F64: {
-            const unsigned nb = blocks_for(P.N, 64 * 2);
-            k_adjoint<double, 2, 2><<<nb, 256, 0, st>>>(P, (const double *)it.Gr, (const double *)it.Gi,
-                                                        (const double *)it.Ar, (const double *)it.Ai,
-                                                        (const double *)it.Wt, it.flags, grad, hdiag);
+            auto go = [&](auto rb, auto cb, auto hess) {
+                k_adjoint<double, decltype(rb)::value, decltype(cb)::value, decltype(hess)::value>
+                    <<<dim3(blocks_for(P.N, 64 * decltype(cb)::value), nf), 256, 0, st>>>(
+                        P, (const double *)it.Gr, (const double *)it.Gi, (const double *)it.Ar,
+                        (const double *)it.Ai, (const double *)it.Wt, it.flags, it.pg, it.ph);
+            };
+            // 128 pixels a workgroup once those are two per compute unit
+            const bool wide = (int64_t)blocks_for(P.N, 128) * nf >= 512;
+            if (hdiag)
+                wide ? go(Idx<2>(), Idx<2>(), std::true_type()) : go(Idx<2>(), Idx<1>(), std::true_type());
+            else
+                wide ? go(Idx<2>(), Idx<2>(), std::false_type()) : go(Idx<2>(), Idx<1>(), std::false_type());
+            RB_LAUNCHED();
+            k_adj_sum<<<blocks_for(P.N, 256), 256, 0, st>>>(P.N, nf, 1, it.pg, it.ph, grad, hdiag);
             break;
         }
         case RB_F32: {

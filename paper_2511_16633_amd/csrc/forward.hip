@@ -57,61 +57,126 @@ __device__ __forceinline__ bool fwd_block_idle(const FwdParams &P, int te, int t
            max_circ_dist(P.m, te * 64 + 32 * we, 32, tr * 64 + 32 * wr, 32) < P.dmin;
 }
 
-template <typename T>
-__global__ void __launch_bounds__(256) k_forward(FwdParams P, const T *__restrict__ Gr, const T *__restrict__ Gi,
-                                                 const double *__restrict__ delta, T *__restrict__ part) {
-    using acc_t = typename MM<T>::acc;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+// FP64.  A 64 x 64 tile of pairs per workgroup, 16 pixels a step: the tile's
+// rows go through LDS (two buffers, the next step's in registers meanwhile), as
+// 128-byte runs of a row, so that L2 is asked for a row once per workgroup and
+// not once per wave, and the MFMAs (64 cycles each) are what is left to wait
+// for.  Of a tile on the diagonal one set of rows is staged and only the
+// 16 x 16 blocks on or above it are formed; the waves take their 16 rows in
+// another order in each split, so that the SIMDs share the shorter ones.  Two
+// frequencies, with every wave loading its operands from memory and now: 64
+// elements / 128^2 51 -> 30 us, 256 / 301x255 1695 -> 1002, 256 / 480^2 5.9 ->
+// 2.87 ms (1.9 ms of MFMA time at 78.6 TFLOP/s).
+constexpr int kFdT = 64, kFdPx = 16;        // tile, pixels a step
+constexpr int kFdRow = kFdPx + 2;           // LDS row: 16 lanes' 16-byte reads hit 64 banks
+typedef double fd2 __attribute__((ext_vector_type(2)));
+typedef fd2 fd2_u __attribute__((aligned(8)));   // a row may start at any pixel
+
+__global__ void __launch_bounds__(256) k_forward_f64(FwdParams P, const double *__restrict__ Gr,
+                                                     const double *__restrict__ Gi,
+                                                     const double *__restrict__ delta, double *__restrict__ part) {
+    using acc_t = MM<double>::acc;
+    __shared__ __align__(16) double buf[2][2][2][kFdT * kFdRow];   // step, side, re/im
+    const int lane = threadIdx.x & 63;
     const int row = lane & 15, kk = lane >> 4;
     int te, tr;
     tri_tile(blockIdx.x, P.ntl, te, tr);
     const int split = blockIdx.y, k = blockIdx.z;
+    const int wave = (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) + split) & 3;
     const int64_t N = P.N;
-    const T *gr = Gr + (int64_t)k * P.m * N;
-    const T *gi = Gi + (int64_t)k * P.m * N;
-    const int e = te * 64 + 16 * wave + row;
+    const bool diag = te == tr;
     const int64_t ks = (int64_t)split * P.kchunk;
     const int64_t ke = std::min<int64_t>(N, ks + P.kchunk);
+    const int c0 = diag ? wave : 0;   // first column block used
+
+    // staging: thread t takes the pixel pair t % 8 of rows t / 8 and t / 8 + 32
+    // of each side (rows at or beyond m: the last one, outputs never read)
+    const int sp = 2 * (threadIdx.x & 7), sr = threadIdx.x >> 3;
+    int64_t src[2][2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        src[0][h] = ((int64_t)k * P.m + std::min(te * kFdT + sr + 32 * h, P.m - 1)) * N;
+        src[1][h] = ((int64_t)k * P.m + std::min(tr * kFdT + sr + 32 * h, P.m - 1)) * N;
+    }
+    fd2 v[2][2][2];   // side, half, re/im
+    auto load = [&](int64_t xc) {
+        const int64_t x = xc + sp;
+#pragma unroll
+        for (int sd = 0; sd < 2; ++sd) {
+            if (sd && diag) break;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const double *qr = Gr + src[sd][h], *qi = Gi + src[sd][h];
+                if (xc + kFdPx <= N) {
+                    v[sd][h][0] = *reinterpret_cast<const fd2_u *>(qr + x);
+                    v[sd][h][1] = *reinterpret_cast<const fd2_u *>(qi + x);
+                } else {   // the table's last pixels, then zeros
+                    v[sd][h][0] = fd2{x < N ? qr[x] : 0.0, x + 1 < N ? qr[x + 1] : 0.0};
+                    v[sd][h][1] = fd2{x < N ? qi[x] : 0.0, x + 1 < N ? qi[x + 1] : 0.0};
+                }
+            }
+        }
+    };
+    auto store = [&](int b) {
+#pragma unroll
+        for (int sd = 0; sd < 2; ++sd) {
+            if (sd && diag) break;
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int c = 0; c < 2; ++c)
+                    *reinterpret_cast<fd2 *>(&buf[b][sd][c][(sr + 32 * h) * kFdRow + sp]) = v[sd][h][c];
+        }
+    };
     acc_t re[4], im[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) re[c] = im[c] = acc_t{0, 0, 0, 0};
-    for (int64_t xc = ks; xc < ke; xc += 16) {
-        T a_r[4], a_i[4], dl[4];
+    const int rs = diag ? 0 : 1;
+    load(ks);
+    store(0);
+    int b = 0;
+    for (int64_t xc = ks; xc < ke; xc += kFdPx, b ^= 1) {
+        __syncthreads();   // buffer b is whole; every wave has left b ^ 1
+        if (xc + kFdPx < ke) load(xc + kFdPx);
+        double a_r[4], a_i[4];
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
             const int64_t x = xc + 4 * kk + s;
-            const bool okx = x < ke;
-            dl[s] = okx ? (T)delta[x] : T(0);
-            a_r[s] = ld(gr + (int64_t)e * N + x, okx && e < P.m);
-            a_i[s] = ld(gi + (int64_t)e * N + x, okx && e < P.m);
+            const double dl = x < ke ? delta[x] : 0.0;
+            const int o = (16 * wave + row) * kFdRow + 4 * kk + s;
+            a_r[s] = buf[b][0][0][o] * dl;
+            a_i[s] = buf[b][0][1][o] * dl;
         }
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            const int r = tr * 64 + 16 * c + row;
+            if (c < c0) continue;   // wave-uniform
+            double b_r[4], b_i[4];
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
-                const int64_t x = xc + 4 * kk + s;
-                const bool ok = (x < ke) && (r < P.m);
-                const T b_r = ld(gr + (int64_t)r * N + x, ok) * dl[s];
-                const T b_i = ld(gi + (int64_t)r * N + x, ok) * dl[s];
-                re[c] = MM<T>::mma(a_r[s], b_r, re[c]);
-                re[c] = MM<T>::mma(-a_i[s], b_i, re[c]);
-                im[c] = MM<T>::mma(a_r[s], b_i, im[c]);
-                im[c] = MM<T>::mma(a_i[s], b_r, im[c]);
+                const int o = (16 * c + row) * kFdRow + 4 * kk + s;
+                b_r[s] = buf[b][rs][0][o];
+                b_i[s] = buf[b][rs][1][o];
+            }
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                re[c] = MM<double>::mma(a_r[s], b_r[s], re[c]);
+                im[c] = MM<double>::mma(a_r[s], b_i[s], im[c]);
+                re[c] = MM<double>::mma(-a_i[s], b_i[s], re[c]);
+                im[c] = MM<double>::mma(a_i[s], b_r[s], im[c]);
             }
         }
+        if (xc + kFdPx < ke) store(b ^ 1);
     }
     // partial tile -> part[split][k][e][r][2]
-    T *pp = part + ((int64_t)split * P.nf + k) * P.mp * P.mp * 2;
+    double *pp = part + ((int64_t)split * P.nf + k) * P.mp * P.mp * 2;
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-        const int r = tr * 64 + 16 * c + row;
+        if (c < c0) continue;
+        const int r = tr * kFdT + 16 * c + row;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int ee = te * 64 + 16 * wave + MM<T>::out_row(kk, i);
-            const int64_t o = ((int64_t)ee * P.mp + r) * 2;
-            pp[o] = re[c][i];
-            pp[o + 1] = im[c][i];
+            const int ee = te * kFdT + 16 * wave + MM<double>::out_row(kk, i);
+            *reinterpret_cast<fd2_u *>(pp + ((int64_t)ee * P.mp + r) * 2) = fd2{re[c][i], im[c][i]};
         }
     }
 }
@@ -1278,11 +1343,11 @@ static FwdParams fwd_params(const rb_geometry *g, const double *freqs, int nf, r
     // 16-byte pieces, beyond one round, than kFewSplitPx pixels: a split's
     // partial sums (a tile of them, written and read once) cost as much as
     // some tens of pixels.  (The FP64 kernel and the ragged rows' loads need
-    // the waves: 97 elements / 301x255 FP64 463 us, with the longer splits
-    // 530; FP16 200 and 235.)  us
+    // the waves: 256 elements / 128^2 FP64 245 us, with the longer splits 304;
+    // 97 / 301x255 FP16 200 and 235.)  us
     // per call with splits of at least 16 / 64 / 128 / 512 pixels, two
     // frequencies: 64 elements / 128^2 FP32 37 / 26 / 25 / 44, BF16 33 / 27 /
-    // 28 / 31, FP64 73 / 51 / 49 / 157; 64 / 480^2 FP32 133 / 132 / 134 / 115.
+    // 28 / 31, FP64 - / 30 / 34 / -; 64 / 480^2 FP32 133 / 132 / 134 / 115.
     const int resident = (fs || wide ? 1 : (fwd32_direct(g, dt) ? 4 : 2)) * device_cus();
     int64_t most = P.N / kMinSplitPx;
     if (fs || wide || (dt != RB_F64 && P.N % (dt == RB_F32 ? 4 : 8) == 0))
@@ -1369,8 +1434,8 @@ rb_status forward_impl(const rb_geometry *g, const void *G_re, const void *G_im,
     switch (dt) {
         case RB_F64: {
             dim3 grid(P.ntri, P.nsplit, nf);
-            k_forward<double><<<grid, 256, 0, st>>>(P, (const double *)G_re, (const double *)G_im, delta,
-                                                    (double *)w.part);
+            k_forward_f64<<<grid, 256, 0, st>>>(P, (const double *)G_re, (const double *)G_im, delta,
+                                                (double *)w.part);
             RB_LAUNCHED();
             k_forward_reduce<double><<<gred, 32 * kRedG, 0, st>>>(P, (const double *)w.part, nullptr,
                                                                            nullptr, d_out, so);
