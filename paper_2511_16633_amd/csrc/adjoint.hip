@@ -824,7 +824,7 @@ __device__ __forceinline__ V t16_join(t16v4 lo, t16v4 hi) {
     return __builtin_bit_cast(V, v);
 }
 
-// Aligned full tiles (N a multiple of 8, m a multiple of 32, 32 N elements
+// Aligned tiles (N a multiple of 8, m a multiple of 32, 32 N elements
 // within 32-bit offsets): wave w issues instructions q = 4 w .. 4 w + 3 of
 // the tile's 16 (array q >> 3, rows 4 (q & 7) .. + 3); `goff[j]` is lane l's
 // element offset from the step's first row and pixel (`gr`, `gi`: uniform)
@@ -841,30 +841,46 @@ __device__ __forceinline__ void t16_stage_async(const unsigned short *__restrict
         __builtin_amdgcn_global_load_lds(g + goff[j], (lds_void_t *)(d + j * 4 * kT16Row), 16, 0, 0);
 }
 
-// Ragged or unaligned tiles: through registers, zero beyond m and N; each
-// thread writes four 16-byte chunks.
-__device__ __forceinline__ void t16_stage_regs(const unsigned short *__restrict__ gr,
-                                               const unsigned short *__restrict__ gi, int m, int64_t N, int rc,
-                                               int64_t x0, unsigned char *sT) {
-#pragma unroll 1
-    for (int q = threadIdx.x; q < 2 * kT16KC * 16; q += 256) {
-        const int arr = q >> 9, rl = (q >> 4) & 31, pos = q & 15;
-        const int c = pos ^ (t16_pos(rl, 0));   // the global chunk stored at `pos`
-        const unsigned short *g = arr ? gi : gr;
-        const int r = rc + rl;
-        unsigned short v[8];
+// Where a direct load will not do (rows that are not 16-byte aligned, a chunk
+// with fewer than 32 rows) the same tile goes through registers, loaded during
+// the MFMAs of the step before: 16 bytes of row r from pixel x on, in one load
+// that needs no alignment unless the table's pixels end within the tile (`full`
+// is uniform).  With 2-byte loads, waited for when issued, and now, FP16, two
+// frequencies: 130 elements / 301x255 178 -> 123 us, with the Hessian diagonal
+// 292 -> 186, 100 / 256^2 89 -> 62 us, 1000 / 301x255 (one frequency) 968 -> 443.
+typedef unsigned short t16us8 __attribute__((ext_vector_type(8)));
+typedef t16us8 t16us8_u __attribute__((aligned(2)));
+__device__ __forceinline__ t16us8 t16_load(const unsigned short *__restrict__ g, int r, int64_t N, int64_t x,
+                                           bool full) {
+    const unsigned short *q = g + (int64_t)r * N;
+    if (full) return *reinterpret_cast<const t16us8_u *>(q + x);
+    t16us8 v;
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int64_t x = x0 + 8 * c + u;
-            v[u] = (r < m && x < N) ? g[(int64_t)r * N + x] : (unsigned short)0;
-        }
-        unsigned short *d = reinterpret_cast<unsigned short *>(sT + arr * kT16Arr + rl * kT16Row + pos * 16);
+    for (int u = 0; u < 8; ++u) v[u] = x + u < N ? q[x + u] : (unsigned short)0;
+    return v;
+}
+// Thread t's part of the tile of rows rc .. rc + 31: rows t / 16 and t / 16 +
+// 16 of both arrays, the chunk stored at position t % 16.
+__device__ __forceinline__ void t16_load_tile(const unsigned short *__restrict__ gr,
+                                              const unsigned short *__restrict__ gi, int m, int64_t N, int rc,
+                                              int64_t x0, bool full, t16us8 (&v)[4]) {
+    const int rl = threadIdx.x >> 4;
+    const int64_t x = x0 + 8 * ((threadIdx.x & 15) ^ t16_pos(rl, 0));
 #pragma unroll
-        for (int u = 0; u < 8; ++u) d[u] = v[u];
+    for (int j = 0; j < 4; ++j) v[j] = t16_load(j >> 1 ? gi : gr, min(rc + rl + 16 * (j & 1), m - 1), N, x, full);
+}
+// ... and into LDS, zero for rows at or beyond m
+__device__ __forceinline__ void t16_store_tile(const t16us8 (&v)[4], int m, int rc, unsigned char *sT) {
+    const int rl = threadIdx.x >> 4;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int r = rl + 16 * (j & 1);
+        const t16us8 w = rc + r < m ? v[j] : (t16us8)(unsigned short)0;
+        *reinterpret_cast<t16us8 *>(sT + (j >> 1) * kT16Arr + r * kT16Row + (threadIdx.x & 15) * 16) = w;
     }
 }
 
-template <typename S, bool HESS, typename A>
+template <typename S, bool HESS, bool DIRECT, typename A>
 __global__ void __launch_bounds__(256, HESS ? 1 : 2) k_adjoint16_tr(const A args) {
     typename A::Loc loc;
     const AdjItem &it = args.locate(loc);
@@ -895,27 +911,24 @@ __global__ void __launch_bounds__(256, HESS ? 1 : 2) k_adjoint16_tr(const A args
     const int64_t x0 = (int64_t)loc.tile() * kT16NT;
     const unsigned short *gr = reinterpret_cast<const unsigned short *>((const S *)it.Gr + (int64_t)k * P.m * N);
     const unsigned short *gi = reinterpret_cast<const unsigned short *>((const S *)it.Gi + (int64_t)k * P.m * N);
-    const bool vec = ((N & 7) == 0) && (x0 + kT16NT <= N) && (P.m % kT16KC == 0) && N < ((int64_t)1 << 26) &&
-                     ((((uintptr_t)gr) | ((uintptr_t)gi)) & 15) == 0;   // workgroup-uniform
+    const bool full = x0 + kT16NT <= N;   // workgroup-uniform
     const S *ar = Ar + (int64_t)k * P.mp * P.mp;
     const S *ai = Ai + (int64_t)k * P.mp * P.mp;
     const S *wt = Wt + (int64_t)k * P.mp * P.mp;
     const uint8_t *fl = flags + (int64_t)k * P.nb * P.nb;
     const int half = (P.nb + 1) / 2;   // see AdjChunks
     // lane's element offsets of its four direct-load chunks within a step
+    // (of the last tile's chunks beyond N, the last: dropped)
+    const int lastc = (int)min(N - 8 - x0, (int64_t)kT16NT);
     unsigned goff[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const int rl = 4 * (4 * (wave & 1) + j) + (lane >> 4);
-        goff[j] = (unsigned)(rl * N) + 8u * (unsigned)((lane & 15) ^ (t16_pos(rl, 0)));
+        goff[j] = (unsigned)(rl * N) + (unsigned)min(8 * ((lane & 15) ^ t16_pos(rl, 0)), lastc);
     }
-    // transposing-read offsets: rows 8 kk + 4 h + (row >> 2), pixels
-    // 16 cb + 4 (row & 3) (h = 0, 1; cb = 0 .. 7)
-    int toff[2][8];
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int cb = 0; cb < 8; ++cb) toff[h][cb] = t16_off(8 * kk + 4 * h + (row >> 2), 16 * cb + 4 * (row & 3));
+    // transposing-read offset at rows 8 kk + (row >> 2), pixels 4 (row & 3) of
+    // column block 0 (block cb: XOR 32 cb)
+    const unsigned t0 = t16_off(8 * kk + (row >> 2), 4 * (row & 3));
     float gp[8], hp[8];
 #pragma unroll
     for (int cb = 0; cb < 8; ++cb) gp[cb] = hp[cb] = 0.0f;
@@ -959,12 +972,11 @@ __global__ void __launch_bounds__(256, HESS ? 1 : 2) k_adjoint16_tr(const A args
             return c;
         };
         int b0 = next_bit(), b1 = next_bit(), b2 = next_bit();
-        auto stage = [&](int c, unsigned char *dst, auto vtag) {
-            if (decltype(vtag)::value)
-                t16_stage_async(gr + ((int64_t)c * kT16KC * N + x0), gi + ((int64_t)c * kT16KC * N + x0), goff, dst);
-            else
-                t16_stage_regs(gr, gi, P.m, N, c * kT16KC, x0, dst);
+        auto stage = [&](int c, unsigned char *dst) {
+            t16_stage_async(gr + ((int64_t)c * kT16KC * N + x0), gi + ((int64_t)c * kT16KC * N + x0), goff, dst);
         };
+        t16us8 tv[4];   // without direct loads: the tile of step s + 1
+        auto load_t = [&](int c) { t16_load_tile(gr, gi, P.m, N, c * kT16KC, x0, full, tv); };
         // One k-step s (chunk bit b0) on the tile in buffer s mod 4: wait for
         // its tile and its A, issue A of b1 and the tile of step s + 2 (b2),
         // then the MFMAs.  Per step a wave issues A(s + 1) (2 EB or
@@ -974,20 +986,29 @@ __global__ void __launch_bounds__(256, HESS ? 1 : 2) k_adjoint16_tr(const A args
         // a tile, 2: A only, 1: nothing; 0: decided from s at run time), so
         // that the compiler's own load-counter waits stay exact.
         auto kstep = [&](int s, auto itag, V (&va)[EB], V (&vi)[EB], V (&vw)[EB], V (&na)[EB], V (&ni)[EB],
-                         V (&nw)[EB], auto vtag, auto mode) {
+                         V (&nw)[EB], auto mode) {
             constexpr int I = decltype(itag)::value;
             constexpr int M = decltype(mode)::value;
             const bool has_a = M == 3 || M == 2 || (M == 0 && s + 1 < nstep);
             const bool has_t = M == 3 || (M == 0 && s + 2 < nstep);
-            if (has_a)
+            if (!DIRECT) {
+                // the tile of s + 1, read two barriers from now at the latest
+                if (has_a) t16_store_tile(tv, P.m, AdjChunks::chunk(b1, half) * kT16KC, buf(Idx<I + 1>()));
+            } else if (has_a) {
                 __builtin_amdgcn_s_waitcnt(vmcnt_imm(4));   // tile s + 1
-            else
+            } else {
                 __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+            }
             lds_barrier();
             const bool on = mine.has(b0);
             if (has_a) load_a(AdjChunks::chunk(b1, half), na, ni, nw);
             __builtin_amdgcn_sched_barrier(0);
-            if (has_t) stage(AdjChunks::chunk(b2, half), buf(Idx<I + 2>()), vtag);
+            if (has_t) {
+                if (DIRECT)
+                    stage(AdjChunks::chunk(b2, half), buf(Idx<I + 2>()));
+                else
+                    load_t(AdjChunks::chunk(b2, half));
+            }
             __builtin_amdgcn_sched_barrier(0);
             b0 = b1;
             b1 = b2;
@@ -1001,7 +1022,7 @@ __global__ void __launch_bounds__(256, HESS ? 1 : 2) k_adjoint16_tr(const A args
 #pragma unroll
             for (int cb = 0; cb < 8; ++cb) {
                 t16v4 r0, r1, i0, i1;
-                t16_tr4(sba + (unsigned)toff[0][cb], r0, r1, i0, i1);
+                t16_tr4(sba + (t0 ^ (32u * cb)), r0, r1, i0, i1);
                 const V br = t16_join<V>(r0, r1);
                 const V bi = t16_join<V>(i0, i1);
                 V b2;
@@ -1016,44 +1037,46 @@ __global__ void __launch_bounds__(256, HESS ? 1 : 2) k_adjoint16_tr(const A args
                 }
             }
         };
-        // the k-loop, specialised on the staging path and unrolled by four
-        // (buffer index period 4, A registers period 2); the steady state
+        // the k-loop, unrolled by four (buffer index period 4, A registers period 2); the steady state
         // has no conditional steps, the last two to five follow.  (Making
         // those compile-time as well spills the accumulators.)
-        auto kloop = [&](auto vtag) {
+        auto kloop = [&]() {
             using M3 = std::integral_constant<int, 3>;
             using M2 = std::integral_constant<int, 2>;
             using M1 = std::integral_constant<int, 1>;
             using M0 = std::integral_constant<int, 0>;
             V va[EB], vi[EB], vw[EB], na[EB], ni[EB], nw[EB];
             lds_barrier();   // the previous pass is done with the tile buffers
-            stage(AdjChunks::chunk(b0, half), sG0, vtag);
+            if (DIRECT) {
+                stage(AdjChunks::chunk(b0, half), sG0);
+            } else {
+                load_t(AdjChunks::chunk(b0, half));
+                t16_store_tile(tv, P.m, AdjChunks::chunk(b0, half) * kT16KC, sG0);
+            }
             load_a(AdjChunks::chunk(b0, half), va, vi, vw);
             // unconditional (a one-chunk pass stages chunk 0, unused), so that
             // the loop is always entered with the same loads in flight and
             // the compiler's load-counter waits at its head stay exact
-            stage(AdjChunks::chunk(b1, half), sG1, vtag);
+            if (DIRECT)
+                stage(AdjChunks::chunk(b1, half), sG1);
+            else
+                load_t(AdjChunks::chunk(b1, half));
             int s = 0;
             for (; s + 6 <= nstep; s += 4) {
-                kstep(s, Idx<0>(), va, vi, vw, na, ni, nw, vtag, M3());
-                kstep(s + 1, Idx<1>(), na, ni, nw, va, vi, vw, vtag, M3());
-                kstep(s + 2, Idx<2>(), va, vi, vw, na, ni, nw, vtag, M3());
-                kstep(s + 3, Idx<3>(), na, ni, nw, va, vi, vw, vtag, M3());
+                kstep(s, Idx<0>(), va, vi, vw, na, ni, nw, M3());
+                kstep(s + 1, Idx<1>(), na, ni, nw, va, vi, vw, M3());
+                kstep(s + 2, Idx<2>(), va, vi, vw, na, ni, nw, M3());
+                kstep(s + 3, Idx<3>(), na, ni, nw, va, vi, vw, M3());
             }
-            if (s < nstep) kstep(s, Idx<0>(), va, vi, vw, na, ni, nw, vtag, M0());
-            if (s + 1 < nstep) kstep(s + 1, Idx<1>(), na, ni, nw, va, vi, vw, vtag, M0());
-            if (s + 2 < nstep) kstep(s + 2, Idx<2>(), va, vi, vw, na, ni, nw, vtag, M0());
-            if (s + 3 < nstep) kstep(s + 3, Idx<3>(), na, ni, nw, va, vi, vw, vtag, M0());
-            if (s + 4 < nstep) kstep(s + 4, Idx<0>(), va, vi, vw, na, ni, nw, vtag, M0());
+            if (s < nstep) kstep(s, Idx<0>(), va, vi, vw, na, ni, nw, M0());
+            if (s + 1 < nstep) kstep(s + 1, Idx<1>(), na, ni, nw, va, vi, vw, M0());
+            if (s + 2 < nstep) kstep(s + 2, Idx<2>(), va, vi, vw, na, ni, nw, M0());
+            if (s + 3 < nstep) kstep(s + 3, Idx<3>(), na, ni, nw, va, vi, vw, M0());
+            if (s + 4 < nstep) kstep(s + 4, Idx<0>(), va, vi, vw, na, ni, nw, M0());
             // keep the epilogue's work out of the last k-steps' schedule
             __builtin_amdgcn_sched_barrier(0);
         };
-        if (nstep > 0) {   // workgroup-uniform
-            if (vec)
-                kloop(std::true_type());
-            else
-                kloop(std::false_type());
-        }
+        if (nstep > 0) kloop();   // workgroup-uniform
         // fused epilogue: Re sum_e conj(G_e) Y_e and sum_e |G_e|^2 Z_e.  The
         // tile buffers are free once every wave is done with the k-loop:
         // wave w copies the chunk of its 32 emitter rows (both arrays) into
@@ -1063,24 +1086,35 @@ __global__ void __launch_bounds__(256, HESS ? 1 : 2) k_adjoint16_tr(const A args
         __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
         lds_barrier();
         unsigned char *se = wave == 0 ? sG0 : (wave == 1 ? sG1 : (wave == 2 ? sG2 : sG3));
-        if (vec) {
+        if (DIRECT) {
             if (e0 < P.mp) {
                 const unsigned short *g0 = gr + ((int64_t)e0 * N + x0), *g1 = gi + ((int64_t)e0 * N + x0);
 #pragma unroll
                 for (int q = 0; q < 16; ++q) {
                     const int rl = 4 * (q & 7) + (lane >> 4);
-                    const unsigned go = (unsigned)(rl * N) + 8u * (unsigned)((lane & 15) ^ t16_pos(rl, 0));
+                    const unsigned go =
+                        (unsigned)(rl * N) + (unsigned)min(8 * ((lane & 15) ^ t16_pos(rl, 0)), lastc);
                     __builtin_amdgcn_global_load_lds((q >> 3) ? g1 + go : g0 + go,
                                                      (lds_void_t *)(se + (q >> 3) * kT16Arr + 4 * (q & 7) * kT16Row),
                                                      16, 0, 0);
                 }
             }
             __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-        } else {
-            t16_stage_regs(gr, gi, P.m, N, ec, x0, sG0);
-            t16_stage_regs(gr, gi, P.m, N, ec + kT16KC, x0, sG1);
-            t16_stage_regs(gr, gi, P.m, N, ec + 2 * kT16KC, x0, sG2);
-            t16_stage_regs(gr, gi, P.m, N, ec + 3 * kT16KC, x0, sG3);
+        } else if (e0 < P.mp) {
+            // (rows at or beyond m: the last one, dropped below)
+#pragma unroll
+            for (int q0 = 0; q0 < 16; q0 += 8) {
+                t16us8 v[8];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) {
+                    const int rl = 4 * q + (lane >> 4);
+                    v[q] = t16_load(q0 ? gi : gr, min(e0 + rl, P.m - 1), N,
+                                    x0 + 8 * ((lane & 15) ^ t16_pos(rl, 0)), full);
+                }
+#pragma unroll
+                for (int q = 0; q < 8; ++q)
+                    *reinterpret_cast<t16us8 *>(se + (q0 ? kT16Arr : 0) + 4 * q * kT16Row + 16 * lane) = v[q];
+            }
         }
         lds_barrier();
         if (e0 < P.mp) {
@@ -1134,6 +1168,22 @@ __global__ void __launch_bounds__(256, HESS ? 1 : 2) k_adjoint16_tr(const A args
     }
 }
 
+
+template <typename A>
+void launch_adjoint16(const AdjTask &t, dim3 grid, const A &arg, hipStream_t st) {
+    auto go = [&](auto tag, auto hess) {
+        using S = decltype(tag);
+        constexpr bool H = decltype(hess)::value;
+        if (t.direct)
+            k_adjoint16_tr<S, H, true><<<grid, 256, 0, st>>>(arg);
+        else
+            k_adjoint16_tr<S, H, false><<<grid, 256, 0, st>>>(arg);
+    };
+    if (t.dt == RB_BF16)
+        t.hdiag ? go(__hip_bfloat16(), std::true_type()) : go(__hip_bfloat16(), std::false_type());
+    else
+        t.hdiag ? go(__half(), std::true_type()) : go(__half(), std::false_type());
+}
 
 // ------------------------------------------------------------------ FP32 tables on the FP16 matrix cores
 // Gradient-only backprojection of FP32 tables with every operand split into
@@ -1554,6 +1604,8 @@ rb_status adjoint_prepare(const rb_geometry *g, const void *G_re, const void *G_
     it.pscale = nullptr;
     it.redo = nullptr;
     task->split = adj_split(g, nf, dt, hdiag != nullptr);
+    // (32 N elements within 32-bit offsets)
+    task->direct = (dt == RB_BF16 || dt == RB_F16) && P.N % 8 == 0 && P.m % kT16KC == 0 && P.N < ((int64_t)1 << 26);
     if (task->split) {
         Carver h(w.ph, (size_t)-1);
         it.split_hi = w.Wt;
@@ -1663,19 +1715,7 @@ rb_status adjoint_run(const AdjTask &task, hipStream_t st) {
         }
         case RB_BF16:
         case RB_F16: {
-            dim3 ga((unsigned)it.ntiles * it.npg, nf);
-            const AdjOneSplit one{it};
-            auto go = [&](auto tag) {
-                using S = decltype(tag);
-                if (hdiag)
-                    k_adjoint16_tr<S, true><<<ga, 256, 0, st>>>(one);
-                else
-                    k_adjoint16_tr<S, false><<<ga, 256, 0, st>>>(one);
-            };
-            if (task.dt == RB_BF16)
-                go(__hip_bfloat16());
-            else
-                go(__half());
+            launch_adjoint16(task, dim3((unsigned)it.ntiles * it.npg, nf), AdjOneSplit{it}, st);
             RB_LAUNCHED();
             k_adj_sum<<<blocks_for(P.N, 256), 256, 0, st>>>(P.N, nf, it.npg, it.pg, it.ph, grad, hdiag);
             break;
@@ -1687,8 +1727,11 @@ rb_status adjoint_run(const AdjTask &task, hipStream_t st) {
 
 rb_status adjoint_run_grouped(AdjTask *const *tasks, int n, hipStream_t st) {
     // contraction type and variant of a task: f32 / bf16 / f16, FP32 on the
-    // FP16 cores, with or without the Hessian diagonal; f64 runs alone
-    auto kind = [](const AdjTask &t) { return 4 * (int)t.dt + (t.split ? 2 : 0) + (t.hdiag ? 1 : 0); };
+    // FP16 cores, 16-bit with direct loads, with or without the Hessian
+    // diagonal; f64 runs alone
+    auto kind = [](const AdjTask &t) {
+        return 8 * (int)t.dt + (t.direct ? 4 : 0) + (t.split ? 2 : 0) + (t.hdiag ? 1 : 0);
+    };
     bool done[256] = {};
     RB_CHECK_ARG(n >= 0 && n <= 256, "grouped backprojection: %d problems (at most 256)", n);
     for (int i = 0; i < n; ++i) {
@@ -1730,16 +1773,8 @@ rb_status adjoint_run_grouped(AdjTask *const *tasks, int n, hipStream_t st) {
                     k_adjoint_f32<false><<<(unsigned)blocks, 256, 0, st>>>(arg);
                 break;
             case RB_BF16:
-                if (hess)
-                    k_adjoint16_tr<__hip_bfloat16, true><<<(unsigned)blocks, 256, 0, st>>>(arg);
-                else
-                    k_adjoint16_tr<__hip_bfloat16, false><<<(unsigned)blocks, 256, 0, st>>>(arg);
-                break;
             case RB_F16:
-                if (hess)
-                    k_adjoint16_tr<__half, true><<<(unsigned)blocks, 256, 0, st>>>(arg);
-                else
-                    k_adjoint16_tr<__half, false><<<(unsigned)blocks, 256, 0, st>>>(arg);
+                launch_adjoint16(*tasks[i], dim3((unsigned)blocks), arg, st);
                 break;
             default:
                 break;

@@ -43,6 +43,7 @@ struct AdjTask {
     AdjItem item;
     rb_dtype dt;
     bool split;   // FP32 tables, gradient by k_adjoint_split
+    bool direct;  // 16-bit tables: k_adjoint16_tr with direct loads
     double *grad, *hdiag;
 };
 

@@ -313,3 +313,28 @@ def test_fp64_tiles(rb, shape):
         g_b += 4e-11 * (2 * np.pi * f) ** 2 * geom.h ** 2 * np.einsum("ex,er,rx->x", a, np.abs(wd[k]), a, optimize=True)
     assert (np.abs(grad.cpu().numpy() - g_o) <= g_b).all()
     assert (np.abs(hd.cpu().numpy() - h_o) <= 4e-11 * h_o).all()
+
+
+# 16-bit backprojection by direct loads (rows of whole 16-byte pieces, rings of
+# whole 32-element blocks) and through registers: a last tile of one 16-byte
+# piece, of odd pixels and of one pixel; one, two and many receiver chunks.
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("shape", [(34, 4, 32), (40, 10, 64), (43, 3, 64), (33, 13, 70), (20, 20, 288), (53, 5, 300)])
+def test_16bit_gradient_rows(rb, dtype, shape):
+    nx, ny, m = shape
+    geom, freqs = _geom(nx, ny, m), [3e5, 7e5]
+    N = geom.n_pixels
+    print(f"[gpu-test] 16-bit gradient rows {dtype} {shape}", flush=True)
+    Gr, Gi, sc, G = _tables(rb, geom, freqs, dtype, 15)
+    D = W.random_residual(2, m, 16)
+    w = np.random.default_rng(N + m).uniform(0.0, 2.0, (2, m, m))
+    g_o = sum(born.born_adjoint(G[k], w[k] * D[k], f, geom.h ** 2) for k, f in enumerate(freqs))
+    h_o = sum(born.hessian_diag(G[k], w[k], f, geom.h ** 2) for k, f in enumerate(freqs))
+    d, wd = (torch.as_tensor(v, device=DEV) for v in (np.stack([D.real, D.imag], -1), w))
+    for hess in (True, False):
+        grad = torch.zeros(N, dtype=torch.float64, device=DEV)
+        hd = torch.zeros_like(grad) if hess else None
+        rb.born_adjoint_weighted(geom, Gr, Gi, sc, dtype, freqs, d, wd, grad, hd)
+        close(grad.cpu().numpy(), g_o, TOL[dtype], f"grad {dtype} {shape} hess={hess}")
+        if hess:
+            close(hd.cpu().numpy(), h_o, TOL[dtype], f"hdiag {dtype} {shape}")
