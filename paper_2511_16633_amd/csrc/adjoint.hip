@@ -245,34 +245,42 @@ __global__ void __launch_bounds__(256) k_adj_prep(int m, int mp, const double *_
         return;
     }
     const int col = threadIdx.x & 31, row0 = threadIdx.x >> 5;
-    auto load = [&](int e, int r, double &re, double &im, double &wv) {
-        re = im = wv = 0.0;
-        if (e < m && r < m) {
-            const int64_t q = ((int64_t)k * m + e) * m + r;
-            wv = w[q];
-            re = wv * d[2 * q];
-            im = wv * d[2 * q + 1];
+    // (indices clamped, not guarded, so that all 24 loads are in flight
+    // together: 64 elements, two frequencies, 5.2 -> 3.9 us)
+    double lw[2][4], lr[2][4], li[2][4];   // this block, the transposed one
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int e = (h ? J : I) * 32 + row0 + 8 * q, r = (h ? I : J) * 32 + col;
+            const int64_t o = ((int64_t)k * m + min(e, m - 1)) * m + min(r, m - 1);
+            lw[h][q] = w[o];
+            lr[h][q] = d[2 * o];
+            li[h][q] = d[2 * o + 1];
         }
-    };
-    if (I != J) {
+    const float as = ascale ? ascale[k] : 0.0f;   // 0 when every weight is zero
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int i = row0 + 8 * q;
-            load(J * 32 + i, I * 32 + col, tr[i][col], ti[i][col], tw[i][col]);
+            const bool in = (h ? J : I) * 32 + i < m && (h ? I : J) * 32 + col < m;
+            lr[h][q] = in ? lw[h][q] * lr[h][q] : 0.0;
+            li[h][q] = in ? lw[h][q] * li[h][q] : 0.0;
+            lw[h][q] = in ? lw[h][q] : 0.0;
+            if (h) {
+                tr[i][col] = lr[h][q];
+                ti[i][col] = li[h][q];
+                tw[i][col] = lw[h][q];
+            }
         }
-    }
     __syncthreads();
-    double half = 0.5;
-    if (SCALED) {
-        const float a = ascale[k];   // 0 when every weight is zero
-        half = a > 0.0f ? 0.5 / (double)a : 0.5;
-    }
+    const double half = SCALED && as > 0.0f ? 0.5 / (double)as : 0.5;
     bool any = false;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int i = row0 + 8 * q;
-        double re, im, wv;
-        load(I * 32 + i, J * 32 + col, re, im, wv);
+        double re = lr[0][q], im = li[0][q], wv = lw[0][q];
         any |= wv != 0.0;
         if (I != J) {
             any |= tw[col][i] != 0.0;
@@ -289,7 +297,7 @@ __global__ void __launch_bounds__(256) k_adj_prep(int m, int mp, const double *_
         if (SCALED || !shi) {
             Wt[o] = cvt<T>(wv * 0.5);
         } else {
-            const float sa = split_scale(ascale[k], kSplitTopA);
+            const float sa = split_scale(as, kSplitTopA);
             const float vr = (float)(re * half) * sa, vi = (float)(im * half) * sa;
             const _Float16 hr = (_Float16)vr, hi = (_Float16)vi;
             const int64_t q = 2048 * blk + fr;
@@ -724,14 +732,16 @@ __global__ void __launch_bounds__(256, 3) k_adjoint_f32_list(const AdjItem it) {
 
 
 // ------------------------------------------------------------------ 16-bit
-// |G|^2 of a fragment, rounded to the storage type
+// |G|^2 of a fragment, rounded to the storage type (products of 16-bit values
+// are exact in FP32, so the fused form rounds as a a + b b does; FP16 takes its
+// operands without conversions)
 template <typename S, typename V>
 __device__ __forceinline__ V a16_abs2(V br, V bi) {
     V o;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         const float a = (float)br[i], b = (float)bi[i];
-        o[i] = MM16<S>::from_f(a * a + b * b);
+        o[i] = MM16<S>::from_f(__builtin_fmaf(b, b, __builtin_fmaf(a, a, 0.0f)));
     }
     return o;
 }
@@ -825,19 +835,21 @@ __device__ __forceinline__ V t16_join(t16v4 lo, t16v4 hi) {
 }
 
 // Aligned tiles (N a multiple of 8, m a multiple of 32, 32 N elements
-// within 32-bit offsets): wave w issues instructions q = 4 w .. 4 w + 3 of
-// the tile's 16 (array q >> 3, rows 4 (q & 7) .. + 3); `goff[j]` is lane l's
+// within 32-bit offsets): of the workgroup's NW waves, wave w issues the
+// 16 / NW instructions q from 16 w / NW on of the tile's 16 (array q >> 3, rows 4 (q & 7) .. + 3); `goff[j]` is lane l's
 // element offset from the step's first row and pixel (`gr`, `gi`: uniform)
 // for its j-th instruction, so the loads take a scalar base and a 32-bit
 // lane offset.
+template <int NW>
 __device__ __forceinline__ void t16_stage_async(const unsigned short *__restrict__ gr,
-                                                const unsigned short *__restrict__ gi, const unsigned (&goff)[4],
-                                                unsigned char *sT) {
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const unsigned short *g = (wave >> 1) ? gi : gr;
-    unsigned char *d = sT + (wave >> 1) * kT16Arr + (wave & 1) * 4 * 4 * kT16Row;
+                                                const unsigned short *__restrict__ gi,
+                                                const unsigned *goff, unsigned char *sT) {
+    constexpr int NQ = 16 / NW;
+    const int q = NQ * __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const unsigned short *g = (q >> 3) ? gi : gr;
+    unsigned char *d = sT + (q >> 3) * kT16Arr + (q & 7) * 4 * kT16Row;
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < NQ; ++j)
         __builtin_amdgcn_global_load_lds(g + goff[j], (lds_void_t *)(d + j * 4 * kT16Row), 16, 0, 0);
 }
 
@@ -859,29 +871,44 @@ __device__ __forceinline__ t16us8 t16_load(const unsigned short *__restrict__ g,
     for (int u = 0; u < 8; ++u) v[u] = x + u < N ? q[x + u] : (unsigned short)0;
     return v;
 }
-// Thread t's part of the tile of rows rc .. rc + 31: rows t / 16 and t / 16 +
-// 16 of both arrays, the chunk stored at position t % 16.
+// Thread t's part of the tile of rows rc .. rc + 31 (NW waves): pieces t, t +
+// 64 NW, .. of 512 an array, piece q being the chunk stored at position q % 16
+// of row q / 16.
+template <int NW>
 __device__ __forceinline__ void t16_load_tile(const unsigned short *__restrict__ gr,
                                               const unsigned short *__restrict__ gi, int m, int64_t N, int rc,
-                                              int64_t x0, bool full, t16us8 (&v)[4]) {
+                                              int64_t x0, bool full, t16us8 (&v)[16 / NW]) {
+    constexpr int NJ = 16 / NW, RS = 4 * NW;   // pieces a thread; rows they are apart
     const int rl = threadIdx.x >> 4;
-    const int64_t x = x0 + 8 * ((threadIdx.x & 15) ^ t16_pos(rl, 0));
+    const int64_t x = x0 + 8 * ((threadIdx.x & 15) ^ t16_pos(rl, 0));   // (RS is a multiple of 16)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = t16_load(j >> 1 ? gi : gr, min(rc + rl + 16 * (j & 1), m - 1), N, x, full);
+    for (int j = 0; j < NJ; ++j)
+        v[j] = t16_load(j * RS >> 5 ? gi : gr, min(rc + rl + (j * RS & 31), m - 1), N, x, full);
 }
 // ... and into LDS, zero for rows at or beyond m
-__device__ __forceinline__ void t16_store_tile(const t16us8 (&v)[4], int m, int rc, unsigned char *sT) {
+template <int NW>
+__device__ __forceinline__ void t16_store_tile(const t16us8 (&v)[16 / NW], int m, int rc, unsigned char *sT) {
+    constexpr int NJ = 16 / NW, RS = 4 * NW;
     const int rl = threadIdx.x >> 4;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int r = rl + 16 * (j & 1);
+    for (int j = 0; j < NJ; ++j) {
+        const int r = rl + (j * RS & 31);
         const t16us8 w = rc + r < m ? v[j] : (t16us8)(unsigned short)0;
-        *reinterpret_cast<t16us8 *>(sT + (j >> 1) * kT16Arr + r * kT16Row + (threadIdx.x & 15) * 16) = w;
+        *reinterpret_cast<t16us8 *>(sT + (j * RS >> 5) * kT16Arr + r * kT16Row + (threadIdx.x & 15) * 16) = w;
     }
 }
 
+// Waves per workgroup: four of 32 emitters x 128 pixels; with the Hessian
+// product eight of 32 x 64, whose accumulators (96 registers) leave two waves
+// per SIMD where four of 128 pixels left one.  FP16 / BF16, gradient and
+// Hessian diagonal: 130 elements / 301x255, two frequencies, 186 -> 152 us,
+// 256 / 480^2, three, 764 -> 675, 1024 / 480^2, one, 1.89 -> 1.68 ms; with
+// |G|^2 by fused multiply-adds (20 instead of 44 instructions a fragment in
+// FP16) 145, 608 and 1.46 ms.
+constexpr int t16_waves(bool hess) { return hess ? 8 : 4; }
+
 template <typename S, bool HESS, bool DIRECT, typename A>
-__global__ void __launch_bounds__(256, HESS ? 1 : 2) k_adjoint16_tr(const A args) {
+__global__ void __launch_bounds__(64 * t16_waves(HESS), 2) k_adjoint16_tr(const A args) {
     typename A::Loc loc;
     const AdjItem &it = args.locate(loc);
     const AdjParams &P = it.P;
@@ -894,7 +921,9 @@ __global__ void __launch_bounds__(256, HESS ? 1 : 2) k_adjoint16_tr(const A args
     double *__restrict__ pg = it.pg;
     double *__restrict__ ph = it.ph;
     using V = typename MM16<S>::vec;
-    constexpr int EB = 2;   // 16-row emitter blocks per wave
+    constexpr int NW = t16_waves(HESS);
+    constexpr int EB = 2;          // 16-row emitter blocks per wave
+    constexpr int CB = 32 / NW;    // 16-pixel column blocks per wave
     // four tile buffers as separate LDS objects, addressed by compile-time
     // index inside the k-loop: a direct load into one is then known not to
     // write the one being read
@@ -905,6 +934,7 @@ __global__ void __launch_bounds__(256, HESS ? 1 : 2) k_adjoint16_tr(const A args
     __shared__ float sred[2][4][kT16NT];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int eg = wave & 3, cb0 = wave >> 2 ? CB : 0;   // emitter group, first column block
     const int row = lane & 15, kk = lane >> 4;
     const int64_t N = P.N;
     const int k = loc.k();
@@ -920,18 +950,18 @@ __global__ void __launch_bounds__(256, HESS ? 1 : 2) k_adjoint16_tr(const A args
     // lane's element offsets of its four direct-load chunks within a step
     // (of the last tile's chunks beyond N, the last: dropped)
     const int lastc = (int)min(N - 8 - x0, (int64_t)kT16NT);
-    unsigned goff[4];
+    unsigned goff[16 / NW];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int rl = 4 * (4 * (wave & 1) + j) + (lane >> 4);
+    for (int j = 0; j < 16 / NW; ++j) {
+        const int rl = 4 * ((16 / NW * wave + j) & 7) + (lane >> 4);
         goff[j] = (unsigned)(rl * N) + (unsigned)min(8 * ((lane & 15) ^ t16_pos(rl, 0)), lastc);
     }
     // transposing-read offset at rows 8 kk + (row >> 2), pixels 4 (row & 3) of
     // column block 0 (block cb: XOR 32 cb)
     const unsigned t0 = t16_off(8 * kk + (row >> 2), 4 * (row & 3));
-    float gp[8], hp[8];
+    float gp[CB], hp[CB];
 #pragma unroll
-    for (int cb = 0; cb < 8; ++cb) gp[cb] = hp[cb] = 0.0f;
+    for (int cb = 0; cb < CB; ++cb) gp[cb] = hp[cb] = 0.0f;
     auto buf = [&](auto itag) -> unsigned char * {
         constexpr int I = decltype(itag)::value & 3;
         return I == 0 ? sG0 : (I == 1 ? sG1 : (I == 2 ? sG2 : sG3));
@@ -940,12 +970,12 @@ __global__ void __launch_bounds__(256, HESS ? 1 : 2) k_adjoint16_tr(const A args
     const int npass = (P.mp + kT16NE - 1) / kT16NE, npg = it.npg, qg = loc.group();
     const int pass0 = qg * npass / npg, pass1 = (qg + 1) * npass / npg;
     for (int ec = pass0 * kT16NE; ec < pass1 * kT16NE; ec += kT16NE) {
-        const int e0 = ec + 32 * wave;
-        f4 yr[EB][8], yn[EB][8], z[EB][8];
+        const int e0 = ec + 32 * eg;
+        f4 yr[EB][CB], yn[EB][CB], z[EB][CB];
 #pragma unroll
         for (int b = 0; b < EB; ++b)
 #pragma unroll
-            for (int cb = 0; cb < 8; ++cb) yr[b][cb] = yn[b][cb] = z[b][cb] = f4{0, 0, 0, 0};
+            for (int cb = 0; cb < CB; ++cb) yr[b][cb] = yn[b][cb] = z[b][cb] = f4{0, 0, 0, 0};
         // fragments of block (e0 / 32, c); emitter blocks beyond mp read the
         // last one (their Y is dropped)
         const int eblk = min(e0 >> 5, P.nb - 1) * P.nb;
@@ -961,7 +991,7 @@ __global__ void __launch_bounds__(256, HESS ? 1 : 2) k_adjoint16_tr(const A args
         // the pass's receiver chunks: `all` of its four waves (staged), `mine`
         // of this wave's 32 emitters
         AdjChunks all, mine;
-        adj_chunks(fl, P.nb, ec >> 5, 4, wave, all, mine);
+        adj_chunks(fl, P.nb, ec >> 5, 4, eg, all, mine);
         const int nstep = all.count();
         // the chunks of the current step and the next two (opaque to the
         // compiler, which would otherwise keep a strength-reduced address per
@@ -973,14 +1003,14 @@ __global__ void __launch_bounds__(256, HESS ? 1 : 2) k_adjoint16_tr(const A args
         };
         int b0 = next_bit(), b1 = next_bit(), b2 = next_bit();
         auto stage = [&](int c, unsigned char *dst) {
-            t16_stage_async(gr + ((int64_t)c * kT16KC * N + x0), gi + ((int64_t)c * kT16KC * N + x0), goff, dst);
+            t16_stage_async<NW>(gr + ((int64_t)c * kT16KC * N + x0), gi + ((int64_t)c * kT16KC * N + x0), goff, dst);
         };
-        t16us8 tv[4];   // without direct loads: the tile of step s + 1
-        auto load_t = [&](int c) { t16_load_tile(gr, gi, P.m, N, c * kT16KC, x0, full, tv); };
+        t16us8 tv[16 / NW];   // without direct loads: the tile of step s + 1
+        auto load_t = [&](int c) { t16_load_tile<NW>(gr, gi, P.m, N, c * kT16KC, x0, full, tv); };
         // One k-step s (chunk bit b0) on the tile in buffer s mod 4: wait for
         // its tile and its A, issue A of b1 and the tile of step s + 2 (b2),
         // then the MFMAs.  Per step a wave issues A(s + 1) (2 EB or
-        // 3 EB loads) and then the tile of s + 2 (4 direct loads), so at the
+        // 3 EB loads) and then the tile of s + 2 (16 / NW direct loads), so at the
         // wait only the tile of s + 1 may still be in flight.  `mode` says
         // what the step issues when that is known at compile time (3: A and
         // a tile, 2: A only, 1: nothing; 0: decided from s at run time), so
@@ -993,9 +1023,9 @@ __global__ void __launch_bounds__(256, HESS ? 1 : 2) k_adjoint16_tr(const A args
             const bool has_t = M == 3 || (M == 0 && s + 2 < nstep);
             if (!DIRECT) {
                 // the tile of s + 1, read two barriers from now at the latest
-                if (has_a) t16_store_tile(tv, P.m, AdjChunks::chunk(b1, half) * kT16KC, buf(Idx<I + 1>()));
+                if (has_a) t16_store_tile<NW>(tv, P.m, AdjChunks::chunk(b1, half) * kT16KC, buf(Idx<I + 1>()));
             } else if (has_a) {
-                __builtin_amdgcn_s_waitcnt(vmcnt_imm(4));   // tile s + 1
+                __builtin_amdgcn_s_waitcnt(vmcnt_imm(16 / NW));   // tile s + 1
             } else {
                 __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
             }
@@ -1020,9 +1050,9 @@ __global__ void __launch_bounds__(256, HESS ? 1 : 2) k_adjoint16_tr(const A args
             for (int b = 0; b < EB; ++b) nva[b] = neg(vi[b]);
             const unsigned sba = (unsigned)(uintptr_t)(const __attribute__((address_space(3))) unsigned char *)sb;
 #pragma unroll
-            for (int cb = 0; cb < 8; ++cb) {
+            for (int cb = 0; cb < CB; ++cb) {
                 t16v4 r0, r1, i0, i1;
-                t16_tr4(sba + (t0 ^ (32u * cb)), r0, r1, i0, i1);
+                t16_tr4(sba + (t0 ^ (32u * (cb0 + cb))), r0, r1, i0, i1);
                 const V br = t16_join<V>(r0, r1);
                 const V bi = t16_join<V>(i0, i1);
                 V b2;
@@ -1051,7 +1081,7 @@ __global__ void __launch_bounds__(256, HESS ? 1 : 2) k_adjoint16_tr(const A args
                 stage(AdjChunks::chunk(b0, half), sG0);
             } else {
                 load_t(AdjChunks::chunk(b0, half));
-                t16_store_tile(tv, P.m, AdjChunks::chunk(b0, half) * kT16KC, sG0);
+                t16_store_tile<NW>(tv, P.m, AdjChunks::chunk(b0, half) * kT16KC, sG0);
             }
             load_a(AdjChunks::chunk(b0, half), va, vi, vw);
             // unconditional (a one-chunk pass stages chunk 0, unused), so that
@@ -1079,18 +1109,20 @@ __global__ void __launch_bounds__(256, HESS ? 1 : 2) k_adjoint16_tr(const A args
         if (nstep > 0) kloop();   // workgroup-uniform
         // fused epilogue: Re sum_e conj(G_e) Y_e and sum_e |G_e|^2 Z_e.  The
         // tile buffers are free once every wave is done with the k-loop:
-        // wave w copies the chunk of its 32 emitter rows (both arrays) into
-        // buffer w again, and a transposing read at rows 16 b + 4 kk gives
+        // group g's waves copy the chunk of its 32 emitter rows (both arrays)
+        // into buffer g again, and a transposing read at rows 16 b + 4 kk gives
         // lane (kk, row) emitters 16 b + 4 kk + i (i = 0..3) of pixel
         // 16 cb + row, the layout of the accumulators (zero beyond m and N).
         __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
         lds_barrier();
-        unsigned char *se = wave == 0 ? sG0 : (wave == 1 ? sG1 : (wave == 2 ? sG2 : sG3));
+        unsigned char *se = eg == 0 ? sG0 : (eg == 1 ? sG1 : (eg == 2 ? sG2 : sG3));
+        const int q1 = NW == 8 ? 8 * (wave >> 2) : 0;   // first of this wave's 64 / NW copies
         if (DIRECT) {
             if (e0 < P.mp) {
                 const unsigned short *g0 = gr + ((int64_t)e0 * N + x0), *g1 = gi + ((int64_t)e0 * N + x0);
 #pragma unroll
-                for (int q = 0; q < 16; ++q) {
+                for (int qq = 0; qq < 64 / NW; ++qq) {
+                    const int q = q1 + qq;
                     const int rl = 4 * (q & 7) + (lane >> 4);
                     const unsigned go =
                         (unsigned)(rl * N) + (unsigned)min(8 * ((lane & 15) ^ t16_pos(rl, 0)), lastc);
@@ -1103,7 +1135,7 @@ __global__ void __launch_bounds__(256, HESS ? 1 : 2) k_adjoint16_tr(const A args
         } else if (e0 < P.mp) {
             // (rows at or beyond m: the last one, dropped below)
 #pragma unroll
-            for (int q0 = 0; q0 < 16; q0 += 8) {
+            for (int q0 = q1; q0 < q1 + 64 / NW; q0 += 8) {
                 t16us8 v[8];
 #pragma unroll
                 for (int q = 0; q < 8; ++q) {
@@ -1121,8 +1153,8 @@ __global__ void __launch_bounds__(256, HESS ? 1 : 2) k_adjoint16_tr(const A args
 #pragma unroll
             for (int b = 0; b < EB; ++b) {
 #pragma unroll
-                for (int cb = 0; cb < 8; ++cb) {
-                    const int off = t16_off(16 * b + 4 * kk + (row >> 2), 16 * cb + 4 * (row & 3));
+                for (int cb = 0; cb < CB; ++cb) {
+                    const int off = t16_off(16 * b + 4 * kk + (row >> 2), 16 * (cb0 + cb) + 4 * (row & 3));
                     const t16v4 vr = t16_tr(se + off), vi = t16_tr(se + kT16Arr + off);
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
@@ -1136,17 +1168,17 @@ __global__ void __launch_bounds__(256, HESS ? 1 : 2) k_adjoint16_tr(const A args
             }
         }
     }
-    // the four lane groups of a column, then the waves, in a fixed order
+    // the four lane groups of a column, then the emitter groups, in a fixed order
 #pragma unroll
-    for (int cb = 0; cb < 8; ++cb) {
+    for (int cb = 0; cb < CB; ++cb) {
         float g = gp[cb], h = hp[cb];
         g += __shfl_xor(g, 16);
         h += __shfl_xor(h, 16);
         g += __shfl_xor(g, 32);
         h += __shfl_xor(h, 32);
         if (kk == 0) {
-            sred[0][wave][16 * cb + row] = g;
-            sred[1][wave][16 * cb + row] = h;
+            sred[0][eg][16 * (cb0 + cb) + row] = g;
+            sred[1][eg][16 * (cb0 + cb) + row] = h;
         }
     }
     __syncthreads();
@@ -1175,9 +1207,9 @@ void launch_adjoint16(const AdjTask &t, dim3 grid, const A &arg, hipStream_t st)
         using S = decltype(tag);
         constexpr bool H = decltype(hess)::value;
         if (t.direct)
-            k_adjoint16_tr<S, H, true><<<grid, 256, 0, st>>>(arg);
+            k_adjoint16_tr<S, H, true><<<grid, 64 * t16_waves(H), 0, st>>>(arg);
         else
-            k_adjoint16_tr<S, H, false><<<grid, 256, 0, st>>>(arg);
+            k_adjoint16_tr<S, H, false><<<grid, 64 * t16_waves(H), 0, st>>>(arg);
     };
     if (t.dt == RB_BF16)
         t.hdiag ? go(__hip_bfloat16(), std::true_type()) : go(__hip_bfloat16(), std::false_type());
