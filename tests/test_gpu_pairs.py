@@ -338,3 +338,43 @@ def test_16bit_gradient_rows(rb, dtype, shape):
         close(grad.cpu().numpy(), g_o, TOL[dtype], f"grad {dtype} {shape} hess={hess}")
         if hess:
             close(hd.cpu().numpy(), h_o, TOL[dtype], f"hdiag {dtype} {shape}")
+
+
+# The banded Hessian diagonal at the edges of its block variants (rings up to
+# 128, 256, 512, 768 and 1024 elements, above; groups with and without a
+# partial last one), of its last pixels' block, of the band (none, one pair,
+# part of a group, the whole ring) and of its chunks of zeroed pairs.  Each
+# pixel's value is a sum of at most about 200 dependent FP32 (FP64) additions
+# of terms whose magnitudes add up to `mag`: 200 2^-24 = 1.2e-5.
+@pytest.mark.parametrize("dtype", ["f64", "f32", "bf16", "f16"])
+@pytest.mark.parametrize("m, dmin, nz", [(5, 0, 3), (33, 5, 70), (64, 64, 0), (129, 1, 513), (250, 32, 1100),
+                                         (257, 33, 2049), (500, 62, 5000), (513, 100, 1), (770, 97, 9000),
+                                         (1024, 128, 8193), (1030, 129, 600)])
+def test_banded_hessian_blocks(rb, dtype, m, dmin, nz):
+    geom, freqs = _geom(9, 5, m), [3e5, 7e5]
+    N = geom.n_pixels
+    print(f"[gpu-test] banded Hessian {dtype} m={m} dmin={dmin} zeroed={nz}", flush=True)
+    rng = np.random.default_rng(m)
+    td = rb._binding.TORCH_DTYPES[rb.DTYPES[dtype]]
+    gr, gi = (torch.as_tensor(rng.uniform(-1, 1, (2, m, N)), device=DEV).to(td) for _ in range(2))
+    sc = np.array([0.5, 2.0]) if dtype in ("bf16", "f16") else np.ones(2)
+    scale = torch.as_tensor(sc, dtype=torch.float32, device=DEV) if dtype in ("bf16", "f16") else None
+    cap = max(nz, 1) + 3
+    pairs = rng.integers(0, m, (2, cap, 2)).astype(np.int32)
+    pairs[:, 0] = (m, 0)          # out of range: ignored
+    n = np.array([nz, max(nz - 1, 0)], dtype=np.int32)
+    hd = torch.zeros(N, dtype=torch.float64, device=DEV)
+    rb.born_hessian_banded(geom, gr, gi, scale, dtype, freqs, dmin, torch.as_tensor(pairs, device=DEV),
+                           torch.as_tensor(n, device=DEV), hd)
+    i = np.arange(m)
+    dist = np.abs(i[:, None] - i[None, :])
+    sel = (np.minimum(dist, m - dist) >= dmin).astype(np.float64)
+    want, mag = np.zeros(N), np.zeros(N)
+    for k, f in enumerate(freqs):
+        G = (gr[k].double().cpu().numpy() + 1j * gi[k].double().cpu().numpy()) * sc[k]
+        z = np.zeros((m, m))
+        p = pairs[k, 1:n[k]]
+        np.add.at(z, (p[:, 0], p[:, 1]), 1.0)
+        want += born.hessian_diag(G, sel - z, f, geom.h ** 2)
+        mag += born.hessian_diag(G, 2.0 + z, f, geom.h ** 2)
+    assert (np.abs(hd.cpu().numpy() - want) <= (200 * 2.0 ** (-53 if dtype == "f64" else -24)) * mag).all()
