@@ -490,6 +490,7 @@ __global__ void __launch_bounds__(256, 2) k_forward_f32_regs(FwdParams P, const 
 // once.
 constexpr int kFdKC = 16, kFdArr = 64 * 64, kFdBuf = 4 * kFdArr + 64;
 constexpr int64_t kFdSplitPx = 16384;   // longest pixel split (1024 k-steps)
+constexpr int64_t kWidePx = 900000;         // see fwd16_wide
 constexpr int64_t kMinSplitPx = 64, kFewSplitPx = 512;   // shortest, see fwd_params
 typedef __attribute__((address_space(3))) void lds_void_t;
 
@@ -1129,6 +1130,19 @@ constexpr int kWArrE = kWE * 64, kWArrR = kWR * 64;   // one array of a side (by
 constexpr int kWBuf = 2 * kWArrE + 2 * kWArrR;        // e re, e im, r re, r im
 typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
 
+// tile (te, tr), split and frequency of a workgroup: consecutive logical ids are
+// the tiles of one pixel split (see fwd_block)
+__device__ __forceinline__ void wide_block(const FwdParams &P, int &te, int &tr, int &split, int &k) {
+    const int64_t L = xcd_remap(blockIdx.x, gridDim.x);
+    int t = (int)(L % P.ntri);
+    const int64_t rest = L / P.ntri;
+    split = (int)(rest % P.nsplit);
+    k = (int)(rest / P.nsplit);
+    te = 0;
+    while (t >= P.ntl - 2 * te) t -= P.ntl - 2 * te++;
+    tr = 2 * te + t;
+}
+
 template <typename S>
 __global__ void __launch_bounds__(512, 2) k_forward16_wide(FwdParams P, const S *__restrict__ Gr,
                                                            const S *__restrict__ Gi, const float *__restrict__ df,
@@ -1142,17 +1156,7 @@ __global__ void __launch_bounds__(512, 2) k_forward16_wide(FwdParams P, const S 
     // the diagonal, whose lower half is idle, each SIMD has a working wave
     const int wr = wave >> 2, we = (wave + 2 * wr) & 3;
     int te, tr, split, k;
-    {
-        // consecutive logical ids are the tiles of one pixel split (see fwd_block)
-        const int64_t L = xcd_remap(blockIdx.x, gridDim.x);
-        int t = (int)(L % P.ntri);
-        const int64_t rest = L / P.ntri;
-        split = (int)(rest % P.nsplit);
-        k = (int)(rest / P.nsplit);
-        te = 0;
-        while (t >= P.ntl - 2 * te) t -= P.ntl - 2 * te++;
-        tr = 2 * te + t;
-    }
+    wide_block(P, te, tr, split, k);
     const int e0 = te * kWE, r0 = tr * kWR;
     if (P.dmin >= 32 && max_circ_dist(P.m, e0, kWE, r0, kWR) < P.dmin) return;
     const bool idle = e0 + 64 * we >= r0 + 64 * (wr + 1) ||
@@ -1283,6 +1287,208 @@ __global__ void __launch_bounds__(512, 2) k_forward16_wide(FwdParams P, const S 
     }
 }
 
+// The same tile for rows of whole 16-byte pieces, in pieces of 128 bytes (L2
+// serves about as many requests of 128 bytes a second as of 64).  The e rows of
+// 64 pixels go straight to LDS, a pair of steps ahead, into two buffers of 64
+// KB; the r rows pass through registers, loaded a pair ahead, multiplied by
+// delta and stored one step's half at a time.  Piece c of an e row is at
+// position c ^ (row / 2 mod 8), so that the 16 rows of a fragment lie on
+// distinct banks.  Pieces beyond the table's last pixel come from the zeros
+// after delta.  BF16, 1024 elements / 1100^2, four frequencies: 34.9 (pieces of
+// 64 bytes, k_forward16_wide) -> 22.6 ms, 0.90 PFLOP/s, near the 1.0 to 1.1 at
+// which the card's power limits its clock; 1024 / 480^2, one, 1.19 -> 1.02 ms.
+// (Direct loads of the e rows one step later, behind the conversion of the r
+// rows, so that it need not wait for them: 23.7 ms.)
+constexpr int kDArrE = kWE * 128;   // one array of the e side (bytes)
+typedef __attribute__((address_space(3))) void lds_void_t;
+template <int I>
+using Idx = std::integral_constant<int, I>;
+
+template <typename S>
+__global__ void __launch_bounds__(512, 2) k_forward16_direct(FwdParams P, const S *__restrict__ Gr,
+                                                             const S *__restrict__ Gi, const float *__restrict__ df,
+                                                             float *__restrict__ part) {
+    using V = typename MM16<S>::vec;
+    // separate objects, so that a direct load into one is known not to write
+    // the one being read
+    __shared__ __align__(16) unsigned char sE0[2 * kDArrE];
+    __shared__ __align__(16) unsigned char sE1[2 * kDArrE];
+    __shared__ __align__(16) unsigned char sR0[2 * kWArrR];
+    __shared__ __align__(16) unsigned char sR1[2 * kWArrR];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int row = lane & 15, kk = lane >> 4;
+    // (waves and SIMDs, tiles and splits: as k_forward16_wide)
+    const int wr = wave >> 2, we = (wave + 2 * wr) & 3;
+    int te, tr, split, k;
+    wide_block(P, te, tr, split, k);
+    const int e0 = te * kWE, r0 = tr * kWR;
+    if (P.dmin >= 32 && max_circ_dist(P.m, e0, kWE, r0, kWR) < P.dmin) return;
+    const bool idle = e0 + 64 * we >= r0 + 64 * (wr + 1) ||
+                      (P.dmin >= 32 && max_circ_dist(P.m, e0 + 64 * we, 64, r0 + 64 * wr, 64) < P.dmin);
+    const int64_t N = P.N;
+    const int64_t ks = (int64_t)split * P.kchunk;
+    const int64_t ke = std::min<int64_t>(N, ks + P.kchunk);
+    const int last = (int)((ke - ks + kF16KC - 1) / kF16KC) - 1;   // last step
+    const int lastp = last >> 1;                                   // last pair of steps
+    const unsigned short *gr = reinterpret_cast<const unsigned short *>(Gr) + (int64_t)k * P.m * N;
+    const unsigned short *gi = reinterpret_cast<const unsigned short *>(Gi) + (int64_t)k * P.m * N;
+    const unsigned short *zeros = reinterpret_cast<const unsigned short *>(df + N);
+    // e side: wave w fills rows 64 (w mod 4) .. + 63 of array w / 4, eight rows an
+    // instruction; r side: piece tid % 8 of rows tid / 8 and tid / 8 + 64.  Rows
+    // at or beyond m read row m - 1: their outputs are never read.
+    const unsigned short *ge = wave >> 2 ? gi : gr;
+    const int l8 = lane >> 3;
+    unsigned eoff[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const int r = std::min(e0 + 64 * (wave & 3) + 8 * j + l8, P.m - 1) - std::min(e0, P.m - 1);
+        eoff[j] = (unsigned)r * (unsigned)N + 8u * ((lane & 7) ^ ((4 * j + (l8 >> 1)) & 7));
+    }
+    ge += (int64_t)std::min(e0, P.m - 1) * N;
+    const int half = (tid >> 2) & 1, sch = tid & 3, p8 = 8 * (tid & 7), r8 = tid >> 3;
+    unsigned roff[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+        roff[j] = (unsigned)(std::min(r0 + r8 + 64 * j, P.m - 1) - std::min(r0, P.m - 1)) * (unsigned)N + (unsigned)p8;
+    const int64_t rbase = (int64_t)std::min(r0, P.m - 1) * N;
+    auto load_e = [&](int p, unsigned char *buf) {
+        const int64_t x0 = ks + 64 * (int64_t)p;
+        unsigned char *d = buf + (wave >> 2) * kDArrE + 64 * (wave & 3) * 128;
+        const unsigned short *g = ge + x0;
+        const int left = (int)std::min<int64_t>(N - x0, 64);   // pixels of the table (no branch: see step)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int px = 8 * ((lane & 7) ^ ((4 * j + (l8 >> 1)) & 7));
+            __builtin_amdgcn_global_load_lds(px < left ? g + eoff[j] : zeros, (lds_void_t *)(d + j * 1024), 16, 0, 0);
+        }
+    };
+    u32x4 v[2][2];
+    f4 d0, d1;
+    auto load_r = [&](int p) {
+        const int64_t x0 = ks + 64 * (int64_t)p;
+        const unsigned short *ga = gr + rbase + x0, *gb = gi + rbase + x0;
+        const bool in = x0 + p8 < N;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            v[j][0] = *reinterpret_cast<const u32x4 *>(in ? ga + roff[j] : zeros);
+            v[j][1] = *reinterpret_cast<const u32x4 *>(in ? gb + roff[j] : zeros);
+        }
+        const float *q = df + (in ? x0 + p8 : N);
+        d0 = *reinterpret_cast<const f4 *>(q);
+        d1 = *reinterpret_cast<const f4 *>(q + 4);
+    };
+    auto convert = [&]() {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int a = 0; a < 2; ++a) v[j][a] = f16_scale<S, V>(v[j][a], d0, d1);
+    };
+    auto store_r = [&](int h, unsigned char *buf) {
+        if (half != h) return;
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+                *reinterpret_cast<u32x4 *>(buf + a * kWArrR + f16_off(r8 + 64 * j, sch)) = v[j][a];
+    };
+    f4 re[4][4], imv[4][4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) re[b][c] = imv[b][c] = f4{0, 0, 0, 0};
+    const int te0 = (64 * we + row) * 128 + 16 * (kk ^ ((row >> 1) & 7));
+    const int tr0 = f16_off(64 * wr + row, kk);
+    auto mma = [&](const unsigned char *sa, int h, const unsigned char *sb) {
+        V b_r[4], b_i[4];
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) {
+            b_r[cb] = *reinterpret_cast<const V *>(sb + tr0 + 16 * cb * 64);
+            b_i[cb] = *reinterpret_cast<const V *>(sb + kWArrR + tr0 + 16 * cb * 64);
+        }
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const int o = (te0 ^ (64 * h)) + 16 * b * 128;
+            const V a_r = *reinterpret_cast<const V *>(sa + o);
+            const V a_i = *reinterpret_cast<const V *>(sa + kDArrE + o);
+            const V a_n = neg(a_i);
+            // (ar + i ai)(br + i bi) = ar br - ai bi + i (ar bi + ai br)
+#pragma unroll
+            for (int cb = 0; cb < 4; ++cb) {
+                re[b][cb] = MM16<S>::mma(a_r, b_r[cb], re[b][cb]);
+                imv[b][cb] = MM16<S>::mma(a_r, b_i[cb], imv[b][cb]);
+            }
+#pragma unroll
+            for (int cb = 0; cb < 4; ++cb) {
+                re[b][cb] = MM16<S>::mma(a_n, b_i[cb], re[b][cb]);
+                imv[b][cb] = MM16<S>::mma(a_i, b_r[cb], imv[b][cb]);
+            }
+        }
+    };
+    // step c (I = c mod 4; pair c / 2, half c mod 2).  Even steps store the
+    // second half of their pair's r rows and issue the next pair's loads; odd
+    // ones convert those r rows and store their first half.  (The last steps
+    // load and store the last pair again, unused.)
+    auto step = [&](int c, auto itag, auto first) {
+        constexpr int I = decltype(itag)::value, H = I & 1;
+        unsigned char *se = I & 2 ? sE1 : sE0, *sn = I & 2 ? sE0 : sE1;
+        if (!H) __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // this pair's e rows
+        lds_barrier();   // step c is in LDS, and no wave still reads the other buffers
+        auto stage = [&]() {
+            if (H) {
+                convert();
+                store_r(0, sR0);
+            } else {
+                store_r(1, sR1);
+                const int p = std::min((c >> 1) + 1, lastp);
+                load_r(p);
+                __builtin_amdgcn_sched_barrier(0);
+                load_e(p, sn);
+            }
+        };
+        if (decltype(first)::value) {
+            stage();
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (!idle) mma(se, H, H ? sR1 : sR0);
+        if (!decltype(first)::value) {
+            __builtin_amdgcn_sched_barrier(0);
+            stage();
+        }
+    };
+    load_e(0, sE0);
+    load_r(0);
+    convert();
+    store_r(0, sR0);
+    auto kloop = [&](auto first) {   // first: stage before multiplying
+        for (int c = 0; c <= last; c += 4) {
+            step(c, Idx<0>(), first);
+            if (c + 1 <= last) step(c + 1, Idx<1>(), first);
+            if (c + 2 <= last) step(c + 2, Idx<2>(), first);
+            if (c + 3 <= last) step(c + 3, Idx<3>(), first);
+        }
+    };
+    if (wr == 0)
+        kloop(std::true_type());
+    else
+        kloop(std::false_type());
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));   // no direct load outlives the workgroup's LDS
+    if (idle) return;
+    float *pp = part + ((int64_t)split * P.nf + k) * P.mp * P.mp * 2;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) {
+            const int r = r0 + 64 * wr + 16 * cb + row;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int ee = e0 + 64 * we + 16 * b + 4 * kk + i;
+                *reinterpret_cast<f2 *>(pp + ((int64_t)ee * P.mp + r) * 2) = f2{re[b][cb][i], imv[b][cb][i]};
+            }
+        }
+    }
+}
+
 }  // namespace
 
 // ---------------------------------------------------------------- host side
@@ -1296,18 +1502,26 @@ static int device_cus() {
     return cus;
 }
 
+// Wide tiles by direct loads: rows of whole 16-byte pieces, 256 N elements
+// within 32-bit offsets.
+static bool fwd16_direct(int64_t N) { return N % 8 == 0 && N < ((int64_t)1 << 23); }
+
 // The wide-tile 16-bit kernel: rows that are not 16-byte aligned, which the 64
 // x 64-tile kernel reads element by element (us per call, that / this: 64
 // elements / 255x301 107 / 153, 96 200 / 151, 200 548 / 171, 1024 8906 /
-// 1214), and aligned rows of large problems, where its tiles are bound by the
-// bytes they move (384 / 480^2 458 / 840, 512 / 480^2 855 / 750, 1024 / 128^2
-// 284 / 324, 1024 / 260^2 1210 / 974, 1024 / 1100^2, four frequencies, 67.8 /
-// 34.9 ms), unless padding to 256 rows costs more (600 / 480^2 1221 / 1307).
+// 1214), and aligned rows of large problems, where the small tiles are bound by
+// the bytes they move, unless padding to 256 rows costs more: that / this with
+// direct loads 512 / 128^2 58 / 59, 1024 / 200^2, two frequencies, 603 / 457,
+// 600 / 480^2 601 / 655, 1024 / 1100^2, four, 67.8 / 22.6 ms; more padding pays
+// from about 10^6 pixels on: 256 / 728^2 293 / 358, 384 / 728^2 657 / 690, 256 /
+// 1100^2 979 / 652, 384 / 1000^2 1686 / 1297, 300 / 480^2 186 / 347.
 static bool fwd16_wide(const rb_geometry *g, rb_dtype dt) {
     if (dt != RB_BF16 && dt != RB_F16) return false;
     const int64_t N = (int64_t)g->nx * g->ny;
     if (N % 8 != 0) return g->m > 64;
-    return g->m >= 512 && N >= 65536 && 5 * ((g->m + kWE - 1) / kWE * kWE) <= 6 * g->m;
+    const int mp = (g->m + kWE - 1) / kWE * kWE;
+    return (g->m >= 512 && N >= 32768 && 5 * mp <= 6 * g->m) || (g->m >= 256 && fwd16_direct(N) && N >= kWidePx &&
+                                                                2 * mp <= 3 * g->m);
 }
 
 // FP32 tables on the FP16 cores: rings that fill more than half of a 128-element
@@ -1479,7 +1693,15 @@ rb_status forward_impl(const rb_geometry *g, const void *G_re, const void *G_im,
             k_delta_f32<<<blocks_for(P.N + 32, 256), 256, 0, st>>>(P.N, P.N + 32, delta, w.dmax, w.df);
             RB_LAUNCHED();
             if (fwd16_wide(g, dt)) {
-                if (dt == RB_BF16)
+                if (fwd16_direct(P.N)) {
+                    if (dt == RB_BF16)
+                        k_forward16_direct<<<nblk, 512, 0, st>>>(P, (const __hip_bfloat16 *)G_re,
+                                                                 (const __hip_bfloat16 *)G_im, w.df,
+                                                                 (float *)w.part);
+                    else
+                        k_forward16_direct<<<nblk, 512, 0, st>>>(P, (const __half *)G_re, (const __half *)G_im, w.df,
+                                                                 (float *)w.part);
+                } else if (dt == RB_BF16)
                     k_forward16_wide<<<nblk, 512, 0, st>>>(P, (const __hip_bfloat16 *)G_re,
                                                            (const __hip_bfloat16 *)G_im, w.df, (float *)w.part);
                 else

@@ -223,10 +223,12 @@ def test_fp32_forward_outside_the_fp16_range(rb):
 
 # 16-bit tables with rows that are not 16-byte aligned (odd and even pixel
 # counts, a last chunk of 1 to 31 pixels) and, aligned, large enough for the
-# same 256 x 128 tiles; rings of a part of a tile, a tile and two elements, and
-# three rows of tiles.
+# same 256 x 128 tiles by direct loads (a last pair of steps of 64, 8 and 24
+# pixels); rings of a part of a tile, a tile and two elements, and three rows of
+# tiles.
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
-@pytest.mark.parametrize("shape", [(33, 31, 65), (50, 41, 130), (61, 67, 258), (41, 45, 520), (256, 256, 512)])
+@pytest.mark.parametrize("shape", [(33, 31, 65), (50, 41, 130), (61, 67, 258), (41, 45, 520), (256, 256, 512), (199, 168, 512),
+                                   (181, 184, 700)])
 def test_16bit_forward_in_wide_tiles(rb, dtype, shape):
     nx, ny, m = shape
     geom, freqs = _geom(nx, ny, m), [3e5]
