@@ -1567,6 +1567,13 @@ static FwdParams fwd_params(const rb_geometry *g, const double *freqs, int nf, r
     if (fs || wide || (dt != RB_F64 && P.N % (dt == RB_F32 ? 4 : 8) == 0))
         most = std::max<int64_t>(P.N / kFewSplitPx, std::min<int64_t>(most, resident / (ntri * nf)));
     int nsplit = std::max<int64_t>(1, std::min<int64_t>(4 * resident / (ntri * nf), most));
+    // whole rounds where that is less work in a row (rounds / splits): a last
+    // round with a tenth of the workgroups takes as long as a full one.  us,
+    // before and now: 97 elements / 301x255, two frequencies, FP32 113 / 77 (1.1
+    // rounds -> 1), BF16 152 / 119, 256 / 301x255 FP32 246 / 216, BF16 190 / 149
+    const int64_t full = (int64_t)nsplit * ntri * nf / resident * resident / (ntri * nf);
+    auto rounds = [&](int64_t n) { return (n * ntri * nf + resident - 1) / resident; };
+    if (full > 0 && rounds(full) * nsplit < rounds(nsplit) * full) nsplit = (int)full;
     // the kernels with direct loads (FP32, and 16-bit for large rings) also
     // keep a split to at most kFdSplitPx pixels: the tiles of a split share
     // its table rows in L2 only while they stay within a few k-steps of each
