@@ -46,6 +46,9 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK = {"f32": 157.3, "f64": 78.6, "bf16": 2500.0, "f16": 2500.0}   # dense MFMA TFLOP/s
+# FP32 contractions of these sizes run on the FP16 cores in two pieces per
+# operand, three FP16 products for one
+PEAK_CONTRACTION = {**PEAK, "f32": PEAK["f16"] / 3}
 # HBM traffic of the backprojection kernel per workload, from two rocprofv3
 # --pmc passes (FETCH_SIZE, WRITE_SIZE) scaled by the same counters on a copy
 # of known size.
@@ -121,6 +124,19 @@ def issued_mfma_flop(w: np.ndarray, n_pixels: int, products: int) -> float:
     wp[:, :m, :m] = w != 0
     on = wp.reshape(nf, mp // 32, 32, mp // 32, 32).any(axis=(2, 4))
     return float(on.sum()) * 32 * 32 * n_pixels * 2 * products
+
+
+def folded_weights(w: np.ndarray) -> np.ndarray:
+    """The weights as the backprojection contracts them: each unordered pair
+    once, a 32 x 32 block (I, J) of the ring's nb blocks standing for (J, I)
+    too where J lies less than half a ring after I (at exactly half, I < J)."""
+    nf, m, _ = w.shape
+    nb = (m + 31) // 32
+    i, j = np.meshgrid(np.arange(nb), np.arange(nb), indexing="ij")
+    d = (j - i) % nb
+    keep = (2 * d < nb) | ((2 * d == nb) & (i < j))
+    keep = np.kron(keep, np.ones((32, 32), bool))[:m, :m]
+    return np.where(keep, (w != 0) | (w.transpose(0, 2, 1) != 0), False)
 
 
 def measured_traffic(dtype: str, workload: str):
@@ -256,24 +272,27 @@ def backprojection_roofline(sw: Sweep, reps: int, workload: str, stages: bool):
     adj = lambda: rb.born_adjoint_weighted(g, Gr, Gi, sc, dtype, fs, sw.pms[0], Wd, grad, None, ws=aws,
                                            stream=stream)
     adj_ms = timed_events(torch, stream, adj, reps=reps, warm=2)
-    flops = 8.0 * N * P * nf
+    flops = 8.0 * N * (P / 2) * nf   # unordered pairs: G_e G_r is symmetric
     achieved = flops / (adj_ms * 1e-3) / 1e12
     esize = {"f64": 8, "f32": 4, "bf16": 2, "f16": 2}[dtype]
     alg_bytes = 2 * nf * g.m * N * esize + nf * N * 8   # G (re, im) once + per-frequency gradient partials
-    issued = issued_mfma_flop(Wd.cpu().numpy(), N, 3 if dtype == "f32" else 4) if dtype != "f64" else None
-    kname = {"f32": "k_adjoint_f32", "bf16": "k_adjoint16_tr", "f16": "k_adjoint16_tr", "f64": "k_adjoint"}[dtype]
-    roof = {"bound": "mfma", "achieved": round(achieved, 3), "peak": PEAK[dtype], "unit": "TFLOP/s",
-            "frac": round(achieved / PEAK[dtype], 4), "traffic": measured_traffic(dtype, workload),
+    issued = (issued_mfma_flop(folded_weights(Wd.cpu().numpy()), N, 12 if dtype == "f32" else 4)
+              if dtype != "f64" else None)
+    peak, core = PEAK_CONTRACTION[dtype], PEAK["f16" if dtype == "f32" else dtype]
+    kname = {"f32": "k_adjoint_split", "bf16": "k_adjoint16_tr", "f16": "k_adjoint16_tr", "f64": "k_adjoint"}[dtype]
+    roof = {"bound": "mfma", "achieved": round(achieved, 3), "peak": round(peak, 1), "unit": "TFLOP/s",
+            "frac": round(achieved / peak, 4), "traffic": measured_traffic(dtype, workload),
             "kernel": kname + " (fused complex backprojection, gradient as the step runs it)",
             "launch_ms": round(adj_ms, 4), "launches_timed": reps,
             "algorithmic_flop_per_launch": flops, "algorithmic_bytes_per_launch": alg_bytes,
-            "unit_of_work": f"{N} pixels x {P} selected pairs x {nf} frequencies, 8 flop each",
+            "unit_of_work": f"{N} pixels x {P // 2} unordered selected pairs x {nf} frequencies, 8 flop each",
             "mfma_issued": None if issued is None else {
                 "flop_per_launch": issued,
-                "frac": round(issued / (adj_ms * 1e-3) / 1e12 / PEAK[dtype], 4),
-                "what": "real matrix-core work the kernel issues: 32-emitter x 32-receiver blocks with a nonzero "
-                        "weight (unselected pairs inside them carry weight 0), 3 real products per complex MAC "
-                        "in FP32, 4 in 16-bit"}}
+                "frac": round(issued / (adj_ms * 1e-3) / 1e12 / core, 4),
+                "what": "real matrix-core work the kernel issues, of the 16-bit cores' peak: 32-emitter x "
+                        "32-receiver blocks with a nonzero weight, each unordered pair once (unselected pairs "
+                        "inside them carry weight 0), 4 real products per complex MAC, of 3 FP16 pieces each in "
+                        "FP32"}}
     st = None
     if stages:
         dmin = int(math.ceil((1.0 - prob.inv.recv_fraction) * 0.5 * g.m - 1e-9))
@@ -466,11 +485,11 @@ def ring256_leg(args, dev):
         t_k = timed_events(torch, stream, lambda: cg_set(args.cg_iters))
         _, alphas, rzs = cg_set(args.cg_iters)
         t_it = (t_k - t_1) / max(args.cg_iters - 1, 1)
-        it_flop = 12.0 * N * P * nf
+        it_flop = 8.0 * N * P * nf   # both contractions on unordered pairs
         cg = {"iters": args.cg_iters, "ms_per_set": round(t_k, 3), "ms_per_set_one_iteration": round(t_1, 3),
               "ms_per_set_single_step": round(t_one, 3), "ms_per_extra_iteration": round(t_it, 3),
               "iteration_tflops": round(it_flop / (t_it * 1e-3) / 1e12, 3),
-              "iteration_frac": round(it_flop / (t_it * 1e-3) / 1e12 / PEAK["f32"], 4),
+              "iteration_frac": round(it_flop / (t_it * 1e-3) / 1e12 / PEAK_CONTRACTION["f32"], 4),
               "rz_first_last": [rzs[0], rzs[-1]]}
         del cws
         asws = torch.empty(rb.invert_asymptotic_workspace_bytes(g, topts, nf, "f32", 0), dtype=torch.uint8, device=dev)
