@@ -1556,9 +1556,9 @@ struct AdjWs {
 // (64 emitters in the FP32 kernel, 128 in the 16-bit one) goes to a
 // workgroup of its own once there are four or more, the passes of a tile
 // adjacent in logical order and on one XCD (AdjOneSplit), so that the
-// tile's G rows come from HBM once and from L2 for the other passes (FP32,
-// 1024 elements / 1100^2: 221.6 -> 209.6 ms per 4-frequency launch; 16-bit:
-// 51.9 -> 47.6 ms).  Ordering the split workgroups pass-major instead (all
+// tile's G rows come from HBM once and from L2 for the other passes (measured
+// while every ordered pair was contracted, FP32, 1024 elements / 1100^2: 221.6 ->
+// 209.6 ms per 4-frequency launch; 16-bit: 51.9 -> 47.6 ms).  Ordering the split workgroups pass-major instead (all
 // workgroups in flight on one pass, sharing its W.D rows) was slower: 224.7
 // and 60.0 ms; so was nothing in between: dealing a tile's groups into 2
 // or 4 subsets on their own XCDs (each L2 then holds a half or a quarter of
