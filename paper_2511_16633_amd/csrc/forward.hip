@@ -723,9 +723,17 @@ __global__ void __launch_bounds__(512, 2) k_forward_split(FwdParams P, const flo
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int row = lane & 15, kk = lane >> 4;
-    const int we = wave & 3, wr = wave >> 2;
     int te, tr, split, k;
     fwd_block(P, te, tr, split, k);
+    // Rows 32 we, columns 64 wr of the tile.  Waves s and s + 4 share a SIMD: on
+    // the diagonal, where two of the eight blocks lie below it and two need
+    // half of their columns (the upper ones), these are dealt so that no SIMD has
+    // more than one and a half (two, before): 128 elements / 480^2, two
+    // frequencies, 204 -> 191 us, 97 / 301x255 80 -> 75; from 200 elements on, where
+    // power limits the matrix cores, no difference.
+    const int dw = (0x71326054 >> (4 * wave)) & 15;   // we + 4 wr
+    const int we = te == tr ? dw & 3 : wave & 3, wr = te == tr ? dw >> 2 : wave >> 2;
+    const bool upper = te == tr && (we == 1 + 2 * wr);
     if (P.dmin >= 32 && max_circ_dist(P.m, te * kFsT, kFsT, tr * kFsT, kFsT) < P.dmin) return;
     const bool idle = (te == tr && 32 * we >= 64 * (wr + 1)) ||
                       (P.dmin >= 32 && max_circ_dist(P.m, te * kFsT + 32 * we, 32, tr * kFsT + 64 * wr, 64) < P.dmin);
@@ -796,7 +804,7 @@ __global__ void __launch_bounds__(512, 2) k_forward_split(FwdParams P, const flo
 #pragma unroll
         for (int c = 0; c < 4; ++c) re[b][c] = imv[b][c] = f4{0, 0, 0, 0};
     auto frag = [&](const unsigned char *q, int r) { return *reinterpret_cast<const h8 *>(q + f16_off(r, kk)); };
-    auto mma = [&](const unsigned char *sa, const unsigned char *sb) {
+    auto mma = [&](const unsigned char *sa, const unsigned char *sb, auto c0) {
         h8 a[4][2], n[2][2];
 #pragma unroll
         for (int b = 0; b < 2; ++b) {
@@ -806,7 +814,7 @@ __global__ void __launch_bounds__(512, 2) k_forward_split(FwdParams P, const flo
             n[1][b] = neg(a[3][b]);
         }
 #pragma unroll
-        for (int cb = 0; cb < 4; ++cb) {
+        for (int cb = decltype(c0)::value; cb < 4; ++cb) {
             h8 u[4];
 #pragma unroll
             for (int t = 0; t < 4; ++t) u[t] = frag(sb + t * kFsArr, 64 * wr + 16 * cb + row);
@@ -848,7 +856,7 @@ __global__ void __launch_bounds__(512, 2) k_forward_split(FwdParams P, const flo
     load(0);
     store(sT[0]);
     load(std::min(1, last));
-    auto kloop = [&](auto first) {   // first: convert before multiplying
+    auto kloop = [&](auto first, auto c0) {   // first: convert before multiplying
         for (int c = 0; c <= last; ++c) {
             lds_barrier();   // chunk c is in LDS, and no wave still reads the other buffer
             const unsigned char *sa = sT[c & 1];
@@ -859,7 +867,7 @@ __global__ void __launch_bounds__(512, 2) k_forward_split(FwdParams P, const flo
                 load(std::min(c + 2, last));
                 __builtin_amdgcn_sched_barrier(0);
             }
-            if (!idle) mma(sa, sa + 4 * kFsArr);
+            if (!idle) mma(sa, sa + 4 * kFsArr, c0);
             if (!decltype(first)::value) {
                 __builtin_amdgcn_sched_barrier(0);
                 store(sn);
@@ -867,10 +875,14 @@ __global__ void __launch_bounds__(512, 2) k_forward_split(FwdParams P, const flo
             }
         }
     };
-    if (wr == 0)
-        kloop(std::true_type());
+    typedef std::integral_constant<int, 0> C0;
+    typedef std::integral_constant<int, 2> C2;
+    if (wave < 4)
+        kloop(std::true_type(), C0());
+    else if (!upper)
+        kloop(std::false_type(), C0());
     else
-        kloop(std::false_type());
+        kloop(std::false_type(), C2());
     const int beyond = __syncthreads_or(!(top < kFsMax));
     if (beyond && tid == 0) {
         const int64_t id = ((int64_t)k * P.nsplit + split) * P.ntri + te * P.ntl - te * (te - 1) / 2 + (tr - te);
