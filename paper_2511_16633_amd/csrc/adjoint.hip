@@ -428,8 +428,8 @@ __device__ __forceinline__ void adj_stage_regs(const float *__restrict__ gr, con
 // three real products, P1 = Ar Gr, P2 = Ai Gi, P3 = (Ar + Ai)(Gr - Gi)
 // (Ar + Ai formed in registers), so Yr = P1 + P2 and Yi = P3 - P1 + P2; with
 // the Hessian term Z = W |G|^2 (HESS) that is four MFMAs per block and step,
-// each on a different accumulator.
-template <int NB, bool HESS>
+// each on a different accumulator.  Without GRAD, Z alone.
+template <int NB, bool GRAD, bool HESS>
 __device__ __forceinline__ void adj_mma_steps(const f4 (&va)[2][2], const f4 (&vi)[2][2], const f4 (&vw)[2][2],
                                               const float *sBr, const float *sBi, int kk, const int (&coff)[2],
                                               f4 (&p1)[2][2], f4 (&p2)[2][2], f4 (&p3)[2][2], f4 (&z)[2][2],
@@ -458,13 +458,15 @@ __device__ __forceinline__ void adj_mma_steps(const f4 (&va)[2][2], const f4 (&v
 #pragma unroll
         for (int q = 0; q < NB; ++q) {
             const int b = b0 + q;
-            const float a_r = va[b][s8 >> 2][s8 & 3], a_i = vi[b][s8 >> 2][s8 & 3];
+            const float a_r = GRAD ? va[b][s8 >> 2][s8 & 3] : 0.0f, a_i = GRAD ? vi[b][s8 >> 2][s8 & 3] : 0.0f;
             const float a_s = a_r + a_i;
 #pragma unroll
             for (int cb = 0; cb < 2; ++cb) {
-                p1[b][cb] = MM<float>::mma(a_r, br[q4][cb], p1[b][cb]);
-                p2[b][cb] = MM<float>::mma(a_i, bi[q4][cb], p2[b][cb]);
-                p3[b][cb] = MM<float>::mma(a_s, bd[cb], p3[b][cb]);
+                if (GRAD) {
+                    p1[b][cb] = MM<float>::mma(a_r, br[q4][cb], p1[b][cb]);
+                    p2[b][cb] = MM<float>::mma(a_i, bi[q4][cb], p2[b][cb]);
+                    p3[b][cb] = MM<float>::mma(a_s, bd[cb], p3[b][cb]);
+                }
                 if (HESS) z[b][cb] = MM<float>::mma(vw[b][s8 >> 2][s8 & 3], b2[cb], z[b][cb]);
             }
         }
@@ -541,7 +543,8 @@ struct AdjGroupArg {
 // group of problems (AdjGroup: flat grid over every problem's work items).
 // Pixel tile `tile` of frequency k: the partial of emitter-pass group qg of
 // npg, its passes [pass0, pass1) of 64 emitters.
-template <bool HESS>
+// (GRAD without HESS, both, or HESS alone, whose partials go to pg)
+template <bool GRAD, bool HESS>
 __device__ __forceinline__ void adj_f32_tile(const AdjItem &it, int64_t tile, int k, int npg, int qg, int pass0,
                                              int pass1) {
     const AdjParams &P = it.P;
@@ -599,10 +602,12 @@ __device__ __forceinline__ void adj_f32_tile(const AdjItem &it, int64_t tile, in
                     // rows beyond mp (when mp is not a multiple of 64) read row
                     // mp - 1: finite values whose products the epilogue drops
                     const int64_t off = (int64_t)min(ec + 32 * we + 16 * b + row, P.mp - 1) * P.mp + rc + 8 * kk;
-                    va[b][0] = *reinterpret_cast<const f4 *>(ar + off);
-                    va[b][1] = *reinterpret_cast<const f4 *>(ar + off + 4);
-                    vi[b][0] = *reinterpret_cast<const f4 *>(ai + off);
-                    vi[b][1] = *reinterpret_cast<const f4 *>(ai + off + 4);
+                    if (GRAD) {
+                        va[b][0] = *reinterpret_cast<const f4 *>(ar + off);
+                        va[b][1] = *reinterpret_cast<const f4 *>(ar + off + 4);
+                        vi[b][0] = *reinterpret_cast<const f4 *>(ai + off);
+                        vi[b][1] = *reinterpret_cast<const f4 *>(ai + off + 4);
+                    }
                     if (HESS) {
                         vw[b][0] = *reinterpret_cast<const f4 *>(wt + off);
                         vw[b][1] = *reinterpret_cast<const f4 *>(wt + off + 4);
@@ -635,7 +640,7 @@ __device__ __forceinline__ void adj_f32_tile(const AdjItem &it, int64_t tile, in
                     on_n = mine.has(bit);
                     if (on_n) load_a(c * kAdjKC, na, ni, nw);
                 }
-                if (on) adj_mma_steps<2, HESS>(va, vi, vw, sB[buf], sB[buf] + kAdjTile, kk, coff, p1, p2, p3, z, 0);
+                if (on) adj_mma_steps<2, GRAD, HESS>(va, vi, vw, sB[buf], sB[buf] + kAdjTile, kk, coff, p1, p2, p3, z, 0);
                 __builtin_amdgcn_s_waitcnt(0);   // the next chunk has landed in LDS
                 __syncthreads();
                 on = on_n;
@@ -673,9 +678,11 @@ __device__ __forceinline__ void adj_f32_tile(const AdjItem &it, int64_t tile, in
 #pragma unroll
                         for (int cb = 0; cb < 2; ++cb) {
                             const float ge_r = ger[i][cb], ge_i = gei[i][cb];
-                            const float yr = p1[b][cb][i] + p2[b][cb][i];
-                            const float yi = (p3[b][cb][i] - p1[b][cb][i]) + p2[b][cb][i];
-                            gp[cb] += ge_r * yr + ge_i * yi;
+                            if (GRAD) {
+                                const float yr = p1[b][cb][i] + p2[b][cb][i];
+                                const float yi = (p3[b][cb][i] - p1[b][cb][i]) + p2[b][cb][i];
+                                gp[cb] += ge_r * yr + ge_i * yi;
+                            }
                             if (HESS) hp[cb] += (ge_r * ge_r + ge_i * ge_i) * z[b][cb][i];
                         }
                     }
@@ -705,21 +712,22 @@ __device__ __forceinline__ void adj_f32_tile(const AdjItem &it, int64_t tile, in
     if (tid < kAdjNT) {
         const int64_t x = x0 + tid;
         if (x < N) {
-            pg[((int64_t)k * npg + qg) * N + x] = sred[0][0][tid] + sred[1][0][tid];
-            if (HESS) ph[((int64_t)k * npg + qg) * N + x] = sred[0][1][tid] + sred[1][1][tid];
+            const double h = sred[0][1][tid] + sred[1][1][tid];
+            pg[((int64_t)k * npg + qg) * N + x] = GRAD ? sred[0][0][tid] + sred[1][0][tid] : h;
+            if (GRAD && HESS) ph[((int64_t)k * npg + qg) * N + x] = h;
         }
     }
 }
 
-template <bool HESS, typename A>
-__global__ void __launch_bounds__(256, HESS ? 2 : 3) k_adjoint_f32(const A args) {
+template <bool HESS, typename A, bool GRAD = true>
+__global__ void __launch_bounds__(256, GRAD ? (HESS ? 2 : 3) : 4) k_adjoint_f32(const A args) {
     typename A::Loc loc;
     const AdjItem &it = args.locate(loc);
     // one frequency per workgroup (finer work units), and this workgroup's
     // emitter passes (64 emitters each): group qg of npg
     const int npg = A::kSplit ? it.npg : 1, qg = A::kSplit ? loc.group() : 0;
     const int npass = (it.P.mp + 63) / 64;
-    adj_f32_tile<HESS>(it, loc.tile(), loc.k(), npg, qg, qg * npass / npg, (qg + 1) * npass / npg);
+    adj_f32_tile<GRAD, HESS>(it, loc.tile(), loc.k(), npg, qg, qg * npass / npg, (qg + 1) * npass / npg);
 }
 
 // The work items that k_adjoint_split listed, again from the FP32 tables and
@@ -733,7 +741,7 @@ __global__ void __launch_bounds__(256, 3) k_adjoint_f32_list(const AdjItem it) {
         const int k = id / per, rem = id - k * per, q = rem % it.npg;
         const int64_t tile = 2 * (int64_t)(rem / it.npg) + (i & 1);
         if (tile * kAdjNT < it.P.N)
-            adj_f32_tile<false>(it, tile, k, it.npg, q, 2 * (q * np16 / it.npg), min(2 * ((q + 1) * np16 / it.npg), np));
+            adj_f32_tile<true, false>(it, tile, k, it.npg, q, 2 * (q * np16 / it.npg), min(2 * ((q + 1) * np16 / it.npg), np));
         __syncthreads();   // the next item reuses the LDS
     }
 }
@@ -1590,8 +1598,8 @@ static int adj_groups(const rb_geometry *g, rb_dtype dt) {
 // 291 / 200, 96 / 128^2 (256 workgroups) 39 / 43, 96 / 256^2 103 / 75, 128 /
 // 256^2 130 / 86, 256 / 181^2 209 / 122, 512 / 480^2 2947 / 1314; one
 // frequency, 256 / 128x150 (300 workgroups) 70 / 61.
-static bool adj_split(const rb_geometry *g, int nf, rb_dtype dt, bool hess) {
-    if (dt != RB_F32 || hess || g->m <= 64) return false;
+static bool adj_split(const rb_geometry *g, int nf, rb_dtype dt) {
+    if (dt != RB_F32 || g->m <= 64) return false;
     const int npass = (pad_m(g->m) + kT16NE - 1) / kT16NE;
     const int64_t tiles = blocks_for((int64_t)g->nx * g->ny, kT16NT);
     if (nf * tiles * (adj_groups(g, dt) > 1 ? npass : 1) <= 256) return false;
@@ -1640,10 +1648,43 @@ rb_status adjoint_prepare(const rb_geometry *g, const void *G_re, const void *G_
     AdjParams P = adj_params(g, freqs, nf);
     const dim3 gp(P.nb * P.nb, nf);
     AdjItem &it = task->item;
+    it.P = P;
+    it.Gr = G_re;
+    it.Gi = G_im;
+    it.Ar = w.Ar;
+    it.Ai = w.Ai;
+    it.Wt = w.Wt;
+    it.flags = w.flags;
+    it.gscale = gscale;
+    it.ascale = w.ascale;
+    it.pg = w.pg;
+    it.ph = w.ph;
+    it.begin = 0;
     it.split_hi = it.split_lo = nullptr;
     it.pscale = nullptr;
     it.redo = nullptr;
-    task->split = adj_split(g, nf, dt, hdiag != nullptr);
+    if (hdiag && adj_split(g, nf, dt)) {
+        // The Hessian diagonal by itself, its one product on the FP32 cores,
+        // before the gradient's pieces take the place of W (gradient and
+        // diagonal as four products there, and so: 1024 elements / 1100^2, four
+        // frequencies, 159 -> 94 ms, 256 / 480^2, three, 2.21 -> 1.50, 96 / 256^2,
+        // two, 129 -> 122 us)
+        k_adj_prep<float, false, 1><<<gp, 256, 0, st>>>(g->m, P.mp, d_res, w_data, nullptr, (float *)w.Ar,
+                                                        (float *)w.Ai, (float *)w.Wt, w.flags);
+        RB_LAUNCHED();
+        it.npg = adj_groups(g, dt);
+        it.ntiles = (int)blocks_for(P.N, kAdjNT);
+        if (it.npg == 1)
+            k_adjoint_f32<true, AdjOne, false><<<dim3(it.ntiles, nf), 256, 0, st>>>(AdjOne{it});
+        else
+            k_adjoint_f32<true, AdjOneSplit, false><<<dim3((unsigned)it.ntiles * it.npg, nf), 256, 0, st>>>(
+                AdjOneSplit{it});
+        RB_LAUNCHED();
+        k_adj_sum<<<blocks_for(P.N, 256), 256, 0, st>>>(P.N, nf, it.npg, it.pg, nullptr, hdiag, nullptr);
+        RB_LAUNCHED();
+        hdiag = nullptr;
+    }
+    task->split = !hdiag && adj_split(g, nf, dt);
     // (32 N elements within 32-bit offsets)
     task->direct = (dt == RB_BF16 || dt == RB_F16) && P.N % 8 == 0 && P.m % kT16KC == 0 && P.N < ((int64_t)1 << 26);
     if (task->split) {
@@ -1685,19 +1726,7 @@ rb_status adjoint_prepare(const rb_geometry *g, const void *G_re, const void *G_
             break;
     }
     RB_LAUNCHED();
-    it.P = P;
-    it.Gr = G_re;
-    it.Gi = G_im;
-    it.Ar = w.Ar;
-    it.Ai = w.Ai;
-    it.Wt = w.Wt;
-    it.flags = w.flags;
-    it.gscale = gscale;
-    it.ascale = w.ascale;
-    it.pg = w.pg;
-    it.ph = w.ph;
     it.ntiles = (int)blocks_for(P.N, dt == RB_F32 && !task->split ? kAdjNT : kT16NT);
-    it.begin = 0;
     // (fewer than four passes of k_adjoint_f32: one group, as carved)
     it.npg = task->split && adj_groups(g, dt) > 1 ? (P.mp + kT16NE - 1) / kT16NE : adj_groups(g, dt);
     task->dt = dt;

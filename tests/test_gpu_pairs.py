@@ -380,3 +380,27 @@ def test_banded_hessian_blocks(rb, dtype, m, dmin, nz):
         want += born.hessian_diag(G, sel - z, f, geom.h ** 2)
         mag += born.hessian_diag(G, 2.0 + z, f, geom.h ** 2)
     assert (np.abs(hd.cpu().numpy() - want) <= (200 * 2.0 ** (-53 if dtype == "f64" else -24)) * mag).all()
+
+
+# FP32 gradient and Hessian diagonal where the gradient takes the FP16 cores:
+# the diagonal is a contraction of its own, with tiles of 64 pixels (the last of
+# 1 to 64), one and several emitter passes per workgroup.
+@pytest.mark.parametrize("shape", [(183, 180, 65), (129, 257, 192), (160, 128, 300)])
+def test_fp32_hessian_beside_split_gradient(rb, shape):
+    nx, ny, m = shape
+    geom, freqs = _geom(nx, ny, m), [3e5, 7e5]
+    N = geom.n_pixels
+    print(f"[gpu-test] FP32 Hessian beside split gradient {shape}", flush=True)
+    gr, gi = _random_g(2, m, N, 21)
+    D = W.random_residual(2, m, 22)
+    w = np.random.default_rng(23).uniform(0.0, 2.0, (2, m, m))
+    w[:, :32, 32:64] = 0.0
+    grad, hd = (torch.ones(N, dtype=torch.float64, device=DEV) for _ in range(2))   # both are added to
+    rb.born_adjoint_weighted(geom, torch.as_tensor(gr, device=DEV), torch.as_tensor(gi, device=DEV), None, "f32", freqs,
+                             torch.as_tensor(np.stack([D.real, D.imag], -1), device=DEV),
+                             torch.as_tensor(w, device=DEV), grad, hd)
+    G = [gr[k] + 1j * gi[k].astype(np.float64) for k in range(2)]
+    g_o = sum(born.born_adjoint(G[k], w[k] * D[k], f, geom.h ** 2) for k, f in enumerate(freqs))
+    h_o = sum(born.hessian_diag(G[k], w[k], f, geom.h ** 2) for k, f in enumerate(freqs))
+    close(grad.cpu().numpy() - 1.0, g_o, TOL["f32"], f"grad {shape}")
+    close(hd.cpu().numpy() - 1.0, h_o, TOL["f32"], f"hdiag {shape}")
