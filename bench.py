@@ -53,8 +53,8 @@ PEAK_CONTRACTION = {**PEAK, "f32": PEAK["f16"] / 3}
 # --pmc passes (FETCH_SIZE, WRITE_SIZE) scaled by the same counters on a copy
 # of known size.
 TRAFFIC_SUMMARIES = {
-    "ring1024_grid1100": os.path.join(ROOT, "profiles", "hbm_traffic_k_adjoint_f32_ring1024_grid1100.md"),
-    "ring256_grid480": os.path.join(ROOT, "profiles", "hbm_traffic_k_adjoint_f32_ring256_grid480.md"),
+    "ring1024_grid1100": os.path.join(ROOT, "profiles", "hbm_traffic_k_adjoint_split_ring1024_grid1100.md"),
+    "ring256_grid480": os.path.join(ROOT, "profiles", "hbm_traffic_k_adjoint_split_ring256_grid480.md"),
 }
 ADJOINT_SOURCES = ["adjoint.hip", "mma.h", "born.h", "common.h"]
 COPY_BYTES = 256 << 20   # calibration copy: reads and writes this many bytes once
