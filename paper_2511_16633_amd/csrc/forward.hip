@@ -213,14 +213,14 @@ __global__ void __launch_bounds__(32 * kRedG) k_forward_reduce(FwdParams P, cons
     const T2 *pp = reinterpret_cast<const T2 *>(part) + (int64_t)k * P.mp * P.mp + (int64_t)e * P.mp + r;
     double sr = 0.0, si = 0.0;
     // k_forward_split's partials carry the scales of their two rows, unless
-    // the split's tile is flagged
+    // the block of either is flagged
     double inv = 1.0, dsc = 1.0;
-    const uint8_t *fl = nullptr;
+    const uint8_t *fe = nullptr, *fr = nullptr;
     if (so.flags && use) {
         inv = 1.0 / ((double)so.scale[k * P.m + e] * (double)so.scale[k * P.m + r]);
         dsc = 1.0 / (double)so.dscale[0];
-        const int te = e / so.tile, tr = r / so.tile;
-        fl = so.flags + (int64_t)k * P.nsplit * P.ntri + te * P.ntl - te * (te - 1) / 2 + (tr - te);
+        fe = so.flags + (int64_t)k * P.nsplit * P.ntl + e / so.tile;
+        fr = so.flags + (int64_t)k * P.nsplit * P.ntl + r / so.tile;
     }
     constexpr int kU = 8;
     const int s1 = (int)((int64_t)P.nsplit * (g + 1) / kRedG);
@@ -230,7 +230,8 @@ __global__ void __launch_bounds__(32 * kRedG) k_forward_reduce(FwdParams P, cons
         for (int u = 0; u < kU; ++u) v[u] = use && s0 + u < s1 ? pp[(s0 + u) * stride] : T2{0, 0};
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
-            const double f = fl && s0 + u < s1 && fl[(int64_t)(s0 + u) * P.ntri] ? 1.0 : inv;
+            const bool raw = fe && s0 + u < s1 && (fe[(s0 + u) * P.ntl] | fr[(s0 + u) * P.ntl]);
+            const double f = raw ? 1.0 : inv;
             sr += (double)v[u][0] * f;
             si += (double)v[u][1] * f;
         }
@@ -618,10 +619,23 @@ __device__ __forceinline__ int f16_off(int row, int ch) { return row * 64 + 16 *
 
 // ------------------------------------------------------------------ FP32 tables on the FP16 matrix cores
 // Forward with FP32 tables, both operands split into two FP16 pieces (x s =
-// hi + lo, s a power of two) and hi hi + hi lo + lo hi accumulated in FP32 on
-// the 16x16x32 FP16 cores, as the backprojection's k_adjoint_split.  Scales:
-// row r of G at frequency k by its largest magnitude over kFsSamples sampled
-// pixels (2^8 there, 2^8 of headroom), delta by its largest magnitude.
+// hi + 2^-11 lo, s a power of two) and hi hi + 2^-11 (hi lo + lo hi) accumulated
+// in FP32 on the 16x16x32 FP16 cores.
+//
+// FP16 holds x s to FP32's accuracy only between kFsMin (below, the low piece
+// runs out of bits) and kFsMax.  What has to lie there is what the sums
+// contain: delta (brought below 1 by its largest magnitude) is dealt to both
+// sides, u = 2^round(log2 |delta| / 2) to G_e and delta / u to G_r, so that where
+// delta is zero G does not count at all, and where it is small each operand
+// shrinks only by its square root.  Row r of G at frequency k is scaled by its
+// largest |G| sqrt(|delta|) over kFsSamples sampled pixels (2^8 there, 2^8 of
+// headroom above and 2^21 below).  One workgroup per block of 128 rows, split and
+// frequency looks whether every value of the block but zero lies in the range
+// (testing all that is staged cost 73 of 849 us at 256 elements / 480^2); if not,
+// the block is put on a list and flagged, and k_forward_f32_list computes its
+// tiles from FP32 (unscaled partials, which the reduction tells by the flag).  A
+// split with a delta below kFsDelta, which brings most values of G below the
+// range, goes to the list at once.
 //
 // A 128 x 128 (e, r) tile per workgroup of eight waves, 4 x 2 of 32 x 64, 32
 // pixels per k-step.  A step's 256 rows of G (128 bytes each and array) pass
@@ -633,22 +647,19 @@ __device__ __forceinline__ int f16_off(int row, int ch) { return row * 64 + 16 *
 // and waves 4 to 7, which share their SIMDs, multiply first, so that the matrix
 // cores work while vector instructions convert.
 //
-// 1024 elements / 1100^2, four frequencies: 130.8 ms on the FP32 cores, 68.7
-// here (62.4 with the hi lo products in the main sums; 12 MFMAs per complex
-// product of blocks: 1.0 PFLOP/s, as the backprojection, whose clock power
-// holds at 1.9 GHz); 256 / 480^2, three frequencies: 1.36 -> 0.76 ms; 1024 /
-// 255x301 (rows not 16-byte aligned): 11.8 -> 2.5 ms.  Relative L2 error
-// against FP64, rounded to FP32: 256 / 480^2 5.7e-7 -> 2.6e-7 (5.8e-7 with the
-// hi lo products in the main sums), 97 / 301x255 1.6e-7 -> 6e-8.  Four waves of
-// 64 x 64 with 512 registers each spilled: the compiler moved accumulators
-// between register files at every step.
-//
-// A workgroup that meets a value beyond FP16's range puts its (tile, split,
-// frequency) on a list and flags it; k_forward_f32_list computes those from
-// FP32 (unscaled partials, which the reduction tells by the flag).
+// 1024 elements / 1100^2, four frequencies: 139.2 ms on the FP32 cores, 72.5
+// here (12 MFMAs per complex product of blocks: 1.0 PFLOP/s, as the
+// backprojection, whose clock power holds at 1.9 GHz); 256 / 480^2, three
+// frequencies: 1.43 -> 0.80 ms; 1024 / 255x301 (rows not 16-byte aligned), two:
+// 11.7 -> 2.5 ms.  Relative L2 error against FP64: 256 / 480^2 5.6e-7 -> 1.2e-7, 97 /
+// 301x255 1.5e-7 -> 6e-8.  Four waves of 64 x 64 with 512 registers each spilled:
+// the compiler moved accumulators between register files at every step.
 constexpr int kFsT = 128, kFsKC = 32, kFsArr = kFsT * kFsKC * 2, kFsSamples = 256;
 constexpr int kFsTop = 8;
-constexpr float kFsMax = 65504.0f;   // largest FP16 value
+constexpr float kFsMax = 65504.0f;      // largest FP16 value
+constexpr float kFsMin = 0x1p-13f;      // steps of 2^-24 2^-11 are 2^-22 of it
+constexpr float kFsDelta = 0x1p-42f;    // u = 2^-21
+constexpr float kFsLo = 0x1p11f;        // scale of the low pieces
 typedef _Float16 h4 __attribute__((ext_vector_type(4)));
 typedef float f2 __attribute__((ext_vector_type(2)));
 
@@ -660,40 +671,50 @@ __device__ __forceinline__ float fs_scale(float top, int e) {
     return ldexpf(1.0f, min(max(e - x, -100), 100));
 }
 
-// Blocks 0 .. rows - 1: scale[row] of the rows (k m + r); 2^100 for a row that
-// is zero at every sampled pixel, so that any normal value overflows.  The
-// other blocks: partial maxima of |delta| (kReduceBlocks of them).
+// Blocks 0 .. rows - 1: scale[row] of the rows (k m + r) = the largest |G|
+// sqrt(|delta|) over the sampled pixels, or, if that is zero, minus the largest
+// |G|.  The other blocks: partial maxima of |delta| (kReduceBlocks of them).
 __global__ void __launch_bounds__(256) k_fs_scales(int64_t N, int rows, const float *__restrict__ Gr,
                                                    const float *__restrict__ Gi, const double *__restrict__ delta,
                                                    float *__restrict__ scale, float *__restrict__ dpart) {
-    __shared__ float sm[4];
-    float v = 0.0f;
+    __shared__ float sm[4], sg[4];
+    float v = 0.0f, g = 0.0f;
     if ((int)blockIdx.x < rows) {
-        const int64_t o = (int64_t)blockIdx.x * N + (int64_t)threadIdx.x * N / kFsSamples;
-        v = fmaxf(fabsf(Gr[o]), fabsf(Gi[o]));
+        const int64_t x = (int64_t)threadIdx.x * N / kFsSamples, o = (int64_t)blockIdx.x * N + x;
+        g = fmaxf(fabsf(Gr[o]), fabsf(Gi[o]));
+        v = g * sqrtf(fabsf((float)delta[x]));
     } else {
         for (int64_t i = (int64_t)(blockIdx.x - rows) * 256 + threadIdx.x; i < N; i += kReduceBlocks * 256)
             v = fmaxf(v, fabsf((float)delta[i]));
     }
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
-    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = v;
+    for (int o = 32; o > 0; o >>= 1) {
+        v = fmaxf(v, __shfl_xor(v, o));
+        g = fmaxf(g, __shfl_xor(g, o));
+    }
+    if ((threadIdx.x & 63) == 0) {
+        sm[threadIdx.x >> 6] = v;
+        sg[threadIdx.x >> 6] = g;
+    }
     __syncthreads();
     if (threadIdx.x == 0) {
         v = fmaxf(fmaxf(sm[0], sm[1]), fmaxf(sm[2], sm[3]));
+        g = fmaxf(fmaxf(sg[0], sg[1]), fmaxf(sg[2], sg[3]));
         if ((int)blockIdx.x < rows)
-            scale[blockIdx.x] = v > 0.0f ? fs_scale(v, kFsTop) : 0x1p100f;
+            scale[blockIdx.x] = v > 0.0f ? v : -g;
         else
             dpart[blockIdx.x - rows] = v;
     }
 }
 
 // df[x] = (float)delta[x] sd (zero from N to n), sd = fs_scale(max |delta|, 0)
-// to dscale[0]; clears the list and the flags.
+// to dscale[0]; the rows' scales from their samples (2^100 for a row that is
+// zero at every sampled pixel); clears the list and the flags.
 __global__ void __launch_bounds__(256) k_fs_delta(int64_t N, int64_t n, const double *__restrict__ delta,
                                                   const float *__restrict__ dpart, float *__restrict__ df,
-                                                  float *__restrict__ dscale, int *__restrict__ redo,
-                                                  uint8_t *__restrict__ flags, int64_t nflags) {
+                                                  float *__restrict__ dscale, int rows, float *__restrict__ scale,
+                                                  int *__restrict__ redo, uint8_t *__restrict__ flags,
+                                                  int64_t nflags) {
     __shared__ float sm[4];
     float v = 0.0f;
 #pragma unroll
@@ -709,6 +730,10 @@ __global__ void __launch_bounds__(256) k_fs_delta(int64_t N, int64_t n, const do
         redo[0] = 0;
     }
     if (x < n) df[x] = x < N ? (float)delta[x] * sd : 0.0f;
+    for (int64_t q = x; q < rows; q += (int64_t)gridDim.x * 256) {
+        const float t = scale[q];
+        scale[q] = t > 0.0f ? fs_scale(t * sqrtf(sd), kFsTop) : (t < 0.0f ? fs_scale(-t, kFsTop) : 0x1p100f);
+    }
     for (int64_t q = x; q < nflags; q += (int64_t)gridDim.x * 256) flags[q] = 0;
 }
 
@@ -756,7 +781,23 @@ __global__ void __launch_bounds__(512, 2) k_forward_split(FwdParams P, const flo
     }
     const int64_t im = Gi - Gr;
     f4 v[4][2], dl;
-    float top = 0.0f;
+    // Which workgroup looks at block b: its tile with the first of the blocks b,
+    // b + 1, .. (around the ring) that is not skipped above.
+    auto owner = [&](int b, int other) {
+        for (int d = 0; d < P.ntl; ++d) {
+            const int x = b + d < P.ntl ? b + d : b + d - P.ntl;
+            if (x == other) return true;
+            if (P.dmin < 32 || max_circ_dist(P.m, std::min(b, x) * kFsT, kFsT, std::max(b, x) * kFsT, kFsT) >= P.dmin)
+                return false;
+        }
+        return false;
+    };
+    const bool own_e = owner(te, tr), own_r = te != tr && owner(tr, te);
+    // of the values looked at (largest of re and im): the largest, and the bits
+    // of the smallest but zero, minus one.  The other side's are less than twice
+    // as large or half as small.
+    float top[2] = {0.0f, 0.0f};
+    unsigned low[2] = {0xffffffffu, 0xffffffffu};
     typedef f4 f4_a4 __attribute__((aligned(4)));   // rows need no alignment
     auto load = [&](int c) {
         const int64_t xc = ks + (int64_t)c * kFsKC + p4;
@@ -779,22 +820,37 @@ __global__ void __launch_bounds__(512, 2) k_forward_split(FwdParams P, const flo
         dl = *reinterpret_cast<const f4 *>(df + xc);
     };
     auto store = [&](unsigned char *buf) {
+        f4 du, dq;   // u and delta / u
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const unsigned ub = (((__float_as_uint(dl[q]) & 0x7f800000u) + 0x40000000u) >> 1) & 0x7f800000u;
+            du[q] = dl[q] != 0.0f ? __uint_as_float(ub) : 0.0f;
+            dq[q] = dl[q] * __uint_as_float(0x7f000000u - ub);
+        }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const f4 s = j < 2 ? f4{sc[j], sc[j], sc[j], sc[j]} : dl * sc[j];
+            const f4 s = (j < 2 ? du : dq) * sc[j];
+            f4 w[2];
 #pragma unroll
             for (int a = 0; a < 2; ++a) {
-                const f4 w = v[j][a] * s;
-                const h4 h = __builtin_convertvector(w, h4);
+                w[a] = v[j][a] * s;
+                const h4 h = __builtin_convertvector(w[a], h4);
                 f4 rem;
 #pragma unroll
-                for (int q = 0; q < 4; ++q) rem[q] = w[q] - (float)h[q];
+                for (int q = 0; q < 4; ++q) rem[q] = (w[a][q] - (float)h[q]) * kFsLo;
                 const h4 l = __builtin_convertvector(rem, h4);
-                top = fmaxf(top, fmaxf(fmaxf(fabsf(w[0]), fabsf(w[1])), fmaxf(fabsf(w[2]), fabsf(w[3]))));
                 unsigned char *d =
                     buf + ((j < 2 ? 0 : 4) + a) * kFsArr + f16_off(r8 + 64 * (j & 1), p4 >> 3) + 2 * (p4 & 4);
                 *reinterpret_cast<h4 *>(d) = h;
                 *reinterpret_cast<h4 *>(d + 2 * kFsArr) = l;
+            }
+            if (j < 2 ? own_e : own_r) {   // workgroup-uniform
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float m = fmaxf(fabsf(w[0][q]), fabsf(w[1][q]));
+                    top[j >> 1] = fmaxf(top[j >> 1], m);
+                    low[j >> 1] = min(low[j >> 1], __float_as_uint(m) - 1u);
+                }
             }
         }
     };
@@ -819,9 +875,9 @@ __global__ void __launch_bounds__(512, 2) k_forward_split(FwdParams P, const flo
 #pragma unroll
             for (int t = 0; t < 4; ++t) u[t] = frag(sb + t * kFsArr, 64 * wr + 16 * cb + row);
             // (ar + i ai)(br + i bi) = ar br - ai bi + i (ar bi + ai br)
-            // The hi lo products are summed apart and added once per step: in
-            // the long sums over pixels it is the number of roundings at the
-            // sum's own size that sets the error (three a step, not six).
+            // A step's products are summed by themselves, the hi lo ones first,
+            // and added once: in the long sums over pixels it is the number of
+            // roundings at the sum's own size that sets the error.
             f4 tr_[2], ti_[2];
 #pragma unroll
             for (int b = 0; b < 2; ++b) tr_[b] = ti_[b] = f4{0, 0, 0, 0};
@@ -838,14 +894,11 @@ __global__ void __launch_bounds__(512, 2) k_forward_split(FwdParams P, const flo
             term(n[1], u[1], a[3], u[0]);
 #pragma unroll
             for (int b = 0; b < 2; ++b) {
-                re[b][cb] = M::mma(a[0][b], u[0], re[b][cb]);
-                imv[b][cb] = M::mma(a[0][b], u[1], imv[b][cb]);
+                tr_[b] *= 1.0f / kFsLo;
+                ti_[b] *= 1.0f / kFsLo;
             }
-#pragma unroll
-            for (int b = 0; b < 2; ++b) {
-                re[b][cb] = M::mma(n[0][b], u[1], re[b][cb]);
-                imv[b][cb] = M::mma(a[1][b], u[0], imv[b][cb]);
-            }
+            term(a[0], u[0], a[0], u[1]);
+            term(n[0], u[1], a[1], u[0]);
 #pragma unroll
             for (int b = 0; b < 2; ++b) {
                 re[b][cb] += tr_[b];
@@ -853,6 +906,24 @@ __global__ void __launch_bounds__(512, 2) k_forward_split(FwdParams P, const flo
             }
         }
     };
+    // the deltas of the split
+    bool tiny = false;
+    for (int64_t x = ks + tid; x < ke; x += 512) {
+        const float d = fabsf(df[x]);
+        tiny |= d > 0.0f && d < kFsDelta;
+    }
+    auto list = [&](int b) {
+        const int id = (k * P.nsplit + split) * P.ntl + b;
+        flags[id] = 1;
+        redo[1 + atomicAdd(redo, 1)] = id;
+    };
+    if (__syncthreads_or(tiny)) {
+        if (tid == 0) {
+            if (own_e) list(te);
+            if (own_r) list(tr);
+        }
+        return;
+    }
     load(0);
     store(sT[0]);
     load(std::min(1, last));
@@ -883,11 +954,12 @@ __global__ void __launch_bounds__(512, 2) k_forward_split(FwdParams P, const flo
         kloop(std::false_type(), C0());
     else
         kloop(std::false_type(), C2());
-    const int beyond = __syncthreads_or(!(top < kFsMax));
-    if (beyond && tid == 0) {
-        const int64_t id = ((int64_t)k * P.nsplit + split) * P.ntri + te * P.ntl - te * (te - 1) / 2 + (tr - te);
-        flags[id] = 1;
-        redo[1 + atomicAdd(redo, 1)] = (int)id;
+#pragma unroll
+    for (int sd = 0; sd < 2; ++sd) {
+        if (!(sd ? own_r : own_e)) continue;
+        const int beyond =
+            __syncthreads_or(!(top[sd] < 0.5f * kFsMax) || low[sd] < __float_as_uint(2.0f * kFsMin) - 1u);
+        if (beyond && tid == 0) list(sd ? tr : te);
     }
     if (idle) return;
     float *pp = part + ((int64_t)split * P.nf + k) * P.mp * P.mp * 2;
@@ -905,23 +977,25 @@ __global__ void __launch_bounds__(512, 2) k_forward_split(FwdParams P, const flo
     }
 }
 
-// The listed (tile, split, frequency)s of k_forward_split from FP32: each is
-// three or four 64 x 64 tiles.  Partials in units of (float)delta sd, G
-// unscaled.  VEC: rows of whole 16-byte pieces (N a multiple of 4).
+// The listed (block of rows, split, frequency)s of k_forward_split from FP32: each
+// is ntl tiles, each of three or four 64 x 64 tiles.  Partials in units of
+// (float)delta sd, G unscaled.  VEC: rows of whole 16-byte pieces (N a multiple
+// of 4).
 template <bool VEC>
 __global__ void __launch_bounds__(256, 2) k_forward_f32_list(FwdParams P, const float *__restrict__ Gr,
                                                              const float *__restrict__ Gi,
                                                              const float *__restrict__ df,
-                                                             float *__restrict__ part, const int *__restrict__ redo) {
-    const int n = 4 * redo[0];
-    for (int i = blockIdx.x; i < n; i += gridDim.x) {
-        const int id = redo[1 + (i >> 2)];
-        const int rest = id / P.ntri;
-        int te, tr;
-        tri_tile(id - rest * P.ntri, P.ntl, te, tr);
+                                                             float *__restrict__ part, const int *__restrict__ redo,
+                                                             const uint8_t *__restrict__ flags) {
+    const int64_t per = 4 * P.ntl, n = per * redo[0];
+    for (int64_t i = blockIdx.x; i < n; i += gridDim.x) {
+        const int id = redo[1 + i / per], q = (int)(i % per);
+        const int rest = id / P.ntl, b = id - rest * P.ntl, x = q >> 2;
+        // (a tile of two listed blocks is the lower one's)
+        if (x < b && flags[rest * P.ntl + x]) continue;   // workgroup-uniform
         const int split = rest % P.nsplit, k = rest / P.nsplit;
-        const int e64 = 2 * te + ((i >> 1) & 1), r64 = 2 * tr + (i & 1);
-        if (e64 <= r64) {   // workgroup-uniform
+        const int e64 = 2 * std::min(b, x) + ((q >> 1) & 1), r64 = 2 * std::max(b, x) + (q & 1);
+        if (e64 <= r64) {
             if (VEC)
                 fwd_f32_tile(P, Gr, Gi, df, part, e64, r64, split, k);
             else
@@ -1631,7 +1705,7 @@ static FwdWs carve_fwd(Carver &c, const FwdParams &P, rb_dtype dt, bool fs) {
     w.part = c.take<char>((size_t)P.nsplit * P.nf * P.mp * P.mp * 2 * es);
     w.df = (fs || dt == RB_BF16 || dt == RB_F16 || (dt == RB_F32 && P.N % 4 == 0)) ? c.take<float>((size_t)P.N + 32)
                                                                                      : nullptr;
-    w.nflags = fs ? (int64_t)P.nf * P.nsplit * P.ntri : 0;
+    w.nflags = fs ? (int64_t)P.nf * P.nsplit * P.ntl : 0;
     if (fs) {
         w.fscale = c.take<float>((size_t)P.nf * P.m);
         w.fpart = c.take<float>(kReduceBlocks);
@@ -1682,15 +1756,15 @@ rb_status forward_impl(const rb_geometry *g, const void *G_re, const void *G_im,
                                                                       w.fpart);
                 RB_LAUNCHED();
                 k_fs_delta<<<blocks_for(P.N + 32, 256), 256, 0, st>>>(P.N, P.N + 32, delta, w.fpart, w.df, w.fdscale,
-                                                                      w.redo, w.flags, w.nflags);
+                                                                      nf * P.m, w.fscale, w.redo, w.flags, w.nflags);
                 RB_LAUNCHED();
-                const unsigned nl = (unsigned)std::min<int64_t>(4 * w.nflags, 2 * device_cus());
+                const unsigned nl = (unsigned)std::min<int64_t>(4 * P.ntl * w.nflags, (P.N % 4 == 0 ? 4 : 2) * device_cus());
                 k_forward_split<<<nblk, 512, 0, st>>>(P, gr, gi, w.df, w.fscale, pt, w.redo, w.flags);
                 RB_LAUNCHED();
                 if (P.N % 4 == 0)
-                    k_forward_f32_list<true><<<nl, 256, 0, st>>>(P, gr, gi, w.df, pt, w.redo);
+                    k_forward_f32_list<true><<<nl, 256, 0, st>>>(P, gr, gi, w.df, pt, w.redo, w.flags);
                 else
-                    k_forward_f32_list<false><<<nl, 256, 0, st>>>(P, gr, gi, w.df, pt, w.redo);
+                    k_forward_f32_list<false><<<nl, 256, 0, st>>>(P, gr, gi, w.df, pt, w.redo, w.flags);
                 so = FwdSplitOut{w.flags, w.fscale, w.fdscale, kFsT};
             } else if (fwd32_direct(g, dt)) {
                 k_delta_cast<<<blocks_for(P.N + 16, 256), 256, 0, st>>>(P.N, P.N + 16, delta, w.df);

@@ -1,0 +1,120 @@
+"""FP32 contractions on operands of a wide range.  The contractions of larger
+rings run on the FP16 matrix cores in two pieces per operand; FP16 holds 40
+binary orders, FP32 more than 250, and a call must return what FP32 operands
+give whatever part of a table its sums use.  Errors are measured against each
+result's sum of magnitudes: sums of n random products rounded to FP32 are off
+by about 2^-24 (sqrt(n) additions and 2 roundings) of it at most.
+"""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+import workload as W
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def rb():
+    import paper_2511_16633_amd as m
+    return m
+
+
+def _geom(nx, ny, m):
+    g = W.centred_grid(nx, 0.5e-3, m, 12e-3, 1500.0)
+    return dataclasses.replace(g, ny=ny, y0=-0.5 * (ny - 1) * 0.5e-3)
+
+
+def _random_g(m, N, seed):
+    rng = np.random.default_rng(seed)
+    mag = np.exp(rng.uniform(np.log(1e-2), 0.0, (m, N)))
+    ph = rng.uniform(0.0, 2 * np.pi, (m, N))
+    return mag * np.cos(ph), mag * np.sin(ph)
+
+
+def _forward(rb, geom, gr, gi, f, delta):
+    d = torch.zeros((1, geom.m, geom.m, 2), dtype=torch.float64, device=DEV)
+    rb.born_forward(geom, torch.as_tensor(gr[None], dtype=torch.float32, device=DEV),
+                    torch.as_tensor(gi[None], dtype=torch.float32, device=DEV), None, "f32", [f],
+                    torch.as_tensor(delta, device=DEV), d)
+    return torch.view_as_complex(d).cpu().numpy()[0]
+
+
+def _check_forward(rb, geom, gr, gi, delta, rows=None):
+    f = 4e5
+    gr, gi = gr.astype(np.float32), gi.astype(np.float32)
+    g = gr + 1j * gi.astype(np.float64)
+    c = (2 * np.pi * f) ** 2 * geom.h ** 2
+    got = _forward(rb, geom, gr, gi, f, delta)
+    rows = np.arange(geom.m) if rows is None else rows
+    ref = c * (g[rows] * delta) @ g[rows].T
+    size = c * (np.abs(g[rows]) * np.abs(delta)) @ np.abs(g[rows]).T
+    err = np.abs(got[np.ix_(rows, rows)] - ref)
+    ok = size > 0
+    assert np.all(err[~ok] == 0.0)
+    worst = float(np.max(err[ok] / size[ok]))
+    print(f"[gpu-test] worst error {worst:.2e} of the sum of magnitudes", flush=True)
+    assert worst <= (np.sqrt(geom.n_pixels) + 2) * 2.0 ** -24
+    return got
+
+
+# Tables that are loud where delta is zero (near the elements, outside of the
+# support) and quiet where it counts, by 60 to 200 dB; two and three blocks of
+# 128 rows, rows of whole 16-byte pieces and not.
+@pytest.mark.parametrize("shape", [(96, 90, 130), (93, 97, 300)])
+@pytest.mark.parametrize("db", [60, 100, 140, 200])
+def test_forward_loud_where_delta_is_zero(rb, shape, db):
+    nx, ny, m = shape
+    geom = _geom(nx, ny, m)
+    N = geom.n_pixels
+    print(f"[gpu-test] forward, loud where delta is zero, {shape} {db} dB", flush=True)
+    gr, gi = _random_g(m, N, 1)
+    rng = np.random.default_rng(2)
+    counts = rng.random(N) < 0.5
+    s = np.where(counts, 10.0 ** (-db / 20), 1.0)
+    delta = W.random_delta(N, 3) * counts
+    _check_forward(rb, geom, gr * s, gi * s, delta)
+
+
+# The same with a delta that is small, not zero, where the table is loud, and
+# with a delta that falls off without end; one pixel alone; both with an element
+# that covers nothing.
+@pytest.mark.parametrize("shape", [(96, 90, 130), (93, 97, 300)])
+@pytest.mark.parametrize("kind", ["small", "tail", "point"])
+def test_forward_of_a_wide_ranging_delta(rb, shape, kind):
+    nx, ny, m = shape
+    geom = _geom(nx, ny, m)
+    N = geom.n_pixels
+    print(f"[gpu-test] forward, wide-ranging delta, {shape} {kind}", flush=True)
+    gr, gi = _random_g(m, N, 4)
+    gr[7] = gi[7] = 0.0
+    rng = np.random.default_rng(5)
+    delta = W.random_delta(N, 6)
+    if kind == "small":
+        loud = rng.random(N) < 0.3
+        s = np.where(loud, 1e6, 1.0)
+        gr, gi = gr * s, gi * s
+        delta = delta * np.where(loud, 1e-11, 1.0)
+    elif kind == "tail":
+        x, y = np.meshgrid(np.arange(nx) - nx / 2, np.arange(ny) - ny / 2)
+        delta = delta * np.exp(-0.5 * (x ** 2 + y ** 2) / 25.0).reshape(-1)
+    else:
+        delta[:] = 0.0
+        delta[N // 2 + 3] = 1e-8
+        gr[:, N // 2 + 3] *= 1e-7
+        gi[:, N // 2 + 3] *= 1e-7
+    _check_forward(rb, geom, gr, gi, delta)
+
+
+def test_forward_keeps_infinities_to_their_rows(rb):
+    geom = _geom(96, 90, 200)
+    print("[gpu-test] forward, one infinite value", flush=True)
+    gr, gi = _random_g(200, geom.n_pixels, 7)
+    gr[50, 333] = np.inf
+    rows = np.delete(np.arange(200), 50)
+    with np.errstate(invalid="ignore"):
+        got = _check_forward(rb, geom, gr, gi, W.random_delta(geom.n_pixels, 8), rows)
+    assert not np.any(np.isfinite(got[50])) and not np.any(np.isfinite(got[:, 50]))
