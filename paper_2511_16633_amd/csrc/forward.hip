@@ -492,7 +492,7 @@ __global__ void __launch_bounds__(256, 2) k_forward_f32_regs(FwdParams P, const 
 constexpr int kFdKC = 16, kFdArr = 64 * 64, kFdBuf = 4 * kFdArr + 64;
 constexpr int64_t kFdSplitPx = 16384;   // longest pixel split (1024 k-steps)
 constexpr int64_t kWidePx = 900000;         // see fwd16_wide
-constexpr int64_t kMinSplitPx = 64, kFewSplitPx = 512;   // shortest, see fwd_params
+constexpr int64_t kMinSplitPx = 64, kMinSplitPx32 = 16, kFewSplitPx = 512;   // shortest, see fwd_params
 typedef __attribute__((address_space(3))) void lds_void_t;
 
 __device__ __forceinline__ int fd_off(int row, int ch) { return row * 64 + 16 * (ch ^ ((row >> 1) & 3)); }
@@ -1614,10 +1614,10 @@ static bool fwd16_wide(const rb_geometry *g, rb_dtype dt) {
 // tile, and problems large enough to pay for its two more launches.  us per
 // call on the FP32 cores / split, two frequencies: 64 elements / 480^2 108 /
 // 191; 96 / 64x66 24 / 32, 96 / 128^2 42 / 39, 96 / 480^2 300 / 203; 256 /
-// 64x66 43 / 44, 256 / 128^2 89 / 68, 256 / 255x301 909 / 305; 512 / 64x66 98 /
-// 86; 1024 / 480^2 12272 / 6769.
+// 64x66 43 / 44, 256 / 128^2 89 / 68, 256 / 255x301 909 / 305; 512 / 32^2 54 / 62,
+// 512 / 64x66 98 / 81; 1024 / 480^2 12272 / 7100.
 static bool fwd32_split(const rb_geometry *g, rb_dtype dt) {
-    return dt == RB_F32 && g->m > 64 && ((int64_t)g->nx * g->ny >= 8192 || g->m > 256);
+    return dt == RB_F32 && g->m > 64 && (int64_t)g->nx * g->ny >= (g->m > 256 ? 4096 : 8192);
 }
 
 // The FP32 kernel with direct loads: rows of whole 16-byte chunks.
@@ -1639,18 +1639,20 @@ static FwdParams fwd_params(const rb_geometry *g, const double *freqs, int nf, r
     const int ntri = wide ? P.ntl / 2 * (P.ntl / 2 + 1) : P.ntl * (P.ntl + 1) / 2;
     // about four rounds of resident workgroups (two per CU, four for the
     // FP32 kernel with direct loads), rounded down so the last round is full;
-    // but no split is shorter than kMinSplitPx, and where rows are loaded in
-    // 16-byte pieces, beyond one round, than kFewSplitPx pixels: a split's
-    // partial sums (a tile of them, written and read once) cost as much as
-    // some tens of pixels.  (The FP64 kernel and the ragged rows' loads need
-    // the waves: 256 elements / 128^2 FP64 245 us, with the longer splits 304;
-    // 97 / 301x255 FP16 200 and 235.)  us
-    // per call with splits of at least 16 / 64 / 128 / 512 pixels, two
-    // frequencies: 64 elements / 128^2 FP32 37 / 26 / 25 / 44, BF16 33 / 27 /
-    // 28 / 31, FP64 - / 30 / 34 / -; 64 / 480^2 FP32 133 / 132 / 134 / 115.
+    // but no split is shorter than kMinSplitPx, and with the large tiles, beyond
+    // one round, than kFewSplitPx pixels: a split's partial sums (a tile of them,
+    // written and read once) cost as much as some tens of pixels.  (The small
+    // tiles need the waves: 256 elements / 128^2 FP64 245 us, with the longer
+    // splits 304; 97 / 301x255 FP16 200 and 235; 768 / 64x66 FP16 68 and 82.)  The
+    // FP32 cores' kernels, which add to a split's sums once per four pixels, keep
+    // them as short as 16 pixels: the splits are added in FP64, and with 64
+    // pixels or 512 the error of the result is up to 2.9 times as large (20
+    // elements / 41x82, two frequencies: 3.3e-8, 9.1e-8).  us per call with splits
+    // of at least 16 / 64 / 128 / 512 pixels, two frequencies: 64 elements /
+    // 128^2 FP32 37 / 26 / 25 / 44, BF16 33 / 27 / 28 / 31, FP64 - / 30 / 34 / -.
     const int resident = (fs || wide ? 1 : (fwd32_direct(g, dt) ? 4 : 2)) * device_cus();
-    int64_t most = P.N / kMinSplitPx;
-    if (fs || wide || (dt != RB_F64 && P.N % (dt == RB_F32 ? 4 : 8) == 0))
+    int64_t most = dt == RB_F32 && !fs ? (P.N + kMinSplitPx32 - 1) / kMinSplitPx32 : P.N / kMinSplitPx;
+    if (fs || wide)
         most = std::max<int64_t>(P.N / kFewSplitPx, std::min<int64_t>(most, resident / (ntri * nf)));
     int nsplit = std::max<int64_t>(1, std::min<int64_t>(4 * resident / (ntri * nf), most));
     // whole rounds where that is less work in a row (rounds / splits): a last
@@ -1659,7 +1661,7 @@ static FwdParams fwd_params(const rb_geometry *g, const double *freqs, int nf, r
     // rounds -> 1), BF16 152 / 119, 256 / 301x255 FP32 246 / 216, BF16 190 / 149
     const int64_t full = (int64_t)nsplit * ntri * nf / resident * resident / (ntri * nf);
     auto rounds = [&](int64_t n) { return (n * ntri * nf + resident - 1) / resident; };
-    if (full > 0 && rounds(full) * nsplit < rounds(nsplit) * full) nsplit = (int)full;
+    if ((dt != RB_F32 || fs) && full > 0 && rounds(full) * nsplit < rounds(nsplit) * full) nsplit = (int)full;
     // the kernels with direct loads (FP32, and 16-bit for large rings) also
     // keep a split to at most kFdSplitPx pixels: the tiles of a split share
     // its table rows in L2 only while they stay within a few k-steps of each

@@ -118,3 +118,26 @@ def test_forward_keeps_infinities_to_their_rows(rb):
     with np.errstate(invalid="ignore"):
         got = _check_forward(rb, geom, gr, gi, W.random_delta(geom.n_pixels, 8), rows)
     assert not np.any(np.isfinite(got[50])) and not np.any(np.isfinite(got[:, 50]))
+
+
+# FP32 tables of one sign, whose sums only grow: what the kernel keeps in FP32
+# are the sums of at most 16 pixels (a rounding per 4, each at most 2^-24 of a
+# partial sum, rms 0.42 2^-24: together 0.6 2^-24 of the 16 pixels' sum), and the N /
+# 16 of them, and the rounded products, are as good as independent: 1.4 2^-24 /
+# sqrt(N / 16) is 8e-9 at the smallest grid here, and a third of 2^-24 far above
+# it.  Sums of 512 pixels would be off by 2.7 2^-24 each.
+@pytest.mark.parametrize("shape", [(41, 82, 20), (40, 80, 16), (72, 36, 80), (96, 76, 144)])
+def test_forward_of_small_grids_sums_in_fp64(rb, shape):
+    nx, ny, m = shape
+    geom, f = _geom(nx, ny, m), 4e5
+    N = geom.n_pixels
+    print(f"[gpu-test] forward of one sign {shape}", flush=True)
+    rng = np.random.default_rng(9)
+    gr = rng.uniform(0.5, 1.0, (m, N)).astype(np.float32)
+    delta = rng.uniform(0.5e-8, 1e-8, N)
+    got = _forward(rb, geom, gr, np.zeros_like(gr), f, delta)
+    g = gr.astype(np.float64)
+    ref = (2 * np.pi * f) ** 2 * geom.h ** 2 * (g * delta) @ g.T
+    rel = float(np.linalg.norm(got.real - ref) / np.linalg.norm(ref))
+    print(f"[gpu-test] {rel:.2e}", flush=True)
+    assert np.all(got.imag == 0.0) and rel <= 2.0 ** -24 / 3
