@@ -182,28 +182,30 @@ __global__ void __launch_bounds__(256) k_forward_f64(FwdParams P, const double *
 }
 
 // d[k][e][r] = c_k * sum_split part (fixed order) over the upper triangle
-// e <= r, written to (e, r) and (r, e).  A block takes 32 entries of a row
-// (grid: 32-entry runs, rows, frequencies; runs below the diagonal exit); its
-// kRedG thread groups each sum a contiguous eighth of the splits, eight loads
-// in flight, and the group sums are added in order.  With one thread per entry
-// the loop over the splits was a serial chain of load latencies (64 elements /
-// 128^2: 122 us with 512 splits in FP64; the whole call 177 -> 51 us, in FP32
-// with 1024 splits 370 -> 26 us).
-constexpr int kRedG = 8;
+// e <= r, written to (e, r) and (r, e).  A block takes NT / RG entries of a
+// row (grid: runs of them, rows, frequencies; runs below the diagonal exit); its
+// RG thread groups each sum a contiguous part of the splits, eight loads in
+// flight, and the group sums are added in order.  Eight groups where there are
+// few entries: with one thread per entry the loop over the splits was a serial
+// chain of load latencies (64 elements / 128^2: 122 us with 512 splits in FP64;
+// the whole call 177 -> 51 us).  One group from kRedEntries entries on, which fill the
+// card by themselves (1000 elements / 32^2, two frequencies, 13 splits: 151 -> 100 us a call, BF16 110 -> 52).
+constexpr int64_t kRedEntries = 1 << 18;
 struct FwdSplitOut {   // of k_forward_split, or null
     const uint8_t *flags;
     const float *scale, *dscale;
     int tile;
 };
-template <typename T>
-__global__ void __launch_bounds__(32 * kRedG) k_forward_reduce(FwdParams P, const T *__restrict__ part,
+template <typename T, int RG, int NT>
+__global__ void __launch_bounds__(NT) k_forward_reduce(FwdParams P, const T *__restrict__ part,
                                                                const float *__restrict__ gscale,
                                                                const double *__restrict__ dmax,
                                                                double *__restrict__ d, FwdSplitOut so) {
-    __shared__ double s_r[kRedG][32], s_i[kRedG][32];
-    const int t = threadIdx.x & 31, g = threadIdx.x >> 5;
-    const int k = blockIdx.z, e = blockIdx.y, r0 = blockIdx.x * 32, r = r0 + t;
-    if (r0 + 31 < e) return;   // block-uniform
+    constexpr int RN = NT / RG;   // entries
+    __shared__ double s_r[RG][RN], s_i[RG][RN];
+    const int t = threadIdx.x % RN, g = threadIdx.x / RN;
+    const int k = blockIdx.z, e = blockIdx.y, r0 = blockIdx.x * RN, r = r0 + t;
+    if (r0 + RN - 1 < e) return;   // block-uniform
     // (pairs closer than dmin are weighted by zero by the caller, and their
     // tile may not have been computed)
     const bool near = P.dmin >= 32 && min(abs(r - e), P.m - abs(r - e)) < P.dmin;
@@ -223,8 +225,8 @@ __global__ void __launch_bounds__(32 * kRedG) k_forward_reduce(FwdParams P, cons
         fr = so.flags + (int64_t)k * P.nsplit * P.ntl + r / so.tile;
     }
     constexpr int kU = 8;
-    const int s1 = (int)((int64_t)P.nsplit * (g + 1) / kRedG);
-    for (int s0 = (int)((int64_t)P.nsplit * g / kRedG); s0 < s1; s0 += kU) {
+    const int s1 = (int)((int64_t)P.nsplit * (g + 1) / RG);
+    for (int s0 = (int)((int64_t)P.nsplit * g / RG); s0 < s1; s0 += kU) {
         T2 v[kU];
 #pragma unroll
         for (int u = 0; u < kU; ++u) v[u] = use && s0 + u < s1 ? pp[(s0 + u) * stride] : T2{0, 0};
@@ -242,7 +244,7 @@ __global__ void __launch_bounds__(32 * kRedG) k_forward_reduce(FwdParams P, cons
     if (g != 0 || r < e || r >= P.m) return;
     sr = si = 0.0;
 #pragma unroll
-    for (int q = 0; q < kRedG; ++q) {
+    for (int q = 0; q < RG; ++q) {
         sr += s_r[q][t];
         si += s_i[q][t];
     }
@@ -1654,6 +1656,8 @@ static FwdParams fwd_params(const rb_geometry *g, const double *freqs, int nf, r
     int64_t most = dt == RB_F32 && !fs ? (P.N + kMinSplitPx32 - 1) / kMinSplitPx32 : P.N / kMinSplitPx;
     if (fs || wide)
         most = std::max<int64_t>(P.N / kFewSplitPx, std::min<int64_t>(most, resident / (ntri * nf)));
+    if (dt == RB_F64)   // within one round, a step each (16 elements / 32^2: 16.6 -> 11.6 us)
+        most = std::max<int64_t>(most, std::min<int64_t>((P.N + 15) / 16, resident / (ntri * nf)));
     int nsplit = std::max<int64_t>(1, std::min<int64_t>(4 * resident / (ntri * nf), most));
     // whole rounds where that is less work in a row (rounds / splits): a last
     // round with a tenth of the workgroups takes as long as a full one.  us,
@@ -1739,15 +1743,22 @@ rb_status forward_impl(const rb_geometry *g, const void *G_re, const void *G_im,
     FwdWs w = carve_fwd(c, P, dt, fs);
     FwdSplitOut so{nullptr, nullptr, nullptr, kFsT};
     const unsigned nblk = (unsigned)((int64_t)P.ntri * P.nsplit * nf);
-    const dim3 gred(blocks_for(P.m, 32), P.m, nf);
+    auto reduce = [&](auto tag, const float *gs, const double *dmax) {
+        using T = decltype(tag);
+        if ((int64_t)nf * P.m * P.m >= kRedEntries)
+            k_forward_reduce<T, 1, 64>
+                <<<dim3(blocks_for(P.m, 64), P.m, nf), 64, 0, st>>>(P, (const T *)w.part, gs, dmax, d_out, so);
+        else
+            k_forward_reduce<T, 8, 256>
+                <<<dim3(blocks_for(P.m, 32), P.m, nf), 256, 0, st>>>(P, (const T *)w.part, gs, dmax, d_out, so);
+    };
     switch (dt) {
         case RB_F64: {
             dim3 grid(P.ntri, P.nsplit, nf);
             k_forward_f64<<<grid, 256, 0, st>>>(P, (const double *)G_re, (const double *)G_im, delta,
                                                 (double *)w.part);
             RB_LAUNCHED();
-            k_forward_reduce<double><<<gred, 32 * kRedG, 0, st>>>(P, (const double *)w.part, nullptr,
-                                                                           nullptr, d_out, so);
+            reduce(double(), nullptr, nullptr);
             break;
         }
         case RB_F32:
@@ -1779,8 +1790,7 @@ rb_status forward_impl(const rb_geometry *g, const void *G_re, const void *G_im,
                                                                                (float *)w.part);
             }
             RB_LAUNCHED();
-            k_forward_reduce<float><<<gred, 32 * kRedG, 0, st>>>(P, (const float *)w.part, gscale,
-                                                                          nullptr, d_out, so);
+            reduce(float(), gscale, nullptr);
             break;
         case RB_BF16:
         case RB_F16:
@@ -1810,8 +1820,7 @@ rb_status forward_impl(const rb_geometry *g, const void *G_re, const void *G_im,
                 k_forward16_lds<__half><<<nblk, 256, 0, st>>>(P, (const __half *)G_re, (const __half *)G_im,
                                                               w.df, (float *)w.part);
             RB_LAUNCHED();
-            k_forward_reduce<float><<<gred, 32 * kRedG, 0, st>>>(P, (const float *)w.part, gscale,
-                                                                          w.dmax, d_out, so);
+            reduce(float(), gscale, w.dmax);
             break;
     }
     RB_LAUNCHED();
