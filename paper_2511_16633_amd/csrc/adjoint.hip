@@ -171,7 +171,9 @@ __device__ __forceinline__ __half cvt<__half>(double v) { return __float2half((f
 
 // The power of two that brings a value of magnitude `top` into [2^(e-1),
 // 2^e) (1 for 0): exact to apply and to take back.
-constexpr int kSplitTopA = 14, kSplitTopG = 9;
+constexpr int kSplitTopA = 14, kSplitTopG = 10;
+// The range in which two FP16 pieces hold FP32's bits (see k_adjoint_split).
+constexpr float kSplitMinG = 0x1p-2f, kSplitMax = 65504.0f;
 __device__ __forceinline__ float split_scale(float top, int e) {
     if (!(top > 0.0f)) return 1.0f;
     int x;
@@ -1237,11 +1239,11 @@ void launch_adjoint16(const AdjTask &t, dim3 grid, const A &arg, hipStream_t st)
 // Gradient-only backprojection of FP32 tables with every operand split into
 // two FP16 pieces, x s = hi + lo: hi = x s rounded to FP16, lo = the exact
 // remainder rounded to FP16, s a power of two.  hi hi + hi lo + lo hi on the
-// 16x16x32 FP16 cores (products exact, FP32 accumulation) keeps about 22 bits
-// of every product, and an MFMA sums 32 products at a time instead of 4, so
-// that the result is nearer to FP64 than the FP32 cores' (relative L2 error of
-// the gradient, rounded to FP32: 1024 elements / 1100^2 8.1e-8 -> 6.3e-8, 256 /
-// 480^2 1.4e-7 -> 1.2e-7).
+// 16x16x32 FP16 cores (products exact, FP32 accumulation) keeps about 22 bits of every product, and an MFMA sums 32
+// products at a time instead of 4, so that the result is nearer to FP64 than
+// the FP32 cores' (relative L2 error of the gradient: 1024 elements / 1100^2 8.1e-8
+// -> 6.3e-8, 256 / 480^2 1.4e-7 -> 1.2e-7; 65 to 512 elements, 128x150 to 256^2, 0.62
+// to 0.88 of it).
 //
 // 1024 elements / 1100^2, four frequencies: 107.9 ms on the FP32 cores, 43.0
 // ms here (12 MFMAs per complex product of blocks: 1.1 PFLOP/s).  The matrix
@@ -1250,13 +1252,12 @@ void launch_adjoint16(const AdjTask &t, dim3 grid, const A &arg, hipStream_t st)
 // three frequencies: 1.59 -> 0.77 ms.  On the way there: rows of G loaded half
 // a chunk ahead 55.1 ms, passes four chunks apart (AdjChunks) 64.8 ms.
 //
-// Scales: A by its largest magnitude per frequency; G per (frequency, pixel)
-// by its largest magnitude over kSplitRows sampled elements, brought to 2^9
-// (k_adj_colscale).  FP16 then has 2^7 of headroom over the sampled maximum
-// and resolves 2^-32 of it.  A workgroup that meets a |G s| beyond the range
-// (nonzero G at a pixel that no sampled element reaches; infinities) puts its
-// work item on a list, and k_adjoint_f32_list computes it from FP32, so that
-// any table an FP32 call accepts gives an FP32 result.
+// Scales: A by its largest magnitude per frequency; G per (frequency, pixel) by
+// its largest magnitude over kSplitRows sampled elements, brought to 2^10
+// (k_adj_colscale).  The pieces hold FP32's bits (a last place of 2^-22 or less)
+// of every G s from 2^-2 on, up to 65504 (1024 elements / 1100^2 phantom: 2^-7 to
+// 2^4.4 of the sample).  A workgroup that has staged a G beyond these, but zero,
+// puts its work item on a list, and k_adjoint_f32_list computes it from FP32.
 //
 // Workgroup tile, receiver chunks, transposing reads and LDS swizzle are
 // those of k_adjoint16_tr; here a chunk's 32 x 128 FP32 tile passes through
@@ -1264,14 +1265,13 @@ void launch_adjoint16(const AdjTask &t, dim3 grid, const A &arg, hipStream_t st)
 // previous chunk), is split there once for all four waves and stored as four
 // FP16 arrays of 8 KB, double buffered.
 constexpr int kSplitRows = 16, kSplitRowsMore = 128;
-constexpr float kSplitMax = 65504.0f;   // largest FP16 value
 typedef _Float16 h4 __attribute__((ext_vector_type(4)));
 
 // scale[k][x] = split_scale(max over the sampled rows of |re|, |im|).  Pixels
 // that none of the kSplitRows rows covers (outside the ring, or at its edge,
-// where rays end) take kSplitRowsMore rows; 2^100 where those are zero too,
-// so that any normal value of the other rows overflows.  Also clears what
-// the following launches accumulate into: amax [nf] and the list's length.
+// where rays end) take kSplitRowsMore rows; 2^100 where those are zero too.
+// Also clears what the following launches accumulate into: amax [nf] and the
+// list's length.
 __global__ void __launch_bounds__(256) k_adj_colscale(int m, int nf, int64_t N, const float *__restrict__ Gr,
                                                       const float *__restrict__ Gi, float *__restrict__ scale,
                                                       float *__restrict__ amax, int *__restrict__ redo) {
@@ -1332,7 +1332,10 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_split(const A args) {
     f4 ps;
 #pragma unroll
     for (int q = 0; q < 4; ++q) ps[q] = sc[min(x0 + p4 + q, N - 1)];
-    float top = 0.0f;   // largest |G s| this thread has staged
+    // of the values this thread has staged (largest of re and im): the largest,
+    // and the bits of the smallest but zero, minus one
+    float top = 0.0f;
+    unsigned low = 0xffffffffu;
     // byte offsets are taken from the chunk's first row and pixel, uniform
     // bases, and fit 32 bits (32 N < 2^30 elements)
     auto at = [](const float *base, unsigned off) {
@@ -1356,19 +1359,29 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_split(const A args) {
             }
         }
     };
-    auto store = [&](const f4 (&v)[4], unsigned char *hi, unsigned char *lo) {
+    auto store = [&](const f4 (&vr)[4], const f4 (&vi)[4], unsigned char *d) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const f4 w = v[j] * ps;
-            const h4 h = __builtin_convertvector(w, h4);
-            f4 rem;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) rem[q] = __builtin_fmaf(v[j][q], ps[q], -(float)h[q]);
-            const h4 l = __builtin_convertvector(rem, h4);
-            top = fmaxf(top, fmaxf(fmaxf(fabsf(w[0]), fabsf(w[1])), fmaxf(fabsf(w[2]), fabsf(w[3]))));
             const int o = t16_off(r8 + 8 * j, p4);
-            *reinterpret_cast<h4 *>(hi + o) = h;
-            *reinterpret_cast<h4 *>(lo + o) = l;
+            f4 w[2];
+#pragma unroll
+            for (int a = 0; a < 2; ++a) {
+                const f4 v = a ? vi[j] : vr[j];
+                w[a] = v * ps;
+                const h4 h = __builtin_convertvector(w[a], h4);
+                f4 rem;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) rem[q] = __builtin_fmaf(v[q], ps[q], -(float)h[q]);
+                const h4 l = __builtin_convertvector(rem, h4);
+                *reinterpret_cast<h4 *>(d + a * kT16Arr + o) = h;
+                *reinterpret_cast<h4 *>(d + (2 + a) * kT16Arr + o) = l;
+            }
+#pragma unroll
+            for (int q = 0; q < 4; q += 2) {
+                const float m0 = fmaxf(fabsf(w[0][q]), fabsf(w[1][q])), m1 = fmaxf(fabsf(w[0][q + 1]), fabsf(w[1][q + 1]));
+                top = fmaxf(top, fmaxf(m0, m1));
+                low = min(low, min(__float_as_uint(m0) - 1u, __float_as_uint(m1) - 1u));
+            }
         }
     };
     // transposing-read offset of column block 0, rows 8 kk + (row >> 2);
@@ -1446,8 +1459,7 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_split(const A args) {
             load(gi, c, vi, vtag);
             load_a(c, a);
             lds_barrier();   // the previous pass is done with the tile buffers
-            store(vr, sT[0], sT[0] + 2 * kT16Arr);
-            store(vi, sT[0] + kT16Arr, sT[0] + 3 * kT16Arr);
+            store(vr, vi, sT[0]);
             int s = 0;
             for (; s + 1 < nstep; ++s) {
                 lds_barrier();   // chunk s is in LDS, and no wave still reads the other buffer
@@ -1460,9 +1472,7 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_split(const A args) {
                 if (on) mma(s, a);
                 load_a(c, a);
                 __builtin_amdgcn_sched_barrier(0);
-                unsigned char *sn = sT[(s & 1) ^ 1];
-                store(vr, sn, sn + 2 * kT16Arr);
-                store(vi, sn + kT16Arr, sn + 3 * kT16Arr);
+                store(vr, vi, sT[(s & 1) ^ 1]);
             }
             lds_barrier();
             if (mine.has(bit)) mma(s, a);
@@ -1498,7 +1508,9 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_split(const A args) {
             }
         }
     }
-    const int beyond = __syncthreads_or(!(top < kSplitMax));
+    // (a scale below 2^-60: G_e Y could leave FP32's range before it is taken back)
+    const float smin = fminf(fminf(ps[0], ps[1]), fminf(ps[2], ps[3]));
+    const int beyond = __syncthreads_or(!(top < kSplitMax) || low < __float_as_uint(kSplitMinG) - 1u || smin < 0x1p-60f);
     if (beyond && tid == 0)
         it.redo[1 + atomicAdd(it.redo, 1)] = (int)(((int64_t)k * it.ntiles + loc.tile()) * npg + qg);
     // the four lane groups of a column, then the waves, in a fixed order

@@ -141,3 +141,66 @@ def test_forward_of_small_grids_sums_in_fp64(rb, shape):
     rel = float(np.linalg.norm(got.real - ref) / np.linalg.norm(ref))
     print(f"[gpu-test] {rel:.2e}", flush=True)
     assert np.all(got.imag == 0.0) and rel <= 2.0 ** -24 / 3
+
+
+def _check_gradient(rb, geom, gr, gi, D, w):
+    f = 4e5
+    gr, gi = gr.astype(np.float32), gi.astype(np.float32)
+    g = gr + 1j * gi.astype(np.float64)
+    c = (2 * np.pi * f) ** 2 * geom.h ** 2
+    grad = torch.zeros(geom.n_pixels, dtype=torch.float64, device=DEV)
+    rb.born_adjoint_weighted(geom, torch.as_tensor(gr[None], device=DEV), torch.as_tensor(gi[None], device=DEV), None,
+                             "f32", [f], torch.as_tensor(np.stack([D.real, D.imag], -1)[None], device=DEV),
+                             torch.as_tensor(np.ascontiguousarray(w[None]), device=DEV), grad, None)
+    ref = c * (np.conj(g) * ((w * D) @ np.conj(g))).sum(0).real
+    size = c * (np.abs(g) * (np.abs(w * D) @ np.abs(g))).sum(0)
+    err = np.abs(grad.cpu().numpy() - ref)
+    ok = size > 0
+    assert np.all(err[~ok] == 0.0)
+    worst = float(np.max(err[ok] / size[ok]))
+    print(f"[gpu-test] worst error {worst:.2e} of the sum of magnitudes", flush=True)
+    assert worst <= (np.sqrt(geom.m) + 2) * 2.0 ** -24
+
+
+# Elements that are loud at a pixel and carry no weight beside quiet ones that
+# do, by 60 to 200 dB: any of the elements, and the near part of the ring under
+# a receiver selection.  One and several emitter passes per workgroup.
+@pytest.mark.parametrize("shape", [(190, 190, 96), (140, 144, 256)])
+@pytest.mark.parametrize("db", [60, 100, 140, 200])
+@pytest.mark.parametrize("kind", ["unweighted", "ring"])
+def test_gradient_loud_where_the_weight_is_zero(rb, shape, db, kind):
+    nx, ny, m = shape
+    geom = _geom(nx, ny, m)
+    N = geom.n_pixels
+    print(f"[gpu-test] gradient, loud where the weight is zero, {shape} {db} dB {kind}", flush=True)
+    gr, gi = _random_g(m, N, 10)
+    rng = np.random.default_rng(11)
+    D = W.random_residual(1, m, 12)[0]
+    if kind == "unweighted":
+        loud = rng.random(m) < 0.3
+        loud[::m // 16] = True
+        s = np.where(loud, 1.0, 10.0 ** (-db / 20))[:, None]
+        w = np.outer(~loud, ~loud) * rng.uniform(0.5, 1.0, (m, m))
+    else:
+        i = np.arange(m)
+        d = np.abs(i[:, None] - i[None, :])
+        d = np.minimum(d, m - d)
+        s = 10.0 ** (-db / 20 * d[rng.integers(0, m, N)].T / (m // 2))
+        w = (d >= m // 8).astype(np.float64)
+    _check_gradient(rb, geom, gr * s, gi * s, D, w)
+
+
+# Tables and residuals far from 1 whose gradient is not.
+@pytest.mark.parametrize("shape", [(190, 190, 96), (140, 144, 256)])
+@pytest.mark.parametrize("kind", ["large", "small"])
+def test_gradient_of_any_scale(rb, shape, kind):
+    nx, ny, m = shape
+    geom = _geom(nx, ny, m)
+    print(f"[gpu-test] gradient, {kind} tables, {shape}", flush=True)
+    gr, gi = _random_g(m, geom.n_pixels, 13)
+    D = W.random_residual(1, m, 14)[0]
+    if kind == "large":
+        gr, gi, D = gr * 2.0 ** 112, gi * 2.0 ** 112, D * 2.0 ** -110
+    else:
+        gr, gi, D = gr * 2.0 ** -55, gi * 2.0 ** -55, D * 2.0 ** 60
+    _check_gradient(rb, geom, gr, gi, D, np.ones((m, m)))
