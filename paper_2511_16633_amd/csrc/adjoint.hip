@@ -171,9 +171,10 @@ __device__ __forceinline__ __half cvt<__half>(double v) { return __float2half((f
 
 // The power of two that brings a value of magnitude `top` into [2^(e-1),
 // 2^e) (1 for 0): exact to apply and to take back.
-constexpr int kSplitTopA = 14, kSplitTopG = 10;
-// The range in which two FP16 pieces hold FP32's bits (see k_adjoint_split).
-constexpr float kSplitMinG = 0x1p-2f, kSplitMax = 65504.0f;
+constexpr int kSplitTopA = 15, kSplitTopG = 10;
+// The ranges in which two FP16 pieces hold FP32's bits (see k_adjoint_split).
+constexpr float kSplitMinA = 0x1p-14f, kSplitMinG = 0x1p-2f, kSplitMax = 65504.0f;
+constexpr float kSplitLoA = 0x1p12f;   // scale of the low pieces of A
 __device__ __forceinline__ float split_scale(float top, int e) {
     if (!(top > 0.0f)) return 1.0f;
     int x;
@@ -231,13 +232,14 @@ __global__ void __launch_bounds__(256) k_adj_amax(int m, int nb, const double *_
 // 16-row halves (lane 16 kk + row holds columns 8 kk .. 8 kk + 7 of the row),
 // so that a fragment is one contiguous 1 KB load.  With `shi` (FP32 only) A is
 // also stored as two FP16 pieces of A split_scale(amax[k]), each [I][J][re,
-// im] in fragments, and W, which only the Hessian diagonal needs, is not.
+// im] in fragments, and W, which only the Hessian diagonal needs, is not;
+// bad[k] is set if a value but zero is too small for them.
 template <typename T, bool SCALED, int LAYOUT = 0>
 __global__ void __launch_bounds__(256) k_adj_prep(int m, int mp, const double *__restrict__ d,
                                                   const double *__restrict__ w, const float *__restrict__ ascale,
                                                   T *__restrict__ Ar, T *__restrict__ Ai, T *__restrict__ Wt,
                                                   uint8_t *__restrict__ flags, _Float16 *__restrict__ shi = nullptr,
-                                                  _Float16 *__restrict__ slo = nullptr) {
+                                                  _Float16 *__restrict__ slo = nullptr, int *__restrict__ bad = nullptr) {
     __shared__ double tr[32][33], ti[32][33], tw[32][33];
     const int nb = mp / 32;
     const int k = blockIdx.y, I = blockIdx.x / nb, J = blockIdx.x - (blockIdx.x / nb) * nb;
@@ -305,8 +307,10 @@ __global__ void __launch_bounds__(256) k_adj_prep(int m, int mp, const double *_
             const int64_t q = 2048 * blk + fr;
             shi[q] = hr;
             shi[q + 1024] = hi;
-            slo[q] = (_Float16)(vr - (float)hr);
-            slo[q + 1024] = (_Float16)(vi - (float)hi);
+            slo[q] = (_Float16)((vr - (float)hr) * kSplitLoA);
+            slo[q + 1024] = (_Float16)((vi - (float)hi) * kSplitLoA);
+            const float top = fmaxf(fabsf(vr), fabsf(vi));
+            if (top > 0.0f && top < kSplitMinA) bad[k] = 1;
         }
     }
     const int on = __syncthreads_or(any);
@@ -1237,9 +1241,10 @@ void launch_adjoint16(const AdjTask &t, dim3 grid, const A &arg, hipStream_t st)
 
 // ------------------------------------------------------------------ FP32 tables on the FP16 matrix cores
 // Gradient-only backprojection of FP32 tables with every operand split into
-// two FP16 pieces, x s = hi + lo: hi = x s rounded to FP16, lo = the exact
-// remainder rounded to FP16, s a power of two.  hi hi + hi lo + lo hi on the
-// 16x16x32 FP16 cores (products exact, FP32 accumulation) keeps about 22 bits of every product, and an MFMA sums 32
+// two FP16 pieces of x s, s a power of two: G s = hi + lo, A s = hi + 2^-12 lo, hi
+// the value rounded to FP16, lo the exact remainder (of A, times 2^12) rounded to
+// FP16.  hi hi + hi lo + lo (2^-12 hi) on the 16x16x32 FP16 cores (products exact,
+// FP32 accumulation) keeps about 22 bits of every product, and an MFMA sums 32
 // products at a time instead of 4, so that the result is nearer to FP64 than
 // the FP32 cores' (relative L2 error of the gradient: 1024 elements / 1100^2 8.1e-8
 // -> 6.3e-8, 256 / 480^2 1.4e-7 -> 1.2e-7; 65 to 512 elements, 128x150 to 256^2, 0.62
@@ -1252,12 +1257,16 @@ void launch_adjoint16(const AdjTask &t, dim3 grid, const A &arg, hipStream_t st)
 // three frequencies: 1.59 -> 0.77 ms.  On the way there: rows of G loaded half
 // a chunk ahead 55.1 ms, passes four chunks apart (AdjChunks) 64.8 ms.
 //
-// Scales: A by its largest magnitude per frequency; G per (frequency, pixel) by
-// its largest magnitude over kSplitRows sampled elements, brought to 2^10
-// (k_adj_colscale).  The pieces hold FP32's bits (a last place of 2^-22 or less)
-// of every G s from 2^-2 on, up to 65504 (1024 elements / 1100^2 phantom: 2^-7 to
-// 2^4.4 of the sample).  A workgroup that has staged a G beyond these, but zero,
-// puts its work item on a list, and k_adjoint_f32_list computes it from FP32.
+// Scales: A by its largest magnitude per frequency, brought to 2^15; G per
+// (frequency, pixel) by its largest magnitude over kSplitRows sampled elements,
+// brought to 2^10 (k_adj_colscale).  The pieces hold FP32's bits (a last place of
+// 2^-22 or less) of every A s from 2^-14 on and every G s from 2^-2 on, up to
+// 65504; the scale of A's low piece is shared out so because residuals range
+// further than a pixel's G (1024 elements / 1100^2 phantom: 2^-19 of the largest
+// for A, 2^-7 to 2^4.4 of the sample for G).  Whatever lies outside of these
+// ranges, but zeros, is computed from FP32 by k_adjoint_f32_list: of a frequency
+// with a smaller A all work items, without delay (bad); otherwise those whose
+// workgroup has staged such a G.
 //
 // Workgroup tile, receiver chunks, transposing reads and LDS swizzle are
 // those of k_adjoint16_tr; here a chunk's 32 x 128 FP32 tile passes through
@@ -1270,15 +1279,19 @@ typedef _Float16 h4 __attribute__((ext_vector_type(4)));
 // scale[k][x] = split_scale(max over the sampled rows of |re|, |im|).  Pixels
 // that none of the kSplitRows rows covers (outside the ring, or at its edge,
 // where rays end) take kSplitRowsMore rows; 2^100 where those are zero too.
-// Also clears what the following launches accumulate into: amax [nf] and the
-// list's length.
+// Also clears what the following launches accumulate into: amax [nf], bad [nf]
+// and the list's length.
 __global__ void __launch_bounds__(256) k_adj_colscale(int m, int nf, int64_t N, const float *__restrict__ Gr,
                                                       const float *__restrict__ Gi, float *__restrict__ scale,
-                                                      float *__restrict__ amax, int *__restrict__ redo) {
+                                                      float *__restrict__ amax, int *__restrict__ bad,
+                                                      int *__restrict__ redo) {
     const int k = blockIdx.y;
     const int64_t x = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (blockIdx.x == 0 && k == 0) {
-        if (threadIdx.x < nf) amax[threadIdx.x] = 0.0f;
+        if (threadIdx.x < nf) {
+            amax[threadIdx.x] = 0.0f;
+            bad[threadIdx.x] = 0;
+        }
         if (threadIdx.x == 0) redo[0] = 0;
     }
     if (x >= N) return;
@@ -1326,6 +1339,13 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_split(const A args) {
     const uint8_t *fl = flags + (int64_t)k * P.nb * P.nb;
     const float *__restrict__ sc = it.pscale + (int64_t)k * N;
     const int half = (P.nb + 1) / 2;   // see AdjChunks
+    auto list = [&]() {
+        it.redo[1 + atomicAdd(it.redo, 1)] = (int)(((int64_t)k * it.ntiles + loc.tile()) * it.npg + loc.group());
+    };
+    if (it.bad[k]) {   // workgroup-uniform
+        if (tid == 0) list();
+        return;
+    }
 
     // staging: this thread's four pixels (p4 ..) of tile rows r8 + 8 j
     const int p4 = (tid & 31) * 4, r8 = tid >> 5;
@@ -1418,7 +1438,7 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_split(const A args) {
             using M = MM16<__half>;
             t16v4 r[8];
             t16_tr8(sba + (unsigned)(t0 ^ (32 * cb)), r);
-            const h8 b0 = t16_join<h8>(r[0], r[1]), b1 = t16_join<h8>(r[2], r[3]);
+            h8 b0 = t16_join<h8>(r[0], r[1]), b1 = t16_join<h8>(r[2], r[3]);
             const h8 b2 = t16_join<h8>(r[4], r[5]), b3 = t16_join<h8>(r[6], r[7]);
             auto term = [&](const h8 (&x)[EB], const h8 &u, const h8 (&y)[EB], const h8 &v) {
 #pragma unroll
@@ -1431,6 +1451,8 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_split(const A args) {
             term(a[1], b1, n[0], b0);
             term(a[0], b2, a[0], b3);
             term(a[1], b3, n[0], b2);
+            b0 *= (_Float16)(1.0f / kSplitLoA);   // exact from 2^-2 on
+            b1 *= (_Float16)(1.0f / kSplitLoA);
             term(a[2], b0, a[2], b1);
             term(a[3], b1, n[1], b0);
         };
@@ -1511,8 +1533,7 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_split(const A args) {
     // (a scale below 2^-60: G_e Y could leave FP32's range before it is taken back)
     const float smin = fminf(fminf(ps[0], ps[1]), fminf(ps[2], ps[3]));
     const int beyond = __syncthreads_or(!(top < kSplitMax) || low < __float_as_uint(kSplitMinG) - 1u || smin < 0x1p-60f);
-    if (beyond && tid == 0)
-        it.redo[1 + atomicAdd(it.redo, 1)] = (int)(((int64_t)k * it.ntiles + loc.tile()) * npg + qg);
+    if (beyond && tid == 0) list();
     // the four lane groups of a column, then the waves, in a fixed order
 #pragma unroll
     for (int cb = 0; cb < 8; ++cb) {
@@ -1603,6 +1624,11 @@ static int adj_groups(const rb_geometry *g, rb_dtype dt) {
     return npass >= 4 ? npass : 1;
 }
 
+// Length of an AdjItem's bad and redo together.
+static size_t split_ints(const rb_geometry *g, int nf, rb_dtype dt) {
+    return RB_MAX_NF + 1 + (size_t)nf * blocks_for((int64_t)g->nx * g->ny, kT16NT) * adj_groups(g, dt);
+}
+
 // Whether a gradient-only FP32 problem takes k_adjoint_split: from 65
 // elements (a pass has 128, and at 64 half of its waves are idle) and with
 // more workgroups than compute units.  us per call, k_adjoint_f32 against
@@ -1622,7 +1648,7 @@ static bool adj_split(const rb_geometry *g, int nf, rb_dtype dt) {
     Carver c(nullptr, 0);
     c.take<_Float16>((size_t)nf * 2 * mp * mp);
     c.take<float>((size_t)nf * N);
-    c.take<int>(1 + (size_t)nf * blocks_for(N, kT16NT) * adj_groups(g, dt));
+    c.take<int>(split_ints(g, nf, dt));
     return c.used <= (size_t)nf * adj_groups(g, dt) * N * sizeof(double);
 }
 
@@ -1674,7 +1700,7 @@ rb_status adjoint_prepare(const rb_geometry *g, const void *G_re, const void *G_
     it.begin = 0;
     it.split_hi = it.split_lo = nullptr;
     it.pscale = nullptr;
-    it.redo = nullptr;
+    it.redo = it.bad = nullptr;
     if (hdiag && adj_split(g, nf, dt)) {
         // The Hessian diagonal by itself, its one product on the FP32 cores,
         // before the gradient's pieces take the place of W (gradient and
@@ -1705,9 +1731,10 @@ rb_status adjoint_prepare(const rb_geometry *g, const void *G_re, const void *G_
         it.split_lo = h.take<_Float16>((size_t)nf * 2 * P.mp * P.mp);
         float *ps = h.take<float>((size_t)nf * P.N);
         it.pscale = ps;
-        it.redo = h.take<int>(1 + (size_t)nf * blocks_for(P.N, kT16NT) * adj_groups(g, dt));
+        it.bad = h.take<int>(split_ints(g, nf, dt));
+        it.redo = it.bad + RB_MAX_NF;
         k_adj_colscale<<<dim3(blocks_for(P.N, 256), nf), 256, 0, st>>>(
-            g->m, nf, P.N, (const float *)G_re, (const float *)G_im, ps, w.ascale, it.redo);
+            g->m, nf, P.N, (const float *)G_re, (const float *)G_im, ps, w.ascale, it.bad, it.redo);
         RB_LAUNCHED();
         k_adj_amax<<<gp, 256, 0, st>>>(g->m, P.nb, d_res, w_data, reinterpret_cast<unsigned *>(w.ascale));
         RB_LAUNCHED();
@@ -1725,7 +1752,7 @@ rb_status adjoint_prepare(const rb_geometry *g, const void *G_re, const void *G_
         case RB_F32:
             k_adj_prep<float, false, 1><<<gp, 256, 0, st>>>(g->m, P.mp, d_res, w_data, w.ascale, (float *)w.Ar,
                                                                (float *)w.Ai, (float *)w.Wt, w.flags,
-                                                               (_Float16 *)it.split_hi, (_Float16 *)it.split_lo);
+                                                               (_Float16 *)it.split_hi, (_Float16 *)it.split_lo, it.bad);
             break;
         case RB_BF16:
             k_adj_prep<__hip_bfloat16, true, 2><<<gp, 256, 0, st>>>(g->m, P.mp, d_res, w_data, w.ascale,

@@ -25,11 +25,12 @@ struct AdjItem {
     double *pg, *ph;
     int ntiles, begin;
     int npg;   // emitter-pass groups per pixel tile, each a workgroup of its own (partials [nf][npg][N])
-    // FP32 tables on the FP16 cores: split operands, G scales [nf][N], and
-    // the list of work items to compute in FP32 (its length, then the items)
+    // FP32 tables on the FP16 cores: split operands, G scales [nf][N], whether
+    // a frequency's A does not fit them [nf], and the list of work items to
+    // compute in FP32 (its length, then the items)
     void *split_hi, *split_lo;
     const float *pscale;
-    int *redo;
+    int *bad, *redo;
 };
 constexpr int kAdjGroupMax = 8;   // problems per grouped launch (kernel-argument size)
 struct AdjGroup {
