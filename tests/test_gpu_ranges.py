@@ -222,3 +222,31 @@ def test_gradient_of_a_wide_ranging_residual(rb, shape, db):
     D[:, c] *= 10.0 ** (db / 20)
     gr[c, :N // 2] = gi[c, :N // 2] = 0.0
     _check_gradient(rb, geom, gr, gi, D, np.ones((m, m)), slice(0, N // 2))
+
+
+# The FP32 Hessian diagonal of a small ring.  The sum over the receivers is one of
+# up to m / 4 FP32 additions of growing sums (rms 0.42 2^-24 sqrt(m / 12): 1.2 2^-24
+# at 100 elements), with its products' roundings 1.4 2^-24, different for every
+# emitter, over whom it is summed in FP64: 0.14 2^-24, and twice that is allowed.
+# With the emitters' terms summed in FP32 by eight threads (16 additions each, 1.0
+# 2^-24, together 0.35) it would be more.
+@pytest.mark.parametrize("shape", [(92, 92, 100), (190, 190, 100), (80, 40, 100)])
+def test_fp32_hessian_of_small_rings_sums_in_fp64(rb, shape):
+    nx, ny, m = shape
+    geom, f = _geom(nx, ny, m), 4e5
+    N = geom.n_pixels
+    print(f"[gpu-test] FP32 Hessian diagonal {shape}", flush=True)
+    rng = np.random.default_rng(15)
+    gr, gi = (rng.uniform(0.5, 1.0, (1, m, N)).astype(np.float32) for _ in range(2))
+    D = W.random_residual(1, m, 16)
+    w = rng.uniform(0.5, 1.0, (1, m, m))
+    grad, hd = (torch.zeros(N, dtype=torch.float64, device=DEV) for _ in range(2))
+    rb.born_adjoint_weighted(geom, torch.as_tensor(gr, device=DEV), torch.as_tensor(gi, device=DEV), None, "f32", [f],
+                             torch.as_tensor(np.stack([D.real, D.imag], -1), device=DEV),
+                             torch.as_tensor(w, device=DEV), grad, hd)
+    p = gr[0].astype(np.float64) ** 2 + gi[0].astype(np.float64) ** 2
+    c = (2 * np.pi * f) ** 2 * geom.h ** 2
+    ref = c * c * (p * (w[0] @ p)).sum(0)
+    rel = float(np.linalg.norm(hd.cpu().numpy() - ref) / np.linalg.norm(ref))
+    print(f"[gpu-test] {rel:.2e}", flush=True)
+    assert rel <= 0.28 * 2.0 ** -24
