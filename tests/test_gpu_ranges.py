@@ -250,3 +250,33 @@ def test_fp32_hessian_of_small_rings_sums_in_fp64(rb, shape):
     rel = float(np.linalg.norm(hd.cpu().numpy() - ref) / np.linalg.norm(ref))
     print(f"[gpu-test] {rel:.2e}", flush=True)
     assert rel <= 0.28 * 2.0 ** -24
+
+
+# The 16-bit Hessian diagonal under weights that vary.  Contracted in both orders of
+# a pair, its error is that of m rounded |G|^2 (uniform over half a last place of
+# numbers of any mantissa: rms 0.42 2^-p, p the type's bits), each on 1 / m of the
+# sum: 0.42 2^-p / sqrt(m), and m^2 rounded weights, sqrt(m) times less.  Contracted
+# once per pair, it must not be more.
+@pytest.mark.parametrize("dtype, bits", [("bf16", 8), ("f16", 11)])
+@pytest.mark.parametrize("shape", [(72, 72, 48), (88, 88, 64), (96, 64, 96), (72, 72, 130), (60, 61, 227)])
+def test_16bit_hessian_of_varied_weights(rb, dtype, bits, shape):
+    nx, ny, m = shape
+    geom, f = _geom(nx, ny, m), 4e5
+    N = geom.n_pixels
+    print(f"[gpu-test] 16-bit Hessian diagonal {dtype} {shape}", flush=True)
+    rng = np.random.default_rng(17)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float16
+    mag, ph = np.exp2(rng.uniform(-1.0, 0.0, (1, m, N))), rng.uniform(0.0, 2 * np.pi, (1, m, N))
+    gr, gi = (torch.as_tensor(v, device=DEV).to(td) for v in (mag * np.cos(ph), mag * np.sin(ph)))
+    D = W.random_residual(1, m, 18)
+    w = rng.uniform(0.5, 1.0, (1, m, m))
+    grad, hd = (torch.zeros(N, dtype=torch.float64, device=DEV) for _ in range(2))
+    rb.born_adjoint_weighted(geom, gr, gi, torch.ones(1, device=DEV), dtype, [f],
+                             torch.as_tensor(np.stack([D.real, D.imag], -1), device=DEV),
+                             torch.as_tensor(w, device=DEV), grad, hd)
+    p = (gr[0].double() ** 2 + gi[0].double() ** 2).cpu().numpy()
+    c = (2 * np.pi * f) ** 2 * geom.h ** 2
+    ref = c * c * (p * (w[0] @ p)).sum(0)
+    rel = float(np.linalg.norm(hd.cpu().numpy() - ref) / np.linalg.norm(ref))
+    print(f"[gpu-test] {rel * 2.0 ** bits * np.sqrt(m):.3f} of 2^-{bits} / sqrt(m)", flush=True)
+    assert rel <= 0.45 * 2.0 ** -bits / np.sqrt(m)
