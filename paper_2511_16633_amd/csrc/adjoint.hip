@@ -237,9 +237,21 @@ __global__ void __launch_bounds__(256) k_adj_amax(int m, int nb, const double *_
 //
 // In 16 bits the mean of a pair is rounded once where the pair was twice: the
 // squared error is the same where its two values are independent or equal, up to
-// twice as large where they are close (weights, residuals of reciprocal data with
-// noise).  Two blocks around the ring would gain no k-step by it (the pass stages both
+// twice as large where they are close (residuals of reciprocal data with noise).
+// A block whose squared errors add up to more than kLowRatio times those of the
+// ordered pairs gets flag 3, if its J is odd or the ring's last, and the low-order
+// parts of A, the means less their 16-bit values, lie in the place of the block
+// (J, I), which is not kept.  The contraction adds those in k-steps of their own:
+// with half of the blocks free of rounding errors the sum's is that of the ordered
+// pairs again (relative error of the gradient, 256 elements, residual reciprocal but
+// for 5 %, FP16: 0.30 2^-11, without these 0.41 2^-11, with both orders of a pair 0.31
+// 2^-11).  BF16, gradient, both orders / folded / with such steps: 1024 / 1100^2, four
+// frequencies, 32.9 / 17.2 / 23.5 ms, 256 / 480^2, three, 468 / 346 / 431 us.  (Up to
+// kAdjLowBlocks blocks: see adj_chunks.)
+// Two blocks around the ring would gain no k-step by it (the pass stages both
 // chunks anyway), so there both orders are kept, each as the diagonal blocks.
+constexpr float kLowRatio = 1.3f;
+constexpr int kAdjLowBlocks = 64;
 template <typename T, bool SCALED, int LAYOUT = 0>
 __global__ void __launch_bounds__(256) k_adj_prep(int m, int mp, const double *__restrict__ d,
                                                   const double *__restrict__ w, const float *__restrict__ ascale,
@@ -287,6 +299,11 @@ __global__ void __launch_bounds__(256) k_adj_prep(int m, int mp, const double *_
         }
     __syncthreads();
     const double half = SCALED && as > 0.0f ? 0.5 / (double)as : 0.5;
+    // (blocks with less than half of their rows or columns in the ring hold too
+    // few pairs to tell)
+    const bool split = SCALED && fold && ((J & 1) || J == nb - 1) && 32 * max(I, J) + 16 <= m &&
+                       nb <= kAdjLowBlocks;
+    float err = 0.0f;   // squared errors: of twice the means less kLowRatio times the pairs'
     bool any = false;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -305,9 +322,21 @@ __global__ void __launch_bounds__(256) k_adj_prep(int m, int mp, const double *_
         const int64_t o = LAYOUT == 2 ? 1024 * blk + fr : ((int64_t)k * mp + I * 32 + i) * mp + J * 32 + c;
         Ar[o] = cvt<T>(re * half);
         Ai[o] = cvt<T>(im * half);
-        if (SCALED || !shi) {
-            Wt[o] = cvt<T>(wv * 0.5);
-        } else {
+        if (SCALED || !shi) Wt[o] = cvt<T>(wv * 0.5);
+        if constexpr (SCALED) {
+            if (split) {   // workgroup-uniform
+                const int64_t lo = 1024 * (((int64_t)k * nb + J) * nb + I) + fr;
+                auto part = [&](double a, double b, T *A) {   // the pair; its mean is at A[o]
+                    auto off = [](float v) { return MM16<T>::to_f(cvt<T>((double)v)) - v; };
+                    const float r = (float)((a + b) * half) - MM16<T>::to_f(A[o]);
+                    const float e = off((float)(a * (2.0 * half))) + off((float)(b * (2.0 * half)));
+                    err += 4.0f * r * r - kLowRatio * e * e;
+                    A[lo] = cvt<T>((double)r);
+                };
+                part(lr[0][q], tr[col][i], Ar);
+                part(li[0][q], ti[col][i], Ai);
+            }
+        } else if (shi) {
             const float sa = split_scale(as, kSplitTopA);
             const float vr = (float)(re * half) * sa, vi = (float)(im * half) * sa;
             const _Float16 hr = (_Float16)vr, hi = (_Float16)vi;
@@ -320,8 +349,14 @@ __global__ void __launch_bounds__(256) k_adj_prep(int m, int mp, const double *_
             if (top > 0.0f && top < kSplitMinA) bad[k] = 1;
         }
     }
+    __shared__ float se[4];
+    if (split) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) err += __shfl_xor(err, o);
+        if ((threadIdx.x & 63) == 0) se[threadIdx.x >> 6] = err;
+    }
     const int on = __syncthreads_or(any);
-    if (threadIdx.x == 0) *fl = on ? 1 : 0;
+    if (threadIdx.x == 0) *fl = on ? (split && (se[0] + se[1]) + (se[2] + se[3]) > 0.0f ? 3 : 1) : 0;
 }
 
 // The receiver chunks (32 receivers each, at most 128) an emitter pass works
@@ -350,8 +385,9 @@ struct AdjChunks {
 };
 
 // The chunks of NQ emitter blocks from eb0 on: `all` of any of them, `mine`
-// of block eb0 + q.
-template <int NQ>
+// of block eb0 + q.  With LOW, those with low-order parts (k_adj_prep) follow as
+// bits 64 and up, which rings of up to kAdjLowBlocks blocks do not use otherwise.
+template <int NQ, bool LOW = false>
 __device__ __forceinline__ void adj_chunks(const uint8_t *__restrict__ fl, int nb, int eb0, int q,
                                            AdjChunks &all, AdjChunks &mine) {
     const int lane = threadIdx.x & 63, half = (nb + 1) / 2;
@@ -371,6 +407,11 @@ __device__ __forceinline__ void adj_chunks(const uint8_t *__restrict__ fl, int n
             const uint64_t b = __ballot(ok && eb0 + i < nb && f[i] != 0);
             (h ? all.m1 : all.m0) |= b;
             if (i == q) (h ? mine.m1 : mine.m0) = b;
+            if (LOW && !h && half <= 32) {
+                const uint64_t l = __ballot(ok && eb0 + i < nb && f[i] > 1);
+                all.m1 |= l;
+                if (i == q) mine.m1 = l;
+            }
         }
     }
 }
@@ -979,6 +1020,8 @@ __global__ void __launch_bounds__(64 * t16_waves(HESS), 2) k_adjoint16_tr(const 
     const S *wt = Wt + (int64_t)k * P.mp * P.mp;
     const uint8_t *fl = flags + (int64_t)k * P.nb * P.nb;
     const int half = (P.nb + 1) / 2;   // see AdjChunks
+    const int cmask = half <= 32 ? 63 : 127;   // bits beyond: low-order parts
+    auto chunk = [&](int bit) { return AdjChunks::chunk(bit & cmask, half); };
     // lane's element offsets of its four direct-load chunks within a step
     // (of the last tile's chunks beyond N, the last: dropped)
     const int lastc = (int)min(N - 8 - x0, (int64_t)kT16NT);
@@ -1010,9 +1053,10 @@ __global__ void __launch_bounds__(64 * t16_waves(HESS), 2) k_adjoint16_tr(const 
             for (int cb = 0; cb < CB; ++cb) yr[b][cb] = yn[b][cb] = z[b][cb] = f4{0, 0, 0, 0};
         // fragments of block (e0 / 32, c); emitter blocks beyond mp read the
         // last one (their Y is dropped)
-        const int eblk = min(e0 >> 5, P.nb - 1) * P.nb;
-        auto load_a = [&](int c, V (&va)[EB], V (&vi)[EB], V (&vw)[EB]) {
-            const int64_t co = (int64_t)(eblk + c) * 1024;   // uniform
+        const int eb = min(e0 >> 5, P.nb - 1);
+        auto load_a = [&](int bit, V (&va)[EB], V (&vi)[EB], V (&vw)[EB]) {
+            const int c = chunk(bit);
+            const int64_t co = (int64_t)(bit <= cmask ? eb * P.nb + c : c * P.nb + eb) * 1024;   // uniform
 #pragma unroll
             for (int b = 0; b < EB; ++b) {
                 va[b] = *reinterpret_cast<const V *>(ar + co + 512 * b + 8 * lane);
@@ -1023,7 +1067,7 @@ __global__ void __launch_bounds__(64 * t16_waves(HESS), 2) k_adjoint16_tr(const 
         // the pass's receiver chunks: `all` of its four waves (staged), `mine`
         // of this wave's 32 emitters
         AdjChunks all, mine;
-        adj_chunks<4>(fl, P.nb, ec >> 5, eg, all, mine);
+        adj_chunks<4, true>(fl, P.nb, ec >> 5, eg, all, mine);
         const int nstep = all.count();
         // the chunks of the current step and the next two (opaque to the
         // compiler, which would otherwise keep a strength-reduced address per
@@ -1034,11 +1078,12 @@ __global__ void __launch_bounds__(64 * t16_waves(HESS), 2) k_adjoint16_tr(const 
             return c;
         };
         int b0 = next_bit(), b1 = next_bit(), b2 = next_bit();
-        auto stage = [&](int c, unsigned char *dst) {
+        auto stage = [&](int bit, unsigned char *dst) {
+            const int c = chunk(bit);
             t16_stage_async<NW>(gr + ((int64_t)c * kT16KC * N + x0), gi + ((int64_t)c * kT16KC * N + x0), goff, dst);
         };
         t16us8 tv[16 / NW];   // without direct loads: the tile of step s + 1
-        auto load_t = [&](int c) { t16_load_tile<NW>(gr, gi, P.m, N, c * kT16KC, x0, full, tv); };
+        auto load_t = [&](int bit) { t16_load_tile<NW>(gr, gi, P.m, N, chunk(bit) * kT16KC, x0, full, tv); };
         // One k-step s (chunk bit b0) on the tile in buffer s mod 4: wait for
         // its tile and its A, issue A of b1 and the tile of step s + 2 (b2),
         // then the MFMAs.  Per step a wave issues A(s + 1) (2 EB or
@@ -1055,21 +1100,21 @@ __global__ void __launch_bounds__(64 * t16_waves(HESS), 2) k_adjoint16_tr(const 
             const bool has_t = M == 3 || (M == 0 && s + 2 < nstep);
             if (!DIRECT) {
                 // the tile of s + 1, read two barriers from now at the latest
-                if (has_a) t16_store_tile<NW>(tv, P.m, AdjChunks::chunk(b1, half) * kT16KC, buf(Idx<I + 1>()));
+                if (has_a) t16_store_tile<NW>(tv, P.m, chunk(b1) * kT16KC, buf(Idx<I + 1>()));
             } else if (has_a) {
                 __builtin_amdgcn_s_waitcnt(vmcnt_imm(16 / NW));   // tile s + 1
             } else {
                 __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
             }
             lds_barrier();
-            const bool on = mine.has(b0);
-            if (has_a) load_a(AdjChunks::chunk(b1, half), na, ni, nw);
+            const bool on = mine.has(b0), low = b0 > cmask;
+            if (has_a) load_a(b1, na, ni, nw);
             __builtin_amdgcn_sched_barrier(0);
             if (has_t) {
                 if (DIRECT)
-                    stage(AdjChunks::chunk(b2, half), buf(Idx<I + 2>()));
+                    stage(b2, buf(Idx<I + 2>()));
                 else
-                    load_t(AdjChunks::chunk(b2, half));
+                    load_t(b2);
             }
             __builtin_amdgcn_sched_barrier(0);
             b0 = b1;
@@ -1095,7 +1140,7 @@ __global__ void __launch_bounds__(64 * t16_waves(HESS), 2) k_adjoint16_tr(const 
                     yr[b][cb] = MM16<S>::mma(vi[b], bi, yr[b][cb]);
                     yn[b][cb] = MM16<S>::mma(va[b], bi, yn[b][cb]);
                     yn[b][cb] = MM16<S>::mma(nva[b], br, yn[b][cb]);
-                    if (HESS) z[b][cb] = MM16<S>::mma(vw[b], b2, z[b][cb]);
+                    if (HESS) z[b][cb] = MM16<S>::mma(low ? V{} : vw[b], b2, z[b][cb]);   // W: no low-order parts
                 }
             }
         };
@@ -1110,19 +1155,19 @@ __global__ void __launch_bounds__(64 * t16_waves(HESS), 2) k_adjoint16_tr(const 
             V va[EB], vi[EB], vw[EB], na[EB], ni[EB], nw[EB];
             lds_barrier();   // the previous pass is done with the tile buffers
             if (DIRECT) {
-                stage(AdjChunks::chunk(b0, half), sG0);
+                stage(b0, sG0);
             } else {
-                load_t(AdjChunks::chunk(b0, half));
-                t16_store_tile<NW>(tv, P.m, AdjChunks::chunk(b0, half) * kT16KC, sG0);
+                load_t(b0);
+                t16_store_tile<NW>(tv, P.m, chunk(b0) * kT16KC, sG0);
             }
-            load_a(AdjChunks::chunk(b0, half), va, vi, vw);
+            load_a(b0, va, vi, vw);
             // unconditional (a one-chunk pass stages chunk 0, unused), so that
             // the loop is always entered with the same loads in flight and
             // the compiler's load-counter waits at its head stay exact
             if (DIRECT)
-                stage(AdjChunks::chunk(b1, half), sG1);
+                stage(b1, sG1);
             else
-                load_t(AdjChunks::chunk(b1, half));
+                load_t(b1);
             int s = 0;
             for (; s + 6 <= nstep; s += 4) {
                 kstep(s, Idx<0>(), va, vi, vw, na, ni, nw, M3());

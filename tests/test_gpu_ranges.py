@@ -280,3 +280,31 @@ def test_16bit_hessian_of_varied_weights(rb, dtype, bits, shape):
     rel = float(np.linalg.norm(hd.cpu().numpy() - ref) / np.linalg.norm(ref))
     print(f"[gpu-test] {rel * 2.0 ** bits * np.sqrt(m):.3f} of 2^-{bits} / sqrt(m)", flush=True)
     assert rel <= 0.45 * 2.0 ** -bits / np.sqrt(m)
+
+
+# The 16-bit gradient of residuals that are reciprocal but for noise.  Contracted in
+# both orders of a pair, its two values are rounded apart (rms 0.42 2^-p each): 0.30
+# 2^-p of their sum, and of the gradient, a sum of independent such terms.  Contracted
+# once per pair, it must not be more (rounded once: 0.42).
+@pytest.mark.parametrize("dtype, bits", [("bf16", 8), ("f16", 11)])
+@pytest.mark.parametrize("shape", [(72, 72, 64), (72, 72, 130), (60, 61, 200), (64, 40, 256)])
+def test_16bit_gradient_of_reciprocal_residuals(rb, dtype, bits, shape):
+    nx, ny, m = shape
+    geom, f = _geom(nx, ny, m), 4e5
+    N = geom.n_pixels
+    print(f"[gpu-test] 16-bit gradient, reciprocal residual {dtype} {shape}", flush=True)
+    rng = np.random.default_rng(19)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float16
+    mag, ph = np.exp2(rng.uniform(-1.0, 0.0, (1, m, N))), rng.uniform(0.0, 2 * np.pi, (1, m, N))
+    gr, gi = (torch.as_tensor(v, device=DEV).to(td) for v in (mag * np.cos(ph), mag * np.sin(ph)))
+    D = rng.standard_normal((m, m)) + 1j * rng.standard_normal((m, m))
+    D = (D + D.T) * (1.0 + 0.05 * rng.standard_normal((m, m)))
+    grad = torch.zeros(N, dtype=torch.float64, device=DEV)
+    rb.born_adjoint_weighted(geom, gr, gi, torch.ones(1, device=DEV), dtype, [f],
+                             torch.as_tensor(np.stack([D.real, D.imag], -1)[None], device=DEV),
+                             torch.ones((1, m, m), dtype=torch.float64, device=DEV), grad, None)
+    g = (gr[0].double() + 1j * gi[0].double()).cpu().numpy()
+    ref = (2 * np.pi * f) ** 2 * geom.h ** 2 * (np.conj(g) * (D @ np.conj(g))).sum(0).real
+    rel = float(np.linalg.norm(grad.cpu().numpy() - ref) / np.linalg.norm(ref))
+    print(f"[gpu-test] {rel * 2.0 ** bits:.3f} of 2^-{bits}", flush=True)
+    assert rel <= 0.33 * 2.0 ** -bits
