@@ -71,19 +71,19 @@ __global__ void __launch_bounds__(256) k_adjoint(AdjParams P, const T *__restric
         gp[c] = hp[c] = T(0);
         xs[c] = min(xw + 16 * c + row, N - 1);   // pixels beyond N: the last one, dropped below
     }
-    for (int ec = 0; ec < P.mp; ec += 16 * RB) {
+    // (16 elements at a time: of a 32-element block only those below m)
+    for (int ec = 0; ec < P.m; ec += 16 * RB) {
         acc_t yr[RB][CB], yn[RB][CB], z[RB][CB];
 #pragma unroll
         for (int b = 0; b < RB; ++b)
 #pragma unroll
             for (int c = 0; c < CB; ++c) yr[b][c] = yn[b][c] = z[b][c] = acc_t{0, 0, 0, 0};
-        for (int rc = 0; rc < P.mp; rc += 16) {
+        for (int rc = 0; rc < P.m; rc += 16) {
             bool on[RB];
             bool any = false;
 #pragma unroll
             for (int b = 0; b < RB; ++b) {
-                const int eb = (ec + 16 * b) / 32;
-                on[b] = (eb < P.nb) && fl[eb * P.nb + rc / 32];
+                on[b] = ec + 16 * b < P.m && fl[(ec + 16 * b) / 32 * P.nb + rc / 32];
                 any |= on[b];
             }
             if (!any) continue;
@@ -130,6 +130,7 @@ __global__ void __launch_bounds__(256) k_adjoint(AdjParams P, const T *__restric
         // (rows at or beyond m: the last one, whose Y and Z are zero)
 #pragma unroll
         for (int b = 0; b < RB; ++b) {
+            if (ec + 16 * b >= P.m) break;   // uniform
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int64_t eo = (int64_t)min(ec + 16 * b + MM<T>::out_row(kk, i), P.m - 1) * N;
