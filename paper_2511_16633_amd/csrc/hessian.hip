@@ -360,10 +360,13 @@ rb_status hessian_band_impl(const rb_geometry *g, const void *G_re, const void *
     // pixels per block: [m][pb] values within 40 KiB.  For 256 < m <= 1024
     // and 32/16-bit tables a block of 1024 threads keeps 32 pixels (up to
     // 128 KiB of LDS): reads of a table row then span 64 or 128 bytes
-    // instead of 16 or 32.  Rows a thread loads at once, us for 8 / 16 / 32:
-    // FP32, three frequencies of 480^2, 64 elements 95 / 128 / 194, 128: 162 /
-    // 179 / 244, 256: 358 / 321 / 350 (64 pixels a block: 362); FP64 500 / 256^2
-    // 278 / 443 / -.  A frequency ahead where one block fills a compute unit and for
+    // instead of 16 or 32.  Rows a thread loads at once: all of its rows up to 16, half
+    // of them beyond (rounded up to even; a load beyond a thread's rows is one too
+    // many).  us with 8 or 16 by the ring's size alone / all / half / a third, FP32,
+    // two frequencies: 100 elements / 256^2 29.4 / 27.3 / 29.4 / 31.2, 130 / 728^2 (one)
+    // 156.6 / - / 123.8 / 124.1, 160 / 480^2 159.7 / - / 126.6 / 132.2, 256 / 480^2
+    // (three) 310 / - / 310 / 336 (64 pixels a block: 362); FP64 500 / 256^2 8 / 16 rows
+    // 278 / 443.  A frequency ahead where one block fills a compute unit and for
     // 16-bit tables, whose rows take half the registers (256 elements, BF16 351
     // -> 229 us; FP32 330 -> 362).
     const bool f64 = dt == RB_F64;
@@ -400,11 +403,22 @@ rb_status hessian_band_impl(const rb_geometry *g, const void *G_re, const void *
         const Int<kHbThreads> nt;
         const std::true_type ahead;
         const std::false_type now;
+        // ... at once (see above)
+        auto rows = [&](auto pbt, int rm) {
+            switch ((rm + 1) / 2 * 2) {
+                case 2: case 4: launch(pbt, Int<4>(), now, nt); break;
+                case 6: launch(pbt, Int<6>(), now, nt); break;
+                case 8: launch(pbt, Int<8>(), now, nt); break;
+                case 10: launch(pbt, Int<10>(), now, nt); break;
+                case 12: launch(pbt, Int<12>(), now, nt); break;
+                case 14: launch(pbt, Int<14>(), now, nt); break;
+                default: launch(pbt, Int<16>(), now, nt); break;
+            }
+        };
+        const int per = (P.m + kHbThreads / pb - 1) / (kHbThreads / pb);
         if constexpr (std::is_same<T, double>::value) {
-            if (pb == 16 && P.m > 128)
-                launch(Int<16>(), Int<16>(), now, nt);
-            else if (pb == 16)
-                launch(Int<16>(), Int<8>(), now, nt);
+            if (pb == 16)
+                rows(Int<16>(), per);
             else if (pb == 4)
                 launch(Int<4>(), Int<8>(), now, nt);
             else
@@ -420,10 +434,7 @@ rb_status hessian_band_impl(const rb_geometry *g, const void *G_re, const void *
         } else if (pb == 2) {
             launch(Int<2>(), Int<16>(), now, nt);
         } else if constexpr (sizeof(T) == 4) {
-            if (P.m > 128)
-                launch(Int<32>(), Int<16>(), now, nt);
-            else
-                launch(Int<32>(), Int<8>(), now, nt);
+            rows(Int<32>(), per > 16 ? (per + 1) / 2 : per);
         } else if (P.m <= 64) {
             launch(Int<32>(), Int<8>(), ahead, nt);
         } else if (P.m <= 128) {
