@@ -1012,10 +1012,13 @@ __global__ void __launch_bounds__(64 * t16_waves(HESS), 2) k_adjoint16_tr(const 
     const int row = lane & 15, kk = lane >> 4;
     const int64_t N = P.N;
     const int k = loc.k();
-    const int64_t x0 = (int64_t)loc.tile() * kT16NT;
+    // the last tile ends with the table (its first pixels are the previous one's,
+    // and not written), so that every load is whole: as the only one with loads of
+    // single values it was what a launch of few tiles waited for
+    const int64_t xt = (int64_t)loc.tile() * kT16NT, x0 = max(min(xt, N - kT16NT), (int64_t)0);
     const unsigned short *gr = reinterpret_cast<const unsigned short *>((const S *)it.Gr + (int64_t)k * P.m * N);
     const unsigned short *gi = reinterpret_cast<const unsigned short *>((const S *)it.Gi + (int64_t)k * P.m * N);
-    const bool full = x0 + kT16NT <= N;   // workgroup-uniform
+    const bool full = x0 + kT16NT <= N;   // uniform; but for tables of fewer pixels
     const S *ar = Ar + (int64_t)k * P.mp * P.mp;
     const S *ai = Ai + (int64_t)k * P.mp * P.mp;
     const S *wt = Wt + (int64_t)k * P.mp * P.mp;
@@ -1273,7 +1276,7 @@ __global__ void __launch_bounds__(64 * t16_waves(HESS), 2) k_adjoint16_tr(const 
     __syncthreads();
     if (tid < kT16NT) {
         const int64_t x = x0 + tid;
-        if (x < N) {
+        if (x >= xt && x < N) {
             const double gs = (double)gscale[k], as = ascale[k] > 0.0f ? (double)ascale[k] : 1.0;
             const double g2 = gs * gs;
             double g = 0.0, h = 0.0;
