@@ -1398,11 +1398,11 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_split(const A args) {
     const int row = lane & 15, kk = lane >> 4;
     const int64_t N = P.N;
     const int k = loc.k();
-    const int64_t x0 = (int64_t)loc.tile() * kT16NT;
+    // (the last tile ends with the table: see k_adjoint16_tr; N is at least a tile)
+    const int64_t xt = (int64_t)loc.tile() * kT16NT, x0 = min(xt, N - kT16NT);
     const float *__restrict__ gr = (const float *)it.Gr + (int64_t)k * P.m * N;
     const float *__restrict__ gi = (const float *)it.Gi + (int64_t)k * P.m * N;
-    const bool vec = x0 + kT16NT <= N;   // workgroup-uniform; rows need no alignment
-    typedef f4 f4_a4 __attribute__((aligned(4)));
+    typedef f4 f4_a4 __attribute__((aligned(4)));   // rows need no alignment
     const int64_t per = (int64_t)P.mp * P.mp;
     const _Float16 *__restrict__ ahi = (const _Float16 *)it.split_hi + 2 * k * per;
     const _Float16 *__restrict__ alo = (const _Float16 *)it.split_lo + 2 * k * per;
@@ -1421,7 +1421,7 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_split(const A args) {
     const int p4 = (tid & 31) * 4, r8 = tid >> 5;
     f4 ps;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) ps[q] = sc[min(x0 + p4 + q, N - 1)];
+    for (int q = 0; q < 4; ++q) ps[q] = sc[x0 + p4 + q];
     // of the values this thread has staged (largest of re and im): the largest,
     // and the bits of the smallest but zero, minus one
     float top = 0.0f;
@@ -1432,21 +1432,14 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_split(const A args) {
         return reinterpret_cast<const float *>(reinterpret_cast<const char *>(base) + off);
     };
     const unsigned nb4 = 4u * (unsigned)N;
-    const int xl = (int)min(N - 1 - x0, (int64_t)kT16NT);   // last pixel of the tile's range
-    auto load = [&](const float *__restrict__ g, int c, f4 (&v)[4], auto vtag) {
+    auto load = [&](const float *__restrict__ g, int c, f4 (&v)[4]) {
         const float *base = g + (int64_t)c * kT16KC * N + x0;
         const int rl = P.m - 1 - c * kT16KC;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            // rows at or beyond m read row m - 1: their A entries are zero;
-            // pixels at or beyond N read the last one: theirs are dropped
+            // rows at or beyond m read row m - 1: their A entries are zero
             const unsigned ro = (unsigned)min(r8 + 8 * j, rl) * nb4;
-            if (decltype(vtag)::value) {
-                v[j] = *reinterpret_cast<const f4_a4 *>(at(base, ro + 4u * p4));
-            } else {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) v[j][q] = *at(base, ro + 4u * (unsigned)min(p4 + q, xl));
-            }
+            v[j] = *reinterpret_cast<const f4_a4 *>(at(base, ro + 4u * p4));
         }
     };
     auto store = [&](const f4 (&vr)[4], const f4 (&vi)[4], unsigned char *d) {
@@ -1543,12 +1536,12 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_split(const A args) {
         // condition, so that the compiler's load-counter waits stay exact: the
         // rows of G at the start, used at the end, and A, whose registers are
         // in use until then, before the conversions.
-        auto kloop = [&](auto vtag) {
+        auto kloop = [&]() {
             f4 vr[4], vi[4];
             h8 a[4][EB];
             int bit = all.pop(), c = AdjChunks::chunk(bit, half);
-            load(gr, c, vr, vtag);
-            load(gi, c, vi, vtag);
+            load(gr, c, vr);
+            load(gi, c, vi);
             load_a(c, a);
             lds_barrier();   // the previous pass is done with the tile buffers
             store(vr, vi, sT[0]);
@@ -1558,8 +1551,8 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_split(const A args) {
                 const bool on = mine.has(bit);
                 bit = all.pop();
                 c = AdjChunks::chunk(bit, half);
-                load(gr, c, vr, vtag);
-                load(gi, c, vi, vtag);
+                load(gr, c, vr);
+                load(gi, c, vi);
                 __builtin_amdgcn_sched_barrier(0);
                 if (on) mma(s, a);
                 load_a(c, a);
@@ -1569,15 +1562,9 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_split(const A args) {
             lds_barrier();
             if (mine.has(bit)) mma(s, a);
         };
-        if (nstep > 0) {   // workgroup-uniform
-            if (vec)
-                kloop(std::true_type());
-            else
-                kloop(std::false_type());
-        }
+        if (nstep > 0) kloop();   // workgroup-uniform
         // fused epilogue: Re sum_e conj(G_e) Y_e, with G_e in FP32.  Rows at or
-        // beyond m read row m - 1 (their Y is zero), pixels at or beyond N the
-        // last one (dropped below).
+        // beyond m read row m - 1 (their Y is zero).
         if (e0 < P.mp) {   // wave-uniform
             const float *br = gr + (int64_t)e0 * N + x0, *bi = gi + (int64_t)e0 * N + x0;
             const int rl = P.m - 1 - e0;
@@ -1589,7 +1576,7 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_split(const A args) {
                     float ger[8], gei[8];
 #pragma unroll
                     for (int cb = 0; cb < 8; ++cb) {
-                        const unsigned o = ro + 4u * (unsigned)min(16 * cb + row, xl);
+                        const unsigned o = ro + 4u * (unsigned)(16 * cb + row);
                         ger[cb] = *at(br, o);
                         gei[cb] = *at(bi, o);
                     }
@@ -1615,7 +1602,7 @@ __global__ void __launch_bounds__(256, 2) k_adjoint_split(const A args) {
     __syncthreads();
     if (tid < kT16NT) {
         const int64_t x = x0 + tid;
-        if (x < N) {
+        if (x >= xt) {
             const double g = ((double)sred[0][tid] + (double)sred[1][tid]) +
                              ((double)sred[2][tid] + (double)sred[3][tid]);
             const double s = (double)split_scale(it.ascale[k], kSplitTopA) * (double)sc[x];
@@ -1711,7 +1698,8 @@ static bool adj_split(const rb_geometry *g, int nf, rb_dtype dt) {
     const int npass = (pad_m(g->m) + kT16NE - 1) / kT16NE;
     const int64_t tiles = blocks_for((int64_t)g->nx * g->ny, kT16NT);
     if (nf * tiles * (adj_groups(g, dt) > 1 ? npass : 1) <= 256) return false;
-    if ((int64_t)g->nx * g->ny >= (int64_t)1 << 25) return false;   // 32-bit offsets within 32 rows
+    // 32-bit offsets within 32 rows; a whole tile
+    if ((int64_t)g->nx * g->ny >= (int64_t)1 << 25 || (int64_t)g->nx * g->ny < kT16NT) return false;
     // its high operands live in place of W, the low ones and the scales in
     // the Hessian partials, neither of which a gradient needs
     const int64_t mp = pad_m(g->m), N = (int64_t)g->nx * g->ny;
