@@ -23,9 +23,9 @@
 // and blocks whose weights are all zero (the receiver selection removes a
 // band around the diagonal), are skipped: neither staged nor multiplied.
 // Against contracting both orders (1024 elements / 1100^2, four frequencies;
-// bound by the matrix cores): FP32 209.9 -> 107.9 ms, BF16 32.8 -> 20.0 ms;
-// 256 / 480^2, three frequencies, FP32: 2.31 -> 1.59 ms (three or four
-// chunks per pass are left, so a pass's fixed cost weighs more).
+// bound by the matrix cores): FP32 (on its own cores) 209.9 -> 105.6 ms, BF16
+// 32.9 -> 17.2 ms; 256 / 480^2, three frequencies, FP32: 2.31 -> 1.46 ms (three
+// or four chunks per pass are left, so a pass's fixed cost weighs more).
 #include <algorithm>
 #include <cmath>
 #include <mutex>
@@ -932,8 +932,9 @@ __device__ __forceinline__ void t16_stage_async(const unsigned short *__restrict
 // the MFMAs of the step before: 16 bytes of row r from pixel x on, in one load
 // that needs no alignment unless the table's pixels end within the tile (`full`
 // is uniform).  With 2-byte loads, waited for when issued, and now, FP16, two
-// frequencies: 130 elements / 301x255 178 -> 123 us, with the Hessian diagonal
-// 292 -> 186, 100 / 256^2 89 -> 62 us, 1000 / 301x255 (one frequency) 968 -> 443.
+// frequencies: 130 elements / 301x255 178 -> 102 us, with the Hessian diagonal
+// (eight waves, see t16_waves) 292 -> 120, 100 / 256^2 89 -> 54 us, 1000 / 301x255
+// (one frequency) 968 -> 404.
 typedef unsigned short t16us8 __attribute__((ext_vector_type(8)));
 typedef t16us8 t16us8_u __attribute__((aligned(2)));
 __device__ __forceinline__ t16us8 t16_load(const unsigned short *__restrict__ g, int r, int64_t N, int64_t x,
@@ -978,7 +979,7 @@ __device__ __forceinline__ void t16_store_tile(const t16us8 (&v)[16 / NW], int m
 // Hessian diagonal: 130 elements / 301x255, two frequencies, 186 -> 152 us,
 // 256 / 480^2, three, 764 -> 675, 1024 / 480^2, one, 1.89 -> 1.68 ms; with
 // |G|^2 by fused multiply-adds (20 instead of 44 instructions a fragment in
-// FP16) 145, 608 and 1.46 ms.
+// FP16) and the sum of its roundings taken off at the end 120, 615 and 1.51 ms.
 constexpr int t16_waves(bool hess) { return hess ? 8 : 4; }
 
 template <typename S, bool HESS, bool DIRECT, typename A>
@@ -1316,16 +1317,17 @@ void launch_adjoint16(const AdjTask &t, dim3 grid, const A &arg, hipStream_t st)
 // FP16.  hi hi + hi lo + lo (2^-12 hi) on the 16x16x32 FP16 cores (products exact,
 // FP32 accumulation) keeps about 22 bits of every product, and an MFMA sums 32
 // products at a time instead of 4, so that the result is nearer to FP64 than
-// the FP32 cores' (relative L2 error of the gradient: 1024 elements / 1100^2 8.1e-8
-// -> 6.3e-8, 256 / 480^2 1.4e-7 -> 1.2e-7; 65 to 512 elements, 128x150 to 256^2, 0.62
-// to 0.88 of it).
+// the FP32 cores' (relative L2 error of the gradient, ordered pairs on the FP32 cores
+// and so: 256 elements / 480^2, three frequencies, 1.7e-7 -> 1.0e-7, 130 / 301x255, two,
+// 1.9e-7 -> 1.3e-7; 65 to 1000 elements, 0.6 to 1.0 of it).
 //
-// 1024 elements / 1100^2, four frequencies: 107.9 ms on the FP32 cores, 43.0
+// 1024 elements / 1100^2, four frequencies: 105.6 ms on the FP32 cores, 44.3
 // ms here (12 MFMAs per complex product of blocks: 1.1 PFLOP/s).  The matrix
-// cores are busy 0.55 of the time at 1.9 GHz, the clock that the card's power
-// leaves (2.3 GHz at 0.36 busy), so what is left is mostly power.  256 / 480^2,
-// three frequencies: 1.59 -> 0.77 ms.  On the way there: rows of G loaded half
-// a chunk ahead 55.1 ms, passes four chunks apart (AdjChunks) 64.8 ms.
+// cores are busy 0.53 of the time at 2.0 GHz, to which the card's power limits the
+// clock (kernels that draw less run at 2.4); a large FP16 product of the library
+// reaches 1.23 PFLOP/s.  256 / 480^2, three frequencies: 1.46
+// -> 0.75 ms.  On the way there: rows of G loaded half a chunk ahead 55.1 ms,
+// passes four chunks apart (AdjChunks) 64.8 ms.
 //
 // Scales: A by its largest magnitude per frequency, brought to 2^15; G per
 // (frequency, pixel) by its largest magnitude over kSplitRows sampled elements,
@@ -1336,7 +1338,9 @@ void launch_adjoint16(const AdjTask &t, dim3 grid, const A &arg, hipStream_t st)
 // for A, 2^-7 to 2^4.4 of the sample for G).  Whatever lies outside of these
 // ranges, but zeros, is computed from FP32 by k_adjoint_f32_list: of a frequency
 // with a smaller A all work items, without delay (bad); otherwise those whose
-// workgroup has staged such a G.
+// workgroup has staged such a G.  (Phantom tables have them: in 28 of 1,800 tiles
+// at 256 elements, in 172 of 9,454 at 1024, pixels just outside the ring that a few
+// elements cover and none of the sampled ones: 1.0 ms for these tiles beside 41.9.)
 //
 // Workgroup tile, receiver chunks, transposing reads and LDS swizzle are
 // those of k_adjoint16_tr; here a chunk's 32 x 128 FP32 tile passes through
@@ -1663,7 +1667,7 @@ struct AdjWs {
 // workgroup of its own once there are four or more, the passes of a tile
 // adjacent in logical order and on one XCD (AdjOneSplit), so that the
 // tile's G rows come from HBM once and from L2 for the other passes (measured
-// while every ordered pair was contracted, FP32, 1024 elements / 1100^2: 221.6 ->
+// while every ordered pair was contracted, FP32 cores, 1024 elements / 1100^2: 221.6 ->
 // 209.6 ms per 4-frequency launch; 16-bit: 51.9 -> 47.6 ms).  Ordering the split workgroups pass-major instead (all
 // workgroups in flight on one pass, sharing its W.D rows) was slower: 224.7
 // and 60.0 ms; so was nothing in between: dealing a tile's groups into 2
@@ -1689,10 +1693,10 @@ static size_t split_ints(const rb_geometry *g, int nf, rb_dtype dt) {
 // Whether a gradient-only FP32 problem takes k_adjoint_split: from 65
 // elements (a pass has 128, and at 64 half of its waves are idle) and with
 // more workgroups than compute units.  us per call, k_adjoint_f32 against
-// k_adjoint_split, two frequencies: 64 elements / 480^2 156 / 163, 80 / 480^2
-// 291 / 200, 96 / 128^2 (256 workgroups) 39 / 43, 96 / 256^2 103 / 75, 128 /
-// 256^2 130 / 86, 256 / 181^2 209 / 122, 512 / 480^2 2947 / 1314; one
-// frequency, 256 / 128x150 (300 workgroups) 70 / 61.
+// k_adjoint_split, two frequencies: 64 elements / 480^2 129 / 134, 80 / 480^2
+// 254 / 168, 96 / 128^2 (256 workgroups) 27 / 31, 96 / 256^2 82 / 61, 128 /
+// 256^2 106 / 73, 130 / 301x255 238 / 117, 256 / 181^2 187 / 89, 512 / 480^2 2873 /
+// 1363; one frequency, 256 / 128x150 (300 workgroups) 54 / 50.
 static bool adj_split(const rb_geometry *g, int nf, rb_dtype dt) {
     if (dt != RB_F32 || g->m <= 64) return false;
     const int npass = (pad_m(g->m) + kT16NE - 1) / kT16NE;
@@ -1763,8 +1767,8 @@ rb_status adjoint_prepare(const rb_geometry *g, const void *G_re, const void *G_
         // The Hessian diagonal by itself, its one product on the FP32 cores,
         // before the gradient's pieces take the place of W (gradient and
         // diagonal as four products there, and so: 1024 elements / 1100^2, four
-        // frequencies, 159 -> 94 ms, 256 / 480^2, three, 2.21 -> 1.50, 96 / 256^2,
-        // two, 129 -> 122 us)
+        // frequencies, 156 -> 89 ms, 256 / 480^2, three, 2.18 -> 1.44, 96 / 256^2,
+        // two, 113 -> 105 us)
         k_adj_prep<float, false, 1><<<gp, 256, 0, st>>>(g->m, P.mp, d_res, w_data, nullptr, (float *)w.Ar,
                                                         (float *)w.Ai, (float *)w.Wt, w.flags);
         RB_LAUNCHED();

@@ -50,7 +50,7 @@ struct AdjTask {
 
 struct FwdParams {
     int m, mp, nf, ntl, ntri, nsplit;
-    int dmin;              // >= 32: diagonal 32 x 32 blocks need not be computed
+    int dmin;              // >= 32: pairs closer than this need not be computed
     int64_t N, kchunk;
     double cg[RB_MAX_NF];  // omega^2 h^2
 };
@@ -73,9 +73,9 @@ rb_status adjoint_prepare(const rb_geometry *g, const void *G_re, const void *G_
 rb_status adjoint_run(const AdjTask &task, hipStream_t st);
 rb_status adjoint_run_grouped(AdjTask *const *tasks, int n, hipStream_t st);
 // d_out = J delta, [nf][m][m] complex.  With dmin >= 32 (a caller that
-// weights every pair of circular index distance below dmin by zero) the
-// 32/16-bit kernels may return 0 for the pairs of a diagonal 32 x 32 block,
-// all of which lie below that distance.
+// weights every pair of circular index distance below dmin by zero) those
+// pairs are returned as 0, whatever the type, and the 32/16-bit kernels skip
+// the tiles and blocks that hold no other pair.
 rb_status forward_impl(const rb_geometry *g, const void *G_re, const void *G_im, const float *gscale,
                        rb_dtype dt, const double *freqs, int nf, const double *delta, double *d_out, void *ws,
                        size_t ws_bytes, hipStream_t st, int dmin = 0);

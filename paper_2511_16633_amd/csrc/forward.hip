@@ -649,12 +649,12 @@ __device__ __forceinline__ int f16_off(int row, int ch) { return row * 64 + 16 *
 // and waves 4 to 7, which share their SIMDs, multiply first, so that the matrix
 // cores work while vector instructions convert.
 //
-// 1024 elements / 1100^2, four frequencies: 139.2 ms on the FP32 cores, 72.5
-// here (12 MFMAs per complex product of blocks: 1.0 PFLOP/s, as the
-// backprojection, whose clock power holds at 1.9 GHz); 256 / 480^2, three
-// frequencies: 1.43 -> 0.80 ms; 1024 / 255x301 (rows not 16-byte aligned), two:
-// 11.7 -> 2.5 ms.  Relative L2 error against FP64: 256 / 480^2 5.6e-7 -> 1.2e-7, 97 /
-// 301x255 1.5e-7 -> 6e-8.  Four waves of 64 x 64 with 512 registers each spilled:
+// 1024 elements / 1100^2, four frequencies: 130.2 ms on the FP32 cores, 68.5
+// here (12 MFMAs per complex product of blocks: 0.91 PFLOP/s, the matrix cores busy
+// 0.44 of the time at 2.0 GHz); 256 / 480^2, three frequencies: 1.36 -> 0.78 ms; 1024 /
+// 255x301 (rows not 16-byte aligned), two: 11.6 -> 2.2 ms.  Relative L2 error
+// against FP64, ordered pairs on the FP32 cores and so: 256 / 480^2 4.7e-7 -> 1.0e-7, 97 /
+// 301x255 1.2e-7 -> 4.8e-8.  Four waves of 64 x 64 with 512 registers each spilled:
 // the compiler moved accumulators between register files at every step.
 constexpr int kFsT = 128, kFsKC = 32, kFsArr = kFsT * kFsKC * 2, kFsSamples = 256;
 constexpr int kFsTop = 8;
@@ -1384,7 +1384,7 @@ __global__ void __launch_bounds__(512, 2) k_forward16_wide(FwdParams P, const S 
 // distinct banks.  Pieces beyond the table's last pixel come from the zeros
 // after delta.  BF16, 1024 elements / 1100^2, four frequencies: 34.9 (pieces of
 // 64 bytes, k_forward16_wide) -> 22.6 ms, 0.90 PFLOP/s, near the 1.0 to 1.1 at
-// which the card's power limits its clock; 1024 / 480^2, one, 1.19 -> 1.02 ms.
+// which the card's power limits its clock; 1024 / 480^2, one, 1.19 -> 0.99 ms.
 // (Direct loads of the e rows one step later, behind the conversion of the r
 // rows, so that it need not wait for them: 23.7 ms.)
 constexpr int kDArrE = kWE * 128;   // one array of the e side (bytes)
@@ -1613,11 +1613,14 @@ static bool fwd16_wide(const rb_geometry *g, rb_dtype dt) {
 }
 
 // FP32 tables on the FP16 cores: rings that fill more than half of a 128-element
-// tile, and problems large enough to pay for its two more launches.  us per
-// call on the FP32 cores / split, two frequencies: 64 elements / 480^2 108 /
-// 191; 96 / 64x66 24 / 32, 96 / 128^2 42 / 39, 96 / 480^2 300 / 203; 256 /
-// 64x66 43 / 44, 256 / 128^2 89 / 68, 256 / 255x301 909 / 305; 512 / 32^2 54 / 62,
-// 512 / 64x66 98 / 81; 1024 / 480^2 12272 / 7100.
+// tile, and grids whose sums are long enough for its accuracy and, with small rings,
+// for its two more launches.  us per call on the FP32 cores / split, two
+// frequencies: 64 elements / 480^2 127 / 159; 96 / 64x66 25 / 26, 96 / 128^2 44 / 35,
+// 96 / 480^2 297 / 170, 97 / 301x255 234 / 69; 256 / 64x66 48 / 41, 256 / 128^2 101 / 66,
+// 256 / 255x301 925 / 229; 512 / 64x66 105 / 64; 1024 / 480^2 12270 / 6610.  At 512 / 32^2 it
+// would be 48 / 41, but with splits of 16 pixels the FP32 cores are nearer to
+// FP64 there (relative L2 error at 257 to 1000 elements, split against ordered pairs on
+// the FP32 cores: 16^2 up to 1.24 of it, 32^2 1.11; from 48^2 on below it).
 static bool fwd32_split(const rb_geometry *g, rb_dtype dt) {
     return dt == RB_F32 && g->m > 64 && (int64_t)g->nx * g->ny >= (g->m > 256 ? 4096 : 8192);
 }

@@ -394,7 +394,9 @@ __global__ void __launch_bounds__(kWT) k_zlist(int m, int dmin, int nb, const do
 // and the ranks of ties and of zeroed pairs pass through LDS.  The same keys,
 // digits and tie order as above, so the same weights and list.  At 64 elements
 // and two frequencies the thirteen launches above took 117 us, most of it
-// latency, and this takes 24 (the whole FP64 set 852 -> 771 us).
+// latency, and this takes 24.  Up to all that the registers hold it is the faster:
+// whole sets, two frequencies, with the launches above / with this, FP64 / 64^2, 16
+// elements 426 / 374 us, 64: 502 / 412, 128: 624 / 500; FP32 / 128^2, 128: 870 / 756.
 constexpr int kWSmall = 16384, kWST = 1024, kWSU = kWSmall / kWST;
 __global__ void __launch_bounds__(kWST) k_wsmall(int m, int dmin, int64_t kzero, const double *__restrict__ pmeas,
                                                  double *__restrict__ W, int zcap, int2 *__restrict__ zl,
