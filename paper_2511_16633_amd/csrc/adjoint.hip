@@ -239,19 +239,23 @@ __global__ void __launch_bounds__(256) k_adj_amax(int m, int nb, const double *_
 // In 16 bits the mean of a pair is rounded once where the pair was twice: the
 // squared error is the same where its two values are independent or equal, up to
 // twice as large where they are close (residuals of reciprocal data with noise).
-// A block whose squared errors add up to more than kLowRatio times those of the
-// ordered pairs gets flag 3, if its J is odd or the ring's last, and the low-order
-// parts of A, the means less their 16-bit values, lie in the place of the block
-// (J, I), which is not kept.  The contraction adds those in k-steps of their own:
-// with half of the blocks free of rounding errors the sum's is that of the ordered
-// pairs again (relative error of the gradient, 256 elements, residual reciprocal but
-// for 5 %, FP16: 0.30 2^-11, without these 0.41 2^-11, with both orders of a pair 0.31
-// 2^-11).  BF16, gradient, both orders / folded / with such steps: 1024 / 1100^2, four
-// frequencies, 32.9 / 17.2 / 23.5 ms, 256 / 480^2, three, 468 / 346 / 431 us.  (Up to
-// kAdjLowBlocks blocks: see adj_chunks.)
+// A block whose squared errors add up to more than kLowRatio + kLowDoubt / sqrt(pairs)
+// times those of the ordered pairs gets flag 3, if its J is odd or the ring's last,
+// and the low-order parts of A, the means less their 16-bit values, lie in the place
+// of the block (J, I), which is not kept.  The contraction adds those in k-steps of
+// their own: with half of the blocks free of rounding errors the sum's is that of the
+// ordered pairs again (relative error of the gradient, 256 elements, residual
+// reciprocal but for 5 %, FP16: 0.30 2^-11, without these 0.41 2^-11, with both orders
+// of a pair 0.31 2^-11).  BF16, gradient, both orders / folded / with such steps: 1024 /
+// 1100^2, four frequencies, 32.9 / 17.2 / 23.5 ms, 256 / 480^2, three, 468 / 346 / 431 us.
+// (Up to kAdjLowBlocks blocks: see adj_chunks.)
+// A ratio of few pairs says little; the line is three or more standard deviations
+// from that of independent values.  (At kLowRatio alone blocks at the edge of the
+// selected band got the flag by chance: FP16, 880 / 268x134, four frequencies, 623 us,
+// now 599.)
 // Two blocks around the ring would gain no k-step by it (the pass stages both
 // chunks anyway), so there both orders are kept, each as the diagonal blocks.
-constexpr float kLowRatio = 1.3f;
+constexpr float kLowRatio = 1.3f, kLowDoubt = 4.0f;
 constexpr int kAdjLowBlocks = 64;
 template <typename T, bool SCALED, int LAYOUT = 0>
 __global__ void __launch_bounds__(256) k_adj_prep(int m, int mp, const double *__restrict__ d,
@@ -304,7 +308,8 @@ __global__ void __launch_bounds__(256) k_adj_prep(int m, int mp, const double *_
     // few pairs to tell)
     const bool split = SCALED && fold && ((J & 1) || J == nb - 1) && 32 * max(I, J) + 16 <= m &&
                        nb <= kAdjLowBlocks;
-    float err = 0.0f;   // squared errors: of twice the means less kLowRatio times the pairs'
+    float err = 0.0f, errp = 0.0f;   // squared errors: of twice the means less kLowRatio the pairs'; the pairs'
+    int pairs = 0;                   // of the wave
     bool any = false;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -332,10 +337,12 @@ __global__ void __launch_bounds__(256) k_adj_prep(int m, int mp, const double *_
                     const float r = (float)((a + b) * half) - MM16<T>::to_f(A[o]);
                     const float e = off((float)(a * (2.0 * half))) + off((float)(b * (2.0 * half)));
                     err += 4.0f * r * r - kLowRatio * e * e;
+                    errp += e * e;
                     A[lo] = cvt<T>((double)r);
                 };
                 part(lr[0][q], tr[col][i], Ar);
                 part(li[0][q], ti[col][i], Ai);
+                pairs += __popcll(__ballot(wv != 0.0));
             }
         } else if (shi) {
             const float sa = split_scale(as, kSplitTopA);
@@ -350,14 +357,29 @@ __global__ void __launch_bounds__(256) k_adj_prep(int m, int mp, const double *_
             if (top > 0.0f && top < kSplitMinA) bad[k] = 1;
         }
     }
-    __shared__ float se[4];
+    __shared__ float se[4], sp[4];
+    __shared__ int sn[4];
     if (split) {
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) err += __shfl_xor(err, o);
-        if ((threadIdx.x & 63) == 0) se[threadIdx.x >> 6] = err;
+        for (int o = 32; o > 0; o >>= 1) {
+            err += __shfl_xor(err, o);
+            errp += __shfl_xor(errp, o);
+        }
+        if ((threadIdx.x & 63) == 0) {
+            se[threadIdx.x >> 6] = err;
+            sp[threadIdx.x >> 6] = errp;
+            sn[threadIdx.x >> 6] = pairs;
+        }
     }
     const int on = __syncthreads_or(any);
-    if (threadIdx.x == 0) *fl = on ? (split && (se[0] + se[1]) + (se[2] + se[3]) > 0.0f ? 3 : 1) : 0;
+    if (threadIdx.x == 0) {
+        bool low = false;
+        if (split) {
+            const float n = (float)(sn[0] + sn[1] + sn[2] + sn[3]);
+            low = ((se[0] + se[1]) + (se[2] + se[3])) * sqrtf(n) > kLowDoubt * ((sp[0] + sp[1]) + (sp[2] + sp[3]));
+        }
+        *fl = on ? (low ? 3 : 1) : 0;
+    }
 }
 
 // The receiver chunks (32 receivers each, at most 128) an emitter pass works
