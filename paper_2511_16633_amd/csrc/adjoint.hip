@@ -247,7 +247,7 @@ __global__ void __launch_bounds__(256) k_adj_amax(int m, int nb, const double *_
 // ordered pairs again (relative error of the gradient, 256 elements, residual
 // reciprocal but for 5 %, FP16: 0.30 2^-11, without these 0.41 2^-11, with both orders
 // of a pair 0.31 2^-11).  BF16, gradient, both orders / folded / with such steps: 1024 /
-// 1100^2, four frequencies, 32.9 / 17.2 / 23.5 ms, 256 / 480^2, three, 468 / 346 / 431 us.
+// 1100^2, four frequencies, 32.4 / 16.8 / 22.8 ms, 256 / 480^2, three, 463 / 337 / 423 us.
 // (Up to kAdjLowBlocks blocks: see adj_chunks.)
 // A ratio of few pairs says little; the line is three or more standard deviations
 // from that of independent values.  (At kLowRatio alone blocks at the edge of the
@@ -342,6 +342,7 @@ __global__ void __launch_bounds__(256) k_adj_prep(int m, int mp, const double *_
                 };
                 part(lr[0][q], tr[col][i], Ar);
                 part(li[0][q], ti[col][i], Ai);
+                Wt[lo] = T(0.0f);
                 pairs += __popcll(__ballot(wv != 0.0));
             }
         } else if (shi) {
@@ -407,35 +408,42 @@ struct AdjChunks {
     }
 };
 
-// The chunks of NQ emitter blocks from eb0 on: `all` of any of them, `mine`
+// The chunks of NQ emitter blocks from eb0 < nb on: `all` of any of them, `mine`
 // of block eb0 + q.  With LOW, those with low-order parts (k_adj_prep) follow as
 // bits 64 and up, which rings of up to kAdjLowBlocks blocks do not use otherwise.
+// (Clamped, not guarded, so that the loads are in flight together: BF16, 256
+// elements / 480^2, three frequencies, 360 -> 343 us, FP32 781 -> 769.  The flags of a
+// chunk are joined before they are voted on: with votes and conditions block by
+// block some of the conditions were spilled, and waiting for them took 1 us of each
+// workgroup: FP16, four frequencies, 61 / 635x317 171 -> 159 us, 272 / 608x304 703 -> 655.)
 template <int NQ, bool LOW = false>
 __device__ __forceinline__ void adj_chunks(const uint8_t *__restrict__ fl, int nb, int eb0, int q,
                                            AdjChunks &all, AdjChunks &mine) {
     const int lane = threadIdx.x & 63, half = (nb + 1) / 2;
     all = mine = AdjChunks{0, 0};
+    auto flags = [&](int bit, unsigned &a, unsigned &w) {   // of any block, of block eb0 + q
+        const int c = AdjChunks::chunk(bit, half);
+        const uint8_t *f = fl + min(c, nb - 1);
+        a = 0;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        if (h && half <= 32) break;   // uniform
-        const int bit = 64 * h + lane, c = AdjChunks::chunk(bit, half);
+        for (int i = 0; i < NQ; ++i) a |= f[min(eb0 + i, nb - 1) * nb];   // (row nb - 1 is one of them)
+        w = f[min(eb0 + q, nb - 1) * nb];
         const bool ok = (bit >> 1) < half && c < nb;
-        // (clamped, not guarded, so that the loads are in flight together: BF16,
-        // 256 elements / 480^2, three frequencies, 360 -> 343 us, FP32 781 -> 769)
-        uint8_t f[NQ];
-#pragma unroll
-        for (int i = 0; i < NQ; ++i) f[i] = fl[min(eb0 + i, nb - 1) * nb + min(c, nb - 1)];
-#pragma unroll
-        for (int i = 0; i < NQ; ++i) {
-            const uint64_t b = __ballot(ok && eb0 + i < nb && f[i] != 0);
-            (h ? all.m1 : all.m0) |= b;
-            if (i == q) (h ? mine.m1 : mine.m0) = b;
-            if (LOW && !h && half <= 32) {
-                const uint64_t l = __ballot(ok && eb0 + i < nb && f[i] > 1);
-                all.m1 |= l;
-                if (i == q) mine.m1 = l;
-            }
-        }
+        a = ok ? a : 0;
+        w = ok && eb0 + q < nb ? w : 0;
+    };
+    unsigned a, w;
+    flags(lane, a, w);
+    all.m0 = __ballot(a != 0);
+    mine.m0 = __ballot(w != 0);
+    if (LOW) {
+        all.m1 = __ballot(a > 1);
+        mine.m1 = __ballot(w > 1);
+    }
+    if (half > 32) {   // uniform
+        flags(64 + lane, a, w);
+        all.m1 |= __ballot(a != 0);
+        mine.m1 |= __ballot(w != 0);
     }
 }
 
@@ -1083,12 +1091,14 @@ __global__ void __launch_bounds__(64 * t16_waves(HESS), 2) k_adjoint16_tr(const 
         const int eb = min(e0 >> 5, P.nb - 1);
         auto load_a = [&](int bit, V (&va)[EB], V (&vi)[EB], V (&vw)[EB]) {
             const int c = chunk(bit);
-            const int64_t co = (int64_t)(bit <= cmask ? eb * P.nb + c : c * P.nb + eb) * 1024;   // uniform
+            const bool lo = bit > cmask;
+            const int bi = lo ? c : eb, bj = lo ? eb : c;
+            const unsigned co = (unsigned)(bi * P.nb + bj) * 1024u;   // uniform
 #pragma unroll
             for (int b = 0; b < EB; ++b) {
                 va[b] = *reinterpret_cast<const V *>(ar + co + 512 * b + 8 * lane);
                 vi[b] = *reinterpret_cast<const V *>(ai + co + 512 * b + 8 * lane);
-                if (HESS) vw[b] = *reinterpret_cast<const V *>(wt + co + 512 * b + 8 * lane);
+                if (HESS) vw[b] = *reinterpret_cast<const V *>(wt + co + 512 * b + 8 * lane);   // (0 for low-order parts)
             }
         };
         // the pass's receiver chunks: `all` of its four waves (staged), `mine`
@@ -1134,7 +1144,7 @@ __global__ void __launch_bounds__(64 * t16_waves(HESS), 2) k_adjoint16_tr(const 
                 __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
             }
             lds_barrier();
-            const bool on = mine.has(b0), low = b0 > cmask;
+            const bool on = mine.has(b0);
             if (has_a) load_a(b1, na, ni, nw);
             __builtin_amdgcn_sched_barrier(0);
             if (has_t) {
@@ -1167,7 +1177,7 @@ __global__ void __launch_bounds__(64 * t16_waves(HESS), 2) k_adjoint16_tr(const 
                     yr[b][cb] = MM16<S>::mma(vi[b], bi, yr[b][cb]);
                     yn[b][cb] = MM16<S>::mma(va[b], bi, yn[b][cb]);
                     yn[b][cb] = MM16<S>::mma(nva[b], br, yn[b][cb]);
-                    if (HESS) z[b][cb] = MM16<S>::mma(low ? V{} : vw[b], b2, z[b][cb]);   // W: no low-order parts
+                    if (HESS) z[b][cb] = MM16<S>::mma(vw[b], b2, z[b][cb]);
                 }
             }
         };
