@@ -1644,11 +1644,13 @@ static FwdParams fwd_params(const rb_geometry *g, const double *freqs, int nf, r
     const int ntri = wide ? P.ntl / 2 * (P.ntl / 2 + 1) : P.ntl * (P.ntl + 1) / 2;
     // about four rounds of resident workgroups (two per CU, four for the
     // FP32 kernel with direct loads), rounded down so the last round is full;
-    // but no split is shorter than kMinSplitPx, and with the large tiles, beyond
-    // one round, than kFewSplitPx pixels: a split's partial sums (a tile of them,
-    // written and read once) cost as much as some tens of pixels.  (The small
-    // tiles need the waves: 256 elements / 128^2 FP64 245 us, with the longer
-    // splits 304; 97 / 301x255 FP16 200 and 235; 768 / 64x66 FP16 68 and 82.)  The
+    // but no split is shorter than kMinSplitPx, and with the large tiles and 16-bit
+    // rows of whole 16-byte pieces, beyond one round, than kFewSplitPx pixels: a
+    // split's partial sums (a tile of them, written and read once) cost as much as some
+    // tens of pixels (BF16, without / with: 97 elements / 230x152, three frequencies,
+    // 42.9 / 33.2 us, 256 / 128^2, two, 44.0 / 35.4, 768 / 64x66, two, 60.1 / 56.2).  The
+    // other small tiles need the waves: 256 elements / 128^2 FP64 245 us, with the longer
+    // splits 304; 40 / 655x501, rows not aligned, BF16 235 and 280.  The
     // FP32 cores' kernels, which add to a split's sums once per four pixels, keep
     // them as short as 16 pixels: the splits are added in FP64, and with 64
     // pixels or 512 the error of the result is up to 2.9 times as large (20
@@ -1657,7 +1659,8 @@ static FwdParams fwd_params(const rb_geometry *g, const double *freqs, int nf, r
     // 128^2 FP32 37 / 26 / 25 / 44, BF16 33 / 27 / 28 / 31, FP64 - / 30 / 34 / -.
     const int resident = (fs || wide ? 1 : (fwd32_direct(g, dt) ? 4 : 2)) * device_cus();
     int64_t most = dt == RB_F32 && !fs ? (P.N + kMinSplitPx32 - 1) / kMinSplitPx32 : P.N / kMinSplitPx;
-    if (fs || wide)
+    const bool small16 = (dt == RB_BF16 || dt == RB_F16) && !wide;
+    if (fs || wide || (small16 && P.N % 8 == 0))
         most = std::max<int64_t>(P.N / kFewSplitPx, std::min<int64_t>(most, resident / (ntri * nf)));
     if (dt == RB_F64)   // within one round, a step each (16 elements / 32^2: 16.6 -> 11.6 us)
         most = std::max<int64_t>(most, std::min<int64_t>((P.N + 15) / 16, resident / (ntri * nf)));
