@@ -248,7 +248,7 @@ __global__ void __launch_bounds__(256) k_adj_amax(int m, int nb, const double *_
 // reciprocal but for 5 %, FP16: 0.30 2^-11, without these 0.41 2^-11, with both orders
 // of a pair 0.31 2^-11).  BF16, gradient, both orders / folded / with such steps: 1024 /
 // 1100^2, four frequencies, 32.4 / 16.8 / 22.8 ms, 256 / 480^2, three, 463 / 337 / 423 us.
-// (Up to kAdjLowBlocks blocks: see adj_chunks.)
+// (Up to kAdjLowBlocks blocks: see adj_chunks_low.)
 // A ratio of few pairs says little; the line is three or more standard deviations
 // from that of independent values.  (At kLowRatio alone blocks at the edge of the
 // selected band got the flag by chance: FP16, 880 / 268x134, four frequencies, 623 us,
@@ -408,19 +408,43 @@ struct AdjChunks {
     }
 };
 
-// The chunks of NQ emitter blocks from eb0 < nb on: `all` of any of them, `mine`
-// of block eb0 + q.  With LOW, those with low-order parts (k_adj_prep) follow as
-// bits 64 and up, which rings of up to kAdjLowBlocks blocks do not use otherwise.
-// (Clamped, not guarded, so that the loads are in flight together: BF16, 256
-// elements / 480^2, three frequencies, 360 -> 343 us, FP32 781 -> 769.  The flags of a
-// chunk are joined before they are voted on: with votes and conditions block by
-// block some of the conditions were spilled, and waiting for them took 1 us of each
-// workgroup: FP16, four frequencies, 61 / 635x317 171 -> 159 us, 272 / 608x304 703 -> 655.)
-template <int NQ, bool LOW = false>
+// The chunks of NQ emitter blocks from eb0 on: `all` of any of them, `mine` of block
+// eb0 + q.
+template <int NQ>
 __device__ __forceinline__ void adj_chunks(const uint8_t *__restrict__ fl, int nb, int eb0, int q,
                                            AdjChunks &all, AdjChunks &mine) {
     const int lane = threadIdx.x & 63, half = (nb + 1) / 2;
     all = mine = AdjChunks{0, 0};
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        if (h && half <= 32) break;   // uniform
+        const int bit = 64 * h + lane, c = AdjChunks::chunk(bit, half);
+        const bool ok = (bit >> 1) < half && c < nb;
+        // (clamped, not guarded, so that the loads are in flight together: BF16,
+        // 256 elements / 480^2, three frequencies, 360 -> 343 us, FP32 781 -> 769)
+        uint8_t f[NQ];
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) f[i] = fl[min(eb0 + i, nb - 1) * nb + min(c, nb - 1)];
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) {
+            const uint64_t b = __ballot(ok && eb0 + i < nb && f[i] != 0);
+            (h ? all.m1 : all.m0) |= b;
+            if (i == q) (h ? mine.m1 : mine.m0) = b;
+        }
+    }
+}
+
+// The same of eb0 < nb, with the chunks with low-order parts (k_adj_prep) as bits 64
+// and up, which rings of up to kAdjLowBlocks blocks do not use otherwise.  A chunk's
+// flags are joined before the vote: voted on block by block, with the low-order
+// parts, some of the conditions were spilled, and waiting for them took 1 us of each
+// workgroup (FP16, four frequencies, 61 elements / 635x317 171 -> 159 us, 272 / 608x304
+// 703 -> 655).  In the FP32 kernels this form is the one that spills more (256 / 480^2,
+// three frequencies, 720 -> 738 us).
+template <int NQ>
+__device__ __forceinline__ void adj_chunks_low(const uint8_t *__restrict__ fl, int nb, int eb0, int q,
+                                               AdjChunks &all, AdjChunks &mine) {
+    const int lane = threadIdx.x & 63, half = (nb + 1) / 2;
     auto flags = [&](int bit, unsigned &a, unsigned &w) {   // of any block, of block eb0 + q
         const int c = AdjChunks::chunk(bit, half);
         const uint8_t *f = fl + min(c, nb - 1);
@@ -434,12 +458,8 @@ __device__ __forceinline__ void adj_chunks(const uint8_t *__restrict__ fl, int n
     };
     unsigned a, w;
     flags(lane, a, w);
-    all.m0 = __ballot(a != 0);
-    mine.m0 = __ballot(w != 0);
-    if (LOW) {
-        all.m1 = __ballot(a > 1);
-        mine.m1 = __ballot(w > 1);
-    }
+    all = AdjChunks{__ballot(a != 0), __ballot(a > 1)};
+    mine = AdjChunks{__ballot(w != 0), __ballot(w > 1)};
     if (half > 32) {   // uniform
         flags(64 + lane, a, w);
         all.m1 |= __ballot(a != 0);
@@ -962,9 +982,9 @@ __device__ __forceinline__ void t16_stage_async(const unsigned short *__restrict
 // the MFMAs of the step before: 16 bytes of row r from pixel x on, in one load
 // that needs no alignment unless the table's pixels end within the tile (`full`
 // is uniform).  With 2-byte loads, waited for when issued, and now, FP16, two
-// frequencies: 130 elements / 301x255 178 -> 102 us, with the Hessian diagonal
-// (eight waves, see t16_waves) 292 -> 120, 100 / 256^2 89 -> 54 us, 1000 / 301x255
-// (one frequency) 968 -> 404.
+// frequencies: 130 elements / 301x255 178 -> 93 us, with the Hessian diagonal
+// (eight waves, see t16_waves) 292 -> 115, 100 / 256^2 89 -> 51 us, 1000 / 301x255
+// (one frequency) 968 -> 392.
 typedef unsigned short t16us8 __attribute__((ext_vector_type(8)));
 typedef t16us8 t16us8_u __attribute__((aligned(2)));
 __device__ __forceinline__ t16us8 t16_load(const unsigned short *__restrict__ g, int r, int64_t N, int64_t x,
@@ -1009,7 +1029,7 @@ __device__ __forceinline__ void t16_store_tile(const t16us8 (&v)[16 / NW], int m
 // Hessian diagonal: 130 elements / 301x255, two frequencies, 186 -> 152 us,
 // 256 / 480^2, three, 764 -> 675, 1024 / 480^2, one, 1.89 -> 1.68 ms; with
 // |G|^2 by fused multiply-adds (20 instead of 44 instructions a fragment in
-// FP16) and the sum of its roundings taken off at the end 120, 615 and 1.51 ms.
+// FP16) and the sum of its roundings taken off at the end 115, 594 and 1.42 ms.
 constexpr int t16_waves(bool hess) { return hess ? 8 : 4; }
 
 template <typename S, bool HESS, bool DIRECT, typename A>
@@ -1104,7 +1124,7 @@ __global__ void __launch_bounds__(64 * t16_waves(HESS), 2) k_adjoint16_tr(const 
         // the pass's receiver chunks: `all` of its four waves (staged), `mine`
         // of this wave's 32 emitters
         AdjChunks all, mine;
-        adj_chunks<4, true>(fl, P.nb, ec >> 5, eg, all, mine);
+        adj_chunks_low<4>(fl, P.nb, ec >> 5, eg, all, mine);
         const int nstep = all.count();
         // the chunks of the current step and the next two (opaque to the
         // compiler, which would otherwise keep a strength-reduced address per
