@@ -52,6 +52,7 @@ struct FwdParams {
     int m, mp, nf, ntl, ntri, nsplit;
     int dmin;              // >= 32: pairs closer than this need not be computed
     int64_t N, kchunk;
+    bool sum64;            // FP32: the partials are FP64
     double cg[RB_MAX_NF];  // omega^2 h^2
 };
 

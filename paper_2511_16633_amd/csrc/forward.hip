@@ -505,9 +505,14 @@ __global__ void k_delta_cast(int64_t N, int64_t n, const double *__restrict__ de
     if (x < n) out[x] = x < N ? (float)delta[x] : 0.0f;
 }
 
+// With O double the sums of each step (kFdKC pixels) are added in FP64, so that a
+// split of any length is as exact as splits of a step whose partials are added in
+// FP64, with fewer partials to write and read (see fwd_params).
+template <typename O>
 __device__ __forceinline__ void fwd_f32_tile(const FwdParams &P, const float *__restrict__ Gr,
                                              const float *__restrict__ Gi, const float *__restrict__ df,
-                                             float *__restrict__ part, int te, int tr, int split, int k) {
+                                             O *__restrict__ part, int te, int tr, int split, int k) {
+    constexpr bool SUM64 = sizeof(O) == 8;
     __shared__ __align__(16) unsigned char sm[2][kFdBuf];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -546,6 +551,25 @@ __device__ __forceinline__ void fwd_f32_tile(const FwdParams &P, const float *__
     for (int b = 0; b < 2; ++b)
 #pragma unroll
         for (int c = 0; c < 2; ++c) p1[b][c] = p2[b][c] = p3[b][c] = f4{0, 0, 0, 0};
+    typedef double d4 __attribute__((ext_vector_type(4)));
+    d4 tre[2][2], tim[2][2];   // with SUM64
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) tre[b][c] = tim[b][c] = d4{0, 0, 0, 0};
+    auto add_step = [&]() {
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    tre[b][c][i] += (double)(p1[b][c][i] - p2[b][c][i]);
+                    tim[b][c][i] += (double)((p3[b][c][i] - p1[b][c][i]) - p2[b][c][i]);
+                }
+                p1[b][c] = p2[b][c] = p3[b][c] = f4{0, 0, 0, 0};
+            }
+    };
     if (nch > 0) stage(0, 0);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
@@ -586,12 +610,13 @@ __device__ __forceinline__ void fwd_f32_tile(const FwdParams &P, const float *__
                     }
                 }
             }
+            if (SUM64) add_step();
         }
         __builtin_amdgcn_s_waitcnt(0);   // tile c + 1 has landed in LDS
         __syncthreads();
     }
     if (idle) return;
-    float *pp = part + ((int64_t)split * P.nf + k) * P.mp * P.mp * 2;
+    O *pp = part + ((int64_t)split * P.nf + k) * P.mp * P.mp * 2;
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
 #pragma unroll
@@ -601,16 +626,24 @@ __device__ __forceinline__ void fwd_f32_tile(const FwdParams &P, const float *__
             for (int i = 0; i < 4; ++i) {
                 const int ee = te * 64 + 32 * we + 16 * b + MM<float>::out_row(kk, i);
                 const int64_t o = ((int64_t)ee * P.mp + r) * 2;
-                pp[o] = p1[b][cb][i] - p2[b][cb][i];
-                pp[o + 1] = (p3[b][cb][i] - p1[b][cb][i]) - p2[b][cb][i];
+                if (SUM64) {
+                    pp[o] = tre[b][cb][i];
+                    pp[o + 1] = tim[b][cb][i];
+                } else {
+                    pp[o] = p1[b][cb][i] - p2[b][cb][i];
+                    pp[o + 1] = (p3[b][cb][i] - p1[b][cb][i]) - p2[b][cb][i];
+                }
             }
         }
     }
 }
 
-__global__ void __launch_bounds__(256, 4) k_forward_f32(FwdParams P, const float *__restrict__ Gr,
-                                                        const float *__restrict__ Gi, const float *__restrict__ df,
-                                                        float *__restrict__ part) {
+template <typename O>
+__global__ void __launch_bounds__(256, sizeof(O) == 8 ? 2 : 4) k_forward_f32(FwdParams P,
+                                                                             const float *__restrict__ Gr,
+                                                                             const float *__restrict__ Gi,
+                                                                             const float *__restrict__ df,
+                                                                             O *__restrict__ part) {
     int te, tr, split, k;
     fwd_block(P, te, tr, split, k);
     fwd_f32_tile(P, Gr, Gi, df, part, te, tr, split, k);
@@ -1650,17 +1683,23 @@ static FwdParams fwd_params(const rb_geometry *g, const double *freqs, int nf, r
     // tens of pixels (BF16, without / with: 97 elements / 230x152, three frequencies,
     // 42.9 / 33.2 us, 256 / 128^2, two, 44.0 / 35.4, 768 / 64x66, two, 60.1 / 56.2).  The
     // other small tiles need the waves: 256 elements / 128^2 FP64 245 us, with the longer
-    // splits 304; 40 / 655x501, rows not aligned, BF16 235 and 280.  The
-    // FP32 cores' kernels, which add to a split's sums once per four pixels, keep
-    // them as short as 16 pixels: the splits are added in FP64, and with 64
-    // pixels or 512 the error of the result is up to 2.9 times as large (20
-    // elements / 41x82, two frequencies: 3.3e-8, 9.1e-8).  us per call with splits
-    // of at least 16 / 64 / 128 / 512 pixels, two frequencies: 64 elements /
-    // 128^2 FP32 37 / 26 / 25 / 44, BF16 33 / 27 / 28 / 31, FP64 - / 30 / 34 / -.
-    const int resident = (fs || wide ? 1 : (fwd32_direct(g, dt) ? 4 : 2)) * device_cus();
+    // splits 304; 40 / 655x501, rows not aligned, BF16 235 and 280.
+    //
+    // The FP32 cores' kernels add to a split's sums once per four pixels; with splits of
+    // 64 or 512 pixels in FP32 the error of the result is up to 2.9 times that with 16 (20
+    // elements / 41x82, two frequencies: 3.3e-8, 9.1e-8).  Where splits of 16 to 64 pixels
+    // would come out (sum64; rows of whole 16-byte pieces), the sums of 16 pixels are
+    // added in FP64 within a split instead, and the splits are few: us per call, FP32
+    // partials of 16 pixels and so, 33 elements / 266x194, one frequency, 66 / 32, 64 /
+    // 128^2, two, 34 / 25, 200 / 80^2, two, 54 / 48; longer splits gain nothing by it (64 /
+    // 480^2, two, 130 / 135, 1000 / 32^2, two, 99 / 119, 64 / 1100^2, four, 926 / 1199).
+    // Rows that are not aligned keep splits of 16 pixels.
+    P.sum64 = !fs && fwd32_direct(g, dt) && P.N <= 64 * (int64_t)(16 * device_cus() / (ntri * nf));
+    const int resident = (fs || wide ? 1 : (fwd32_direct(g, dt) && !P.sum64 ? 4 : 2)) * device_cus();
     int64_t most = dt == RB_F32 && !fs ? (P.N + kMinSplitPx32 - 1) / kMinSplitPx32 : P.N / kMinSplitPx;
     const bool small16 = (dt == RB_BF16 || dt == RB_F16) && !wide;
-    if (fs || wide || (small16 && P.N % 8 == 0))
+    if (P.sum64) most = (P.N + kMinSplitPx - 1) / kMinSplitPx;
+    if (fs || wide || P.sum64 || (small16 && P.N % 8 == 0))
         most = std::max<int64_t>(P.N / kFewSplitPx, std::min<int64_t>(most, resident / (ntri * nf)));
     if (dt == RB_F64)   // within one round, a step each (16 elements / 32^2: 16.6 -> 11.6 us)
         most = std::max<int64_t>(most, std::min<int64_t>((P.N + 15) / 16, resident / (ntri * nf)));
@@ -1671,7 +1710,7 @@ static FwdParams fwd_params(const rb_geometry *g, const double *freqs, int nf, r
     // rounds -> 1), BF16 152 / 119, 256 / 301x255 FP32 246 / 216, BF16 190 / 149
     const int64_t full = (int64_t)nsplit * ntri * nf / resident * resident / (ntri * nf);
     auto rounds = [&](int64_t n) { return (n * ntri * nf + resident - 1) / resident; };
-    if ((dt != RB_F32 || fs) && full > 0 && rounds(full) * nsplit < rounds(nsplit) * full) nsplit = (int)full;
+    if ((dt != RB_F32 || fs || P.sum64) && full > 0 && rounds(full) * nsplit < rounds(nsplit) * full) nsplit = (int)full;
     // the kernels with direct loads (FP32, and 16-bit for large rings) also
     // keep a split to at most kFdSplitPx pixels: the tiles of a split share
     // its table rows in L2 only while they stay within a few k-steps of each
@@ -1710,7 +1749,7 @@ struct FwdWs {
 };
 
 static FwdWs carve_fwd(Carver &c, const FwdParams &P, rb_dtype dt, bool fs) {
-    const size_t es = dt == RB_F64 ? 8 : 4;
+    const size_t es = dt == RB_F64 || P.sum64 ? 8 : 4;
     FwdWs w;
     w.dmax = c.take<double>(1);
     w.dparts = (dt == RB_BF16 || dt == RB_F16) ? c.take<double>(kReduceBlocks) : nullptr;
@@ -1788,8 +1827,14 @@ rb_status forward_impl(const rb_geometry *g, const void *G_re, const void *G_im,
             } else if (fwd32_direct(g, dt)) {
                 k_delta_cast<<<blocks_for(P.N + 16, 256), 256, 0, st>>>(P.N, P.N + 16, delta, w.df);
                 RB_LAUNCHED();
-                k_forward_f32<<<nblk, 256, 0, st>>>(P, (const float *)G_re, (const float *)G_im, w.df,
-                                                    (float *)w.part);
+                const float *gr = (const float *)G_re, *gi = (const float *)G_im;
+                if (P.sum64) {
+                    k_forward_f32<double><<<nblk, 256, 0, st>>>(P, gr, gi, w.df, (double *)w.part);
+                    RB_LAUNCHED();
+                    reduce(double(), gscale, nullptr);
+                    break;
+                }
+                k_forward_f32<float><<<nblk, 256, 0, st>>>(P, gr, gi, w.df, (float *)w.part);
             } else {
                 k_forward_f32_regs<<<dim3(P.ntri, P.nsplit, nf), 256, 0, st>>>(P, (const float *)G_re,
                                                                                (const float *)G_im, delta,

@@ -143,6 +143,15 @@ def test_forward_of_small_grids_sums_in_fp64(rb, shape):
     assert np.all(got.imag == 0.0) and rel <= 2.0 ** -24 / 3
 
 
+# The same where the 16 pixels' sums are added in FP64 within a split: a last step of
+# 12 and of 4 pixels, the largest grid that takes this kernel (64 pixels for each of 16
+# splits a compute unit, 256 of them) and the next, which adds at most 80 pixels in
+# FP32: 20 roundings, 1.1 2^-24 of their sum, / sqrt(N / 80), 2 % of 2^-24.
+@pytest.mark.parametrize("shape", [(34, 30, 64), (20, 33, 33), (512, 512, 16), (516, 512, 16)])
+def test_forward_sums_of_steps(rb, shape):
+    test_forward_of_small_grids_sums_in_fp64(rb, shape)
+
+
 def _check_gradient(rb, geom, gr, gi, D, w, pixels=slice(None)):
     f = 4e5
     gr, gi = gr.astype(np.float32), gi.astype(np.float32)
